@@ -62,11 +62,6 @@ __device__ __forceinline__ void push_arcs_wave(const BatchArgs &a, unsigned long
     }
 }
 
-#ifndef BC_UNROLL
-#define BC_UNROLL 4
-#endif
-constexpr int kUnroll = BC_UNROLL;  // matched neighbours whose values are loaded together
-
 // Per-source values live in vertex-major slabs [n][64]: path count, c and
 // delta of vertex v for lane k at v * 64 + k.  Each (vertex, lane) pair is on
 // exactly one level of a batch, so the slot is written once per batch and
@@ -77,121 +72,146 @@ __device__ __forceinline__ unsigned long long readlane_u64(unsigned long long x,
     return ((unsigned long long)hi << 32) | lo;
 }
 
-// Up to kUnroll matches, popped in ascending lane order: the lanes x that
-// take the neighbour's value, the slab row of the neighbour (v * 64) and the
-// group entry the match belongs to (all wavefront-uniform).
-struct Matches {
-    unsigned long long x[kUnroll];
-    size_t row[kUnroll];
-    int own[kUnroll];
+// A slab row read or written for the lanes of a wavefront-uniform mask: the
+// row is a buffer of 512 bytes whose address sits in scalar registers, and a
+// lane outside the mask takes an offset outside the buffer, for which loads
+// return zero and stores do nothing (the buffer instructions' range check).
+// A masked row access is then one select and one memory instruction: no
+// change of the execution mask, no branch, no zeroed register.
+constexpr unsigned kNoSlot = 0xfffffff0u;
+constexpr int kRowBytes = kLanes * 8;
+typedef unsigned row_data __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ unsigned row_slot(unsigned long long m) {
+    return __builtin_amdgcn_inverse_ballot_w64(m) ? (unsigned)lane_id() * 8u : kNoSlot;
+}
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_at(unsigned long long addr) {
+    return __builtin_amdgcn_make_buffer_rsrc((void *)addr, 0, kRowBytes, 0x00020000);
+}
+__device__ __forceinline__ unsigned long long row_load(unsigned long long addr, unsigned slot) {
+    const row_data d = __builtin_amdgcn_raw_buffer_load_b64(row_at(addr), (int)slot, 0, 0);
+    return ((unsigned long long)d.y << 32) | d.x;
+}
+__device__ __forceinline__ void row_store(unsigned long long addr, unsigned slot, unsigned long long v) {
+    row_data d;
+    d.x = (unsigned)v;
+    d.y = (unsigned)(v >> 32);
+    __builtin_amdgcn_raw_buffer_store_b64(d, row_at(addr), (int)slot, 0, 0);
+}
+__device__ __forceinline__ unsigned long long row_addr(const void *slab, int v) {
+    return (unsigned long long)slab + ((unsigned long long)(unsigned)v << 9);
+}
+
+// A frontier word in one 16-byte load (tag and mask together).
+__device__ __forceinline__ unsigned long long tagged_lanes(const Tagged *fw, int u, uint32_t T, unsigned long long m) {
+    const uint4 f = *reinterpret_cast<const uint4 *>(fw + u);
+    return f.z == T ? ((((unsigned long long)f.y << 32) | f.x) & m) : 0ull;
+}
+
+// What a path-count or backward sum adds up, in the order of the arcs.
+enum : int { OP_U64 = 0, OP_F64 = 1, OP_C = 2 };
+template <int OP>
+struct RowSum {
+    unsigned long long lo = 0;  // OP_U64: 64-bit sum and its carries (fewer than 2^31 terms)
+    unsigned hi = 0;
+    double d = 0.0;             // OP_F64: counts scaled by 2^-sh; OP_C: c values
+    __device__ __forceinline__ void add(unsigned long long v, int sh) {
+        if (OP == OP_U64) {
+            lo += v;
+            hi += (lo < v) ? 1u : 0u;
+        } else if (OP == OP_F64) {
+            d += ldexp(as_f64(v), -sh);
+        } else {
+            d += as_f64(v);
+        }
+    }
+    __device__ __forceinline__ void clear() {
+        lo = 0;
+        hi = 0;
+        d = 0.0;
+    }
 };
 
-__device__ __forceinline__ void pop_matches(unsigned long long &bal, unsigned long long xj, int uj, int ownj,
-                                            Matches &mt) {
+#ifndef BC_UNROLL
+#define BC_UNROLL 8
+#endif
+constexpr int kUnroll = BC_UNROLL;  // matched neighbours whose rows are loaded together
+
+// The rows of up to kUnroll matches of a chunk (bal: lanes whose arc's far
+// end matches, in arc order; xj: its lanes; rj: its row; ownj: the group entry
+// of the arc) are requested together, then handed to use(value, owner) in arc
+// order.  Everything but the values is wavefront-uniform; a slot beyond the
+// last match loads nothing (its value is zero) and repeats the owner before.
+template <class Use>
+__device__ __forceinline__ void take_matches(unsigned long long &bal, unsigned long long xj, unsigned long long rj,
+                                             int ownj, Use use) {
+    unsigned long long val[kUnroll];
+    int own[kUnroll];
+    static_assert(kUnroll % 4 == 0, "matches are taken four at a time");
 #pragma unroll
-    for (int q = 0; q < kUnroll; ++q) {
-        if (bal) {
-            const int j = __ffsll(bal) - 1;
+    for (int h = 0; h < kUnroll; h += 4) {
+        own[h] = -1;
+        if (h && !bal) continue;
+#pragma unroll
+        for (int q = h; q < h + 4; ++q) {
+            const int j = bal ? __ffsll(bal) - 1 : 0;
+            const unsigned long long x = bal ? readlane_u64(xj, j) : 0ull;
+            own[q] = bal ? __builtin_amdgcn_readlane(ownj, j) : own[q > h ? q - 1 : h];
             bal &= bal - 1;
-            mt.x[q] = readlane_u64(xj, j);
-            mt.row[q] = (size_t)__builtin_amdgcn_readlane(uj, j) * kLanes;
-            mt.own[q] = __builtin_amdgcn_readlane(ownj, j);
-        } else {
-            mt.x[q] = 0ull;
-            mt.row[q] = 0;
-            mt.own[q] = -1;
+            val[q] = row_load(readlane_u64(rj, j), row_slot(x));
         }
+    }
+#pragma unroll
+    for (int h = 0; h < kUnroll; h += 4) {
+        if (h && own[h] < 0) break;
+#pragma unroll
+        for (int q = h; q < h + 4; ++q) use(val[q], own[q]);
     }
 }
 
-// Path counts: sum over arcs [a0, a1) of w's neighbours u on level l (tag T)
-// of sigma_k(u) for the lanes k of m; lane k accumulates its own source, in
-// CSR order.  Loads of up to kUnroll neighbours are issued together.
-template <int MODE>
-__device__ __forceinline__ void sig_arcs(const BatchArgs &a, const Tagged *__restrict__ fw_cur, uint32_t T,
-                                         unsigned long long m, int a0, int a1, int sh,
-                                         const int32_t *__restrict__ col, unsigned long long &lo,
-                                         unsigned long long &hi, double &accd, unsigned long long &my_larcs,
-                                         unsigned long long &my_pairs) {
+// Counters of a wavefront's path-count or backward items.
+struct ArcCounters {
+    unsigned long long larcs = 0, arcs = 0, pairs = 0;
+};
+
+// Sum over arcs [a0, a1) (one entry's, wavefront-uniform bounds) of the rows
+// of the far ends that carry tag T, for the lanes of m; lane k accumulates
+// source k's value in CSR order.  The next chunk's frontier words and the
+// column indices after them are requested before this chunk's rows.
+template <int OP>
+__device__ __forceinline__ void row_arcs(const Tagged *fw, uint32_t T, unsigned long long m, int a0, int a1, int sh,
+                                         const int32_t *__restrict__ col, const void *slab, RowSum<OP> &acc,
+                                         ArcCounters &ac) {
+    if (a0 >= a1) return;
     const int lane = lane_id();
+    int u = col[min(a0 + lane, a1 - 1)];
+    int un = col[min(a0 + kWave + lane, a1 - 1)];
+    unsigned long long f = tagged_lanes(fw, u, T, m);
+    unsigned larcs = 0, pairs = 0;
     for (int eb = a0; eb < a1; eb += kWave) {
-        const int e = eb + lane;
-        unsigned long long xj = 0;
-        int uj = 0;
-        if (e < a1) {
-            uj = col[e];
-            const Tagged F = fw_cur[uj];
-            if (F.tag == T) xj = F.mask & m;
-        }
+        const unsigned long long xj = eb + lane < a1 ? f : 0ull;
+        const unsigned long long rj = row_addr(slab, u);
         unsigned long long bal = __ballot(xj != 0ull);
-        while (bal) {
-            Matches mt;
-            pop_matches(bal, xj, uj, 0, mt);
-            unsigned long long val[kUnroll];
-#pragma unroll
-            for (int q = 0; q < kUnroll; ++q)
-                val[q] = ((mt.x[q] >> lane) & 1ull) ? a.sigma[mt.row[q] + lane] : 0ull;
-#pragma unroll
-            for (int q = 0; q < kUnroll; ++q) {
-                if ((mt.x[q] >> lane) & 1ull) {
-                    if (MODE == 0) {
-                        lo += val[q];
-                        hi += (lo < val[q]) ? 1ull : 0ull;
-                    } else {
-                        accd += ldexp(as_f64(val[q]), -sh);
-                    }
-                }
-                if (lane == 0) {
-                    my_larcs += (unsigned)__popcll(mt.x[q]);
-                    my_pairs += mt.x[q] ? 1u : 0u;
-                }
-            }
+        if (eb + kWave < a1) {
+            u = un;
+            f = tagged_lanes(fw, u, T, m);
+            un = col[min(eb + 2 * kWave + lane, a1 - 1)];
         }
+        larcs += (unsigned)__popcll(xj);
+        pairs += (unsigned)__popcll(bal);
+        while (bal) take_matches(bal, xj, rj, 0, [&](unsigned long long v, int) { acc.add(v, sh); });
+    }
+    ac.larcs += larcs;
+    if (lane == 0) {
+        ac.pairs += pairs;
+        ac.arcs += (unsigned)(a1 - a0);
     }
 }
-
-// Dependencies: sum over arcs [a0, a1) of v's neighbours w on level l+1 (tag
-// TB1) of c_k(w) for the lanes k of M, in CSR order.
-__device__ __forceinline__ double bwd_arcs(const BatchArgs &a, const Tagged *__restrict__ fb_nxt, uint32_t TB1,
-                                           unsigned long long M, int a0, int a1, const int32_t *__restrict__ col,
-                                           unsigned long long &my_larcs, unsigned long long &my_pairs) {
-    const int lane = lane_id();
-    double acc = 0.0;
-    for (int eb = a0; eb < a1; eb += kWave) {
-        const int e = eb + lane;
-        unsigned long long xj = 0;
-        int uj = 0;
-        if (e < a1) {
-            uj = col[e];
-            const Tagged F = fb_nxt[uj];
-            if (F.tag == TB1) xj = F.mask & M;
-        }
-        unsigned long long bal = __ballot(xj != 0ull);
-        while (bal) {
-            Matches mt;
-            pop_matches(bal, xj, uj, 0, mt);
-            double val[kUnroll];
-#pragma unroll
-            for (int q = 0; q < kUnroll; ++q)
-                val[q] = ((mt.x[q] >> lane) & 1ull) ? a.chat[mt.row[q] + lane] : 0.0;
-#pragma unroll
-            for (int q = 0; q < kUnroll; ++q) {
-                if ((mt.x[q] >> lane) & 1ull) acc += val[q];
-                if (lane == 0) {
-                    my_larcs += (unsigned)__popcll(mt.x[q]);
-                    my_pairs += mt.x[q] ? 1u : 0u;
-                }
-            }
-        }
-    }
-    return acc;
-}
-
 
 // Per-lane counters the path-count finalisation feeds.
 struct SigCounters {
-    unsigned long long edges = 0, act = 0, ovf = 0, full_n = 0, full_m = 0, larcs = 0, arcs = 0, pairs = 0, lent = 0;
+    unsigned long long edges = 0, act = 0, ovf = 0, full_n = 0, full_m = 0, lent = 0;
     int maxe = INT_MIN, mine = INT_MAX;
+    ArcCounters ac;
 };
 
 // New vertex w (queue position p, visited/next words vis/m, degree deg)
@@ -217,64 +237,90 @@ __device__ __forceinline__ void sig_publish(const BatchArgs &a, Tagged *fw_nxt, 
     }
 }
 
-// Store the path counts of new vertex w (queue position p, visited/next words
-// vis/m, degree deg) and publish it as part of the level-(l+1) frontier.
-template <int MODE>
-__device__ __forceinline__ void sig_finalize(const BatchArgs &a, Tagged *fw_nxt, uint32_t T1, int p, int w,
-                                             unsigned long long vis, unsigned long long m, int deg,
-                                             unsigned long long lo, unsigned long long hi, double accd,
-                                             unsigned long long lmask, SigCounters &sc) {
-    const int lane = lane_id();
-    if ((m >> lane) & 1ull) {
-        const size_t at = (size_t)w * kLanes + lane;
-        if (MODE == 0) a.sigma[at] = lo;
-        else a.sigma[at] = as_u64(accd);
-        if (MODE == 0) {
-            if (hi != 0 || lo > a.sigma_limit) sc.ovf |= 1ull << lane;
-        } else if (accd > 0.0) {
-            int ex;
-            frexp(accd, &ex);
-            sc.maxe = max(sc.maxe, ex);
-            sc.mine = min(sc.mine, ex);
-        }
-    }
-    if (lane == 0) sig_publish(a, fw_nxt, T1, p, w, vis, m, deg, lmask, sc);
-}
-
-// Dependencies of vertex v (entry mask Mf, live lanes M) from the sum acc:
-// delta into the delta slab (read by PH_BC), c into the c slab.
-template <int MODE>
-__device__ __forceinline__ void bwd_finalize(const BatchArgs &a, Tagged *fb_cur, uint32_t TB, int v,
-                                             unsigned long long Mf, unsigned long long M, double acc, int sh,
-                                             int shn) {
-    const int lane = lane_id();
-    if ((M >> lane) & 1ull) {
-        const size_t at = (size_t)v * kLanes + lane;
-        const unsigned long long raw = a.sigma[at];
-        const double sv = MODE ? ldexp(as_f64(raw), -sh) : (double)raw;
-        double delta = sv * acc;
-        if (MODE) delta = ldexp(delta, -shn);
-        a.chat[at] = (1.0 + delta) / sv;
-        a.delta[at] = delta;
-    }
-    if (lane == 0) {
-        Tagged tg;
-        tg.mask = Mf;
-        tg.tag = TB;
-        fb_cur[v] = tg;
+// Store the path counts s of a new vertex (lanes m, row address ra).
+template <int OP>
+__device__ __forceinline__ void sig_store(const RowSum<OP> &s, unsigned long long m, unsigned long long ra,
+                                          unsigned long long limit, unsigned long long &ovf, SigCounters &sc) {
+    row_store(ra, row_slot(m), OP == OP_U64 ? s.lo : as_u64(s.d));
+    if (OP == OP_U64) {
+        // (lanes outside m hold a zero sum)
+        ovf |= __ballot(s.hi != 0u || s.lo > limit);
+    } else if (s.d > 0.0) {
+        int ex;
+        frexp(s.d, &ex);
+        sc.maxe = max(sc.maxe, ex);
+        sc.mine = min(sc.mine, ex);
     }
 }
 
-// Owner of packed arc index ai: the number of entries whose inclusive arc
-// prefix is <= ai (all lanes take part; incl[63] > ai is required).
-__device__ __forceinline__ int packed_owner(int incl, int ai) {
-    int o = 0;
-#pragma unroll
-    for (int step = 32; step > 0; step >>= 1) {
-        const int v = __shfl(incl, o + step - 1);
-        if (v <= ai) o += step;
+// Dependencies of one (vertex, lane) from the sum acc of its successors' c:
+// delta, and c = (1 + delta) / sigma.
+template <int MODE>
+__device__ __forceinline__ void bwd_values(unsigned long long raw, double acc, int sh, int shn, double &delta,
+                                           double &c) {
+    const double sv = MODE ? ldexp(as_f64(raw), -sh) : (double)raw;
+    delta = sv * acc;
+    if (MODE) delta = ldexp(delta, -shn);
+    c = (1.0 + delta) / sv;
+}
+
+// Packing of up to kBudget / 2 entries into one list of positions (arcs, or
+// (entry, source) pairs), 64 positions to a chunk.  A bit per position marks
+// where an entry starts; an entry's record is found by counting the starts up
+// to a position: one broadcast read of the word and one read of the record per
+// chunk (searching the prefix sums across lanes took six dependent LDS
+// round trips and five more to fetch the entry's values).
+constexpr int kPack = 64;                // entries of degree <= kPack are packed
+constexpr int kPackEntries = kBudget / 2;
+constexpr int kPackWords = kPackEntries + 4;  // up to 64 positions per entry
+struct Packing {
+    unsigned long long start[kPackWords];
+    uint4 rec[kPackEntries];
+    uint4 rec2[kPackEntries];
+};
+
+// LDS scratch of one wavefront, one use at a time.
+union WaveScratch {
+    Stage st;                   // discover: staged queue entries
+    Packing pk;                 // path counts and backward
+    double tile[kWave * 8];     // score accumulation: 64 rows x 8 lanes
+};
+
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Enter the packing: this lane's entry covers cnt positions (0: not packed)
+// and has the records r and r2.  Returns the number of positions (uniform) and this
+// entry's first one in off.
+__device__ __forceinline__ int pack_entries(Packing &pk, int cnt, uint4 r, uint4 r2, int &off) {
+    const int incl = wave_incl_scan(cnt);
+    off = incl - cnt;
+    const int total = __builtin_amdgcn_readlane(incl, 63);
+    for (int i = lane_id(); i < (total + 63) / 64; i += kWave) pk.start[i] = 0ull;
+    wave_lds_fence();
+    const unsigned long long on = __ballot(cnt > 0);
+    if (cnt > 0) {
+        const int rank = (int)lanes_below(on);
+        r.x -= (unsigned)off;  // arc of position i: r.x + i
+        r2.z = (unsigned)off;
+        pk.rec[rank] = r;
+        pk.rec2[rank] = r2;
+        atomicOr(&pk.start[off >> 6], 1ull << (off & 63));
     }
-    return o;
+    wave_lds_fence();
+    return total;
+}
+// Rank of the entry that holds position 64 * c + lane; before = entries that
+// start before chunk c (advanced to the next chunk).
+__device__ __forceinline__ int packed_rank(const Packing &pk, int c, int &before) {
+    const unsigned long long w = readlane_u64(pk.start[c], 0);
+    const int lane = lane_id();
+    const int r = before + (int)lanes_below(w) + (int)((w >> lane) & 1ull) - 1;
+    before += __popcll(w);
+    return r;
 }
 
 // Index of the j-th set bit (j counted from 0) of m; m has more than j bits.
@@ -283,40 +329,123 @@ __device__ __forceinline__ int nth_set_bit(unsigned long long m, int j) {
     return __ffsll(m) - 1;
 }
 
-// Entry-lane items: when the entries of a group carry few sources each, the
-// per-source sums run one thread per (entry, source) pair instead of one
-// wavefront lane per source.  Each thread then scans its entry's adjacency
-// on its own and reads only its source's value of each matched neighbour, so
-// the matched neighbours of single-source entries are no longer visited one
-// after another by the whole wavefront.  Every sum is still taken over the
-// entry's arcs in CSR order with the same operations, so the results are the
-// same bits as in the per-lane form.
-//   cnt   this lane's entry's item count (0 for entries handled elsewhere)
-// Returns the group's items; item it belongs to entry packed_owner(incl, it).
-__device__ __forceinline__ int group_items(int cnt, int &incl) {
-    incl = wave_incl_scan(cnt);
-    return __shfl(incl, 63);
+// Sums of a group's packed entries: every entry's arcs in CSR order, 64 arcs
+// of the list per chunk; fin(owner lane, sum) is called when an entry's last
+// match has been added (an entry without matches is passed over).  Returns
+// with the last entry's sum in acc and its lane in cur (-1: no match at all).
+// Pipelined like row_arcs: what a chunk needs (record, column, frontier word)
+// is requested one chunk ahead.
+template <int OP, class Fin>
+__device__ __forceinline__ void row_packed(const Packing &pk, int total, const Tagged *fw, uint32_t T, int sh,
+                                           const int32_t *__restrict__ col, const void *slab, RowSum<OP> &acc,
+                                           int &cur, ArcCounters &ac, Fin fin) {
+    const int lane = lane_id();
+    cur = -1;
+    if (total == 0) return;
+    int before = 0;
+    unsigned larcs = 0, pairs = 0;
+    // positions beyond the last one read the last entry's record and its last arc
+    uint4 r = pk.rec[packed_rank(pk, 0, before)];
+    int u = col[(int)r.x + min(lane, total - 1)];
+    unsigned long long f = tagged_lanes(fw, u, T, ((unsigned long long)r.z << 32) | r.y);
+    int own = (int)r.w;
+    uint4 rn = r;
+    int un = u;
+    if (kWave < total) {
+        rn = pk.rec[packed_rank(pk, 1, before)];
+        un = col[(int)rn.x + min(kWave + lane, total - 1)];
+    }
+    for (int base = 0; base < total; base += kWave) {
+        const unsigned long long xj = base + lane < total ? f : 0ull;
+        const unsigned long long rj = row_addr(slab, u);
+        const int ownj = own;
+        unsigned long long bal = __ballot(xj != 0ull);
+        if (base + kWave < total) {
+            u = un;
+            own = (int)rn.w;
+            f = tagged_lanes(fw, u, T, ((unsigned long long)rn.z << 32) | rn.y);
+            if (base + 2 * kWave < total) {
+                rn = pk.rec[packed_rank(pk, base / kWave + 2, before)];
+                un = col[(int)rn.x + min(base + 2 * kWave + lane, total - 1)];
+            }
+        }
+        larcs += (unsigned)__popcll(xj);
+        pairs += (unsigned)__popcll(bal);
+        while (bal) {
+            take_matches(bal, xj, rj, ownj, [&](unsigned long long v, int o) {
+                if (o != cur) {
+                    if (cur >= 0) fin(cur, acc);
+                    acc.clear();
+                    cur = o;
+                }
+                acc.add(v, sh);
+            });
+        }
+    }
+    ac.larcs += larcs;
+    if (lane == 0) {
+        ac.pairs += pairs;
+        ac.arcs += (unsigned)total;
+    }
 }
 
-#ifndef BC_PACK
-#define BC_PACK 64
-#endif
-constexpr int kPack = BC_PACK;    // entries of degree <= kPack share 64-arc scan chunks
+// Entry-lane items: when the entries of a group carry few sources each, the
+// per-source sums run one thread per (entry, source) pair instead of one
+// wavefront lane per source: each thread scans its entry's arcs [e0, e1)
+// on its own and reads only source k's value of each matched far end.  Four
+// arcs are followed at once (columns, then words, then values), and
+// use(value) is called in CSR order, so the sum has the same bits as in the
+// per-lane form.  Returns the matches.
+template <class Use>
+__device__ __forceinline__ unsigned item_arcs(const Tagged *fw, uint32_t T, int k, int e0, int e1,
+                                              const int32_t *__restrict__ col, const unsigned long long *slab,
+                                              Use use) {
+    unsigned matched = 0;
+    for (int e = e0; e < e1; e += 4) {
+        int u[4];
+        bool on[4];
+        unsigned long long v[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) u[q] = col[min(e + q, e1 - 1)];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) on[q] = e + q < e1 && tagged_lanes(fw, u[q], T, 1ull << k) != 0ull;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = on[q] ? slab[(size_t)u[q] * kLanes + k] : 0ull;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (on[q]) use(v[q]);
+            matched += on[q] ? 1u : 0u;
+        }
+    }
+    return matched;
+}
 
-// Path counts for the entries [i0, i1) of level l+1 (one group, at most 64):
+// Path counts for the entries [i0, i1) of level l+1 (one group):
 // entries of degree <= kPack have their adjacencies packed into dense 64-arc
 // chunks; entries of degree <= kSeg follow one at a time; heavier ones run as
 // segments elsewhere.  Every entry's sum keeps CSR order.
+//
+// What bounds it: on R-MAT 22 the bytes fetched beyond the L2 (5.8 TB/s: a
+// matched row has 16 of 64 lanes in use but touches 2.8 of its four 128-byte
+// lines), on smaller graphs the latency of the chain entry -> row offsets ->
+// column -> frontier word -> row and the instructions per match.  Rows as
+// scalar buffers, records by bit counting, one load per frontier word and
+// loads a chunk ahead, against vector addresses, searches across lanes and
+// tag-then-mask loads: path-count and backward device time on R-MAT 18 (2048
+// sources, summed over 8 replicas) 90 + 95 -> 70 + 85 ms, R-MAT 22 (1024
+// sources, 4 replicas) 342 + 439 -> 327 + 385 ms; ER(2000), all sources, in the
+// block engine 7.1 -> 5.0 ms.  8 matches at a time: R-MAT 18 38.2 ms a run
+// against 39.2 for 4 and 38.4 for 16.
 template <int MODE>
-__device__ __forceinline__ void sig_group(const BatchArgs &a, const Tagged *__restrict__ fw_cur, Tagged *fw_nxt,
-                                          uint32_t T, int qs, int i0, int i1, int sh, unsigned long long lmask,
-                                          SigCounters &sc, int l, int *s_emax, int *s_emin, float il) {
+__device__ __forceinline__ void sig_group(const BatchArgs &a, const Tagged *fw_cur, Tagged *fw_nxt, uint32_t T, int qs,
+                                          int i0, int i1, int sh, unsigned long long lmask, SigCounters &sc, int l,
+                                          int *s_emax, int *s_emin, float il, Packing &pk) {
+    constexpr int OP = MODE ? OP_F64 : OP_U64;
     // predecessors: the in-arcs (the adjacency itself for undirected graphs)
     const int32_t *__restrict__ rp = a.g.in_row_ptr;
     const int32_t *__restrict__ col = a.g.in_col;
     const int lane = lane_id();
     const int i = i0 + lane;
-    const int ne = i1 - i0;
     const bool valid = i < i1;
     const int p = qs + i;
     const int w = valid ? a.lq_vtx[p] : 0;
@@ -332,146 +461,83 @@ __device__ __forceinline__ void sig_group(const BatchArgs &a, const Tagged *__re
         vis = x.vis;
         nxt = x.nxt;
     }
+    const unsigned long long ra = row_addr(a.sigma, w);
+    const unsigned long long limit = a.sigma_limit;
+    unsigned long long ovf = 0;  // lanes whose counts overflowed (wavefront-uniform)
     // few sources per light entry: one thread per (entry, source) pair
-    int iincl = 0;
-    const int n_items = group_items(light ? __popcll(nxt) : 0, iincl);
+    const int n_items = (int)wave_sum_u32(light ? (unsigned)__popcll(nxt) : 0u);
     const int n_light = __popcll(__ballot(light));
+    int off;
     if (n_light > 0 && (float)n_items <= il * (float)n_light) {
-        for (int base = 0; base < n_items; base += kWave) {
-            const int it = base + lane;
-            const int o = packed_owner(iincl, min(it, n_items - 1));
-            const int wo = __shfl(w, o), e0o = __shfl(e0, o), dgo = __shfl(na, o), io = __shfl(iincl, o);
-            const unsigned long long mo = shfl_u64(nxt, o);
+        pack_entries(pk, light ? __popcll(nxt) : 0,
+                     make_uint4(0u, (unsigned)nxt, (unsigned)(nxt >> 32), (unsigned)w),
+                     make_uint4((unsigned)e0, (unsigned)na, 0u, 0u), off);
+        int before = 0;
+        for (int c = 0; c * kWave < n_items; ++c) {
+            const int rank = packed_rank(pk, c, before);
+            const int it = c * kWave + lane;
             if (it < n_items) {
-                const int k = nth_set_bit(mo, it - (io - __popcll(mo)));
+                const uint4 r = pk.rec[rank], r2 = pk.rec2[rank];
+                const int k = nth_set_bit(((unsigned long long)r.z << 32) | r.y, it - (int)r2.z);
                 const int shk = MODE ? a.shift[(size_t)l * kLanes + k] : 0;
-                unsigned long long ilo = 0, ihi = 0;
-                double iacc = 0.0;
-                unsigned matched = 0;
-                for (int e = e0o; e < e0o + dgo; ++e) {
-                    const int u = col[e];
-                    const Tagged F = fw_cur[u];
-                    if (F.tag == T && ((F.mask >> k) & 1ull)) {
-                        const unsigned long long v = a.sigma[(size_t)u * kLanes + k];
-                        if (MODE == 0) {
-                            ilo += v;
-                            ihi += (ilo < v) ? 1ull : 0ull;
-                        } else {
-                            iacc += ldexp(as_f64(v), -shk);
-                        }
-                        ++matched;
-                    }
-                }
-                sc.larcs += matched;
-                sc.pairs += matched;
-                sc.arcs += (unsigned)dgo;
-                const size_t at = (size_t)wo * kLanes + k;
+                RowSum<OP> s;
+                const unsigned matched = item_arcs(fw_cur, T, k, (int)r2.x, (int)(r2.x + r2.y), col, a.sigma,
+                                                   [&](unsigned long long v) { s.add(v, shk); });
+                sc.ac.larcs += matched;
+                sc.ac.pairs += matched;
+                sc.ac.arcs += r2.y;
+                a.sigma[(size_t)r.w * kLanes + k] = MODE ? as_u64(s.d) : s.lo;
                 if (MODE == 0) {
-                    a.sigma[at] = ilo;
-                    if (ihi != 0 || ilo > a.sigma_limit) sc.ovf |= 1ull << k;
-                } else {
-                    a.sigma[at] = as_u64(iacc);
-                    if (iacc > 0.0) {
-                        int ex;
-                        frexp(iacc, &ex);
-                        atomicMax(&s_emax[k], ex);
-                        atomicMin(&s_emin[k], ex);
-                    }
+                    if (s.hi != 0u || s.lo > a.sigma_limit) sc.ovf |= 1ull << k;
+                } else if (s.d > 0.0) {
+                    int ex;
+                    frexp(s.d, &ex);
+                    atomicMax(&s_emax[k], ex);
+                    atomicMin(&s_emin[k], ex);
                 }
             }
         }
-        if (light) sig_publish(a, fw_nxt, T + 1u, p, w, vis, nxt, od, lmask, sc);
-    } else {
-    const int dl = light ? na : 0;
-    const int incl = wave_incl_scan(dl);
-    const int off = incl - dl;
-    const int total = __shfl(incl, 63);
-    unsigned long long lo = 0, hi = 0;
-    double accd = 0.0;
-    int cur = 0;  // entries below cur are finalised; cur is being summed
-    auto finalize_upto = [&](int upto) {  // finalise cur (with the sum) .. upto-1 (empty sums)
-        for (int e = cur; e < upto; ++e) {
-            if (__builtin_amdgcn_readlane((int)light, e)) {
-                sig_finalize<MODE>(a, fw_nxt, T + 1u, __builtin_amdgcn_readlane(p, e),
-                                   __builtin_amdgcn_readlane(w, e), readlane_u64(vis, e), readlane_u64(nxt, e),
-                                   __builtin_amdgcn_readlane(od, e), lo, hi, accd, lmask, sc);
-            }
-            lo = hi = 0;
-            accd = 0.0;
-        }
-        cur = upto;
-    };
-    for (int base = 0; base < total; base += kWave) {
-        const int ai = base + lane;
-        const int o = packed_owner(incl, min(ai, total - 1));
-        const int e0o = __shfl(e0, o), offo = __shfl(off, o);
-        const unsigned long long mo = shfl_u64(nxt, o);
-        unsigned long long xj = 0;
-        int uj = 0;
-        if (ai < total) {
-            uj = col[e0o + (ai - offo)];
-            const Tagged F = fw_cur[uj];
-            if (F.tag == T) xj = F.mask & mo;
-        }
-        if (lane == 0) sc.arcs += (unsigned)min(kWave, total - base);
-        unsigned long long bal = __ballot(xj != 0ull);
-        while (bal) {
-            Matches mt;
-            pop_matches(bal, xj, uj, o, mt);
-            unsigned long long val[kUnroll];
-#pragma unroll
-            for (int q = 0; q < kUnroll; ++q)
-                val[q] = ((mt.x[q] >> lane) & 1ull) ? a.sigma[mt.row[q] + lane] : 0ull;
-#pragma unroll
-            for (int q = 0; q < kUnroll; ++q) {
-                if (mt.own[q] < 0) continue;
-                if (mt.own[q] != cur) finalize_upto(mt.own[q]);
-                if ((mt.x[q] >> lane) & 1ull) {
-                    if (MODE == 0) {
-                        lo += val[q];
-                        hi += (lo < val[q]) ? 1ull : 0ull;
-                    } else {
-                        accd += ldexp(as_f64(val[q]), -sh);
-                    }
-                }
-                if (lane == 0) {
-                    sc.larcs += (unsigned)__popcll(mt.x[q]);
-                    sc.pairs += mt.x[q] ? 1u : 0u;
-                }
-            }
-        }
-    }
-    finalize_upto(ne);
+    } else if (n_light > 0) {
+        const int total = pack_entries(pk, light ? na : 0,
+                                       make_uint4((unsigned)e0, (unsigned)nxt, (unsigned)(nxt >> 32), (unsigned)lane),
+                                       make_uint4(0u, 0u, 0u, 0u), off);
+        RowSum<OP> acc;
+        int cur;
+        // every entry was discovered through an arc from level l in each of
+        // its lanes, so every entry has a match
+        auto fin = [&](int e, const RowSum<OP> &s) {
+            sig_store<OP>(s, readlane_u64(nxt, e), readlane_u64(ra, e), limit, ovf, sc);
+        };
+        row_packed<OP>(pk, total, fw_cur, T, sh, col, a.sigma, acc, cur, sc.ac, fin);
+        if (cur >= 0) fin(cur, acc);
     }
     // medium-degree entries: one wavefront-wide scan each
-    unsigned long long mm = __ballot(medium);
-    while (mm) {
+    for (unsigned long long mm = __ballot(medium); mm; mm &= mm - 1) {
         const int j = __ffsll(mm) - 1;
-        mm &= mm - 1;
-        const int wj = __builtin_amdgcn_readlane(w, j);
         const int a0 = __builtin_amdgcn_readlane(e0, j), dj = __builtin_amdgcn_readlane(na, j);
         const unsigned long long mj = readlane_u64(nxt, j);
-        unsigned long long lo = 0, hi = 0;
-        double accd = 0.0;
-        sig_arcs<MODE>(a, fw_cur, T, mj, a0, a0 + dj, sh, col, lo, hi, accd, sc.larcs, sc.pairs);
-        if (lane == 0) sc.arcs += (unsigned)dj;
-        sig_finalize<MODE>(a, fw_nxt, T + 1u, __builtin_amdgcn_readlane(p, j), wj, readlane_u64(vis, j), mj,
-                           __builtin_amdgcn_readlane(od, j), lo, hi, accd, lmask, sc);
+        RowSum<OP> acc;
+        row_arcs<OP>(fw_cur, T, mj, a0, a0 + dj, sh, col, a.sigma, acc, sc.ac);
+        sig_store<OP>(acc, mj, readlane_u64(ra, j), limit, ovf, sc);
     }
+    sc.ovf |= ovf;
+    if (light || medium) sig_publish(a, fw_nxt, T + 1u, p, w, vis, nxt, od, lmask, sc);
+    wave_lds_fence();  // the next group reuses the packing
 }
 
 // Dependencies for the entries [i0, i1) of level l (one group), packed like
-// sig_group.
+// sig_group.  A complete sum is parked in the entry's delta row; at the end of
+// the group the rows are taken up again four entries at a time, together with
+// their path counts (one entry at a time, that load stood at the end of the
+// chain of every entry).
 template <int MODE>
-__device__ __forceinline__ void bwd_group(const BatchArgs &a, const Tagged *__restrict__ fb_nxt, Tagged *fb_cur,
-                                          uint32_t TB, int qb, int i0, int i1, unsigned long long dead, int sh,
-                                          int shn, unsigned long long &my_larcs, unsigned long long &my_arcs,
-                                          unsigned long long &my_pairs, int l, bool has_next, float il) {
+__device__ __forceinline__ void bwd_group(const BatchArgs &a, const Tagged *fb_nxt, Tagged *fb_cur, uint32_t TB,
+                                          int qb, int i0, int i1, unsigned long long dead, int sh, int shn,
+                                          ArcCounters &ac, int l, bool has_next, float il, Packing &pk) {
     const int32_t *__restrict__ rp = a.g.row_ptr;
     const int32_t *__restrict__ col = a.g.col;
     const int lane = lane_id();
     const int i = i0 + lane;
-    const int ne = i1 - i0;
     const bool valid = i < i1;
     const int p = qb + i;
     const int v = valid ? a.lq_vtx[p] : 0;
@@ -482,110 +548,91 @@ __device__ __forceinline__ void bwd_group(const BatchArgs &a, const Tagged *__re
     const bool medium = valid && deg > kPack && deg <= kSeg;
     const unsigned long long Mf = (light || medium) ? a.lq_mask[p] : 0ull;
     const unsigned long long M = Mf & ~dead;
+    unsigned long long todo = 0, parked = 0;  // entries to finish below; those with a sum in their delta row
     // few sources per light entry: one thread per (entry, source) pair
-    int iincl = 0;
-    const int n_items = group_items(light ? __popcll(M) : 0, iincl);
+    const int n_items = (int)wave_sum_u32(light ? (unsigned)__popcll(M) : 0u);
     const int n_light = __popcll(__ballot(light));
+    int off;
     if (n_light > 0 && (float)n_items <= il * (float)n_light) {
-        for (int base = 0; base < n_items; base += kWave) {
-            const int it = base + lane;
-            const int o = packed_owner(iincl, min(it, n_items - 1));
-            const int vo = __shfl(v, o), e0o = __shfl(e0, o), dgo = __shfl(na, o), io = __shfl(iincl, o);
-            const unsigned long long mo = shfl_u64(M, o);
+        pack_entries(pk, light ? __popcll(M) : 0, make_uint4(0u, (unsigned)M, (unsigned)(M >> 32), (unsigned)v),
+                     make_uint4((unsigned)e0, (unsigned)na, 0u, 0u), off);
+        int before = 0;
+        for (int c = 0; c * kWave < n_items; ++c) {
+            const int rank = packed_rank(pk, c, before);
+            const int it = c * kWave + lane;
             if (it < n_items) {
-                const int k = nth_set_bit(mo, it - (io - __popcll(mo)));
-                double iacc = 0.0;
-                unsigned matched = 0;
-                for (int e = e0o; e < e0o + dgo; ++e) {
-                    const int u = col[e];
-                    const Tagged F = fb_nxt[u];
-                    if (F.tag == TB + 1u && ((F.mask >> k) & 1ull)) {
-                        iacc += a.chat[(size_t)u * kLanes + k];
-                        ++matched;
-                    }
-                }
-                my_larcs += matched;
-                my_pairs += matched;
-                my_arcs += (unsigned)dgo;
-                const size_t at = (size_t)vo * kLanes + k;
+                const uint4 r = pk.rec[rank], r2 = pk.rec2[rank];
+                const int k = nth_set_bit(((unsigned long long)r.z << 32) | r.y, it - (int)r2.z);
+                const size_t at = (size_t)r.w * kLanes + k;
+                const unsigned long long raw = a.sigma[at];
+                RowSum<OP_C> s;
+                const unsigned matched =
+                    item_arcs(fb_nxt, TB + 1u, k, (int)r2.x, (int)(r2.x + r2.y), col,
+                              (const unsigned long long *)a.chat, [&](unsigned long long x) { s.add(x, 0); });
+                ac.larcs += matched;
+                ac.pairs += matched;
+                ac.arcs += r2.y;
                 const int shk = MODE ? a.shift[(size_t)l * kLanes + k] : 0;
                 const int shnk = (MODE && has_next) ? a.shift[(size_t)(l + 1) * kLanes + k] : 0;
-                const unsigned long long raw = a.sigma[at];
-                const double sv = MODE ? ldexp(as_f64(raw), -shk) : (double)raw;
-                double delta = sv * iacc;
-                if (MODE) delta = ldexp(delta, -shnk);
-                a.chat[at] = (1.0 + delta) / sv;
+                double delta, cc;
+                bwd_values<MODE>(raw, s.d, shk, shnk, delta, cc);
+                a.chat[at] = cc;
                 a.delta[at] = delta;
             }
         }
-        if (light) {
-            Tagged tg;
-            tg.mask = Mf;
-            tg.tag = TB;
-            fb_cur[v] = tg;
-        }
-    } else {
-    const int dl = (light && M) ? na : 0;
-    const int incl = wave_incl_scan(dl);
-    const int off = incl - dl;
-    const int total = __shfl(incl, 63);
-    double acc = 0.0;
-    int cur = 0;
-    auto finalize_upto = [&](int upto) {
-        for (int e = cur; e < upto; ++e) {
-            if (__builtin_amdgcn_readlane((int)light, e))
-                bwd_finalize<MODE>(a, fb_cur, TB, __builtin_amdgcn_readlane(v, e), readlane_u64(Mf, e),
-                                   readlane_u64(M, e), acc, sh, shn);
-            acc = 0.0;
-        }
-        cur = upto;
-    };
-    for (int base = 0; base < total; base += kWave) {
-        const int ai = base + lane;
-        const int o = packed_owner(incl, min(ai, total - 1));
-        const int e0o = __shfl(e0, o), offo = __shfl(off, o);
-        const unsigned long long mo = shfl_u64(M, o);
-        unsigned long long xj = 0;
-        int uj = 0;
-        if (ai < total) {
-            uj = col[e0o + (ai - offo)];
-            const Tagged F = fb_nxt[uj];
-            if (F.tag == TB + 1u) xj = F.mask & mo;
-        }
-        if (lane == 0) my_arcs += (unsigned)min(kWave, total - base);
-        unsigned long long bal = __ballot(xj != 0ull);
-        while (bal) {
-            Matches mt;
-            pop_matches(bal, xj, uj, o, mt);
-            double val[kUnroll];
-#pragma unroll
-            for (int q = 0; q < kUnroll; ++q)
-                val[q] = ((mt.x[q] >> lane) & 1ull) ? a.chat[mt.row[q] + lane] : 0.0;
-#pragma unroll
-            for (int q = 0; q < kUnroll; ++q) {
-                if (mt.own[q] < 0) continue;
-                if (mt.own[q] != cur) finalize_upto(mt.own[q]);
-                if ((mt.x[q] >> lane) & 1ull) acc += val[q];
-                if (lane == 0) {
-                    my_larcs += (unsigned)__popcll(mt.x[q]);
-                    my_pairs += mt.x[q] ? 1u : 0u;
-                }
-            }
-        }
+    } else if (n_light > 0) {
+        const int total = pack_entries(pk, (light && M) ? na : 0,
+                                       make_uint4((unsigned)e0, (unsigned)M, (unsigned)(M >> 32), (unsigned)lane),
+                                       make_uint4(0u, 0u, 0u, 0u), off);
+        RowSum<OP_C> acc;
+        int cur;
+        auto fin = [&](int e, const RowSum<OP_C> &s) {
+            row_store(row_addr(a.delta, __builtin_amdgcn_readlane(v, e)), row_slot(readlane_u64(M, e)), as_u64(s.d));
+            parked |= 1ull << e;
+        };
+        row_packed<OP_C>(pk, total, fb_nxt, TB + 1u, 0, col, a.chat, acc, cur, ac, fin);
+        if (cur >= 0) fin(cur, acc);
+        todo = __ballot(light && M != 0ull);
     }
-    finalize_upto(ne);
-    }
-    unsigned long long mm = __ballot(medium);
-    while (mm) {
+    for (unsigned long long mm = __ballot(medium && M != 0ull); mm; mm &= mm - 1) {
         const int j = __ffsll(mm) - 1;
-        mm &= mm - 1;
-        const int vj = __builtin_amdgcn_readlane(v, j);
         const int a0 = __builtin_amdgcn_readlane(e0, j), dj = __builtin_amdgcn_readlane(na, j);
-        const unsigned long long Mj = readlane_u64(M, j);
-        const double sm = Mj ? bwd_arcs(a, fb_nxt, TB + 1u, Mj, a0, a0 + dj, col, my_larcs, my_pairs) : 0.0;
-        if (lane == 0) my_arcs += (unsigned)dj;
-        bwd_finalize<MODE>(a, fb_cur, TB, vj, readlane_u64(Mf, j), Mj, sm, sh, shn);
+        const unsigned long long mj = readlane_u64(M, j);
+        RowSum<OP_C> acc;
+        row_arcs<OP_C>(fb_nxt, TB + 1u, mj, a0, a0 + dj, 0, col, a.chat, acc, ac);
+        row_store(row_addr(a.delta, __builtin_amdgcn_readlane(v, j)), row_slot(mj), as_u64(acc.d));
+        parked |= 1ull << j;
+        todo |= 1ull << j;
     }
+    while (todo) {
+        unsigned long long raw[4], sum[4], mq[4];
+        int vq[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int j = todo ? __ffsll(todo) - 1 : 0;
+            mq[q] = todo ? readlane_u64(M, j) : 0ull;
+            vq[q] = __builtin_amdgcn_readlane(v, j);
+            todo &= todo - 1;
+            raw[q] = row_load(row_addr(a.sigma, vq[q]), row_slot(mq[q]));
+            // an entry without a match has no sum: zero
+            sum[q] = row_load(row_addr(a.delta, vq[q]), row_slot((parked >> j) & 1ull ? mq[q] : 0ull));
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const unsigned slot = row_slot(mq[q]);
+            double delta, c;
+            bwd_values<MODE>(raw[q], as_f64(sum[q]), sh, shn, delta, c);
+            row_store(row_addr(a.chat, vq[q]), slot, as_u64(c));
+            row_store(row_addr(a.delta, vq[q]), slot, as_u64(delta));
+        }
+    }
+    if (light || medium) {
+        Tagged tg;
+        tg.mask = Mf;
+        tg.tag = TB;
+        fb_cur[v] = tg;
+    }
+    wave_lds_fence();  // the next group reuses the packing
 }
 
 // The variant of the next level and the summation options chosen with it
@@ -741,15 +788,14 @@ __device__ __forceinline__ void batch_step_body(const BatchArgs &a, const unsign
     __shared__ unsigned long long s_tmp[kLanes];
     __shared__ int s_lsrc[kLanes];
     __shared__ int s_lead[kLanes];
-    __shared__ Stage s_stage[kWavesPerBlock];
+    __shared__ WaveScratch s_scratch[kWavesPerBlock];
     __shared__ float s_lds[2 * kMlpH + kMlpOut + 4];
     __shared__ LevelFeatures s_feat;
     __shared__ float s_il;  // sources-per-entry threshold of this path-count / backward step
     __shared__ int s_usig;  // an undo step restores a path-count step (timing collection)
     __shared__ int s_emax[kLanes], s_emin[kLanes];
-    __shared__ double s_bct[kWavesPerBlock][kWave * 8];  // score accumulation: 64 rows x 8 lanes per wavefront
     Ctl *c = a.ctl;
-    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wid = uniform(tid >> 6);
     if (tid == 0) {
         s_phase = c->phase;
         s_level = c->level;
@@ -836,19 +882,19 @@ __device__ __forceinline__ void batch_step_body(const BatchArgs &a, const unsign
         s_emin[tid] = INT_MAX;
     }
     __syncthreads();
-    const int phase = s_phase;
+    const int phase = uniform(s_phase);
     if (phase == PH_DONE || phase == PH_IDLE) return;
-    const unsigned nblk = s_nblk;
+    const unsigned nblk = (unsigned)uniform((int)s_nblk);
     const bool active = bid < nblk;  // workgroups beyond nblk only count in
 
     const int gw = (int)bid * kWavesPerBlock + wid;
     const int nw = (int)nblk * kWavesPerBlock;
-    const int l = s_level;
+    const int l = uniform(s_level);
     const int32_t *__restrict__ rp = a.g.row_ptr;
     const int32_t *__restrict__ col = a.g.col;
     Tagged *fw_cur = (l & 1) ? a.fw1 : a.fw0;
     Tagged *fw_nxt = (l & 1) ? a.fw0 : a.fw1;
-    const int h0 = s_h0, h1 = s_h1, hseg = s_hseg;
+    const int h0 = uniform(s_h0), h1 = uniform(s_h1), hseg = uniform(s_hseg);
 
     unsigned long long my_edges = 0, my_arcs = 0, my_larcs = 0, my_act = 0, my_ovf = 0;
     unsigned long long my_full_n = 0, my_full_m = 0, my_pairs = 0, my_lent = 0;
@@ -861,7 +907,7 @@ __device__ __forceinline__ void batch_step_body(const BatchArgs &a, const unsign
         const unsigned long long act = s_active;
         const uint32_t hqb = (uint32_t)s_hqb;
         const int variant = s_variant;
-        Stage &st = s_stage[wid];
+        Stage &st = s_scratch[wid].st;
         int sn = 0;
         GroupArgs gr;
         gr.gstart = a.gstart;
@@ -1018,70 +1064,71 @@ __device__ __forceinline__ void batch_step_body(const BatchArgs &a, const unsign
         stage_flush(st, sn, c, a.lq_vtx, (uint32_t)qe, a.lq_cap, a.hq, hqb, &c->err, gr);
     } else if (phase == PH_SIG) {
         // path counts of the new level; lane = source
-        const int qs = s_qe, cnt = s_qn - s_qe;
+        const int qs = uniform(s_qe), cnt = uniform(s_qn) - qs;
         const uint32_t T = s_epoch + (uint32_t)l;
         const int sh = MODE ? a.shift[(size_t)l * kLanes + lane] : 0;
         const unsigned long long lmask = s_lmask;
-        const int n_groups = (int)s_ng;
-        const uint32_t *gs = a.gstart + s_gb;
+        const int n_groups = uniform((int)s_ng);
+        const uint32_t *gs = a.gstart + uniform((int)s_gb);
         const int total = n_groups + hseg;
         const float il = s_il;
+        constexpr int OP = MODE ? OP_F64 : OP_U64;
+        Packing &pk = s_scratch[wid].pk;
         SigCounters sc;
         for (WorkCursor wc(c, nblk, bid); wc.item() < total; wc.next(total)) {
             const int k = wc.item();
             const int it = k < hseg ? n_groups + k : k - hseg;  // heavy segments first
             if (it < n_groups) {
-                const int i0 = (int)gs[it], i1 = min((int)gs[it + 1], cnt);
-                if (i1 > i0) sig_group<MODE>(a, fw_cur, fw_nxt, T, qs, i0, i1, sh, lmask, sc, l, s_emax, s_emin, il);
+                const int i0 = uniform((int)gs[it]), i1 = min(uniform((int)gs[it + 1]), cnt);
+                if (i1 > i0) sig_group<MODE>(a, fw_cur, fw_nxt, T, qs, i0, i1, sh, lmask, sc, l, s_emax, s_emin, il, pk);
                 continue;
             }
             // a segment of a heavy new vertex
             const int t = it - n_groups;
-            const int h = seg_owner(a.hq.seg, h0, h1, t);
-            const int s = t - a.hq.seg[h];
-            const int p = a.hq.pos[h];
-            const int w = a.lq_vtx[p];
-            const int e0 = a.g.in_row_ptr[w], e1 = a.g.in_row_ptr[w + 1];  // predecessors: in-arcs
-            const int od = rp[w + 1] - rp[w];
-            const unsigned long long m = a.vn[w].nxt;
+            const int h = uniform(seg_owner(a.hq.seg, h0, h1, t));
+            const int s0 = uniform(a.hq.seg[h]), s = t - s0;
+            const int p = uniform(a.hq.pos[h]);
+            const int w = uniform(a.lq_vtx[p]);
+            const int e0 = uniform(a.g.in_row_ptr[w]), e1 = uniform(a.g.in_row_ptr[w + 1]);  // predecessors: in-arcs
+            const int od = uniform(rp[w + 1] - rp[w]);
+            const unsigned long long m = uniform(a.vn[w].nxt);
             const int a0 = e0 + s * kSeg, a1 = max(a0, min(e1, a0 + kSeg));
-            unsigned long long lo = 0, hi = 0;
-            double accd = 0.0;
-            sig_arcs<MODE>(a, fw_cur, T, m, a0, a1, sh, a.g.in_col, lo, hi, accd, sc.larcs, sc.pairs);
-            if (lane == 0) sc.arcs += (unsigned)(a1 - a0);
-            const size_t slot = (size_t)(a.hq.seg[h] + s) * kLanes + lane;
+            RowSum<OP> sum;
+            row_arcs<OP>(fw_cur, T, m, a0, a1, sh, a.g.in_col, a.sigma, sum, sc.ac);
+            const size_t slot = (size_t)(s0 + s) * kLanes + lane;
             if (MODE == 0) {
-                part_store(&a.hq.part_lo[slot], lo);
-                part_store(&a.hq.part_hi[slot], hi);
+                part_store(&a.hq.part_lo[slot], sum.lo);
+                part_store(&a.hq.part_hi[slot], sum.hi);
             } else {
-                part_store(&a.hq.part_lo[slot], as_u64(accd));
+                part_store(&a.hq.part_lo[slot], as_u64(sum.d));
             }
-            const int ns = n_segments(class_deg(a.g, w, od));
+            const int ns = n_segments(uniform(class_deg(a.g, w, od)));
             if (!seg_arrive(&a.hq.cnt[h], ns)) continue;
-            lo = hi = 0;
-            accd = 0.0;
-            for (int k = 0; k < ns; ++k) {  // combine in segment order
-                const size_t sl = (size_t)(a.hq.seg[h] + k) * kLanes + lane;
+            sum.clear();
+            for (int k2 = 0; k2 < ns; ++k2) {  // combine in segment order
+                const size_t sl = (size_t)(s0 + k2) * kLanes + lane;
                 if (MODE == 0) {
-                    const unsigned long long x = part_load(&a.hq.part_lo[sl]);
-                    lo += x;
-                    hi += part_load(&a.hq.part_hi[sl]) + ((lo < x) ? 1ull : 0ull);
+                    sum.add(part_load(&a.hq.part_lo[sl]), 0);
+                    sum.hi += (unsigned)part_load(&a.hq.part_hi[sl]);
                 } else {
-                    accd += as_f64(part_load(&a.hq.part_lo[sl]));
+                    sum.d += as_f64(part_load(&a.hq.part_lo[sl]));
                 }
             }
             if (lane == 0) a.hq.cnt[h] = 0;
             const VisNext x = a.vn[w];
-            sig_finalize<MODE>(a, fw_nxt, T + 1u, p, w, x.vis, x.nxt, od, lo, hi, accd, lmask, sc);
+            unsigned long long ovf = 0;
+            sig_store<OP>(sum, m, row_addr(a.sigma, w), a.sigma_limit, ovf, sc);
+            sc.ovf |= ovf;
+            if (lane == 0) sig_publish(a, fw_nxt, T + 1u, p, w, x.vis, x.nxt, od, lmask, sc);
         }
         my_edges += sc.edges;
         my_act |= sc.act;
         my_ovf |= sc.ovf;
         my_full_n += sc.full_n;
         my_full_m += sc.full_m;
-        my_larcs += sc.larcs;
-        my_arcs += sc.arcs;
-        my_pairs += sc.pairs;
+        my_larcs += sc.ac.larcs;
+        my_arcs += sc.ac.arcs;
+        my_pairs += sc.ac.pairs;
         my_lent += sc.lent;
         my_maxe = max(my_maxe, sc.maxe);
         my_mine = min(my_mine, sc.mine);
@@ -1090,41 +1137,56 @@ __device__ __forceinline__ void batch_step_body(const BatchArgs &a, const unsign
         const uint32_t TB = s_epoch_b + (uint32_t)l;
         Tagged *fb_cur = fw_cur;  // written with this level's tag
         Tagged *fb_nxt = fw_nxt;  // read: level l+1's tag
-        const unsigned long long dead = s_dead;
+        const unsigned long long dead = uniform(s_dead);
         const int sh = MODE ? a.shift[(size_t)l * kLanes + lane] : 0;
         const int shn = (MODE && l + 1 < s_L) ? a.shift[(size_t)(l + 1) * kLanes + lane] : 0;
-        const int n_groups = (int)s_ng;
-        const uint32_t *gs = a.gstart + s_gb;
+        const int n_groups = uniform((int)s_ng);
+        const uint32_t *gs = a.gstart + uniform((int)s_gb);
         const int total = n_groups + hseg;
+        const bool has_next = l + 1 < uniform(s_L);
+        const float il = s_il;
+        Packing &pk = s_scratch[wid].pk;
+        ArcCounters ac;
         for (WorkCursor wc(c, nblk, bid); wc.item() < total; wc.next(total)) {
             const int k = wc.item();
             const int it = k < hseg ? n_groups + k : k - hseg;  // heavy segments first
             if (it < n_groups) {
-                const int i0 = (int)gs[it], i1 = min((int)gs[it + 1], cnt);
-                if (i1 > i0)
-                    bwd_group<MODE>(a, fb_nxt, fb_cur, TB, qb, i0, i1, dead, sh, shn, my_larcs, my_arcs, my_pairs, l,
-                                    l + 1 < s_L, s_il);
+                const int i0 = uniform((int)gs[it]), i1 = min(uniform((int)gs[it + 1]), cnt);
+                if (i1 > i0) bwd_group<MODE>(a, fb_nxt, fb_cur, TB, qb, i0, i1, dead, sh, shn, ac, l, has_next, il, pk);
                 continue;
             }
             const int t = it - n_groups;
-            const int h = seg_owner(a.hq.seg, h0, h1, t);
-            const int s = t - a.hq.seg[h];
-            const int p = a.hq.pos[h];
-            const int v = a.lq_vtx[p];
-            const unsigned long long Mf = a.lq_mask[p];
+            const int h = uniform(seg_owner(a.hq.seg, h0, h1, t));
+            const int s0 = uniform(a.hq.seg[h]), s = t - s0;
+            const int p = uniform(a.hq.pos[h]);
+            const int v = uniform(a.lq_vtx[p]);
+            const unsigned long long Mf = uniform(a.lq_mask[p]);
             const unsigned long long M = Mf & ~dead;
-            const int e0 = rp[v], e1 = rp[v + 1];  // successors: out-arcs
+            const int e0 = uniform(rp[v]), e1 = uniform(rp[v + 1]);  // successors: out-arcs
             const int a0 = e0 + s * kSeg, a1 = max(a0, min(e1, a0 + kSeg));
-            double acc = M ? bwd_arcs(a, fb_nxt, TB + 1u, M, a0, a1, col, my_larcs, my_pairs) : 0.0;
-            if (lane == 0) my_arcs += (unsigned)(a1 - a0);
-            part_store(&a.hq.part_lo[(size_t)(a.hq.seg[h] + s) * kLanes + lane], as_u64(acc));
-            const int ns = n_segments(class_deg(a.g, v, e1 - e0));
+            RowSum<OP_C> sum;
+            if (M) row_arcs<OP_C>(fb_nxt, TB + 1u, M, a0, a1, 0, col, a.chat, sum, ac);
+            part_store(&a.hq.part_lo[(size_t)(s0 + s) * kLanes + lane], as_u64(sum.d));
+            const int ns = n_segments(uniform(class_deg(a.g, v, e1 - e0)));
             if (!seg_arrive(&a.hq.cnt[h], ns)) continue;
-            acc = 0.0;
-            for (int k = 0; k < ns; ++k) acc += as_f64(part_load(&a.hq.part_lo[(size_t)(a.hq.seg[h] + k) * kLanes + lane]));
+            double acc = 0.0;
+            for (int k2 = 0; k2 < ns; ++k2) acc += as_f64(part_load(&a.hq.part_lo[(size_t)(s0 + k2) * kLanes + lane]));
             if (lane == 0) a.hq.cnt[h] = 0;
-            bwd_finalize<MODE>(a, fb_cur, TB, v, Mf, M, acc, sh, shn);
+            const unsigned slot = row_slot(M);
+            double delta, cc;
+            bwd_values<MODE>(row_load(row_addr(a.sigma, v), slot), acc, sh, shn, delta, cc);
+            row_store(row_addr(a.chat, v), slot, as_u64(cc));
+            row_store(row_addr(a.delta, v), slot, as_u64(delta));
+            if (lane == 0) {
+                Tagged tg;
+                tg.mask = Mf;
+                tg.tag = TB;
+                fb_cur[v] = tg;
+            }
         }
+        my_larcs += ac.larcs;
+        my_arcs += ac.arcs;
+        my_pairs += ac.pairs;
     } else if (phase == PH_UNDO) {
         const int qs = s_qe, cnt = s_qn;
         if (s_usig) {
@@ -1155,7 +1217,7 @@ __device__ __forceinline__ void batch_step_body(const BatchArgs &a, const unsign
         const int lo = s_lo, span = s_hi - s_lo;
         const unsigned long long keep = s_lmask & ~s_dead;
         const int lane = lane_id(), wv = tid / kWave;
-        double *tile = s_bct[wv];
+        double *tile = s_scratch[wv].tile;
         for (int base = ((int)bid * kWavesPerBlock + wv) * kWave; base < span; base += (int)nblk * kBlock) {
             const int i = base + lane;
             const int w = lo + i;

@@ -16,6 +16,15 @@ __device__ __forceinline__ unsigned lanes_below(unsigned long long m) {
     return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
 }
 
+// A value that is the same in every lane, moved to a scalar register: loop
+// bounds and branches on it then need no change of the execution mask.
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ unsigned long long uniform(unsigned long long x) {
+    const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)x);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(x >> 32));
+    return ((unsigned long long)hi << 32) | lo;
+}
+
 __device__ __forceinline__ int wave_max_i(int x) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) x = max(x, __shfl_xor(x, o));
@@ -111,14 +120,14 @@ struct WorkCursor {
         r = (int)(bid % (unsigned)ncls);
         const int nb = ((int)nblk - r + ncls - 1) / ncls;  // workgroups of class r
         nwr = nb * kWavesPerBlock;
-        j = (int)(bid / (unsigned)ncls) * kWavesPerBlock + (int)(threadIdx.x >> 6);
+        j = (int)(bid / (unsigned)ncls) * kWavesPerBlock + uniform((int)(threadIdx.x >> 6));
         ctr = &c->work[r][0];
         jn = fetch();
     }
     __device__ __forceinline__ int fetch() {
         int x = 0;
         if ((threadIdx.x & 63) == 0) x = (int)atomicAdd(ctr, 1u);
-        return nwr + __shfl(x, 0);
+        return nwr + uniform(x);
     }
     __device__ __forceinline__ int item() const { return r + ncls * j; }
     __device__ __forceinline__ void next(int total) {
@@ -228,15 +237,20 @@ struct Stage {
     int32_t deg[kStage];
 };
 
-// Wavefront-inclusive prefix sum of an int.
+// Wavefront-inclusive prefix sum of an int, by the data-parallel row shifts and
+// broadcasts (no LDS traffic): within rows of 16, then row 0 into 1 and 2
+// into 3, then the lower half into the upper.  All lanes take part.
 __device__ __forceinline__ int wave_incl_scan(int x) {
-    const int lane = lane_id();
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const int y = __shfl_up(x, o);
-        if (lane >= o) x += y;
-    }
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);  // row_shr:1
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);  // row_shr:2
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);  // row_shr:4
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);  // row_shr:8
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
     return x;
+}
+__device__ __forceinline__ unsigned wave_sum_u32(unsigned x) {
+    return (unsigned)__builtin_amdgcn_readlane(wave_incl_scan((int)x), 63);
 }
 
 __device__ __forceinline__ unsigned long long shfl_u64(unsigned long long x, int src) {
