@@ -44,9 +44,10 @@ _COMMON_SOURCES = ["paper_2008_05718_amd/csrc/bc_common.h", "paper_2008_05718_am
 # the sources each step kernel is compiled from (its counters per launch
 # depend on these and on the workload, not on the host driver)
 KERNEL_FILES = {
-    "batch_step": ["paper_2008_05718_amd/csrc/bc_batched.hip"] + _COMMON_SOURCES,
-    "block_run": ["paper_2008_05718_amd/csrc/bc_batched.hip"] + _COMMON_SOURCES,
+    "batch_step": ["paper_2008_05718_amd/csrc/bc_batched.hip", "paper_2008_05718_amd/csrc/bc_rows.h"] + _COMMON_SOURCES,
+    "block_run": ["paper_2008_05718_amd/csrc/bc_batched.hip", "paper_2008_05718_amd/csrc/bc_rows.h"] + _COMMON_SOURCES,
     "weighted_run": ["paper_2008_05718_amd/csrc/bc_weighted.hip"] + _COMMON_SOURCES,
+    "wide_step": ["paper_2008_05718_amd/csrc/bc_wide.hip", "paper_2008_05718_amd/csrc/bc_rows.h"] + _COMMON_SOURCES,
     "wbatch_run": ["paper_2008_05718_amd/csrc/bc_wbatch.hip", "paper_2008_05718_amd/csrc/bc_wbatch.h"]
     + _COMMON_SOURCES,
 }
@@ -84,7 +85,8 @@ def measured_traffic(kernel: str, workload: str):
     sources changed since the counters were taken."""
     tag = {"batch_step<0>": "batch_step_u64", "batch_step<1>": "batch_step_f64", "block_run<0>": "block_run_u64",
            "weighted_run<0>": "weighted_run_u64", "weighted_run<1>": "weighted_run_f64",
-           "wbatch_run<0>": "wbatch_run_u64", "wbatch_run<1>": "wbatch_run_f64"}.get(kernel)
+           "wbatch_run<0>": "wbatch_run_u64", "wbatch_run<1>": "wbatch_run_f64",
+           "wide_step<0>": "wide_step_u64", "wide_step<1>": "wide_step_f64"}.get(kernel)
     path = os.path.join(ROOT, "profiles", f"{tag}_{workload}.md")
     if tag is None or not os.path.exists(path):
         return None
@@ -461,6 +463,8 @@ def main():
     arcs_frac = sum(s["algo_bytes_arcs"] for s in stats) / max(sum(s["algo_bytes"] for s in stats), 1e-12)
     if weighted:
         kernel = f"weighted_run<{k}>" if wlanes == 1 else f"wbatch_run<{k}>"
+        if st["n_batches"]:  # batches on the whole GPU: only that engine counts them
+            wlanes, kernel = 64, f"wide_step<{k}>"
     elif k == 0 and st.get("block_workgroups", 0) > 0:
         kernel = "block_run<0>"
     else:

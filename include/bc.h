@@ -114,12 +114,14 @@ bc_status bc_graph_create(int32_t n, int64_t nnz, const int32_t *row_ptr,
  * builds the in-arcs and their weights).  The handle keeps the caller's
  * numbering; unless BC_KEEP_ORDER is given it still takes the sources of a
  * run in the ranked order described for bc_graph_create (by hop distance
- * from the vertex of largest degree, ...).  It runs the weighted engine: a
- * persistent launch in which every
- * workgroup computes whole batches of 16 sources, or single sources
- * (bc_run_options.weighted_lanes), (distances by relaxation rounds, path
+ * from the vertex of largest degree, ...).  It runs the weighted
+ * engine: batches of up to 64 sources, one at a time on the whole GPU, a launch
+ * per round; or, for many sources of a small graph or on request
+ * (bc_run_options.weighted_lanes), a persistent launch in which every
+ * workgroup computes whole batches of 16 sources, or single sources.  Either
+ * way distances by relaxation rounds, path
  * counts over the shortest-path DAG in rounds of ready vertices, Eq. 2 over
- * those rounds in reverse); uint64 path counts, redone in FP64 (unscaled; a
+ * those rounds in reverse; uint64 path counts, redone in FP64 (unscaled; a
  * count beyond the double range gives BC_ERR_SIGMA_RANGE) for sources whose
  * counts overflow.  Run options other than flags, sigma_limit and weighted_lanes
  * are ignored.
@@ -224,9 +226,10 @@ typedef struct bc_run_options {
                              repeats bit for bit (BC_RUN_ONE_QUEUE: one, whatever
                              this says). */
     int32_t weighted_lanes;/* graphs with arc weights: sources one workgroup runs
-                             together (0 = default 16; 1 = one source per
-                             workgroup; 16; graphs above 2^27 vertices always
-                             run one).  Scores agree to rounding across
+                             together (1; 16; graphs above 2^27 vertices always
+                             run one), or 0 = automatic: batches of up to 64 on
+                             the whole GPU where the graph is large enough for
+                             the number of sources and the state fits, else 16.  Scores agree to rounding across
                              values; a given value repeats bit for bit.     */
     int32_t reserved[4];
 } bc_run_options;
@@ -390,7 +393,7 @@ typedef struct bc_stats {
        mode_* = the engine's launches; algo_bytes_arcs = algo_bytes without
        64 B per reached (vertex, source) pair.  One source per workgroup
        (weighted_lanes 1): algo_bytes = 16 per arc read + 64 per reached pair.
-       Lane batches (weighted_lanes 16; arcs counted once per round entry,
+       Lane batches (weighted_lanes 16, or 0; arcs counted once per round entry,
        for all of its sources): phase_lane_arcs[1] and [2] = (arc, source)
        pairs of the relaxation rounds and of the four passes; algo_bytes = 8
        per arc read (far end and weight) + 8 per (arc, source) pair (that

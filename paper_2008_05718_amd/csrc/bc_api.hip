@@ -23,6 +23,7 @@ template <int MODE> __global__ void batch_step(BatchArgs a);
 template <int MODE> __global__ void block_run(BlockArgs a);
 template <int MODE> __global__ void weighted_run(WeightedArgs a);
 template <int MODE> __global__ void wbatch_run(WeightedArgs a);
+template <int MODE> __global__ void wide_step(WideArgs a);
 }  // namespace bcx
 
 using namespace bcx;
@@ -198,6 +199,11 @@ struct bc_graph {
     int64_t w_pos_cap = 0;
     double *w_partials = nullptr;
     int64_t w_partials_cap = 0;
+    // wide weighted engine: its state for batches of up to wd_k sources (0 = none)
+    int wd_k = 0;
+    WideArgs wd{};
+    void *wd_mem[24] = {};            // its allocations
+    size_t wd_bytes = 0;
     int64_t nonisolated = 0;
     // vertices of degree > kSegBatched (ascending) and their segment prefix
     // sums; p_*: the same for the plain engine's kSegPlain
@@ -209,7 +215,7 @@ struct bc_graph {
     int64_t p_heavy_segs = 0;
     int64_t cost_units = 0;         // sum of entry_cost over all vertices
     double clock_khz = 100000.0;
-    int grid_plain = 1024, grid_batch = 1024;  // resident workgroups of the step kernels
+    int grid_plain = 1024, grid_batch = 1024, grid_wide = 1024;  // resident workgroups of the step kernels
     double *bc = nullptr;
     LevelRec *lvl = nullptr;       // per-level records of the last run [kLevelRecs]
     bool last_parts = false;       // the last run ran on concurrent parts
@@ -311,12 +317,14 @@ static void free_graphs(bc_graph *g) {
 }
 
 static void free_parts(bc_graph *g);
+static void free_wide(bc_graph *g);
 
 extern "C" void bc_destroy(bc_graph *g) {
     if (!g) return;
     (void)hipDeviceSynchronize();
     free_parts(g);
     free_graphs(g);
+    free_wide(g);
     void *dev[] = {g->row_ptr, g->col, g->in_row_ptr, g->in_col, g->wt,
                    g->in_wt == g->wt ? nullptr : g->in_wt, g->w_scratch, g->w_ctr, g->w_chunk, g->w_pos,
                    g->w_partials, g->bc, g->ctl, g->p_d, g->p_queue, g->p_level_off, g->p_shift,
@@ -701,6 +709,10 @@ static bc_status create_impl(int32_t n_graphs, const int32_t *voff_in, int32_t n
             if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&bb, (const void *)batch_step<0>, kBlock, 0) == hipSuccess &&
                 bb > 0)
                 g->grid_batch = cus * bb;
+            int bw = 0;
+            if (weights && hipOccupancyMaxActiveBlocksPerMultiprocessor(&bw, (const void *)wide_step<0>, kBlock, 0) ==
+                               hipSuccess && bw > 0)
+                g->grid_wide = cus * bw;
         }
     }
     CR_TRY(dalloc(&g->bc, (size_t)n, &g->acct));
@@ -1931,13 +1943,287 @@ static bc_status weighted_pass(bc_graph *g, int mode, const bc_run_options &o, c
     return BC_OK;
 }
 
+// ---------------------------------------------------- wide weighted engine
+// (bc_wide.hip) One batch of up to 64 sources at a time on the whole GPU, a
+// launch per round, driven like the unweighted engines.
+
+// The position of every out-arc among the in-arcs of its head (rows ascend).
+__global__ void reverse_arcs(int32_t n, const int32_t *rp, const int32_t *col, const int32_t *irp, const int32_t *icol,
+                             int32_t *rev) {
+    const int lane = threadIdx.x & 63;
+    const int64_t waves = (int64_t)gridDim.x * (blockDim.x >> 6);
+    for (int64_t v = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6; v < n; v += waves)
+        for (int32_t e = rp[v] + lane; e < rp[v + 1]; e += 64) {
+            const int32_t x = col[e];
+            int32_t lo = irp[x], hi = irp[x + 1];
+            while (hi - lo > 1) {
+                const int32_t mid = lo + ((hi - lo) >> 1);
+                if (icol[mid] <= (int32_t)v) lo = mid;
+                else hi = mid;
+            }
+            rev[e] = lo;
+        }
+}
+
+static void free_wide(bc_graph *g) {
+    for (void *&p : g->wd_mem) {
+        if (p) (void)hipFree(p);
+        p = nullptr;
+    }
+    g->acct.bytes -= std::min(g->acct.bytes, g->wd_bytes);
+    g->wd_bytes = 0;
+    g->wd_k = 0;
+}
+
+// Row width for a list of ns sources: rows of fewer sources keep a short
+// list's values closer together.
+static int wide_lanes(int64_t ns) { return ns <= 8 ? 8 : (ns <= 16 ? 16 : (ns <= 32 ? 32 : 64)); }
+
+// Whether one batch at a time on the whole GPU beats a batch of 16 per
+// workgroup.  A wide batch of 64 takes about as long as its rounds' launches
+// (3 to 7 ms on R-MAT 10 to 18) while a workgroup's batch grows with the arcs
+// (6 ms at 12 thousand, 93 ms at 450 thousand, 1.2 s at 7.6 million), but up
+// to 256 of those run at once.  With one wide batch worth nnz / 16384 of them:
+// R-MAT 18, 4096 sources 427 ms wide against 1556 ms; R-MAT 14, 512 sources 27
+// against 96 ms; ER(2000), 16 sources 2.7 against 8.4 ms, but all 2000 sources
+// 98 against 9.5 ms; a path of 5000 vertices 441 against 282 ms.
+static bool wide_pays(const bc_graph *g, int64_t ns) {
+    return ((ns + kLanes - 1) / kLanes) * 16384 <= g->nnz * ((ns + 16 * 256 - 1) / (16 * 256));
+}
+
+// State for batches of k sources.  *fits = false (and BC_OK): it does not fit
+// under the handle's cap or in the device, or the graph is beyond the engine's
+// 32-bit positions; the caller uses the engine that gives a batch to a
+// workgroup.
+static bc_status ensure_wide(bc_graph *g, int k, hipStream_t st, bool *fits) {
+    *fits = false;
+    const int64_t n = std::max<int32_t>(g->n, 1), nnz = std::max<int64_t>(g->nnz, 1);
+    if (n * kLanes > (int64_t)INT32_MAX || g->cost_units >= (int64_t)UINT32_MAX / kLanes) return BC_OK;
+    if (g->wd_k >= k) {
+        *fits = true;
+        return BC_OK;
+    }
+    free_wide(g);
+    const size_t mark = g->acct.bytes;
+    WideArgs &w = g->wd;
+    w = WideArgs{};
+    w.max_levels = (int32_t)(n + 2);
+    const int64_t lq_cap = n * k + kLanes, rgcap = g->cost_units / kBudget + 8;
+    const int64_t gcap = (int64_t)k * g->cost_units / kBudget + 2 * ((int64_t)w.max_levels + 2) + 64;
+    const int64_t hcap = (int64_t)g->n_heavy + 1, hent = (int64_t)g->n_heavy * k + kLanes;
+    const int64_t segs = g->heavy_segs + 1;
+    int at = 0;
+    bool ok = true;
+    auto take = [&](auto **p, int64_t count) {
+        if (!ok) return;
+        const hipError_t e = dalloc(p, (size_t)std::max<int64_t>(count, 1), &g->acct);
+        if (e != hipSuccess) {
+            ok = false;
+            (void)hipGetLastError();
+            return;
+        }
+        g->wd_mem[at++] = (void *)*p;
+    };
+    int32_t *rev = nullptr;
+    uint32_t *sgs = nullptr;
+    take(&w.dist, n * k);
+    take(&w.sigma, n * k);
+    take(&w.chat, n * k);
+    take(&w.delta, n * k);
+    take(&w.cnt, n * k);
+    take(&w.fm, 7 * n);  // three masks of the relaxation, three of the DAG rounds, the reached lanes
+    take(&w.dag_out, 2 * nnz);
+    take(&rev, nnz);
+    take(&w.rq, 3 * n);
+    take(&w.rgs, 3 * rgcap);
+    take(&w.rhq.pos, 3 * hcap);
+    take(&w.rhq.seg, 3 * hcap);
+    take(&w.rhq.cnt, 3 * hcap);
+    take(&sgs, rgcap);
+    take(&w.lq_vtx, lq_cap);
+    take(&w.lq_mask, lq_cap);
+    take(&w.level_off, 4 * ((int64_t)w.max_levels + 4));  // with the group bases and the heavy lists' offsets
+    take(&w.gstart, gcap);
+    take(&w.hq.pos, hent);
+    take(&w.hq.seg, hent);
+    take(&w.hq.cnt, hent);
+    take(&w.hq.part_lo, 2 * segs * kLanes);
+    take(&w.lane_src, kLanes);
+    g->wd_bytes = g->acct.bytes - mark;
+    if (!ok) {
+        free_wide(g);
+        return BC_OK;
+    }
+    w.rdy = w.fm + 3 * n;
+    w.rm = w.fm + 6 * n;
+    w.dag_in = w.dag_out + nnz;
+    w.rgcap = (uint32_t)rgcap;
+    w.rhcap = (uint32_t)hcap;
+    w.rhq.cap = (uint32_t)(3 * hcap);
+    w.lq_cap = (uint32_t)lq_cap;
+    const int64_t lv = (int64_t)w.max_levels + 4;
+    w.gbase = (uint32_t *)(w.level_off + lv);
+    w.hq.off = w.level_off + 2 * lv;
+    w.hq.nseg = w.level_off + 3 * lv;
+    w.gcap = (uint32_t)std::min<int64_t>(gcap, UINT32_MAX);
+    w.hq.cap = (uint32_t)hent;
+    w.hq.part_hi = w.hq.part_lo + segs * kLanes;
+    w.hq.part_cap = (uint32_t)segs;
+    w.rev = rev;
+    w.sgs = sgs;
+    reverse_arcs<<<grid_for((int64_t)g->n * 64, 256, 8192), 256, 0, st>>>(
+        g->n, g->row_ptr, g->col, g->directed ? g->in_row_ptr : g->row_ptr, g->directed ? g->in_col : g->col, rev);
+    HIP_TRY(hipGetLastError());
+    // work groups over all vertices in order (as stage_flush forms them)
+    std::vector<int32_t> rp((size_t)g->n + 1), irp;
+    HIP_TRY(hipMemcpyAsync(rp.data(), g->row_ptr, sizeof(int32_t) * rp.size(), hipMemcpyDeviceToHost, st));
+    if (g->directed) {
+        irp.resize(rp.size());
+        HIP_TRY(hipMemcpyAsync(irp.data(), g->in_row_ptr, sizeof(int32_t) * irp.size(), hipMemcpyDeviceToHost, st));
+    }
+    HIP_TRY(hipStreamSynchronize(st));
+    std::vector<uint32_t> gs((size_t)rgcap, 0u);
+    uint64_t cost = 0;
+    for (int32_t v = 0; v < g->n; ++v) {
+        int32_t d = rp[v + 1] - rp[v];
+        if (g->directed) d = std::max(d, irp[v + 1] - irp[v]);
+        const uint64_t next = cost + entry_cost(d);
+        for (uint64_t q = cost / kBudget + 1; q <= next / kBudget; ++q) gs[q] = (uint32_t)v + 1u;
+        cost = next;
+    }
+    w.n_sgroups = g->n > 0 ? (int32_t)((cost - 1) / kBudget + 1) : 0;
+    gs[w.n_sgroups] = (uint32_t)g->n;
+    HIP_TRY(hipMemcpyAsync(sgs, gs.data(), sizeof(uint32_t) * gs.size(), hipMemcpyHostToDevice, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    g->wd_k = k;
+    *fits = true;
+    return BC_OK;
+}
+
+// One pass over the run positions `pos`, as weighted_pass.
+static bc_status wide_pass(bc_graph *g, int mode, const bc_run_options &o, const int32_t *h_srcs,
+                           const std::vector<int64_t> &pos, int64_t dump_pos_run, DumpBufs *dump, hipStream_t st,
+                           std::vector<int64_t> *ovf, bool *dumped) {
+    ovf->clear();
+    if (pos.empty()) return BC_OK;
+    const int64_t ns = (int64_t)pos.size(), n = std::max<int32_t>(g->n, 1);
+    const int k = std::min(wide_lanes(ns), g->wd_k);
+    std::vector<int32_t> list((size_t)ns);
+    int64_t pdump = -1;
+    for (int64_t i = 0; i < ns; ++i) {
+        list[i] = h_srcs[pos[i]];
+        if (pos[i] == dump_pos_run) pdump = i;
+    }
+    const int64_t nb = (ns + k - 1) / k;
+    std::vector<int64_t> bs((size_t)nb + 1);
+    for (int64_t b = 0; b <= nb; ++b) bs[b] = std::min<int64_t>(ns, b * k);
+    bc_status s = grow(&g->srcs, &g->srcs_cap, ns, &g->acct);
+    if (s == BC_OK) s = grow(&g->ovf, &g->ovf_cap, ns, &g->acct);
+    if (s == BC_OK) s = grow(&g->bstart, &g->bcap[0], nb + 1, &g->acct);
+    if (s != BC_OK) return s;
+    HIP_TRY(hipMemcpyAsync(g->srcs, list.data(), sizeof(int32_t) * ns, hipMemcpyHostToDevice, st));
+    HIP_TRY(hipMemcpyAsync(g->bstart, bs.data(), sizeof(int64_t) * bs.size(), hipMemcpyHostToDevice, st));
+    WideArgs a;
+    std::memcpy(&a, &g->wd, sizeof(a));
+    // between batches: distances infinite, counts and masks zero
+    fill_u64<<<grid_for(n * k, 256, 4096), 256, 0, st>>>(a.dist, n * k, ~0ull);
+    fill_i32<<<grid_for(n * k, 256, 4096), 256, 0, st>>>(a.cnt, n * k, 0);
+    fill_u64<<<grid_for(7 * n, 256, 4096), 256, 0, st>>>(a.fm, 7 * n, 0ull);
+    HIP_TRY(hipGetLastError());
+    a.g.n = g->n;
+    a.g.nnz_lo = (int32_t)g->nnz;
+    a.g.row_ptr = g->row_ptr;
+    a.g.col = g->col;
+    a.g.directed = g->directed ? 1 : 0;
+    a.g.in_row_ptr = g->directed ? g->in_row_ptr : g->row_ptr;
+    a.g.in_col = g->directed ? g->in_col : g->col;
+    a.g.hv_vtx = g->hv_vtx;
+    a.g.hv_seg = g->hv_seg;
+    a.g.n_heavy = g->n_heavy;
+    a.wt = g->wt;
+    a.ctl = g->ctl;
+    a.shift = k == 8 ? 6 : (k == 16 ? 7 : (k == 32 ? 8 : 9));
+    a.bc = g->bc;
+    a.srcs = g->srcs;
+    a.batch_start = g->bstart;
+    a.ovf_list = g->ovf;
+    a.ovf_cap = (uint32_t)std::min<int64_t>(g->ovf_cap, UINT32_MAX);
+    a.sigma_limit = o.sigma_limit > 0 ? (unsigned long long)o.sigma_limit : ~0ull;
+    Ctl *hc = g->ctl_host;
+    init_ctl(hc);
+    hc->mode = mode;
+    hc->phase = WP_BEGIN;
+    hc->pos = 0;
+    hc->n_items = nb;
+    if (dump && pdump >= 0) {
+        hc->dump_pos = pdump;
+        a.dump_d = dump->d64;
+        a.dump_sig = dump->sig;
+        a.dump_delta = dump->delta;
+    }
+    HIP_TRY(hipMemcpyAsync(g->ctl, hc, sizeof(Ctl), hipMemcpyHostToDevice, st));
+    RunCfg cfg{};
+    cfg.engine = 128;
+    cfg.mode = mode;
+    cfg.grid = g->grid_wide;
+    cfg.chunk = 16;
+    cfg.use_graphs = !(o.flags & BC_RUN_NO_GRAPHS);
+    int64_t launches = 0;
+    double dev_ms = 0.0;
+    const int64_t max_steps = (nb + 1) * (3 * (n + 4) + 8) + 64;
+    s = drive(g, a, mode ? wide_step<1> : wide_step<0>, cfg, st, max_steps, &launches, &dev_ms);
+    g->stats.launches += launches;
+    if (s != BC_OK) return s;
+    HIP_TRY(hipMemcpyAsync(hc, g->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipStreamSynchronize(st));
+    if (hc->err & ERR_SIGMA_RANGE) return fail(BC_ERR_SIGMA_RANGE, "FP64 path counts left the double range");
+    if (hc->err) return fail(BC_ERR_DEVICE, "weighted engine capacity error");
+    if (hc->phase != PH_DONE) return fail(BC_ERR_DEVICE, "run ended before the state machine finished");
+    if (hc->n_ovf) {
+        ovf->resize(hc->n_ovf);
+        HIP_TRY(hipMemcpyAsync(ovf->data(), g->ovf, sizeof(int64_t) * hc->n_ovf, hipMemcpyDeviceToHost, st));
+        HIP_TRY(hipStreamSynchronize(st));
+        for (int64_t &q : *ovf) q = pos[q];
+        std::sort(ovf->begin(), ovf->end());
+    }
+    if (pdump >= 0 && dump) *dumped = hc->dump_state == 2;
+    bc_stats &S = g->stats;
+    S.mode_launches[mode] += launches;
+    S.mode_ms[mode] += dev_ms;
+    S.n_batches += (int64_t)hc->st_batches;
+    S.forward_levels += (int64_t)hc->st_fwd_levels;
+    S.steps += (int64_t)hc->st_var[0];
+    S.max_levels = std::max<int64_t>(S.max_levels, (int64_t)hc->st_max_levels);
+    S.arcs_scanned += (int64_t)hc->st_parcs[WP_RELAX];
+    const int64_t later = (int64_t)(hc->st_parcs[WP_MARK] + hc->st_parcs[WP_DAG] + hc->st_parcs[WP_BWD]);
+    const int64_t pairs = (int64_t)(hc->st_plarcs[WP_MARK] + hc->st_plarcs[WP_DAG] + hc->st_plarcs[WP_BWD]);
+    S.lane_arcs += later;
+    S.phase_lane_arcs[1] += (int64_t)hc->st_plarcs[WP_RELAX];
+    S.phase_lane_arcs[2] += pairs;
+    S.reached_pairs += (int64_t)hc->st_lane_entries;
+    S.phase_ms[1] += (double)hc->st_ticks[WP_RELAX] / g->clock_khz;
+    S.phase_ms[2] += (double)(hc->st_ticks[WP_MARK] + hc->st_ticks[WP_DAG]) / g->clock_khz;
+    S.phase_ms[3] += (double)(hc->st_ticks[WP_BWD] + hc->st_ticks[WP_BC]) / g->clock_khz;
+    S.mode_algo_bytes[mode] += algo_bytes_wbatch((double)hc->st_parcs[WP_RELAX] + (double)later,
+                                                 (double)hc->st_plarcs[WP_RELAX] + (double)pairs,
+                                                 (double)hc->st_lane_entries);
+    return BC_OK;
+}
+
 static bc_status run_weighted(bc_graph *g, const int32_t *src, int64_t ns, const bc_run_options &o, hipStream_t st,
                               int64_t dump_index, DumpBufs *db, int *dump_mode) {
     std::vector<int64_t> all((size_t)ns), ovf, none;
     for (int64_t i = 0; i < ns; ++i) all[i] = i;
     bool dumped = false;
     const bool force = (o.flags & BC_RUN_FORCE_F64) != 0;
-    bc_status s = weighted_pass(g, force ? 1 : 0, o, src, all, dump_index, db, st, &ovf, &dumped);
+    // unless the caller asks for a batch per workgroup, the whole GPU works on
+    // one batch at a time
+    bool wide = false;
+    bc_status s = BC_OK;
+    if (o.weighted_lanes == 0 && ns > 0 && wide_pays(g, ns)) s = ensure_wide(g, wide_lanes(ns), st, &wide);
+    if (s != BC_OK) return s;
+    const auto run_sources = wide ? wide_pass : weighted_pass;
+    s = run_sources(g, force ? 1 : 0, o, src, all, dump_index, db, st, &ovf, &dumped);
     if (s != BC_OK) return s;
     *dump_mode = force ? 1 : 0;
     if (force) {
@@ -1946,7 +2232,7 @@ static bc_status run_weighted(bc_graph *g, const int32_t *src, int64_t ns, const
     }
     if (!ovf.empty()) {
         bool dumped2 = false;
-        s = weighted_pass(g, 1, o, src, ovf, dump_index, db, st, &none, &dumped2);
+        s = run_sources(g, 1, o, src, ovf, dump_index, db, st, &none, &dumped2);
         if (s != BC_OK) return s;
         if (dumped2) *dump_mode = 1;
     }

@@ -32,6 +32,14 @@
 // reproducible.
 #include "bc_common.h"
 
+#ifndef BC_UNROLL
+#define BC_UNROLL 8
+#endif
+namespace bcx {
+constexpr int kUnroll = BC_UNROLL;  // matched neighbours whose rows are loaded together
+}
+#include "bc_rows.h"
+
 namespace bcx {
 
 // ------------------------------------------------------------------ pieces
@@ -62,158 +70,6 @@ __device__ __forceinline__ void push_arcs_wave(const BatchArgs &a, unsigned long
     }
 }
 
-// Per-source values live in vertex-major slabs [n][64]: path count, c and
-// delta of vertex v for lane k at v * 64 + k.  Each (vertex, lane) pair is on
-// exactly one level of a batch, so the slot is written once per batch and
-// read only through a matching level tag and lane mask; nothing is cleared.
-__device__ __forceinline__ unsigned long long readlane_u64(unsigned long long x, int j) {
-    const unsigned lo = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)x, j);
-    const unsigned hi = (unsigned)__builtin_amdgcn_readlane((int)(unsigned)(x >> 32), j);
-    return ((unsigned long long)hi << 32) | lo;
-}
-
-// A slab row read or written for the lanes of a wavefront-uniform mask: the
-// row is a buffer of 512 bytes whose address sits in scalar registers, and a
-// lane outside the mask takes an offset outside the buffer, for which loads
-// return zero and stores do nothing (the buffer instructions' range check).
-// A masked row access is then one select and one memory instruction: no
-// change of the execution mask, no branch, no zeroed register.
-constexpr unsigned kNoSlot = 0xfffffff0u;
-constexpr int kRowBytes = kLanes * 8;
-typedef unsigned row_data __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ unsigned row_slot(unsigned long long m) {
-    return __builtin_amdgcn_inverse_ballot_w64(m) ? (unsigned)lane_id() * 8u : kNoSlot;
-}
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_at(unsigned long long addr) {
-    return __builtin_amdgcn_make_buffer_rsrc((void *)addr, 0, kRowBytes, 0x00020000);
-}
-__device__ __forceinline__ unsigned long long row_load(unsigned long long addr, unsigned slot) {
-    const row_data d = __builtin_amdgcn_raw_buffer_load_b64(row_at(addr), (int)slot, 0, 0);
-    return ((unsigned long long)d.y << 32) | d.x;
-}
-__device__ __forceinline__ void row_store(unsigned long long addr, unsigned slot, unsigned long long v) {
-    row_data d;
-    d.x = (unsigned)v;
-    d.y = (unsigned)(v >> 32);
-    __builtin_amdgcn_raw_buffer_store_b64(d, row_at(addr), (int)slot, 0, 0);
-}
-__device__ __forceinline__ unsigned long long row_addr(const void *slab, int v) {
-    return (unsigned long long)slab + ((unsigned long long)(unsigned)v << 9);
-}
-
-// A frontier word in one 16-byte load (tag and mask together).
-__device__ __forceinline__ unsigned long long tagged_lanes(const Tagged *fw, int u, uint32_t T, unsigned long long m) {
-    const uint4 f = *reinterpret_cast<const uint4 *>(fw + u);
-    return f.z == T ? ((((unsigned long long)f.y << 32) | f.x) & m) : 0ull;
-}
-
-// What a path-count or backward sum adds up, in the order of the arcs.
-enum : int { OP_U64 = 0, OP_F64 = 1, OP_C = 2 };
-template <int OP>
-struct RowSum {
-    unsigned long long lo = 0;  // OP_U64: 64-bit sum and its carries (fewer than 2^31 terms)
-    unsigned hi = 0;
-    double d = 0.0;             // OP_F64: counts scaled by 2^-sh; OP_C: c values
-    __device__ __forceinline__ void add(unsigned long long v, int sh) {
-        if (OP == OP_U64) {
-            lo += v;
-            hi += (lo < v) ? 1u : 0u;
-        } else if (OP == OP_F64) {
-            d += ldexp(as_f64(v), -sh);
-        } else {
-            d += as_f64(v);
-        }
-    }
-    __device__ __forceinline__ void clear() {
-        lo = 0;
-        hi = 0;
-        d = 0.0;
-    }
-};
-
-#ifndef BC_UNROLL
-#define BC_UNROLL 8
-#endif
-constexpr int kUnroll = BC_UNROLL;  // matched neighbours whose rows are loaded together
-
-// The rows of up to kUnroll matches of a chunk (bal: lanes whose arc's far
-// end matches, in arc order; xj: its lanes; rj: its row; ownj: the group entry
-// of the arc) are requested together, then handed to use(value, owner) in arc
-// order.  Everything but the values is wavefront-uniform; a slot beyond the
-// last match loads nothing (its value is zero) and repeats the owner before.
-template <class Use>
-__device__ __forceinline__ void take_matches(unsigned long long &bal, unsigned long long xj, unsigned long long rj,
-                                             int ownj, Use use) {
-    unsigned long long val[kUnroll];
-    int own[kUnroll];
-    static_assert(kUnroll % 4 == 0, "matches are taken four at a time");
-#pragma unroll
-    for (int h = 0; h < kUnroll; h += 4) {
-        own[h] = -1;
-        if (h && !bal) continue;
-#pragma unroll
-        for (int q = h; q < h + 4; ++q) {
-            const int j = bal ? __ffsll(bal) - 1 : 0;
-            const unsigned long long x = bal ? readlane_u64(xj, j) : 0ull;
-            own[q] = bal ? __builtin_amdgcn_readlane(ownj, j) : own[q > h ? q - 1 : h];
-            bal &= bal - 1;
-            val[q] = row_load(readlane_u64(rj, j), row_slot(x));
-        }
-    }
-#pragma unroll
-    for (int h = 0; h < kUnroll; h += 4) {
-        if (h && own[h] < 0) break;
-#pragma unroll
-        for (int q = h; q < h + 4; ++q) use(val[q], own[q]);
-    }
-}
-
-// Counters of a wavefront's path-count or backward items.
-struct ArcCounters {
-    unsigned long long larcs = 0, arcs = 0, pairs = 0;
-};
-
-// Sum over arcs [a0, a1) (one entry's, wavefront-uniform bounds) of the rows
-// of the far ends that carry tag T, for the lanes of m; lane k accumulates
-// source k's value in CSR order.  The next chunk's frontier words and the
-// column indices after them are requested before this chunk's rows.
-template <int OP>
-__device__ __forceinline__ void row_arcs(const Tagged *fw, uint32_t T, unsigned long long m, int a0, int a1, int sh,
-                                         const int32_t *__restrict__ col, const void *slab, RowSum<OP> &acc,
-                                         ArcCounters &ac) {
-    if (a0 >= a1) return;
-    const int lane = lane_id();
-    int u = col[min(a0 + lane, a1 - 1)];
-    int un = col[min(a0 + kWave + lane, a1 - 1)];
-    unsigned long long f = tagged_lanes(fw, u, T, m);
-    unsigned larcs = 0, pairs = 0;
-    for (int eb = a0; eb < a1; eb += kWave) {
-        const unsigned long long xj = eb + lane < a1 ? f : 0ull;
-        const unsigned long long rj = row_addr(slab, u);
-        unsigned long long bal = __ballot(xj != 0ull);
-        if (eb + kWave < a1) {
-            u = un;
-            f = tagged_lanes(fw, u, T, m);
-            un = col[min(eb + 2 * kWave + lane, a1 - 1)];
-        }
-        larcs += (unsigned)__popcll(xj);
-        pairs += (unsigned)__popcll(bal);
-        while (bal) take_matches(bal, xj, rj, 0, [&](unsigned long long v, int) { acc.add(v, sh); });
-    }
-    ac.larcs += larcs;
-    if (lane == 0) {
-        ac.pairs += pairs;
-        ac.arcs += (unsigned)(a1 - a0);
-    }
-}
-
-// Per-lane counters the path-count finalisation feeds.
-struct SigCounters {
-    unsigned long long edges = 0, act = 0, ovf = 0, full_n = 0, full_m = 0, lent = 0;
-    int maxe = INT_MIN, mine = INT_MAX;
-    ArcCounters ac;
-};
-
 // New vertex w (queue position p, visited/next words vis/m, degree deg)
 // joins the level-(l+1) frontier; called by one thread per entry.
 __device__ __forceinline__ void sig_publish(const BatchArgs &a, Tagged *fw_nxt, uint32_t T1, int p, int w,
@@ -237,188 +93,12 @@ __device__ __forceinline__ void sig_publish(const BatchArgs &a, Tagged *fw_nxt, 
     }
 }
 
-// Store the path counts s of a new vertex (lanes m, row address ra).
-template <int OP>
-__device__ __forceinline__ void sig_store(const RowSum<OP> &s, unsigned long long m, unsigned long long ra,
-                                          unsigned long long limit, unsigned long long &ovf, SigCounters &sc) {
-    row_store(ra, row_slot(m), OP == OP_U64 ? s.lo : as_u64(s.d));
-    if (OP == OP_U64) {
-        // (lanes outside m hold a zero sum)
-        ovf |= __ballot(s.hi != 0u || s.lo > limit);
-    } else if (s.d > 0.0) {
-        int ex;
-        frexp(s.d, &ex);
-        sc.maxe = max(sc.maxe, ex);
-        sc.mine = min(sc.mine, ex);
-    }
-}
-
-// Dependencies of one (vertex, lane) from the sum acc of its successors' c:
-// delta, and c = (1 + delta) / sigma.
-template <int MODE>
-__device__ __forceinline__ void bwd_values(unsigned long long raw, double acc, int sh, int shn, double &delta,
-                                           double &c) {
-    const double sv = MODE ? ldexp(as_f64(raw), -sh) : (double)raw;
-    delta = sv * acc;
-    if (MODE) delta = ldexp(delta, -shn);
-    c = (1.0 + delta) / sv;
-}
-
-// Packing of up to kBudget / 2 entries into one list of positions (arcs, or
-// (entry, source) pairs), 64 positions to a chunk.  A bit per position marks
-// where an entry starts; an entry's record is found by counting the starts up
-// to a position: one broadcast read of the word and one read of the record per
-// chunk (searching the prefix sums across lanes took six dependent LDS
-// round trips and five more to fetch the entry's values).
-constexpr int kPack = 64;                // entries of degree <= kPack are packed
-constexpr int kPackEntries = kBudget / 2;
-constexpr int kPackWords = kPackEntries + 4;  // up to 64 positions per entry
-struct Packing {
-    unsigned long long start[kPackWords];
-    uint4 rec[kPackEntries];
-    uint4 rec2[kPackEntries];
-};
-
 // LDS scratch of one wavefront, one use at a time.
 union WaveScratch {
     Stage st;                   // discover: staged queue entries
     Packing pk;                 // path counts and backward
     double tile[kWave * 8];     // score accumulation: 64 rows x 8 lanes
 };
-
-__device__ __forceinline__ void wave_lds_fence() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Enter the packing: this lane's entry covers cnt positions (0: not packed)
-// and has the records r and r2.  Returns the number of positions (uniform) and this
-// entry's first one in off.
-__device__ __forceinline__ int pack_entries(Packing &pk, int cnt, uint4 r, uint4 r2, int &off) {
-    const int incl = wave_incl_scan(cnt);
-    off = incl - cnt;
-    const int total = __builtin_amdgcn_readlane(incl, 63);
-    for (int i = lane_id(); i < (total + 63) / 64; i += kWave) pk.start[i] = 0ull;
-    wave_lds_fence();
-    const unsigned long long on = __ballot(cnt > 0);
-    if (cnt > 0) {
-        const int rank = (int)lanes_below(on);
-        r.x -= (unsigned)off;  // arc of position i: r.x + i
-        r2.z = (unsigned)off;
-        pk.rec[rank] = r;
-        pk.rec2[rank] = r2;
-        atomicOr(&pk.start[off >> 6], 1ull << (off & 63));
-    }
-    wave_lds_fence();
-    return total;
-}
-// Rank of the entry that holds position 64 * c + lane; before = entries that
-// start before chunk c (advanced to the next chunk).
-__device__ __forceinline__ int packed_rank(const Packing &pk, int c, int &before) {
-    const unsigned long long w = readlane_u64(pk.start[c], 0);
-    const int lane = lane_id();
-    const int r = before + (int)lanes_below(w) + (int)((w >> lane) & 1ull) - 1;
-    before += __popcll(w);
-    return r;
-}
-
-// Index of the j-th set bit (j counted from 0) of m; m has more than j bits.
-__device__ __forceinline__ int nth_set_bit(unsigned long long m, int j) {
-    for (; j > 0; --j) m &= m - 1;
-    return __ffsll(m) - 1;
-}
-
-// Sums of a group's packed entries: every entry's arcs in CSR order, 64 arcs
-// of the list per chunk; fin(owner lane, sum) is called when an entry's last
-// match has been added (an entry without matches is passed over).  Returns
-// with the last entry's sum in acc and its lane in cur (-1: no match at all).
-// Pipelined like row_arcs: what a chunk needs (record, column, frontier word)
-// is requested one chunk ahead.
-template <int OP, class Fin>
-__device__ __forceinline__ void row_packed(const Packing &pk, int total, const Tagged *fw, uint32_t T, int sh,
-                                           const int32_t *__restrict__ col, const void *slab, RowSum<OP> &acc,
-                                           int &cur, ArcCounters &ac, Fin fin) {
-    const int lane = lane_id();
-    cur = -1;
-    if (total == 0) return;
-    int before = 0;
-    unsigned larcs = 0, pairs = 0;
-    // positions beyond the last one read the last entry's record and its last arc
-    uint4 r = pk.rec[packed_rank(pk, 0, before)];
-    int u = col[(int)r.x + min(lane, total - 1)];
-    unsigned long long f = tagged_lanes(fw, u, T, ((unsigned long long)r.z << 32) | r.y);
-    int own = (int)r.w;
-    uint4 rn = r;
-    int un = u;
-    if (kWave < total) {
-        rn = pk.rec[packed_rank(pk, 1, before)];
-        un = col[(int)rn.x + min(kWave + lane, total - 1)];
-    }
-    for (int base = 0; base < total; base += kWave) {
-        const unsigned long long xj = base + lane < total ? f : 0ull;
-        const unsigned long long rj = row_addr(slab, u);
-        const int ownj = own;
-        unsigned long long bal = __ballot(xj != 0ull);
-        if (base + kWave < total) {
-            u = un;
-            own = (int)rn.w;
-            f = tagged_lanes(fw, u, T, ((unsigned long long)rn.z << 32) | rn.y);
-            if (base + 2 * kWave < total) {
-                rn = pk.rec[packed_rank(pk, base / kWave + 2, before)];
-                un = col[(int)rn.x + min(base + 2 * kWave + lane, total - 1)];
-            }
-        }
-        larcs += (unsigned)__popcll(xj);
-        pairs += (unsigned)__popcll(bal);
-        while (bal) {
-            take_matches(bal, xj, rj, ownj, [&](unsigned long long v, int o) {
-                if (o != cur) {
-                    if (cur >= 0) fin(cur, acc);
-                    acc.clear();
-                    cur = o;
-                }
-                acc.add(v, sh);
-            });
-        }
-    }
-    ac.larcs += larcs;
-    if (lane == 0) {
-        ac.pairs += pairs;
-        ac.arcs += (unsigned)total;
-    }
-}
-
-// Entry-lane items: when the entries of a group carry few sources each, the
-// per-source sums run one thread per (entry, source) pair instead of one
-// wavefront lane per source: each thread scans its entry's arcs [e0, e1)
-// on its own and reads only source k's value of each matched far end.  Four
-// arcs are followed at once (columns, then words, then values), and
-// use(value) is called in CSR order, so the sum has the same bits as in the
-// per-lane form.  Returns the matches.
-template <class Use>
-__device__ __forceinline__ unsigned item_arcs(const Tagged *fw, uint32_t T, int k, int e0, int e1,
-                                              const int32_t *__restrict__ col, const unsigned long long *slab,
-                                              Use use) {
-    unsigned matched = 0;
-    for (int e = e0; e < e1; e += 4) {
-        int u[4];
-        bool on[4];
-        unsigned long long v[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) u[q] = col[min(e + q, e1 - 1)];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) on[q] = e + q < e1 && tagged_lanes(fw, u[q], T, 1ull << k) != 0ull;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = on[q] ? slab[(size_t)u[q] * kLanes + k] : 0ull;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            if (on[q]) use(v[q]);
-            matched += on[q] ? 1u : 0u;
-        }
-    }
-    return matched;
-}
 
 // Path counts for the entries [i0, i1) of level l+1 (one group):
 // entries of degree <= kPack have their adjacencies packed into dense 64-arc
@@ -508,7 +188,7 @@ __device__ __forceinline__ void sig_group(const BatchArgs &a, const Tagged *fw_c
         auto fin = [&](int e, const RowSum<OP> &s) {
             sig_store<OP>(s, readlane_u64(nxt, e), readlane_u64(ra, e), limit, ovf, sc);
         };
-        row_packed<OP>(pk, total, fw_cur, T, sh, col, a.sigma, acc, cur, sc.ac, fin);
+        row_packed<OP>(pk, total, TagLanes{fw_cur, T}, sh, col, a.sigma, acc, cur, sc.ac, fin);
         if (cur >= 0) fin(cur, acc);
     }
     // medium-degree entries: one wavefront-wide scan each
@@ -517,7 +197,7 @@ __device__ __forceinline__ void sig_group(const BatchArgs &a, const Tagged *fw_c
         const int a0 = __builtin_amdgcn_readlane(e0, j), dj = __builtin_amdgcn_readlane(na, j);
         const unsigned long long mj = readlane_u64(nxt, j);
         RowSum<OP> acc;
-        row_arcs<OP>(fw_cur, T, mj, a0, a0 + dj, sh, col, a.sigma, acc, sc.ac);
+        row_arcs<OP>(TagLanes{fw_cur, T}, mj, a0, a0 + dj, sh, col, a.sigma, acc, sc.ac);
         sig_store<OP>(acc, mj, readlane_u64(ra, j), limit, ovf, sc);
     }
     sc.ovf |= ovf;
@@ -590,7 +270,7 @@ __device__ __forceinline__ void bwd_group(const BatchArgs &a, const Tagged *fb_n
             row_store(row_addr(a.delta, __builtin_amdgcn_readlane(v, e)), row_slot(readlane_u64(M, e)), as_u64(s.d));
             parked |= 1ull << e;
         };
-        row_packed<OP_C>(pk, total, fb_nxt, TB + 1u, 0, col, a.chat, acc, cur, ac, fin);
+        row_packed<OP_C>(pk, total, TagLanes{fb_nxt, TB + 1u}, 0, col, a.chat, acc, cur, ac, fin);
         if (cur >= 0) fin(cur, acc);
         todo = __ballot(light && M != 0ull);
     }
@@ -599,33 +279,12 @@ __device__ __forceinline__ void bwd_group(const BatchArgs &a, const Tagged *fb_n
         const int a0 = __builtin_amdgcn_readlane(e0, j), dj = __builtin_amdgcn_readlane(na, j);
         const unsigned long long mj = readlane_u64(M, j);
         RowSum<OP_C> acc;
-        row_arcs<OP_C>(fb_nxt, TB + 1u, mj, a0, a0 + dj, 0, col, a.chat, acc, ac);
+        row_arcs<OP_C>(TagLanes{fb_nxt, TB + 1u}, mj, a0, a0 + dj, 0, col, a.chat, acc, ac);
         row_store(row_addr(a.delta, __builtin_amdgcn_readlane(v, j)), row_slot(mj), as_u64(acc.d));
         parked |= 1ull << j;
         todo |= 1ull << j;
     }
-    while (todo) {
-        unsigned long long raw[4], sum[4], mq[4];
-        int vq[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int j = todo ? __ffsll(todo) - 1 : 0;
-            mq[q] = todo ? readlane_u64(M, j) : 0ull;
-            vq[q] = __builtin_amdgcn_readlane(v, j);
-            todo &= todo - 1;
-            raw[q] = row_load(row_addr(a.sigma, vq[q]), row_slot(mq[q]));
-            // an entry without a match has no sum: zero
-            sum[q] = row_load(row_addr(a.delta, vq[q]), row_slot((parked >> j) & 1ull ? mq[q] : 0ull));
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const unsigned slot = row_slot(mq[q]);
-            double delta, c;
-            bwd_values<MODE>(raw[q], as_f64(sum[q]), sh, shn, delta, c);
-            row_store(row_addr(a.chat, vq[q]), slot, as_u64(c));
-            row_store(row_addr(a.delta, vq[q]), slot, as_u64(delta));
-        }
-    }
+    bwd_finish<MODE>(todo, parked, M, v, a.sigma, a.chat, a.delta, sh, shn);
     if (light || medium) {
         Tagged tg;
         tg.mask = Mf;
@@ -1094,7 +753,7 @@ __device__ __forceinline__ void batch_step_body(const BatchArgs &a, const unsign
             const unsigned long long m = uniform(a.vn[w].nxt);
             const int a0 = e0 + s * kSeg, a1 = max(a0, min(e1, a0 + kSeg));
             RowSum<OP> sum;
-            row_arcs<OP>(fw_cur, T, m, a0, a1, sh, a.g.in_col, a.sigma, sum, sc.ac);
+            row_arcs<OP>(TagLanes{fw_cur, T}, m, a0, a1, sh, a.g.in_col, a.sigma, sum, sc.ac);
             const size_t slot = (size_t)(s0 + s) * kLanes + lane;
             if (MODE == 0) {
                 part_store(&a.hq.part_lo[slot], sum.lo);
@@ -1165,7 +824,7 @@ __device__ __forceinline__ void batch_step_body(const BatchArgs &a, const unsign
             const int e0 = uniform(rp[v]), e1 = uniform(rp[v + 1]);  // successors: out-arcs
             const int a0 = e0 + s * kSeg, a1 = max(a0, min(e1, a0 + kSeg));
             RowSum<OP_C> sum;
-            if (M) row_arcs<OP_C>(fb_nxt, TB + 1u, M, a0, a1, 0, col, a.chat, sum, ac);
+            if (M) row_arcs<OP_C>(TagLanes{fb_nxt, TB + 1u}, M, a0, a1, 0, col, a.chat, sum, ac);
             part_store(&a.hq.part_lo[(size_t)(s0 + s) * kLanes + lane], as_u64(sum.d));
             const int ns = n_segments(uniform(class_deg(a.g, v, e1 - e0)));
             if (!seg_arrive(&a.hq.cnt[h], ns)) continue;

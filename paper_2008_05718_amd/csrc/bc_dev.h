@@ -143,6 +143,9 @@ struct Ctl {
     int32_t f64_check;    // batched FP64 pass: hand back lanes whose counts stay below 2^65
     int32_t lane_E[64];   // batched FP64: power of two of the current level's stored counts, per lane
     int32_t lane_emax[64];  // batched FP64: largest binary exponent of a true count so far, per lane
+    // --- wide weighted engine: the relaxation queue of the current round
+    uint32_t w_cnt, w_groups;   // entries, work groups
+    int32_t w_heavy, w_hsegs;   // heavy entries, their segments
     // --- heavy entries of the level under construction: count | segments << 32
     unsigned long long next_hq;
     // --- per-slot counters and workgroup arrivals of the running step
@@ -417,6 +420,55 @@ struct WeightedArgs {
                               // [3] reached pairs, [4] DAG-pass arcs, [5] relaxation (arc, source)
                               // pairs, [6] DAG-pass (arc, source) pairs, [7..9] clock ticks of the
                               // three phases, [10] longest batch (the last six: lane batches)
+};
+
+// Wide weighted engine (bc_wide.hip): up to 64 sources traversed together by
+// the whole GPU.
+enum : int32_t {
+    WP_RELAX = 1,  // one relaxation round
+    WP_MARK = 2,   // shortest-path arcs and in-arc counts
+    WP_DAG = 3,    // one round of ready vertices: path counts, release of successors
+    WP_BWD = 4,    // dependencies of one round
+    WP_BC = 5,     // scores, reset
+    WP_DUMP = 6,   // copy one source's values out (detail runs only)
+    WP_BEGIN = 7,  // set up the next batch
+};
+struct WideArgs {
+    GraphArgs g;
+    const int32_t *wt;           // weights of the out-arcs
+    const int32_t *rev;          // out-arc -> the same arc's position among the in-arcs
+    Ctl *ctl;
+    int32_t shift;               // log2 of a row's bytes (8 bytes per source of a batch)
+    unsigned long long *dist, *sigma;  // rows of uint64 (sigma: FP64 bits in mode 1)
+    double *chat, *delta;
+    int32_t *cnt;                // rows of DAG in-arcs not yet released (0 between batches)
+    unsigned long long *fm, *rdy;  // [3][n] lane masks of the rounds' queues: read, written, cleared in turn
+    unsigned long long *rm;      // [n] lanes that reached the vertex
+    unsigned long long *dag_out, *dag_in;  // [nnz] lanes for which the out-arc / in-arc is on a shortest path
+    int32_t *rq;                 // [3][n] relaxation queues
+    uint32_t *rgs;               // [3][rgcap] their group starts
+    uint32_t rgcap, rhcap;
+    HeavyQ rhq;                  // [3][rhcap] their heavy entries
+    const uint32_t *sgs;         // group starts over all vertices in order
+    int32_t n_sgroups;
+    int32_t *lq_vtx;             // DAG rounds: entries
+    unsigned long long *lq_mask;
+    uint32_t lq_cap;
+    int32_t *level_off;          // [max_levels + 2]
+    int32_t max_levels;
+    uint32_t *gstart, *gbase;
+    uint32_t gcap;
+    HeavyQ hq;
+    double *bc;
+    const int32_t *srcs;
+    const int64_t *batch_start;
+    int32_t *lane_src;           // [64]
+    int64_t *ovf_list;
+    uint32_t ovf_cap;
+    unsigned long long sigma_limit;
+    int64_t *dump_d;
+    unsigned long long *dump_sig;
+    double *dump_delta;
 };
 
 }  // namespace bcx
