@@ -487,7 +487,7 @@ bc_status bc_mlp_train(float *weights, const float *X, const float *Y, const uin
  * harnesses that forbid hipMalloc.  Same kernels, same result bits.
  *   weights, X, Y, mask   DEVICE pointers, layouts as above; read only.
  *   n                     1 <= n <= 16384 samples, else BC_ERR_INVALID_ARG
- *                         (the intermediates live in a fixed 9.0 MB array of
+ *                         (the intermediates live in a fixed 1.6 MB array of
  *                         the library, one per GPU, kept for the process).
  *   loss, grad            DEVICE pointers to float[1] and float[BC_MLP_PARAMS].
  * The work is enqueued on `stream` and the call returns without waiting:
