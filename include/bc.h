@@ -221,7 +221,8 @@ typedef struct bc_run_options {
     int32_t replicas;     /* single graphs, batched engine: level state machines run
                              concurrently, each with its own per-vertex state and
                              batches dealt to them in turn (0 = by size: 8 up to
-                             2^19 vertices, 4 above; 1 = one; at most 16; autotuned).
+                             2^19 vertices for lists of at least 64 batches, else
+                             4; 1 = one; at most 16; autotuned).
                              Scores agree to rounding across values; a given value
                              repeats bit for bit (BC_RUN_ONE_QUEUE: one, whatever
                              this says). */

@@ -20,7 +20,7 @@
 namespace bcx {
 template <int MODE> __global__ void plain_step(PlainArgs a);
 template <int MODE> __global__ void batch_step(BatchArgs a);
-template <int MODE> __global__ void block_run(BlockArgs a);
+template <int MODE, int NW> __global__ void block_run(BlockArgs a);
 template <int MODE> __global__ void weighted_run(WeightedArgs a);
 template <int MODE> __global__ void wbatch_run(WeightedArgs a);
 template <int MODE> __global__ void wide_step(WideArgs a);
@@ -306,6 +306,7 @@ struct SubPart {
     int32_t *to_parent = nullptr;           // device int32[h->n]
     std::vector<int32_t> to_parent_host;
     hipStream_t stream = nullptr;
+    bool ran = false;                       // had sources in the last run
 };
 
 static void free_graphs(bc_graph *g) {
@@ -939,8 +940,10 @@ static bc_status get_graph(bc_graph *g, const Args &args, void (*kern)(Args), co
     HIP_TRY(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
     Args argcopy = args;
     void *kargs[] = {(void *)&argcopy};
-    for (int i = 0; i < cfg.chunk; ++i)
+    for (int i = 0; i < cfg.chunk; ++i) {
+        argcopy.parity = i & 1;
         (void)hipLaunchKernel((const void *)kern, dim3(cfg.grid), dim3(kBlock), kargs, 0, cs);
+    }
     // flag readback at the end of the chunk
     (void)hipMemcpyAsync(g->flag_host, g->ctl, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, cs);
     hipError_t e = hipStreamEndCapture(cs, &cg.graph);
@@ -961,9 +964,12 @@ static bc_status get_graph(bc_graph *g, const Args &args, void (*kern)(Args), co
 }
 
 // Launch chunks of step kernels until the device state machine reports done.
+// Launches alternate in parity (see Ctl), so a chunk holds an even number.
 template <typename Args>
-static bc_status drive(bc_graph *g, const Args &args, void (*kern)(Args), const RunCfg &cfg, hipStream_t st,
+static bc_status drive(bc_graph *g, const Args &args, void (*kern)(Args), const RunCfg &cfg_in, hipStream_t st,
                        int64_t max_steps, int64_t *launches, double *dev_ms) {
+    RunCfg cfg = cfg_in;
+    cfg.chunk += cfg.chunk & 1;
     hipGraphExec_t exec = nullptr;
     if (cfg.use_graphs) {
         bc_status s = get_graph(g, args, kern, cfg, st, &exec);
@@ -1008,8 +1014,10 @@ static bc_status drive(bc_graph *g, const Args &args, void (*kern)(Args), const 
         } else {
             Args argcopy = args;
             void *kargs[] = {(void *)&argcopy};
-            for (int i = 0; i < cfg.chunk; ++i)
+            for (int i = 0; i < cfg.chunk; ++i) {
+                argcopy.parity = i & 1;
                 (void)hipLaunchKernel((const void *)kern, dim3(cfg.grid), dim3(kBlock), kargs, 0, st);
+            }
             hipError_t e = hipMemcpyAsync(g->flag_host, g->ctl, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, st);
             if (e != hipSuccess) { result = fail(BC_ERR_DEVICE, std::string("flag copy: ") + hipGetErrorString(e)); break; }
         }
@@ -1032,13 +1040,16 @@ static bc_status drive(bc_graph *g, const Args &args, void (*kern)(Args), const 
     return result;
 }
 
-static void init_ctl(Ctl *c) {
+// A control block before its first launch (parity 0); returns the state to fill in.
+static Head *init_ctl(Ctl *c) {
     std::memset(c, 0, sizeof(*c));
-    c->dump_pos = -1;
-    c->dump_lane = -1;
-    c->maxexp = INT_MIN;
-    c->minexp = INT_MAX;
+    c->h[0].dump_pos = -1;
+    c->h[0].dump_lane = -1;
+    return &c->h[0];
 }
+
+// The state written last: steps only grow.
+static const Head &last_head(const Ctl &c) { return c.h[c.h[1].st_steps > c.h[0].st_steps ? 1 : 0]; }
 
 static PolicyArgs policy_args(const bc_graph *g, const bc_run_options &o) {
     PolicyArgs p;
@@ -1089,7 +1100,7 @@ static double algo_bytes_wbatch(double entry_arcs, double lane_arcs, double reac
     return 8.0 * entry_arcs + 8.0 * lane_arcs + 64.0 * reached;
 }
 
-static void accumulate_stats(bc_stats *s, const Ctl &c, double clock_khz) {
+static void accumulate_stats(bc_stats *s, const Head &c, double clock_khz) {
     for (int i = 0; i < kPhases; ++i) s->phase_ms[i] += (double)c.st_ticks[i] / clock_khz;
     for (int i = 0; i < 3; ++i) s->variant_ms[i] += (double)c.st_vticks[i] / clock_khz;
     for (int i = 0; i < kPhases; ++i) {
@@ -1126,7 +1137,7 @@ struct CollectBufs {
 
 static bc_status run_pass(bc_graph *g, const RunCfg &cfg, const bc_run_options &o, const int32_t *h_srcs,
                           int64_t ns, int64_t dump_pos, DumpBufs *dump, hipStream_t st,
-                          std::vector<int64_t> *ovf_positions, int *dump_done, Ctl *ctl_out,
+                          std::vector<int64_t> *ovf_positions, int *dump_done, Head *ctl_out,
                           const CollectBufs *col = nullptr) {
     bc_status s;
     // engine state first: it is by far the largest allocation, so a run
@@ -1138,8 +1149,8 @@ static bc_status run_pass(bc_graph *g, const RunCfg &cfg, const bc_run_options &
     s = grow(&g->ovf, &g->ovf_cap, ns, &g->acct);
     if (s != BC_OK) return s;
     if (ns) HIP_TRY(hipMemcpyAsync(g->srcs, h_srcs, sizeof(int32_t) * ns, hipMemcpyHostToDevice, st));
-    Ctl *hc = g->ctl_host;
-    init_ctl(hc);
+    Ctl *hctl = g->ctl_host;
+    Head *hc = init_ctl(hctl);
     hc->policy = cfg.policy;
     hc->mode = cfg.mode;
     hc->f64_check = cfg.f64_check ? 1 : 0;
@@ -1167,7 +1178,7 @@ static bc_status run_pass(bc_graph *g, const RunCfg &cfg, const bc_run_options &
         hc->pos = -1;
         hc->n_items = ns;
         hc->total_queued = 0;
-        HIP_TRY(hipMemcpyAsync(g->ctl, hc, sizeof(Ctl), hipMemcpyHostToDevice, st));
+        HIP_TRY(hipMemcpyAsync(g->ctl, hctl, sizeof(Ctl), hipMemcpyHostToDevice, st));
         PlainArgs a;
         std::memset(&a, 0, sizeof(a));
         a.g = ga;
@@ -1243,7 +1254,7 @@ static bc_status run_pass(bc_graph *g, const RunCfg &cfg, const bc_run_options &
         hc->range_hi = 0;
         hc->epoch_b = 0;
         hc->n_levels = 0;
-        HIP_TRY(hipMemcpyAsync(g->ctl, hc, sizeof(Ctl), hipMemcpyHostToDevice, st));
+        HIP_TRY(hipMemcpyAsync(g->ctl, hctl, sizeof(Ctl), hipMemcpyHostToDevice, st));
         BatchArgs a;
         std::memset(&a, 0, sizeof(a));
         a.g = ga;
@@ -1295,24 +1306,25 @@ static bc_status run_pass(bc_graph *g, const RunCfg &cfg, const bc_run_options &
     }
     g->stats.launches += launches;
     if (s != BC_OK) return s;
-    HIP_TRY(hipMemcpyAsync(hc, g->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipMemcpyAsync(hctl, g->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
-    *ctl_out = *hc;
+    const Head &last = last_head(*hctl);
+    *ctl_out = last;
     const double bytes0 = algo_bytes(g->stats);
-    accumulate_stats(&g->stats, *hc, g->clock_khz);
+    accumulate_stats(&g->stats, last, g->clock_khz);
     const int mi = cfg.mode ? 1 : 0;
     g->stats.mode_launches[mi] += launches;
     g->stats.mode_ms[mi] += dev_ms;
     g->stats.mode_algo_bytes[mi] += algo_bytes(g->stats) - bytes0;
-    if (hc->err) {
+    if (hctl->err) {
         g->plain_dirty = true;
-        return ctl_error(*hc);
+        return ctl_error(*hctl);
     }
-    if (hc->phase != PH_DONE) return fail(BC_ERR_DEVICE, "run ended before the state machine finished");
-    if (dump_done) *dump_done = hc->dump_state == 2;
-    if (ovf_positions && hc->n_ovf) {
-        std::vector<int64_t> tmp(hc->n_ovf);
-        HIP_TRY(hipMemcpyAsync(tmp.data(), g->ovf, sizeof(int64_t) * hc->n_ovf, hipMemcpyDeviceToHost, st));
+    if (hctl->phase != PH_DONE) return fail(BC_ERR_DEVICE, "run ended before the state machine finished");
+    if (dump_done) *dump_done = last.dump_state == 2;
+    if (ovf_positions && last.n_ovf) {
+        std::vector<int64_t> tmp(last.n_ovf);
+        HIP_TRY(hipMemcpyAsync(tmp.data(), g->ovf, sizeof(int64_t) * last.n_ovf, hipMemcpyDeviceToHost, st));
         HIP_TRY(hipStreamSynchronize(st));
         std::sort(tmp.begin(), tmp.end());
         *ovf_positions = tmp;
@@ -1494,7 +1506,7 @@ static bc_status block_dims(bc_graph *g, int *resident) {
     int dev = 0, cus = 0, per_cu = 0;
     HIP_TRY(hipGetDevice(&dev));
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)block_run<0>, kBlock, 0));
+    HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)block_run<0, 4>, kBlock, 0));
     int64_t want = (int64_t)std::max(1, cus) * std::max(1, per_cu);
     size_t free_b = 0, total_b = 0;
     HIP_TRY(hipMemGetInfo(&free_b, &total_b));
@@ -1660,11 +1672,7 @@ static bc_status run_block(bc_graph *g, const RunCfg &cfg, const bc_run_options 
     HIP_TRY(hipMemcpyAsync(g->blk_gsum, gsum.data(), sizeof(int32_t) * gsum.size(), hipMemcpyHostToDevice, st));
     // control blocks and tags
     std::vector<Ctl> hc((size_t)nwg);
-    for (Ctl &c : hc) {
-        init_ctl(&c);
-        c.policy = cfg.policy;
-        c.mode = 0;
-    }
+    for (Ctl &c : hc) init_ctl(&c)->policy = cfg.policy;
     HIP_TRY(hipMemcpyAsync(g->blk_ctls, hc.data(), sizeof(Ctl) * hc.size(), hipMemcpyHostToDevice, st));
     {
         const BlockLayout L((size_t)dm.nmax, dm.lq_cap, (size_t)dm.max_levels, dm.gcap, dm.hq_entries, dm.hq_levels,
@@ -1711,7 +1719,7 @@ static bc_status run_block(bc_graph *g, const RunCfg &cfg, const bc_run_options 
     HIP_TRY(hipEventCreate(&e0));
     HIP_TRY(hipEventCreate(&e1));
     HIP_TRY(hipEventRecord(e0, st));
-    block_run<0><<<(unsigned)nwg, kBlock, 0, st>>>(ra);
+    block_run<0, 4><<<(unsigned)nwg, kBlock, 0, st>>>(ra);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipEventRecord(e1, st));
     HIP_TRY(hipMemcpyAsync(hc.data(), g->blk_ctls, sizeof(Ctl) * hc.size(), hipMemcpyDeviceToHost, st));
@@ -1736,9 +1744,10 @@ static bc_status run_block(bc_graph *g, const RunCfg &cfg, const bc_run_options 
     }
     const double bytes0 = algo_bytes(g->stats);
     for (int w = 0; w < used; ++w) {
-        accumulate_stats(&g->stats, hc[w], g->clock_khz);
-        if (hc[w].n_ovf) {
-            std::vector<int64_t> tmp(hc[w].n_ovf);
+        const Head &last = hc[w].h[0];
+        accumulate_stats(&g->stats, last, g->clock_khz);
+        if (last.n_ovf) {
+            std::vector<int64_t> tmp(last.n_ovf);
             const BlockLayout L((size_t)dm.nmax, dm.lq_cap, (size_t)dm.max_levels, dm.gcap, dm.hq_entries,
                                 dm.hq_levels, dm.part_cap, dm.ovf_cap);
             HIP_TRY(hipMemcpy(tmp.data(), g->blk_scratch + (size_t)w * g->blk_stride + L.ovf,
@@ -2039,7 +2048,8 @@ static bc_status ensure_wide(bc_graph *g, int k, hipStream_t st, bool *fits) {
     take(&w.rhq.pos, 3 * hcap);
     take(&w.rhq.seg, 3 * hcap);
     take(&w.rhq.cnt, 3 * hcap);
-    take(&sgs, rgcap);
+    const int64_t sgcap = (g->cost_units + n) / kBudget + 8;
+    take(&sgs, sgcap);
     take(&w.lq_vtx, lq_cap);
     take(&w.lq_mask, lq_cap);
     take(&w.level_off, 4 * ((int64_t)w.max_levels + 4));  // with the group bases and the heavy lists' offsets
@@ -2082,12 +2092,13 @@ static bc_status ensure_wide(bc_graph *g, int k, hipStream_t st, bool *fits) {
         HIP_TRY(hipMemcpyAsync(irp.data(), g->in_row_ptr, sizeof(int32_t) * irp.size(), hipMemcpyDeviceToHost, st));
     }
     HIP_TRY(hipStreamSynchronize(st));
-    std::vector<uint32_t> gs((size_t)rgcap, 0u);
+    std::vector<uint32_t> gs((size_t)sgcap, 0u);
     uint64_t cost = 0;
     for (int32_t v = 0; v < g->n; ++v) {
         int32_t d = rp[v + 1] - rp[v];
         if (g->directed) d = std::max(d, irp[v + 1] - irp[v]);
-        const uint64_t next = cost + entry_cost(d);
+        // (at least 2, so that a merged group fits a wavefront with isolated vertices, too)
+        const uint64_t next = cost + std::max(2u, entry_cost(d));
         for (uint64_t q = cost / kBudget + 1; q <= next / kBudget; ++q) gs[q] = (uint32_t)v + 1u;
         cost = next;
     }
@@ -2149,8 +2160,8 @@ static bc_status wide_pass(bc_graph *g, int mode, const bc_run_options &o, const
     a.ovf_list = g->ovf;
     a.ovf_cap = (uint32_t)std::min<int64_t>(g->ovf_cap, UINT32_MAX);
     a.sigma_limit = o.sigma_limit > 0 ? (unsigned long long)o.sigma_limit : ~0ull;
-    Ctl *hc = g->ctl_host;
-    init_ctl(hc);
+    Ctl *hctl = g->ctl_host;
+    Head *hc = init_ctl(hctl);
     hc->mode = mode;
     hc->phase = WP_BEGIN;
     hc->pos = 0;
@@ -2161,7 +2172,7 @@ static bc_status wide_pass(bc_graph *g, int mode, const bc_run_options &o, const
         a.dump_sig = dump->sig;
         a.dump_delta = dump->delta;
     }
-    HIP_TRY(hipMemcpyAsync(g->ctl, hc, sizeof(Ctl), hipMemcpyHostToDevice, st));
+    HIP_TRY(hipMemcpyAsync(g->ctl, hctl, sizeof(Ctl), hipMemcpyHostToDevice, st));
     RunCfg cfg{};
     cfg.engine = 128;
     cfg.mode = mode;
@@ -2174,11 +2185,12 @@ static bc_status wide_pass(bc_graph *g, int mode, const bc_run_options &o, const
     s = drive(g, a, mode ? wide_step<1> : wide_step<0>, cfg, st, max_steps, &launches, &dev_ms);
     g->stats.launches += launches;
     if (s != BC_OK) return s;
-    HIP_TRY(hipMemcpyAsync(hc, g->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipMemcpyAsync(hctl, g->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
-    if (hc->err & ERR_SIGMA_RANGE) return fail(BC_ERR_SIGMA_RANGE, "FP64 path counts left the double range");
-    if (hc->err) return fail(BC_ERR_DEVICE, "weighted engine capacity error");
-    if (hc->phase != PH_DONE) return fail(BC_ERR_DEVICE, "run ended before the state machine finished");
+    hc = hctl->h[1].st_steps > hctl->h[0].st_steps ? &hctl->h[1] : &hctl->h[0];
+    if (hctl->err & ERR_SIGMA_RANGE) return fail(BC_ERR_SIGMA_RANGE, "FP64 path counts left the double range");
+    if (hctl->err) return fail(BC_ERR_DEVICE, "weighted engine capacity error");
+    if (hctl->phase != PH_DONE) return fail(BC_ERR_DEVICE, "run ended before the state machine finished");
     if (hc->n_ovf) {
         ovf->resize(hc->n_ovf);
         HIP_TRY(hipMemcpyAsync(ovf->data(), g->ovf, sizeof(int64_t) * hc->n_ovf, hipMemcpyDeviceToHost, st));
@@ -2269,6 +2281,33 @@ static int n_replicas(const bc_graph *g, const bc_run_options &o) {
     return g->n <= (1 << 19) ? 8 : 4;
 }
 
+// Replicas of a run: as asked for, else four for short lists of batches
+// (R-MAT 18, 2048 sources: 32.8 ms with 4, 33.9 with 8; directed, 1000
+// sources: 16.0 against 18.6), the size's default once every one of them has
+// at least 8 batches (8192 sources: 116.4 ms with 8, 120.7 with 4).
+static int run_replicas(const bc_graph *g, const bc_run_options &o, int64_t ns) {
+    const int r = n_replicas(g, o);
+    if (o.replicas > 0 || std::getenv("BC_REPLICAS")) return r;
+    const int64_t K = o.batch >= 8 ? o.batch : 64;
+    return (ns + K - 1) / K >= 8 * (int64_t)r ? r : std::min(r, 4);
+}
+
+// Workgroups per step launch of state machines that run concurrently: two per
+// compute unit and machine, so that one machine's waves do not queue behind
+// another's (the damaged 1024^2 grid, 256 sources, 4 replicas: 106 ms with
+// 512 workgroups, 136 with 1536; R-MAT 18, 2048 sources: 32.8 against 35.3;
+// 64 preferential-attachment graphs: 109 against 127), a full launch where a
+// single step has work for all of them anyway (R-MAT 20 and up: R-MAT 22 264
+// ms with 1536, 275 with 512).
+static int concurrent_grid(const bc_graph *g) {
+    if (g->nnz >= (int64_t)1 << 24) return 0;  // the default
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        return 0;
+    return 2 * cus;
+}
+
 static bool use_parts(const bc_graph *g, const bc_run_options &o, int64_t ns) {
     if ((o.flags & BC_RUN_ONE_QUEUE) || o.batch == 1 || std::getenv("BC_ONE_QUEUE")) return false;
     if (g->parts_refused) return false;
@@ -2298,8 +2337,8 @@ static bool parts_fit(bc_graph *g, size_t need) {
 static size_t run_buffer_bytes(int64_t ns) { return (size_t)(ns + 16) * 12 + (size_t)(ns + 17) * 16; }
 
 static bc_status ensure_replicas(bc_graph *g, int R) {
-    if (!g->parts.empty() && (int)g->parts.size() == R) return BC_OK;
-    if (!g->parts.empty()) {  // another count was asked for: make them again
+    if ((int)g->parts.size() >= R) return BC_OK;  // a run uses the first R
+    if (!g->parts.empty()) {  // more are asked for: make them again
         (void)hipDeviceSynchronize();
         free_parts(g);
         g->replicas = false;
@@ -2449,7 +2488,8 @@ static bc_status ensure_parts(bc_graph *g) {
 
 static bc_status run_parts(bc_graph *g, const int32_t *sources, int64_t n_sources, const bc_run_options &o,
                            void *stream, int64_t dump_index, bc_detail *detail) {
-    bc_status s = g->n_graphs >= 4 ? ensure_parts(g) : ensure_replicas(g, n_replicas(g, o));
+    const int R = run_replicas(g, o, sources ? n_sources : g->n);
+    bc_status s = g->n_graphs >= 4 ? ensure_parts(g) : ensure_replicas(g, R);
     if (s != BC_OK) return s;
     const bool repl = g->replicas;
     const int64_t K = o.batch >= 8 ? o.batch : 64;
@@ -2458,7 +2498,7 @@ static bc_status run_parts(bc_graph *g, const int32_t *sources, int64_t n_source
     const int64_t ns = sources ? n_sources : g->n;
     if (ns < 0) return fail(BC_ERR_INVALID_ARG, "n_sources < 0");
     if (detail && (dump_index < 0 || dump_index >= ns)) return fail(BC_ERR_INVALID_ARG, "dump_index out of range");
-    const int P = (int)g->parts.size();
+    const int P = repl ? R : (int)g->parts.size();
     std::vector<std::vector<int32_t>> lists(P);
     int dump_part = -1;
     int64_t dump_local = -1;
@@ -2481,6 +2521,7 @@ static bc_status run_parts(bc_graph *g, const int32_t *sources, int64_t n_source
         }
         lists[p].push_back(local);
     }
+    for (size_t p = 0; p < g->parts.size(); ++p) g->parts[p].ran = p < lists.size() && !lists[p].empty();
     const bool acc = (o.flags & BC_RUN_ACCUMULATE) != 0;
     if (!acc && g->n > 0 && !repl) {
         fill_u64<<<grid_for(g->n, 256, 4096), 256, 0, st>>>((unsigned long long *)g->bc, g->n, 0ull);
@@ -2495,7 +2536,7 @@ static bc_status run_parts(bc_graph *g, const int32_t *sources, int64_t n_source
     hipEvent_t ev0;
     HIP_TRY(hipEventCreateWithFlags(&ev0, hipEventDisableTiming));
     HIP_TRY(hipEventRecord(ev0, st));
-    for (SubPart &pt : g->parts) HIP_TRY(hipStreamWaitEvent(pt.stream, ev0, 0));
+    for (int p = 0; p < P; ++p) HIP_TRY(hipStreamWaitEvent(g->parts[p].stream, ev0, 0));
     (void)hipEventDestroy(ev0);
     // sub-detail buffers for the part that holds the dumped source
     const size_t dn = dump_part >= 0 ? (size_t)std::max<int32_t>(g->parts[dump_part].h->n, 1) : 0;
@@ -2512,6 +2553,7 @@ static bc_status run_parts(bc_graph *g, const int32_t *sources, int64_t n_source
     std::vector<std::string> msg(P);
     int dev = 0;
     HIP_TRY(hipGetDevice(&dev));
+    const int part_grid = concurrent_grid(g);
     std::vector<std::thread> th;
     for (int p = 0; p < P; ++p) {
         if (lists[p].empty()) continue;
@@ -2520,6 +2562,7 @@ static bc_status run_parts(bc_graph *g, const int32_t *sources, int64_t n_source
             bc_run_options po = o;
             if (!acc || repl) po.flags &= ~BC_RUN_ACCUMULATE;
             po.flags |= BC_RUN_ONE_QUEUE;
+            if (po.grid_blocks == 0) po.grid_blocks = part_grid;
             SubPart &pt = g->parts[p];
             if (p == dump_part)
                 res[p] = run_impl(pt.h, lists[p].data(), (int64_t)lists[p].size(), &po, pt.stream, dump_local, &sub_det);
@@ -2744,7 +2787,7 @@ static bc_status run_impl(bc_graph *g, const int32_t *sources, int64_t n_sources
     }
     int dump_done = 0;
     int dump_mode = 0;
-    Ctl last{};
+    Head last{};
     const bool force_f64 = (o.flags & BC_RUN_FORCE_F64) != 0;
     // One pass over the sources at the given absolute positions; returns (in
     // *back) the positions the pass handed back: overflowed lanes of a 64-bit
@@ -2991,7 +3034,7 @@ extern "C" bc_status bc_collect_level_times(bc_graph *g, const int32_t *sources,
     if (!(o.flags & BC_RUN_ACCUMULATE) && g->n > 0) {
         fill_u64<<<grid_for(g->n, 256, 4096), 256, 0, st>>>((unsigned long long *)g->bc, g->n, 0ull);
     }
-    Ctl last{};
+    Head last{};
     std::vector<int64_t> ovf;
     RunCfg c0 = cfg;
     c0.use_graphs = false;  // the machine inserts undo steps; keep launches simple
@@ -3064,6 +3107,7 @@ extern "C" bc_status bc_run_stats(const bc_graph *g, bc_stats *out) {
 static bc_status level_records(const bc_graph *g, std::vector<LevelRec> *acc) {
     if (g->last_parts) {
         for (const SubPart &pt : g->parts) {
+            if (!pt.ran) continue;
             bc_status s = level_records(pt.h, acc);
             if (s != BC_OK) return s;
         }

@@ -12,9 +12,10 @@
 // one contiguous 512-byte row.
 //
 // Per level l (Algorithm "Betweenness Centrality Algorithm", forward loop):
-//   PH_FWD  discover: visited/next words, push (thread or wavefront per
+//   PH_FWD  discover: visited/next words, push (packed group or wavefront per
 //           frontier vertex, 64-bit atomicOr) or pull (thread per unvisited
-//           vertex, early exit once every needed lane is found).
+//           vertex, four arcs at a time, early exit once every needed lane is
+//           found).
 //   PH_SIG  sigma_k(w) = sum over neighbours u of w on level l in lane k of
 //           sigma_k(u), in CSR order, one wavefront per new vertex.  uint64
 //           with the carry kept (exact overflow test); scaled FP64 in mode 1.
@@ -24,9 +25,11 @@
 //           order), then the visited words are cleared.
 // Frontier words carry a level tag so stale entries never need clearing.
 //
-// Load balance: a vertex of degree <= kLightDeg is handled by one thread
-// (thread-per-vertex variants), one of degree <= kSeg by one wavefront, and a
-// heavier one is split into kSeg-arc segments, one wavefront each.  Segment
+// Load balance: sums and pushes work on groups of level entries of about equal
+// cost; in a group the arcs of vertices of degree <= kPack are packed into
+// 64-arc chunks, a vertex of degree <= kSeg has the wavefront to itself, and a
+// heavier one is split into kSeg-arc segments, one wavefront each (pull: one
+// thread per vertex up to kLightDeg).  Segment
 // partial sums are combined in segment order by the last segment to finish,
 // so every sum has an order fixed by the vertex and the results are bitwise
 // reproducible.
@@ -44,30 +47,121 @@ namespace bcx {
 
 // ------------------------------------------------------------------ pieces
 
-// Push from frontier vertex u (lane mask f) over arcs [a0, a1), one arc per
-// lane per chunk.  Appends newly reached vertices to the next level.
-__device__ __forceinline__ void push_arcs_wave(const BatchArgs &a, unsigned long long f, int a0, int a1,
-                                               const int32_t *__restrict__ rp, const int32_t *__restrict__ col,
-                                               uint32_t qe, uint32_t hq_base, unsigned long long &my_edges,
-                                               Stage &st, int &sn, const GroupArgs &gr) {
-    Ctl *c = a.ctl;
-    for (int eb = a0; eb < a1; eb += kWave) {
-        const int e = eb + lane_id();
-        bool newly = false;
-        int w = 0, cw = 0;
-        if (e < a1) {
-            w = col[e];
-            const VisNext x = a.vn[w];
-            const unsigned long long add = f & ~x.vis & ~x.nxt;
-            if (add) newly = atomicOr(&a.vn[w].nxt, add) == 0ull;
-            if (newly) {
-                const int dw = rp[w + 1] - rp[w];
-                my_edges += (unsigned)dw;
-                cw = class_deg(a.g, w, dw);
-            }
-        }
-        stage_push(newly, w, cw, st, sn, c, a.lq_vtx, qe, a.lq_cap, a.hq, hq_base, &c->err, gr);
+// Where a discover step appends the next level.
+template <class C>
+struct Append {
+    C *gc;
+    Stage *st;
+    int n;  // staged entries (wavefront-uniform)
+    uint32_t qe, hq_base;
+    GroupArgs gr;
+};
+
+// Write out the staged vertices; their degrees are looked up here, together
+// (vertex by vertex, that lookup stood behind every atomic that found one).
+template <class C>
+__device__ __forceinline__ void append_flush(const BatchArgs &a, Append<C> &ap) {
+    if (ap.n == 0) return;
+    wave_lds_fence();
+    for (int i = lane_id(); i < ap.n; i += kWave) {
+        const int w = ap.st->w[i];
+        ap.st->deg[i] = class_deg(a.g, w, a.g.row_ptr[w + 1] - a.g.row_ptr[w]);
     }
+    stage_flush(*ap.st, ap.n, ap.gc, a.lq_vtx, ap.qe, a.lq_cap, a.hq, ap.hq_base, &ap.gc->err, ap.gr);
+}
+template <class C>
+__device__ __forceinline__ void append(const BatchArgs &a, Append<C> &ap, bool pred, int w) {
+    const unsigned long long m = __ballot(pred);
+    if (m == 0) return;
+    if (pred) ap.st->w[ap.n + (int)lanes_below(m)] = w;
+    ap.n += __popcll(m);
+    if (ap.n >= kWave) append_flush(a, ap);
+}
+
+// Push over the arc of each thread (far end w with visited/next words x, lanes
+// f of the arc's tail): vertices reached for the first time on the next level
+// are appended.
+template <class C>
+__device__ __forceinline__ void push_arc(const BatchArgs &a, Append<C> &ap, int w, unsigned long long f, VisNext x) {
+    const unsigned long long add = f & ~x.vis & ~x.nxt;
+    bool newly = false;
+    if (add) newly = atomicOr(&a.vn[w].nxt, add) == 0ull;
+    append(a, ap, newly, w);
+}
+
+// Push from one frontier vertex (lanes f) over arcs [a0, a1) (uniform), 64 at a
+// time; the next chunk's columns and words are requested first.
+template <class C>
+__device__ __forceinline__ void push_arcs(const BatchArgs &a, Append<C> &ap, unsigned long long f, int a0, int a1,
+                                          const int32_t *__restrict__ col) {
+    if (a0 >= a1) return;
+    const int lane = lane_id();
+    int w = col[min(a0 + lane, a1 - 1)], wn = col[min(a0 + kWave + lane, a1 - 1)];
+    VisNext x = a.vn[w];
+    for (int eb = a0; eb < a1; eb += kWave) {
+        const int wc = w;
+        const VisNext xc = x;
+        if (eb + kWave < a1) {
+            w = wn;
+            x = a.vn[w];
+            wn = col[min(eb + 2 * kWave + lane, a1 - 1)];
+        }
+        push_arc(a, ap, wc, eb + lane < a1 ? f : 0ull, xc);
+    }
+}
+
+// Push from a group of frontier entries: light ones packed like the sums'
+// groups, medium ones one at a time.  Returns (lane 0) the arcs followed.
+template <class C>
+__device__ __forceinline__ unsigned push_group(const BatchArgs &a, Append<C> &ap, Packing &pk, int qb, int i0, int i1,
+                                               unsigned long long act, const int32_t *__restrict__ rp,
+                                               const int32_t *__restrict__ col) {
+    const int lane = lane_id();
+    const bool valid = i0 + lane < i1;
+    const int p = qb + i0 + lane;
+    const int u = valid ? a.lq_vtx[p] : 0;
+    const unsigned long long f = valid ? (a.lq_mask[p] & act) : 0ull;
+    const int e0 = f ? rp[u] : 0, od = f ? rp[u + 1] - e0 : 0;  // out-arcs to push over
+    const int deg = f ? class_deg(a.g, u, od) : 0;
+    const bool light = f && deg <= kPack, medium = f && deg > kPack && deg <= kSeg;
+    int off;
+    const int total = pack_entries(pk, light ? od : 0,
+                                   make_uint4((unsigned)e0, (unsigned)f, (unsigned)(f >> 32), 0u),
+                                   make_uint4(0u, 0u, 0u, 0u), off);
+    unsigned arcs = (unsigned)total;
+    if (total) {
+        int before = 0;
+        uint4 r = pk.rec[packed_rank(pk, 0, before)], rn = r;
+        int w = col[(int)r.x + min(lane, total - 1)], wn = w;
+        VisNext x = a.vn[w];
+        if (kWave < total) {
+            rn = pk.rec[packed_rank(pk, 1, before)];
+            wn = col[(int)rn.x + min(kWave + lane, total - 1)];
+        }
+        for (int base = 0; base < total; base += kWave) {
+            const int wc = w;
+            const VisNext xc = x;
+            const unsigned long long fc = base + lane < total ? (((unsigned long long)r.z << 32) | r.y) : 0ull;
+            if (base + kWave < total) {
+                w = wn;
+                r = rn;
+                x = a.vn[w];
+                if (base + 2 * kWave < total) {
+                    rn = pk.rec[packed_rank(pk, base / kWave + 2, before)];
+                    wn = col[(int)rn.x + min(base + 2 * kWave + lane, total - 1)];
+                }
+            }
+            push_arc(a, ap, wc, fc, xc);
+        }
+    }
+    for (unsigned long long mm = __ballot(medium); mm; mm &= mm - 1) {
+        const int j = __ffsll(mm) - 1;
+        const int a0 = __builtin_amdgcn_readlane(e0, j), n = __builtin_amdgcn_readlane(od, j);
+        push_arcs(a, ap, readlane_u64(f, j), a0, a0 + n, col);
+        arcs += (unsigned)n;
+    }
+    wave_lds_fence();  // the next group reuses the packing
+    return lane == 0 ? arcs : 0u;
 }
 
 // New vertex w (queue position p, visited/next words vis/m, degree deg)
@@ -95,8 +189,10 @@ __device__ __forceinline__ void sig_publish(const BatchArgs &a, Tagged *fw_nxt, 
 
 // LDS scratch of one wavefront, one use at a time.
 union WaveScratch {
-    Stage st;                   // discover: staged queue entries
-    Packing pk;                 // path counts and backward
+    struct {
+        Packing pk;             // sums and push: a group's packed entries
+        Stage st;               // discover: staged queue entries
+    } w;
     double tile[kWave * 8];     // score accumulation: 64 rows x 8 lanes
 };
 
@@ -294,10 +390,27 @@ __device__ __forceinline__ void bwd_group(const BatchArgs &a, const Tagged *fb_n
     wave_lds_fence();  // the next group reuses the packing
 }
 
+// Lanes of `need` found on the level with tag T among the far ends of arcs
+// [a0, a1) (uniform), 64 at a time until every needed lane is found.
+__device__ __forceinline__ unsigned long long pull_arcs(const Tagged *fw, uint32_t T, unsigned long long need, int a0,
+                                                        int a1, const int32_t *__restrict__ col, int &scanned) {
+    unsigned long long got = 0;
+    if (!need || a0 >= a1) return 0ull;
+    const int lane = lane_id();
+    int u = col[min(a0 + lane, a1 - 1)];
+    for (int eb = a0; eb < a1 && got != need; eb += kWave) {
+        const unsigned long long f = tagged_lanes(fw, u, T, need);  // (the last arc again beyond the end)
+        if (eb + kWave < a1) u = col[min(eb + kWave + lane, a1 - 1)];
+        got |= wave_or_u64(f);
+        scanned += min(kWave, a1 - eb);
+    }
+    return got;
+}
+
 // The variant of the next level and the summation options chosen with it
 // (lbo, see choose_variant); when collecting timings, every level starts
 // with variant 0 and its normalised features are kept for the samples.
-__device__ __forceinline__ void set_level_variant(const BatchArgs &a, Ctl *c, int v, int lbo, const LevelFeatures &f,
+__device__ __forceinline__ void set_level_variant(const BatchArgs &a, Head *c, int v, int lbo, const LevelFeatures &f,
                                                   float n, float nnz) {
     if (f.level < a.max_levels + 2) a.lbsel[f.level] = lbo;
     if (c->collect) {
@@ -314,8 +427,8 @@ __device__ __forceinline__ void set_level_variant(const BatchArgs &a, Ctl *c, in
 }
 
 template <int MODE>
-__device__ __forceinline__ void batch_begin(const BatchArgs &a, Ctl *c, int64_t b, float *lds, LevelFeatures *sf, int *s_lsrc,
-                            int *s_cnt, unsigned long long *s_tmp, int *s_lead) {
+__device__ __forceinline__ void batch_begin(const BatchArgs &a, Head *c, int64_t b, float *lds, LevelFeatures *sf,
+                                            int *s_lsrc, int *s_cnt, unsigned long long *s_tmp, int *s_lead) {
     const int t = threadIdx.x;
     const int64_t start = a.batch_start[b], end = a.batch_start[b + 1];
     const int lanes = (int)(end - start);
@@ -366,10 +479,14 @@ __device__ __forceinline__ void batch_begin(const BatchArgs &a, Ctl *c, int64_t 
     if (t == 0) {
         const int cnt = *s_cnt;
         unsigned long long mf = 0;
+        uint32_t cost = 0;
         int nh = 0, segs = 0;
         for (int j = 0; j < cnt; ++j) {
             const int deg = (int)(uint32_t)s_tmp[j], cdeg = (int)(s_tmp[j] >> 32);
             mf += (unsigned long long)deg;
+            const uint32_t ce = entry_cost(cdeg);
+            for (uint32_t k = cost / kBudget + 1; k <= (cost + ce) / kBudget; ++k) a.gstart[k] = (uint32_t)j + 1u;
+            cost += ce;
             if (cdeg > kSeg) {  // heavy source: level-0 segments for the push
                 a.hq.pos[nh] = j;
                 a.hq.seg[nh] = segs;
@@ -381,17 +498,17 @@ __device__ __forceinline__ void batch_begin(const BatchArgs &a, Ctl *c, int64_t 
         a.hq.off[0] = 0;
         a.hq.off[1] = nh;
         a.hq.nseg[0] = segs;
-        c->next_hq = 0;
-        a.gstart[0] = 0u;  // level 0 has no groups; level 1 appends from slot 1
+        const uint32_t ng = (cost - 1u) / (uint32_t)kBudget + 1u;  // groups of level 0
+        a.gstart[0] = 0u;
+        a.gstart[ng] = (uint32_t)cnt;
         a.gbase[0] = 0u;
-        a.gbase[1] = 1u;
+        a.gbase[1] = ng + 1u;
         c->epoch = epoch;
         c->pos = b;
         c->lanes = lanes;
         c->lane_mask = lanes >= 64 ? ~0ull : ((1ull << lanes) - 1ull);
         c->active = c->lane_mask;
         c->dead = 0;
-        c->ovf_lanes = 0;
         c->range_lo = a.batch_lo[b];
         c->range_hi = a.batch_hi[b];
         c->range_arcs = (unsigned long long)(a.g.row_ptr[c->range_hi] - a.g.row_ptr[c->range_lo]);
@@ -402,14 +519,11 @@ __device__ __forceinline__ void batch_begin(const BatchArgs &a, Ctl *c, int64_t 
         c->n_levels = 0;
         a.level_off[0] = 0;
         a.level_off[1] = cnt;
-        c->next_qc = 0ull;
-        c->next_edges = 0;
-        c->next_active = 0;
         c->prev_variant = V_PUSH_TPV;
         c->phase = PH_FWD;
         c->st_batches += 1;
         c->st_lane_entries += (unsigned long long)lanes;
-        if (a.lvl) level_rec(a.lvl, 0).entries += (unsigned long long)cnt;
+        if (a.lvl) (void)atomicAdd(&level_rec(a.lvl, 0).entries, (unsigned long long)cnt);
         const int64_t dp = c->dump_pos;
         c->dump_lane = (dp >= start && dp < end && c->dump_state == 0) ? (int)(dp - start) : -1;
         sf->nf = (float)cnt;
@@ -426,38 +540,58 @@ __device__ __forceinline__ void batch_begin(const BatchArgs &a, Ctl *c, int64_t 
 }
 
 #ifndef BC_WAVES
-#define BC_WAVES 6
+#define BC_WAVES 5
 #endif
 // Register budget of the step kernel: at least BC_WAVES wavefronts per SIMD
-// (memory latency is hidden by resident wavefronts).
+// (memory latency is hidden by resident wavefronts; 5 against 6, which spills:
+// the damaged 1024^2 grid 102 against 106 ms, R-MAT 18 32.7 against 32.9; 4:
+// R-MAT 18 41 against 38.5 with full launches).
+//
+// A step without work to speak of costs 9.8 us per launch (6.3 in the block engine,
+// 7.8 per source) where it cost 21.8 (13.4, 15.9): the state is read and
+// written as a whole through LDS instead of field by field, workgroups
+// without work leave without counting themselves in, a step of one workgroup
+// exchanges no counters, and a level's records are requested together.
 // One step of the level state machine for workgroup bid of a launch of
-// `grid` workgroups: the step kernel below runs it once per launch over the
-// whole grid; the block engine runs it in a loop inside one workgroup
-// (grid = 1), which then owns the state machine alone.
-template <int MODE>
-__device__ __forceinline__ void batch_step_body(const BatchArgs &a, const unsigned bid, const unsigned grid) {
+// `grid` workgroups of NW wavefronts: the step kernel below runs it once per
+// launch over the whole grid; the block engine runs it in a loop inside one
+// workgroup (grid = 1), which then owns the state machine alone, its control block
+// gc in LDS (SOLO).
+// load() gives the arguments anew to each phase, so that no phase holds
+// the others' pointers in its registers.
+template <int MODE, int NW, bool SOLO, class Load, class C>
+__device__ __forceinline__ void batch_step_body(Load load, C *gc, const int parity, const unsigned bid,
+                                                const unsigned grid) {
+    constexpr int NT = NW * kWave;
     __shared__ int s_phase, s_level, s_variant, s_last, s_qb, s_qe, s_qn, s_L, s_lo, s_hi, s_dlane, s_cnt;
-    __shared__ int s_h0, s_h1, s_hseg, s_hqb;
-    __shared__ uint32_t s_gb, s_ng;
+    __shared__ int s_h0, s_h1, s_hseg, s_hqb, s_gm;
+    __shared__ uint32_t s_gb, s_gbn, s_ng;
     __shared__ unsigned s_nblk;
     __shared__ uint32_t s_epoch, s_epoch_b;
     __shared__ unsigned long long s_active, s_dead, s_lmask;
-    __shared__ unsigned long long s_red[kSlots * kNCnt];
+    __shared__ unsigned long long s_red[NW * kNCnt];
     __shared__ unsigned long long s_tot[kNCnt];
     __shared__ unsigned long long s_tmp[kLanes];
     __shared__ int s_lsrc[kLanes];
     __shared__ int s_lead[kLanes];
-    __shared__ WaveScratch s_scratch[kWavesPerBlock];
+    __shared__ WaveScratch s_scratch[NW];
     __shared__ float s_lds[2 * kMlpH + kMlpOut + 4];
     __shared__ LevelFeatures s_feat;
     __shared__ float s_il;  // sources-per-entry threshold of this path-count / backward step
     __shared__ int s_usig;  // an undo step restores a path-count step (timing collection)
     __shared__ int s_emax[kLanes], s_emin[kLanes];
-    Ctl *c = a.ctl;
+    __shared__ Head s_head;
+    Head *c = SOLO ? &gc->h[0] : &s_head;
     const int tid = threadIdx.x, lane = tid & 63, wid = uniform(tid >> 6);
+    if (!SOLO) {
+        head_load<NT>(s_head, gc->h[parity]);
+        __syncthreads();
+    }
     if (tid == 0) {
-        s_phase = c->phase;
-        s_level = c->level;
+        const BatchArgs a = load();
+        const int ph = c->phase, l = c->level;
+        s_phase = ph;
+        s_level = l;
         s_variant = c->variant;
         s_epoch = c->epoch;
         s_epoch_b = c->epoch_b;
@@ -468,75 +602,83 @@ __device__ __forceinline__ void batch_step_body(const BatchArgs &a, const unsign
         s_lo = c->range_lo;
         s_hi = c->range_hi;
         s_dlane = c->dump_lane;
-        s_qb = s_qe = s_qn = 0;
-        s_h0 = s_h1 = s_hseg = s_hqb = 0;
-        s_gb = s_ng = 0;
-        const int l = s_level;
-        s_il = a.p.item_lanes;
-        if (s_phase == PH_SIG || s_phase == PH_BWD) {
-            // the option timed (collection), else the one chosen with level l
-            const int sel = (l < a.max_levels + 2) ? a.lbsel[l] : kLbDefault;
-            const int opt = c->collect ? c->clb : (s_phase == PH_SIG ? (sel & 3) : ((sel >> 2) & 3));
-            s_il = lb_item_lanes(a.p, opt);
-        }
-        if (s_phase == PH_FWD || s_phase == PH_SIG || s_phase == PH_BWD) {
-            s_qb = a.level_off[l];
-            s_qe = a.level_off[l + 1];
-            if (s_phase == PH_SIG) s_qn = a.level_off[l + 2];
-        } else if (s_phase == PH_DUMP_FWD || s_phase == PH_DUMP_BWD) {
-            s_qe = a.level_off[s_L];
-        } else if (s_phase == PH_UNDO) {
-            s_qe = a.level_off[l + 1];
-            s_qn = (int)(uint32_t)c->next_qc;
-        }
         s_usig = c->undo_sig;
-        if (s_phase == PH_FWD) {
-            if (s_variant == V_PULL) {  // static heavy vertices of the batch's range
-                const int i0 = lower_bound_i32(a.g.hv_vtx, a.g.n_heavy, s_lo);
-                const int i1 = lower_bound_i32(a.g.hv_vtx, a.g.n_heavy, s_hi);
-                s_h0 = i0;
-                s_h1 = i1;
-                s_hseg = a.g.hv_seg[i1] - a.g.hv_seg[i0];
-            } else {                    // heavy frontier entries of level l
-                s_h0 = a.hq.off[l];
-                s_h1 = a.hq.off[l + 1];
-                s_hseg = a.hq.nseg[l];
+        int qb = 0, qe = 0, qn = 0, h0 = 0, h1 = 0, hseg = 0, hqb = 0;
+        uint32_t gb = 0, gbn = 0, ng = 0;
+        float il = a.p.item_lanes;
+        if (ph == PH_FWD || ph == PH_SIG || ph == PH_BWD) {
+            // the level's records, requested together: queue offsets, groups, heavy lists
+            const int o0 = a.level_off[l], o1 = a.level_off[l + 1], o2 = ph == PH_SIG ? a.level_off[l + 2] : 0;
+            const uint32_t g0 = a.gbase[l], g1 = a.gbase[l + 1], g2 = ph == PH_SIG ? a.gbase[l + 2] : 0u;
+            const int f0 = a.hq.off[l], f1 = a.hq.off[l + 1], f2 = ph == PH_SIG ? a.hq.off[l + 2] : 0;
+            const int ns = a.hq.nseg[ph == PH_SIG ? l + 1 : l];
+            const int sel = l < a.max_levels + 2 ? a.lbsel[l] : kLbDefault;
+            qb = o0;
+            qe = o1;
+            qn = o2;
+            hqb = f1;   // heavy entries of level l+1 start here
+            gbn = g1;   // groups of level l+1 are appended here
+            hseg = ns;
+            if (ph == PH_SIG) {
+                h0 = f1;
+                h1 = f2;
+                gb = g1;
+                ng = g2 - g1 - 1u;
+            } else {
+                h0 = f0;
+                h1 = f1;
+                gb = g0;
+                ng = g1 - g0 - 1u;
             }
-            s_hqb = a.hq.off[l + 1];    // heavy entries of level l+1 start here
-            s_gb = a.gbase[l + 1];      // groups of level l+1 are appended here
-        } else if (s_phase == PH_SIG) {
-            s_h0 = a.hq.off[l + 1];
-            s_h1 = a.hq.off[l + 2];
-            s_hseg = a.hq.nseg[l + 1];
-            s_gb = a.gbase[l + 1];
-            s_ng = a.gbase[l + 2] - s_gb - 1u;
-        } else if (s_phase == PH_BWD) {
-            s_h0 = a.hq.off[l];
-            s_h1 = a.hq.off[l + 1];
-            s_hseg = a.hq.nseg[l];
-            s_gb = a.gbase[l];
-            s_ng = a.gbase[l + 1] - s_gb - 1u;
+            if (ph != PH_FWD) {
+                // the option timed (collection), else the one chosen with level l
+                const int opt = c->collect ? c->clb : (ph == PH_SIG ? (sel & 3) : ((sel >> 2) & 3));
+                il = lb_item_lanes(a.p, opt);
+            } else if (c->variant == V_PULL) {  // static heavy vertices of the batch's range
+                h0 = lower_bound_i32(a.g.hv_vtx, a.g.n_heavy, c->range_lo);
+                h1 = lower_bound_i32(a.g.hv_vtx, a.g.n_heavy, c->range_hi);
+                hseg = a.g.hv_seg[h1] - a.g.hv_seg[h0];
+            }
+        } else if (ph == PH_DUMP_FWD || ph == PH_DUMP_BWD) {
+            qe = a.level_off[c->n_levels];
+        } else if (ph == PH_UNDO) {
+            qe = a.level_off[l + 1];
+            qn = (int)(uint32_t)gc->next_qc;
         }
+        // consecutive groups of a large level are taken together (a group
+        // costs a wavefront its entries' offsets and words before the first arc)
+        const int gm = merge_groups(ng, grid * NW);
         // wavefront work items of this step -> workgroups taking part
         long long items = 1;
-        const int cnt = s_qe - s_qb;
-        if (s_phase == PH_FWD) {
-            if (s_variant == V_PUSH_TPV) items = (cnt + kWave - 1) / kWave + s_hseg;
-            else if (s_variant == V_PUSH_WPV) items = cnt + s_hseg;
-            else items = (s_hi - s_lo + kWave - 1) / kWave + s_hseg;
-        } else if (s_phase == PH_SIG || s_phase == PH_BWD) {
-            items = (long long)s_ng + s_hseg;
-        } else if (s_phase == PH_BC) {
-            items = (s_hi - s_lo + kWave - 1) / kWave;
-        } else if (s_phase == PH_DUMP_FWD || s_phase == PH_DUMP_BWD) {
-            items = (s_qe + kWave - 1) / kWave;
-        } else if (s_phase == PH_UNDO) {
-            items = (s_qn + kWave - 1) / kWave;
+        const int cnt = qe - qb;
+        if (ph == PH_FWD) {
+            if (c->variant == V_PUSH_TPV) items = ((long long)ng + gm - 1) / gm + hseg;
+            else if (c->variant == V_PUSH_WPV) items = (long long)cnt + hseg;
+            else items = (c->range_hi - c->range_lo + kWave - 1) / kWave + hseg;
+        } else if (ph == PH_SIG || ph == PH_BWD) {
+            items = ((long long)ng + gm - 1) / gm + hseg;
+        } else if (ph == PH_BC) {
+            items = (c->range_hi - c->range_lo + kWave - 1) / kWave;
+        } else if (ph == PH_DUMP_FWD || ph == PH_DUMP_BWD) {
+            items = (qe + kWave - 1) / kWave;
+        } else if (ph == PH_UNDO) {
+            items = (qn + kWave - 1) / kWave;
         }
-        s_nblk = active_blocks(items, grid);
+        s_nblk = SOLO ? 1u : active_blocks(items, grid);
+        s_qb = qb;
+        s_qe = qe;
+        s_qn = qn;
+        s_h0 = h0;
+        s_h1 = h1;
+        s_hseg = hseg;
+        s_hqb = hqb;
+        s_gb = gb;
+        s_gbn = gbn;
+        s_ng = ng;
+        s_gm = gm;
+        s_il = il;
     }
     if (tid < kLanes) {
-        s_lsrc[tid] = a.lane_src[tid];
         s_emax[tid] = INT_MIN;
         s_emin[tid] = INT_MAX;
     }
@@ -544,131 +686,90 @@ __device__ __forceinline__ void batch_step_body(const BatchArgs &a, const unsign
     const int phase = uniform(s_phase);
     if (phase == PH_DONE || phase == PH_IDLE) return;
     const unsigned nblk = (unsigned)uniform((int)s_nblk);
-    const bool active = bid < nblk;  // workgroups beyond nblk only count in
+    if (bid >= nblk) return;  // no work for this workgroup
 
-    const int gw = (int)bid * kWavesPerBlock + wid;
-    const int nw = (int)nblk * kWavesPerBlock;
+    const int gw = (int)bid * NW + wid;
+    const int nw = (int)nblk * NW;
     const int l = uniform(s_level);
-    const int32_t *__restrict__ rp = a.g.row_ptr;
-    const int32_t *__restrict__ col = a.g.col;
-    Tagged *fw_cur = (l & 1) ? a.fw1 : a.fw0;
-    Tagged *fw_nxt = (l & 1) ? a.fw0 : a.fw1;
     const int h0 = uniform(s_h0), h1 = uniform(s_h1), hseg = uniform(s_hseg);
 
-    unsigned long long my_edges = 0, my_arcs = 0, my_larcs = 0, my_act = 0, my_ovf = 0;
-    unsigned long long my_full_n = 0, my_full_m = 0, my_pairs = 0, my_lent = 0;
+    // (one thread's share of a step fits 32 bits: a level holds a vertex and an
+    // arc at most once, spread over the lanes of at least one wavefront)
+    unsigned my_edges = 0, my_arcs = 0, my_larcs = 0, my_full_n = 0, my_full_m = 0, my_pairs = 0, my_lent = 0;
+    unsigned long long my_act = 0, my_ovf = 0;
     int my_maxe = INT_MIN, my_mine = INT_MAX;
 
-    if (!active) {
-    } else if (phase == PH_FWD) {
-        const int qb = s_qb, qe = s_qe, cnt = qe - qb;
+    if (phase == PH_FWD) {
+        const BatchArgs a = load();
+        const int32_t *__restrict__ rp = a.g.row_ptr;
+        const int32_t *__restrict__ col = a.g.col;
+        const Tagged *fw_cur = (l & 1) ? a.fw1 : a.fw0;
+        const int qb = uniform(s_qb), qe = uniform(s_qe), cnt = qe - qb;
         const uint32_t T = s_epoch + (uint32_t)l;
-        const unsigned long long act = s_active;
-        const uint32_t hqb = (uint32_t)s_hqb;
-        const int variant = s_variant;
-        Stage &st = s_scratch[wid].st;
-        int sn = 0;
-        GroupArgs gr;
-        gr.gstart = a.gstart;
-        gr.gb = s_gb;
-        gr.gcap = a.gcap;
+        const unsigned long long act = uniform(s_active);
+        const int variant = uniform(s_variant);
+        Append<C> ap;
+        ap.gc = gc;
+        ap.st = &s_scratch[wid].w.st;
+        ap.n = 0;
+        ap.qe = (uint32_t)qe;
+        ap.hq_base = (uint32_t)uniform(s_hqb);
+        ap.gr.gstart = a.gstart;
+        ap.gr.gb = (uint32_t)uniform((int)s_gbn);
+        ap.gr.gcap = a.gcap;
+        Packing &pk = s_scratch[wid].w.pk;
         if (variant == V_PUSH_TPV || variant == V_PUSH_WPV) {
-            const int n_light = variant == V_PUSH_TPV ? (cnt + kWave - 1) / kWave : cnt;
+            const int ng = uniform((int)s_ng), gm = uniform(s_gm);
+            const uint32_t *gs = a.gstart + uniform((int)s_gb);
+            const int n_light = variant == V_PUSH_TPV ? (ng + gm - 1) / gm : cnt;
             const int total = n_light + hseg;
             for (int k = gw; k < total; k += nw) {
                 const int it = k < hseg ? n_light + k : k - hseg;  // heavy segments first
                 if (it >= n_light) {  // one segment of a heavy frontier vertex
                     const int t = it - n_light;
-                    const int h = seg_owner(a.hq.seg, h0, h1, t);
-                    const int s = t - a.hq.seg[h];
-                    const int p = a.hq.pos[h];
-                    const int u = a.lq_vtx[p];
-                    const unsigned long long f = a.lq_mask[p] & act;
-                    const int a0 = rp[u] + s * kSeg;
-                    const int a1 = max(a0, min(rp[u + 1], a0 + kSeg));
+                    const int h = uniform(seg_owner(a.hq.seg, h0, h1, t));
+                    const int s = t - uniform(a.hq.seg[h]);
+                    const int p = uniform(a.hq.pos[h]);
+                    const int u = uniform(a.lq_vtx[p]);
+                    const unsigned long long f = uniform(a.lq_mask[p]) & act;
+                    const int a0 = uniform(rp[u]) + s * kSeg;
+                    const int a1 = max(a0, min(uniform(rp[u + 1]), a0 + kSeg));
                     if (lane == 0) my_arcs += (unsigned)(a1 - a0);
-                    if (f) push_arcs_wave(a, f, a0, a1, rp, col, (uint32_t)qe, hqb, my_edges, st, sn, gr);
+                    if (f) push_arcs(a, ap, f, a0, a1, col);
                 } else if (variant == V_PUSH_WPV) {
-                    const int u = a.lq_vtx[qb + it];
-                    const unsigned long long f = a.lq_mask[qb + it] & act;
-                    const int e0 = rp[u], e1 = rp[u + 1];
-                    if (!f || class_deg(a.g, u, e1 - e0) > kSeg) continue;  // heavy ones run as segments
+                    const int u = uniform(a.lq_vtx[qb + it]);
+                    const unsigned long long f = uniform(a.lq_mask[qb + it]) & act;
+                    const int e0 = uniform(rp[u]), e1 = uniform(rp[u + 1]);
+                    if (!f || uniform(class_deg(a.g, u, e1 - e0)) > kSeg) continue;  // heavy ones run as segments
                     if (lane == 0) my_arcs += (unsigned)(e1 - e0);
-                    push_arcs_wave(a, f, e0, e1, rp, col, (uint32_t)qe, hqb, my_edges, st, sn, gr);
-                } else {  // TPV: 64 frontier vertices per wavefront
-                    const int i = it * kWave + lane;
-                    const bool valid = i < cnt;
-                    const int u = valid ? a.lq_vtx[qb + i] : 0;
-                    const unsigned long long f = valid ? (a.lq_mask[qb + i] & act) : 0ull;
-                    const int e0 = f ? rp[u] : 0;
-                    const int od = f ? rp[u + 1] - e0 : 0;  // out-arcs to push over
-                    const int deg = f ? class_deg(a.g, u, od) : 0;
-                    const int len = deg <= kLightDeg ? od : 0;
-                    my_arcs += (unsigned)(deg <= kSeg ? od : 0);
-                    const int maxlen = wave_max_i(len);
-                    for (int t = 0; t < maxlen; ++t) {
-                        bool newly = false;
-                        int w = 0, cw = 0;
-                        if (t < len) {
-                            w = col[e0 + t];
-                            const VisNext x = a.vn[w];
-                            const unsigned long long add = f & ~x.vis & ~x.nxt;
-                            if (add) newly = atomicOr(&a.vn[w].nxt, add) == 0ull;
-                            if (newly) {
-                                const int dw = rp[w + 1] - rp[w];
-                                my_edges += (unsigned)dw;
-                                cw = class_deg(a.g, w, dw);
-                            }
-                        }
-                        stage_push(newly, w, cw, st, sn, c, a.lq_vtx, (uint32_t)qe, a.lq_cap, a.hq, hqb, &c->err, gr);
-                    }
-                    // medium-degree vertices: the whole wavefront, one at a time
-                    unsigned long long mm = __ballot(deg > kLightDeg && deg <= kSeg);
-                    while (mm) {
-                        const int j = __ffsll(mm) - 1;
-                        mm &= mm - 1;
-                        const int m0 = __shfl(e0, j), m1 = m0 + __shfl(od, j);
-                        push_arcs_wave(a, shfl_u64(f, j), m0, m1, rp, col, (uint32_t)qe, hqb, my_edges, st, sn, gr);
-                    }
+                    push_arcs(a, ap, f, e0, e1, col);
+                } else {  // a group of frontier vertices per wavefront
+                    const int i0 = uniform((int)gs[it * gm]), i1 = min(uniform((int)gs[min(it * gm + gm, ng)]), cnt);
+                    if (i1 > i0) my_arcs += push_group(a, ap, pk, qb, i0, i1, act, rp, col);
                 }
             }
         } else {  // V_PULL over the batch's vertex range, scanning in-arcs (predecessors)
             const int32_t *__restrict__ irp = a.g.in_row_ptr;
             const int32_t *__restrict__ icol = a.g.in_col;
-            const int lo = s_lo, span = s_hi - s_lo;
+            const int lo = uniform(s_lo), span = uniform(s_hi) - lo;
             const int n_light = (span + kWave - 1) / kWave;
             const int total = n_light + hseg;
-            const int hs0 = a.g.hv_seg[h0];
+            const int hs0 = uniform(a.g.hv_seg[h0]);
             for (int k = gw; k < total; k += nw) {
                 const int it = k < hseg ? n_light + k : k - hseg;  // heavy segments first
                 if (it >= n_light) {  // one segment of a heavy unvisited vertex
                     const int t = hs0 + (it - n_light);
-                    const int h = seg_owner(a.g.hv_seg, h0, h1, t);
-                    const int s = t - a.g.hv_seg[h];
-                    const int w = a.g.hv_vtx[h];
-                    const unsigned long long need = act & ~a.vn[w].vis;
-                    unsigned long long got = 0;
-                    const int a0 = irp[w] + s * kSeg, a1 = max(a0, min(irp[w + 1], a0 + kSeg));
+                    const int h = uniform(seg_owner(a.g.hv_seg, h0, h1, t));
+                    const int s = t - uniform(a.g.hv_seg[h]);
+                    const int w = uniform(a.g.hv_vtx[h]);
+                    const unsigned long long need = act & ~uniform(a.vn[w].vis);
+                    const int a0 = uniform(irp[w]) + s * kSeg, a1 = max(a0, min(uniform(irp[w + 1]), a0 + kSeg));
                     int scanned = 0;
-                    if (need) {
-                        for (int eb = a0; eb < a1; eb += kWave) {
-                            const int e = eb + lane;
-                            if (e < a1) {
-                                const Tagged F = fw_cur[icol[e]];
-                                if (F.tag == T) got |= F.mask & need;
-                            }
-                            scanned += kWave;
-                            got = wave_or_u64(got);
-                            if (got == need) break;
-                        }
-                    }
-                    if (lane == 0) my_arcs += (unsigned)min(scanned, a1 - a0);
+                    const unsigned long long got = pull_arcs(fw_cur, T, need, a0, a1, icol, scanned);
+                    if (lane == 0) my_arcs += (unsigned)scanned;
                     bool newly = false;
                     if (lane == 0 && got) newly = atomicOr(&a.vn[w].nxt, got) == 0ull;
-                    const int od = rp[w + 1] - rp[w];
-                    if (newly) my_edges += (unsigned)od;
-                    stage_push(newly, w, class_deg(a.g, w, od), st, sn, c, a.lq_vtx, (uint32_t)qe, a.lq_cap, a.hq, hqb,
-                               &c->err, gr);
+                    append(a, ap, newly, w);
                     continue;
                 }
                 const int w = lo + it * kWave + lane;
@@ -680,65 +781,58 @@ __device__ __forceinline__ void batch_step_body(const BatchArgs &a, const unsign
                 const int od = (need && a.g.directed) ? rp[w + 1] - rp[w] : ni;
                 const int deg = a.g.directed ? max(ni, od) : ni;  // class degree
                 const int len = deg <= kLightDeg ? ni : 0;
-                const int maxlen = wave_max_i(len);
                 unsigned long long got = 0;
                 int scanned = 0;
-                for (int t = 0; t < maxlen; ++t) {
+                // one thread per vertex, four arcs at a time
+                for (int t = 0; __any(t < len && got != need); t += 4) {
                     if (t < len && got != need) {
-                        ++scanned;
-                        const Tagged F = fw_cur[icol[e0 + t]];
-                        if (F.tag == T) got |= F.mask & need;
+                        int u[4];
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) u[q] = icol[e0 + min(t + q, len - 1)];
+                        unsigned long long g4 = 0;
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) g4 |= tagged_lanes(fw_cur, u[q], T, need);
+                        got |= g4;
+                        scanned += min(4, len - t);
                     }
-                    if (!__any(t + 1 < len && got != need)) break;
                 }
                 // medium-degree vertices: the whole wavefront, one at a time
-                unsigned long long mm = __ballot(deg > kLightDeg && deg <= kSeg);
-                while (mm) {
+                for (unsigned long long mm = __ballot(deg > kLightDeg && deg <= kSeg); mm; mm &= mm - 1) {
                     const int j = __ffsll(mm) - 1;
-                    mm &= mm - 1;
-                    const int m0 = __shfl(e0, j), m1 = m0 + __shfl(ni, j);
-                    const unsigned long long nj = shfl_u64(need, j);
-                    unsigned long long gj = 0;
-                    for (int eb = m0; eb < m1; eb += kWave) {
-                        const int e = eb + lane;
-                        if (e < m1) {
-                            const Tagged F = fw_cur[icol[e]];
-                            if (F.tag == T) gj |= F.mask & nj;
-                        }
-                        if (lane == 0) scanned += min(kWave, m1 - eb);
-                        gj = wave_or_u64(gj);
-                        if (gj == nj) break;
-                    }
+                    const int m0 = __builtin_amdgcn_readlane(e0, j), m1 = m0 + __builtin_amdgcn_readlane(ni, j);
+                    int sc = 0;
+                    const unsigned long long gj = pull_arcs(fw_cur, T, readlane_u64(need, j), m0, m1, icol, sc);
+                    if (lane == 0) scanned += sc;
                     if (lane == j) got = gj;
                 }
                 my_arcs += (unsigned)scanned;
                 const bool found = got != 0ull && deg <= kSeg;
-                if (found) {
-                    a.vn[w].nxt = got;
-                    my_edges += (unsigned)od;
-                }
-                stage_push(found, w, deg, st, sn, c, a.lq_vtx, (uint32_t)qe, a.lq_cap, a.hq, hqb, &c->err, gr);
+                if (found) a.vn[w].nxt = got;
+                append(a, ap, found, w);
             }
         }
-        stage_flush(st, sn, c, a.lq_vtx, (uint32_t)qe, a.lq_cap, a.hq, hqb, &c->err, gr);
+        append_flush(a, ap);
     } else if (phase == PH_SIG) {
+        const BatchArgs a = load();
+        const int32_t *__restrict__ rp = a.g.row_ptr;
+        Tagged *fw_cur = (l & 1) ? a.fw1 : a.fw0, *fw_nxt = (l & 1) ? a.fw0 : a.fw1;
         // path counts of the new level; lane = source
         const int qs = uniform(s_qe), cnt = uniform(s_qn) - qs;
         const uint32_t T = s_epoch + (uint32_t)l;
         const int sh = MODE ? a.shift[(size_t)l * kLanes + lane] : 0;
         const unsigned long long lmask = s_lmask;
-        const int n_groups = uniform((int)s_ng);
+        const int ng = uniform((int)s_ng), gm = uniform(s_gm), n_groups = (ng + gm - 1) / gm;
         const uint32_t *gs = a.gstart + uniform((int)s_gb);
         const int total = n_groups + hseg;
         const float il = s_il;
         constexpr int OP = MODE ? OP_F64 : OP_U64;
-        Packing &pk = s_scratch[wid].pk;
+        Packing &pk = s_scratch[wid].w.pk;
         SigCounters sc;
-        for (WorkCursor wc(c, nblk, bid); wc.item() < total; wc.next(total)) {
+        for (WorkCursor<NW> wc(gc, nblk, bid); wc.item() < total; wc.next(total)) {
             const int k = wc.item();
             const int it = k < hseg ? n_groups + k : k - hseg;  // heavy segments first
             if (it < n_groups) {
-                const int i0 = uniform((int)gs[it]), i1 = min(uniform((int)gs[it + 1]), cnt);
+                const int i0 = uniform((int)gs[it * gm]), i1 = min(uniform((int)gs[min(it * gm + gm, ng)]), cnt);
                 if (i1 > i0) sig_group<MODE>(a, fw_cur, fw_nxt, T, qs, i0, i1, sh, lmask, sc, l, s_emax, s_emin, il, pk);
                 continue;
             }
@@ -792,6 +886,10 @@ __device__ __forceinline__ void batch_step_body(const BatchArgs &a, const unsign
         my_maxe = max(my_maxe, sc.maxe);
         my_mine = min(my_mine, sc.mine);
     } else if (phase == PH_BWD) {
+        const BatchArgs a = load();
+        const int32_t *__restrict__ rp = a.g.row_ptr;
+        const int32_t *__restrict__ col = a.g.col;
+        Tagged *fw_cur = (l & 1) ? a.fw1 : a.fw0, *fw_nxt = (l & 1) ? a.fw0 : a.fw1;
         const int qb = s_qb, cnt = s_qe - s_qb;
         const uint32_t TB = s_epoch_b + (uint32_t)l;
         Tagged *fb_cur = fw_cur;  // written with this level's tag
@@ -799,18 +897,18 @@ __device__ __forceinline__ void batch_step_body(const BatchArgs &a, const unsign
         const unsigned long long dead = uniform(s_dead);
         const int sh = MODE ? a.shift[(size_t)l * kLanes + lane] : 0;
         const int shn = (MODE && l + 1 < s_L) ? a.shift[(size_t)(l + 1) * kLanes + lane] : 0;
-        const int n_groups = uniform((int)s_ng);
+        const int ng = uniform((int)s_ng), gm = uniform(s_gm), n_groups = (ng + gm - 1) / gm;
         const uint32_t *gs = a.gstart + uniform((int)s_gb);
         const int total = n_groups + hseg;
         const bool has_next = l + 1 < uniform(s_L);
         const float il = s_il;
-        Packing &pk = s_scratch[wid].pk;
+        Packing &pk = s_scratch[wid].w.pk;
         ArcCounters ac;
-        for (WorkCursor wc(c, nblk, bid); wc.item() < total; wc.next(total)) {
+        for (WorkCursor<NW> wc(gc, nblk, bid); wc.item() < total; wc.next(total)) {
             const int k = wc.item();
             const int it = k < hseg ? n_groups + k : k - hseg;  // heavy segments first
             if (it < n_groups) {
-                const int i0 = uniform((int)gs[it]), i1 = min(uniform((int)gs[it + 1]), cnt);
+                const int i0 = uniform((int)gs[it * gm]), i1 = min(uniform((int)gs[min(it * gm + gm, ng)]), cnt);
                 if (i1 > i0) bwd_group<MODE>(a, fb_nxt, fb_cur, TB, qb, i0, i1, dead, sh, shn, ac, l, has_next, il, pk);
                 continue;
             }
@@ -847,12 +945,13 @@ __device__ __forceinline__ void batch_step_body(const BatchArgs &a, const unsign
         my_arcs += ac.arcs;
         my_pairs += ac.pairs;
     } else if (phase == PH_UNDO) {
+        const BatchArgs a = load();
         const int qs = s_qe, cnt = s_qn;
         if (s_usig) {
             // timing collection: the entries of level l+1 get back the words
             // they had before their path-count step (that step set the lanes
             // of their queue masks visited and cleared their next words)
-            for (int i = (int)bid * kBlock + tid; i < cnt; i += (int)nblk * kBlock) {
+            for (int i = (int)bid * NT + tid; i < cnt; i += (int)nblk * NT) {
                 const int w = a.lq_vtx[qs + i];
                 const unsigned long long m = a.lq_mask[qs + i];
                 VisNext x = a.vn[w];
@@ -863,9 +962,12 @@ __device__ __forceinline__ void batch_step_body(const BatchArgs &a, const unsign
         } else {
             // timing collection: forget the level just discovered (its
             // entries are the only vertices with next words set)
-            for (int i = (int)bid * kBlock + tid; i < cnt; i += (int)nblk * kBlock) a.vn[a.lq_vtx[qs + i]].nxt = 0ull;
+            for (int i = (int)bid * NT + tid; i < cnt; i += (int)nblk * NT) a.vn[a.lq_vtx[qs + i]].nxt = 0ull;
         }
     } else if (phase == PH_BC) {
+        const BatchArgs a = load();
+        if (tid < kLanes) s_lsrc[tid] = a.lane_src[tid];
+        __syncthreads();
         // dependencies -> BC in lane order (the run's source order), then
         // clear the visited words.  A wavefront takes 64 consecutive
         // vertices; their delta rows are read 8 lanes (64 bytes) at a time,
@@ -875,9 +977,9 @@ __device__ __forceinline__ void batch_step_body(const BatchArgs &a, const unsign
         // leaves the non-negative sum's bits unchanged)
         const int lo = s_lo, span = s_hi - s_lo;
         const unsigned long long keep = s_lmask & ~s_dead;
-        const int lane = lane_id(), wv = tid / kWave;
+        const int wv = wid;
         double *tile = s_scratch[wv].tile;
-        for (int base = ((int)bid * kWavesPerBlock + wv) * kWave; base < span; base += (int)nblk * kBlock) {
+        for (int base = ((int)bid * NW + wv) * kWave; base < span; base += (int)nblk * NT) {
             const int i = base + lane;
             const int w = lo + i;
             VisNext x;
@@ -916,10 +1018,11 @@ __device__ __forceinline__ void batch_step_body(const BatchArgs &a, const unsign
             }
         }
     } else if (phase == PH_DUMP_FWD || phase == PH_DUMP_BWD) {
+        const BatchArgs a = load();
         const int k = s_dlane;
         const int L = s_L;
         const int total = s_qe;
-        for (int j = (int)bid * kBlock + tid; j < total; j += (int)nblk * kBlock) {
+        for (int j = (int)bid * NT + tid; j < total; j += (int)nblk * NT) {
             if (!((a.lq_mask[j] >> k) & 1ull)) continue;
             int lo = 0, hi = L;  // level of entry j: level_off[lvl] <= j < level_off[lvl+1]
             while (hi - lo > 1) {
@@ -936,7 +1039,7 @@ __device__ __forceinline__ void batch_step_body(const BatchArgs &a, const unsign
             }
         }
         if (phase == PH_DUMP_FWD && bid == 0)
-            for (int i = tid; i < L; i += kBlock) a.dump_shift[i] = MODE ? a.shift[(size_t)i * kLanes + k] : 0;
+            for (int i = tid; i < L; i += NT) a.dump_shift[i] = MODE ? a.shift[(size_t)i * kLanes + k] : 0;
     }
 
     // ---- per-launch counters into the slots; the last workgroup continues
@@ -950,25 +1053,25 @@ __device__ __forceinline__ void batch_step_body(const BatchArgs &a, const unsign
     cn.v[SC_OVF] = my_ovf;
     cn.v[SC_PAIRS] = my_pairs;
     cn.v[SC_LENT] = my_lent;
+    const BatchArgs a = load();
     if (MODE == 1 && phase == PH_SIG) {
         // per-lane exponent range of the new level: reduced over the
         // workgroup in LDS, then one atomic per lane into the workgroup's slot
-        if (active) {
-            if (my_maxe != INT_MIN) atomicMax(&s_emax[lane], my_maxe);
-            if (my_mine != INT_MAX) atomicMin(&s_emin[lane], my_mine);
-        }
+        if (my_maxe != INT_MIN) atomicMax(&s_emax[lane], my_maxe);
+        if (my_mine != INT_MAX) atomicMin(&s_emin[lane], my_mine);
         __syncthreads();
-        const int slot = (int)(bid % kSlots);
-        if (tid < kLanes && s_emax[tid] != INT_MIN) atomicMax(&a.maxexp[slot * kLanes + tid], s_emax[tid]);
-        else if (tid >= kLanes && tid < 2 * kLanes && s_emin[tid - kLanes] != INT_MAX)
-            atomicMin(&a.maxexp[(kSlots + slot) * kLanes + tid - kLanes], s_emin[tid - kLanes]);
-        // completed before this workgroup arrives (the last one reads them)
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        __builtin_amdgcn_s_waitcnt(0);
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        if (nblk > 1) {
+            const int slot = (int)(bid % kSlots);
+            if (tid < kLanes && s_emax[tid] != INT_MIN) atomicMax(&a.maxexp[slot * kLanes + tid], s_emax[tid]);
+            else if (tid >= kLanes && tid < 2 * kLanes && s_emin[tid - kLanes] != INT_MAX)
+                atomicMin(&a.maxexp[(kSlots + slot) * kLanes + tid - kLanes], s_emin[tid - kLanes]);
+            // completed before this workgroup arrives (the last one reads them)
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            __builtin_amdgcn_s_waitcnt(0);
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        }
     }
-    if (!step_epilogue(c, cn, s_red, &s_last, active, bid, grid)) return;
-    collect_slots(c, s_tot, s_red);
+    if (!step_epilogue<NW>(gc, cn, s_red, s_tot, &s_last, bid, nblk)) return;
 
     // ---- the last workgroup advances the state machine
     int action = 0;  // 1 = begin batch, 2 = advance level
@@ -987,13 +1090,13 @@ __device__ __forceinline__ void batch_step_body(const BatchArgs &a, const unsign
         if (phase == PH_FWD) c->st_vticks[s_variant] += dt;
         c->last_tick = now;
         const int rl = (phase == PH_FWD || phase == PH_BWD) ? l : (phase == PH_SIG ? l + 1 : -1);
-        if (rl >= 0 && a.lvl) {
+        if (rl >= 0 && a.lvl) {  // (atomics that nothing waits for)
             LevelRec &r = level_rec(a.lvl, rl);
-            r.arcs += s_tot[SC_ARCS];
-            r.ticks += dt;
+            (void)atomicAdd(&r.arcs, s_tot[SC_ARCS]);
+            (void)atomicAdd(&r.ticks, dt);
             if (phase == PH_FWD) {
-                r.visits += 1;
-                r.var[s_variant] += 1;
+                (void)atomicAdd(&r.visits, 1ull);
+                (void)atomicAdd(&r.var[s_variant], 1ull);
             }
         }
         bool timed_again = false;
@@ -1047,24 +1150,24 @@ __device__ __forceinline__ void batch_step_body(const BatchArgs &a, const unsign
             c->clb += 1;
             c->phase = PH_SIG;
         } else if (phase == PH_UNDO) {
-            c->next_qc = 0ull;
-            c->next_hq = 0;
+            gc->next_qc = 0ull;
+            gc->next_hq = 0;
             c->cvar += 1;
             c->variant = c->cvar;
             c->phase = PH_FWD;
         } else if (timed_again) {
         } else if (phase == PH_FWD) {
-            const unsigned long long qc = ld_agent(&c->next_qc);
+            const unsigned long long qc = ld_agent(&gc->next_qc);
             const uint32_t cnt = (uint32_t)qc, cost = (uint32_t)(qc >> 32);
-            const unsigned long long nh = ld_agent(&c->next_hq);
-            const int qe = a.level_off[l + 1];
+            const unsigned long long nh = ld_agent(&gc->next_hq);
+            const int qe = s_qe;  // level_off[l + 1]
             c->st_fwd_levels += 1;
             c->st_var[s_variant] += 1;
             c->st_qentries += cnt;
-            if (a.lvl) level_rec(a.lvl, l + 1).entries += cnt;
-            a.hq.off[l + 2] = a.hq.off[l + 1] + (int)(uint32_t)nh;
+            if (a.lvl) (void)atomicAdd(&level_rec(a.lvl, l + 1).entries, (unsigned long long)cnt);
+            a.hq.off[l + 2] = s_hqb + (int)(uint32_t)nh;
             a.hq.nseg[l + 1] = (int)(nh >> 32);
-            c->next_hq = 0;
+            gc->next_hq = 0;
             if (cnt == 0) {
                 const int L = l + 1;
                 c->n_levels = L;
@@ -1080,7 +1183,7 @@ __device__ __forceinline__ void batch_step_body(const BatchArgs &a, const unsign
                         const int k = __ffsll(o) - 1;
                         const uint32_t q = c->n_ovf;
                         if (q < a.ovf_cap) a.ovf_list[q] = start + k;
-                        else c->err |= ERR_OVF_CAP;
+                        else gc->err |= ERR_OVF_CAP;
                         c->n_ovf = q + 1;
                     }
                     c->dead |= back;
@@ -1092,15 +1195,15 @@ __device__ __forceinline__ void batch_step_body(const BatchArgs &a, const unsign
                 else if (L >= 2) { c->phase = PH_BWD; c->level = L - 1; }
                 else c->phase = PH_BC;
             } else if (l + 2 >= a.max_levels) {
-                c->err |= ERR_LEVEL_CAP;
+                gc->err |= ERR_LEVEL_CAP;
                 c->phase = PH_DONE;
             } else {
                 a.level_off[l + 2] = qe + (int)cnt;
                 // close the groups of level l+1 (every entry costs >= 2 units)
-                const uint32_t gb = a.gbase[l + 1];
+                const uint32_t gb = s_gbn;  // gbase[l + 1]
                 const uint32_t ng = (cost - 1u) / (uint32_t)kBudget + 1u;
                 if ((unsigned long long)gb + ng + 1u > a.gcap) {
-                    c->err |= ERR_QUEUE_CAP;
+                    gc->err |= ERR_QUEUE_CAP;
                     c->phase = PH_DONE;
                 } else {
                     a.gstart[gb] = 0u;
@@ -1142,6 +1245,8 @@ __device__ __forceinline__ void batch_step_body(const BatchArgs &a, const unsign
     __syncthreads();
     action = s_cnt;
     if (action == 1) {
+        gc->next_qc = 0ull;
+        gc->next_hq = 0ull;
         batch_begin<MODE>(a, c, c->pos, s_lds, &s_feat, s_lsrc, &s_qn, s_tmp, s_lead);
     } else if (action == 2) {
         // finish level l+1: lane deaths, FP64 shifts, features, policy
@@ -1155,31 +1260,47 @@ __device__ __forceinline__ void batch_step_body(const BatchArgs &a, const unsign
                     o &= o - 1;
                     const uint32_t q = c->n_ovf;
                     if (q < a.ovf_cap) a.ovf_list[q] = start + k;
-                    else c->err |= ERR_OVF_CAP;
+                    else gc->err |= ERR_OVF_CAP;
                     c->n_ovf = q + 1;
                 }
                 c->dead |= ovf;
             }
             c->active = s_tot[SC_ACT] & ~c->dead;
         }
-        if (MODE && tid < kLanes) {
-            int mx = INT_MIN, mn = INT_MAX;
-            for (int sl = 0; sl < kSlots; ++sl) {
-                mx = max(mx, ld_agent(&a.maxexp[sl * kLanes + tid]));
-                mn = min(mn, ld_agent(&a.maxexp[(kSlots + sl) * kLanes + tid]));
-                a.maxexp[sl * kLanes + tid] = INT_MIN;
-                a.maxexp[(kSlots + sl) * kLanes + tid] = INT_MAX;
+        if (MODE && nblk > 1) {
+            // exponent ranges of the workgroups: all slots read at once
+            constexpr int kPer = kSlots / NW;
+            const int nslots = (int)min(nblk, (unsigned)kSlots);
+            int mx[kPer], mn[kPer];
+#pragma unroll
+            for (int q = 0; q < kPer; ++q) {
+                const int sl = wid + q * NW;
+                mx[q] = sl < nslots ? ld_agent(&a.maxexp[sl * kLanes + lane]) : INT_MIN;
+                mn[q] = sl < nslots ? ld_agent(&a.maxexp[(kSlots + sl) * kLanes + lane]) : INT_MAX;
             }
+#pragma unroll
+            for (int q = 0; q < kPer; ++q) {
+                const int sl = wid + q * NW;
+                if (sl >= nslots) break;
+                atomicMax(&s_emax[lane], mx[q]);
+                atomicMin(&s_emin[lane], mn[q]);
+                a.maxexp[sl * kLanes + lane] = INT_MIN;
+                a.maxexp[(kSlots + sl) * kLanes + lane] = INT_MAX;
+            }
+            __syncthreads();
+        }
+        if (MODE && tid < kLanes) {
+            const int mx = s_emax[tid], mn = s_emin[tid];
             int sh = 0;
             if (mx != INT_MIN && mx > kExpHigh) sh = mx - kExpTarget;
-            if (mn != INT_MAX && mn - sh < kExpLow) atomicOr(&c->err, ERR_SIGMA_RANGE);
+            if (mn != INT_MAX && mn - sh < kExpLow) atomicOr(&gc->err, ERR_SIGMA_RANGE);
             a.shift[(size_t)(l + 1) * kLanes + tid] = sh;
             // true counts of level l+1 are the stored ones times 2^lane_E
             if (mx != INT_MIN) c->lane_emax[tid] = max(c->lane_emax[tid], mx + c->lane_E[tid]);
             c->lane_E[tid] += sh;
         }
         if (tid == 0) {
-            const uint32_t cnt = (uint32_t)ld_agent(&c->next_qc);
+            const uint32_t cnt = (uint32_t)ld_agent(&gc->next_qc);
             const unsigned long long edges = s_tot[SC_EDGES];
             c->level = l + 1;
             c->visited_n += cnt;
@@ -1192,7 +1313,7 @@ __device__ __forceinline__ void batch_step_body(const BatchArgs &a, const unsign
             s_feat.nu = (float)((long long)c->range_nodeg - (long long)fn);
             s_feat.mu = (float)((long long)c->range_arcs - (long long)fm);
             s_feat.level = l + 1;
-            c->next_qc = 0ull;
+            gc->next_qc = 0ull;
             c->prev_variant = c->variant;
             c->phase = PH_FWD;
         }
@@ -1203,19 +1324,36 @@ __device__ __forceinline__ void batch_step_body(const BatchArgs &a, const unsign
         if (tid == 0)
             set_level_variant(a, c, v, lbo, s_feat, (float)(c->range_hi - c->range_lo), (float)c->range_arcs);
     }
+    if constexpr (!SOLO) head_store(gc, s_head, parity);
 }
 
+// Arguments of a step launch, read from the kernel's own argument segment.
+struct LaunchArgs {
+    typedef const __attribute__((address_space(4))) unsigned long long *Words;
+    Words p;
+    __device__ __forceinline__ LaunchArgs() : p((Words)__builtin_amdgcn_kernarg_segment_ptr()) {}
+    __device__ __forceinline__ BatchArgs operator()() const {
+        Words q = p;
+        asm volatile("" : "+s"(q));  // the loads stay in the phase that asks
+        BatchArgs a;
+        static_assert(sizeof(BatchArgs) % 8 == 0, "copied in 8-byte words");
+        unsigned long long *d = (unsigned long long *)&a;
+#pragma unroll
+        for (int i = 0; i < (int)(sizeof(BatchArgs) / 8); ++i) d[i] = q[i];
+        return a;
+    }
+};
+
 template <int MODE>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(BC_WAVES))) void batch_step(BatchArgs a) {
-    batch_step_body<MODE>(a, blockIdx.x, gridDim.x);
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(BC_WAVES))) void batch_step(BatchArgs) {
+    const LaunchArgs load;
+    const BatchArgs a = load();
+    batch_step_body<MODE, kWavesPerBlock, false>(load, a.ctl, a.parity, blockIdx.x, gridDim.x);
 }
 
 template __global__ void batch_step<0>(BatchArgs);
 template __global__ void batch_step<1>(BatchArgs);
 
-#ifndef BC_BLOCK_WAVES
-#define BC_BLOCK_WAVES 2
-#endif
 // Block engine: a persistent launch in which every workgroup owns a level
 // state machine.  A workgroup takes a chunk (batches [b0, b1) of one graph
 // with vertices [lo, hi)), points the per-vertex arrays of its arguments at
@@ -1226,21 +1364,48 @@ template __global__ void batch_step<1>(BatchArgs);
 // chunk to chunk, so tags left by an earlier chunk never match.  Exit: the
 // work queue runs dry (every workgroup takes chunks until the counter passes
 // n_chunks), a step reports an error, or a chunk exceeds max_steps per batch.
-template <int MODE>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(BC_BLOCK_WAVES))) void block_run(BlockArgs ra) {
+// Arguments that sit in LDS, moved to scalar registers.
+struct LdsArgs {
+    const BatchArgs *p;
+    __device__ __forceinline__ BatchArgs operator()() const {
+        BatchArgs a;
+        int *d = (int *)&a;
+        const int *q = (const int *)p;
+#pragma unroll
+        for (int i = 0; i < (int)(sizeof(BatchArgs) / 4); ++i) d[i] = uniform(q[i]);
+        return a;
+    }
+};
+
+template <int MODE, int NW>
+__global__ __launch_bounds__(NW * kWave) void block_run(BlockArgs ra) {
+    constexpr int NT = NW * kWave;
     // the workgroup's arguments live in LDS: thread 0 points them at the
     // chunk's state, every thread reads them there
     __shared__ BatchArgs s_a;
     __shared__ int s_go;
     const int tid = threadIdx.x;
-    Ctl *c = ra.ctls + blockIdx.x;
+    // the control block, too: its fields change every step
+    __shared__ SoloCtl s_ctl;
+    Head *c = &s_ctl.h[0];
+    {
+        const Head &g = ra.ctls[blockIdx.x].h[0];
+        for (int i = tid; i < (int)(sizeof(Head) / 8); i += NT)
+            ((unsigned long long *)c)[i] = ((const unsigned long long *)&g)[i];
+        if (tid == 0) {
+            s_ctl.err = 0;
+            s_ctl.next_qc = 0ull;
+            s_ctl.next_hq = 0ull;
+            s_ctl.work[0][0] = 0u;
+        }
+    }
     char *base = ra.scratch + (size_t)blockIdx.x * ra.stride;
     const BlockLayout L((size_t)ra.nmax, ra.lq_cap, (size_t)ra.max_levels, ra.gcap, ra.hq_entries, ra.hq_levels,
                         ra.part_cap, ra.ovf_cap);
     if (tid == 0) {
         BatchArgs &a = s_a;
         a = ra.a;
-        a.ctl = c;
+        a.ctl = nullptr;
         a.lvl = nullptr;
         a.lq_vtx = (int32_t *)(base + L.lq_vtx);
         a.lq_mask = (unsigned long long *)(base + L.lq_mask);
@@ -1274,12 +1439,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(BC_BLOCK
         a.col_cap = 0;
     }
     int32_t *mx = (int32_t *)(base + L.maxexp);
-    for (int i = tid; i < 2 * kSlots * kLanes; i += kBlock) mx[i] = i < kSlots * kLanes ? INT_MIN : INT_MAX;
+    for (int i = tid; i < 2 * kSlots * kLanes; i += NT) mx[i] = i < kSlots * kLanes ? INT_MIN : INT_MAX;
     for (;;) {
         __syncthreads();
         if (tid == 0) {
             const uint32_t k = atomicAdd(ra.next, 1u);
-            const int t = (k < (uint32_t)ra.n_chunks && c->err == 0) ? ra.order[k] : -1;
+            const int t = (k < (uint32_t)ra.n_chunks && s_ctl.err == 0) ? ra.order[k] : -1;
             s_go = t;
             if (t >= 0) {
                 const int b0 = ra.c_b0[t], b1 = ra.c_b1[t];
@@ -1311,26 +1476,33 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(BC_BLOCK
         const int b0 = ra.c_b0[t], b1 = ra.c_b1[t];
         const int lo = ra.a.batch_lo[b0], hi = ra.a.batch_hi[b0];
         double *part = ra.partials + ra.c_part[t];
-        for (int i = tid; i < hi - lo; i += kBlock) part[i] = 0.0;
+        for (int i = tid; i < hi - lo; i += NT) part[i] = 0.0;
         const int64_t max_steps = (int64_t)(b1 - b0 + 1) * ra.max_steps;
         for (int64_t step = 0;; ++step) {
             __builtin_amdgcn_s_waitcnt(0);
             __syncthreads();
             if (tid == 0) {
-                int go = (c->phase != PH_DONE && c->err == 0) ? 1 : 0;
+                int go = (c->phase != PH_DONE && s_ctl.err == 0) ? 1 : 0;
                 if (go && step >= max_steps) {
-                    c->err |= ERR_LEVEL_CAP;
+                    s_ctl.err |= ERR_LEVEL_CAP;
                     go = 0;
                 }
                 s_go = go;
             }
             __syncthreads();
             if (!s_go) break;
-            batch_step_body<MODE>(s_a, 0u, 1u);
+            batch_step_body<MODE, NW, true>(LdsArgs{&s_a}, &s_ctl, 0, 0u, 1u);
         }
     }
+    // state and statistics back for the host
+    __syncthreads();
+    Ctl &g = ra.ctls[blockIdx.x];
+    for (int i = tid; i < (int)(sizeof(Head) / 8); i += NT)
+        ((unsigned long long *)&g.h[0])[i] = ((const unsigned long long *)c)[i];
+    if (tid == 0) g.err = s_ctl.err;
 }
 
-template __global__ void block_run<0>(BlockArgs);
+template __global__ void block_run<0, 4>(BlockArgs);
+template __global__ void block_run<0, 16>(BlockArgs);
 
 }  // namespace bcx

@@ -103,7 +103,6 @@ __device__ __forceinline__ unsigned active_blocks(long long items, unsigned grid
     if (b > (long long)grid) b = grid;
     return (unsigned)b;
 }
-__device__ __forceinline__ unsigned active_blocks(long long items) { return active_blocks(items, gridDim.x); }
 
 // Work items of a step, [0, total), are dealt to ncls = min(nblk, kSlots)
 // classes k mod ncls; the workgroups of class r (blockIdx.x mod ncls) share
@@ -112,15 +111,17 @@ __device__ __forceinline__ unsigned active_blocks(long long items) { return acti
 // so a wavefront that finishes early takes the next item without all
 // wavefronts meeting on one address.  Items are independent and each sum
 // stays inside one item, so the assignment never changes a result.
+template <int NW = kWavesPerBlock>
 struct WorkCursor {
     uint32_t *ctr;
     int r, ncls, nwr, j, jn;
-    __device__ __forceinline__ WorkCursor(Ctl *c, unsigned nblk, unsigned bid) {
+    template <class C>
+    __device__ __forceinline__ WorkCursor(C *c, unsigned nblk, unsigned bid) {
         ncls = (int)(nblk < (unsigned)kSlots ? nblk : (unsigned)kSlots);
         r = (int)(bid % (unsigned)ncls);
         const int nb = ((int)nblk - r + ncls - 1) / ncls;  // workgroups of class r
-        nwr = nb * kWavesPerBlock;
-        j = (int)(bid / (unsigned)ncls) * kWavesPerBlock + uniform((int)(threadIdx.x >> 6));
+        nwr = nb * NW;
+        j = (int)(bid / (unsigned)ncls) * NW + uniform((int)(threadIdx.x >> 6));
         ctr = &c->work[r][0];
         jn = fetch();
     }
@@ -136,13 +137,34 @@ struct WorkCursor {
     }
 };
 
-// End of a step for one workgroup: reduce the counters over the workgroup,
-// add them into the workgroup's slot, count the workgroup in (two-level
-// arrival so no single address takes one atomic per workgroup).  Returns
-// true in exactly one workgroup -- the last -- once every workgroup of the
-// launch has arrived.  Workgroups without work (active == false) only count
-// themselves in, so the last one cannot move the state machine on while a
-// late workgroup still has to read it.
+// Copy of the state in LDS: one 8-byte load per thread and one round trip
+// (field by field, every update by the last workgroup's one thread stood behind
+// a load of its own: about 10 us of a step).
+template <int NT>
+__device__ __forceinline__ void head_load(Head &s, const Head &g) {
+    unsigned long long *d = (unsigned long long *)&s;
+    const unsigned long long *p = (const unsigned long long *)&g;
+    for (int i = threadIdx.x; i < (int)(sizeof(Head) / 8); i += NT) d[i] = p[i];
+}
+// The next state, for the launch of the other parity (last workgroup, all
+// threads).  Workgroups without work may still be reading the current one.
+__device__ __forceinline__ void head_store(Ctl *c, const Head &s, int parity) {
+    __syncthreads();
+    const unsigned long long *p = (const unsigned long long *)&s;
+    unsigned long long *d = (unsigned long long *)&c->h[1 - parity];
+    for (int i = threadIdx.x; i < (int)(sizeof(Head) / 8); i += kBlock) d[i] = p[i];
+    if (threadIdx.x == 0) {
+        c->phase = s.phase;
+        if (s.phase == PH_DONE) c->h[parity].phase = PH_DONE;
+    }
+}
+
+// End of a step for one workgroup that took part: reduce the counters over
+// the workgroup, add them into the workgroup's slot, count the workgroup in
+// (two-level arrival so no single address takes one atomic per workgroup).
+// Returns true in exactly one workgroup -- the last -- once the nblk workgroups
+// that take part have arrived; s_tot then holds the totals, and slots, arrival
+// and work counters are reset.
 //
 // No fences: within a launch, workgroups exchange only device-scope atomics
 // here (slot counters, arrival counts, queue counters); plain stores are
@@ -153,30 +175,41 @@ struct WorkCursor {
 // atomics that a workgroup issues before calling this (the slot counters
 // here, a caller's exponent ranges) must have completed before it counts
 // itself in: each wave that issued one waits for its memory counters first.
-// s_red needs kWavesPerBlock * kNCnt entries.
-__device__ __forceinline__ bool step_epilogue(Ctl *c, Counters &cn, unsigned long long *s_red, int *s_last,
-                                              bool active, unsigned bid, unsigned grid) {
+// A step of one workgroup (nblk = 1) exchanges nothing.
+// s_red needs NW * kNCnt entries.
+template <int NW, class C>
+__device__ __forceinline__ bool step_epilogue(C *c, Counters &cn, unsigned long long *s_red, unsigned long long *s_tot,
+                                              int *s_last, unsigned bid, unsigned nblk) {
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    const int slot = bid % kSlots;
-    if (active) {
 #pragma unroll
-        for (int k = 0; k < kNCnt; ++k) {
-            unsigned long long x = cn.v[k];
+    for (int k = 0; k < kNCnt; ++k) {
+        unsigned long long x = cn.v[k];
+        if (__any(x != 0ull)) {
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) x = cnt_combine(k, x, __shfl_xor(x, o));
-            if (lane == 0) s_red[wid * kNCnt + k] = x;
         }
+        if (lane == 0) s_red[wid * kNCnt + k] = x;
+    }
+    __syncthreads();
+    unsigned long long t = 0;
+    const int k = threadIdx.x;
+    if (k < kNCnt) {
+        t = s_red[k];
+        for (int w = 1; w < NW; ++w) t = cnt_combine(k, t, s_red[w * kNCnt + k]);
+    }
+    if (nblk == 1) {
+        if (k < kNCnt) s_tot[k] = t;
+        if (k == 0) c->work[0][0] = 0u;
         __syncthreads();
-        if (threadIdx.x < kNCnt) {
-            const int k = threadIdx.x;
-            unsigned long long t = s_red[k];
-            for (int w = 1; w < kWavesPerBlock; ++w) t = cnt_combine(k, t, s_red[w * kNCnt + k]);
-            if (t) {
-                const int op = cnt_op(k);
-                if (op == 0) atomicAdd(&c->slot[slot][k], t);
-                else if (op == 1) atomicOr(&c->slot[slot][k], t);
-                else atomicMax(&c->slot[slot][k], t);
-            }
+        return true;
+    }
+    if constexpr (NW == kWavesPerBlock && sizeof(C) == sizeof(Ctl)) {
+        const int slot = bid % kSlots;
+        if (k < kNCnt && t) {
+            const int op = cnt_op(k);
+            if (op == 0) atomicAdd(&c->slot[slot][k], t);
+            else if (op == 1) atomicOr(&c->slot[slot][k], t);
+            else atomicMax(&c->slot[slot][k], t);
         }
         // The slot atomics return nothing, so nothing has waited for them;
         // the last workgroup reads the slots once every arrival is counted,
@@ -185,47 +218,43 @@ __device__ __forceinline__ bool step_epilogue(Ctl *c, Counters &cn, unsigned lon
         __builtin_amdgcn_s_waitcnt(0);
         __atomic_signal_fence(__ATOMIC_SEQ_CST);
         __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        int last = 0;
-        const unsigned in_slot = (grid - slot + kSlots - 1) / kSlots;
-        const unsigned t = atomicAdd(&c->arrive[slot], 1u);
-        if (t == in_slot - 1) {
-            const unsigned nslots = grid < (unsigned)kSlots ? grid : (unsigned)kSlots;
-            const unsigned t2 = atomicAdd(&c->blocks_done, 1u);
-            last = (t2 == nslots - 1) ? 1 : 0;
+        const unsigned nslots = nblk < (unsigned)kSlots ? nblk : (unsigned)kSlots;
+        if (threadIdx.x == 0) {
+            int last = 0;
+            const unsigned in_slot = (nblk - slot + kSlots - 1) / kSlots;
+            if (atomicAdd(&c->arrive[slot], 1u) == in_slot - 1)
+                last = atomicAdd(&c->blocks_done, 1u) == nslots - 1 ? 1 : 0;
+            *s_last = last;
         }
-        *s_last = last;
-    }
-    __syncthreads();
-    return *s_last != 0;
-}
-__device__ __forceinline__ bool step_epilogue(Ctl *c, Counters &cn, unsigned long long *s_red, int *s_last,
-                                              bool active) {
-    return step_epilogue(c, cn, s_red, s_last, active, blockIdx.x, gridDim.x);
-}
-
-// In the last workgroup: totals of all slots into s_tot[kNCnt] (valid after
-// the call in every thread); slots and arrival counters are reset.
-__device__ __forceinline__ void collect_slots(Ctl *c, unsigned long long *s_tot, unsigned long long *s_tmp /*kSlots*kNCnt*/) {
-    const int t = threadIdx.x;
-    if (t < kSlots) {
+        __syncthreads();
+        if (!*s_last) return false;
+        // totals: wavefront w takes counters w, w + 4, ..., lane = slot
+        unsigned long long x[(kNCnt + NW - 1) / NW];
 #pragma unroll
-        for (int k = 0; k < kNCnt; ++k) {
-            s_tmp[t * kNCnt + k] = __hip_atomic_load(&c->slot[t][k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            c->slot[t][k] = 0ull;
+        for (int q = 0; q < (kNCnt + NW - 1) / NW; ++q) {
+            const int kk = wid + q * NW;
+            x[q] = (kk < kNCnt && lane < (int)nslots)
+                       ? __hip_atomic_load(&c->slot[lane][kk], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                       : 0ull;
         }
-        c->arrive[t] = 0u;
-        c->work[t][0] = 0u;
+#pragma unroll
+        for (int q = 0; q < (kNCnt + NW - 1) / NW; ++q) {
+            const int kk = wid + q * NW;
+            if (kk >= kNCnt) break;
+            unsigned long long y = x[q];
+#pragma unroll
+            for (int o = kSlots / 2; o > 0; o >>= 1) y = cnt_combine(kk, y, __shfl_xor(y, o));
+            if (lane == 0) s_tot[kk] = y;
+            if (lane < (int)nslots) c->slot[lane][kk] = 0ull;
+        }
+        if (threadIdx.x < nslots) {
+            c->arrive[threadIdx.x] = 0u;
+            c->work[threadIdx.x][0] = 0u;
+        }
+        if (threadIdx.x == 0) c->blocks_done = 0u;
+        __syncthreads();
     }
-    __syncthreads();
-    if (t < kNCnt) {
-        unsigned long long x = s_tmp[t];
-        for (int sl = 1; sl < kSlots; ++sl) x = cnt_combine(t, x, s_tmp[sl * kNCnt + t]);
-        s_tot[t] = x;
-    }
-    if (t == 0) c->blocks_done = 0u;
-    __syncthreads();
+    return true;
 }
 
 // ----------------------------------------------------------- staged appends
@@ -274,10 +303,20 @@ __device__ __forceinline__ int class_deg(const GraphArgs &g, int v, int out_deg)
 // Write the n staged entries of this wavefront to the level queue (absolute
 // positions qbase + counter), heavy ones also to the level's heavy list.
 #ifndef BC_BUDGET
-#define BC_BUDGET 64
+#define BC_BUDGET 16
 #endif
 constexpr int kBudget = BC_BUDGET;  // cost units (8 arcs each) per work group
-static_assert(kBudget >= 2 && kBudget <= 128, "a group must fit in one wavefront (every entry costs >= 2 units)");
+#ifndef BC_MERGE
+#define BC_MERGE 8
+#endif
+constexpr int kMergeMax = BC_MERGE;  // consecutive groups a wavefront takes at once on large levels
+static_assert(kBudget >= 2 && kBudget * kMergeMax <= 128, "a merged group must fit in one wavefront (every entry costs >= 2 units)");
+// Groups per item of a step with ng groups on `waves` wavefronts: each wavefront
+// gets one item while the level is small, items of full size beyond (a group
+// costs a wavefront its entries' offsets and words before the first arc).
+__device__ __forceinline__ int merge_groups(uint32_t ng, unsigned waves) {
+    return (int)min((uint32_t)kMergeMax, max(1u, (ng + waves - 1) / waves));
+}
 
 // Work estimate of a level entry in units of 8 arcs: its adjacency plus a
 // fixed part; heavy entries (split into segments elsewhere) count 2.  Every
@@ -299,7 +338,8 @@ struct GroupArgs {
     uint32_t gcap = 0;
 };
 
-__device__ __forceinline__ void stage_flush(Stage &st, int &n, Ctl *c, int32_t *q, uint32_t qbase, uint32_t qcap,
+template <class C>
+__device__ __forceinline__ void stage_flush(Stage &st, int &n, C *c, int32_t *q, uint32_t qbase, uint32_t qcap,
                                             const HeavyQ &hq, uint32_t hq_base, int32_t *err,
                                             const GroupArgs &ga) {
     if (n == 0) return;
@@ -369,7 +409,8 @@ __device__ __forceinline__ void stage_flush(Stage &st, int &n, Ctl *c, int32_t *
 // Stage w (degree deg) for every lane with pred; flushes once 64 or more are
 // waiting.  n is the wavefront-uniform fill count.  The wavefront must be
 // converged.
-__device__ __forceinline__ void stage_push(bool pred, int32_t w, int32_t deg, Stage &st, int &n, Ctl *c, int32_t *q,
+template <class C>
+__device__ __forceinline__ void stage_push(bool pred, int32_t w, int32_t deg, Stage &st, int &n, C *c, int32_t *q,
                                            uint32_t qbase, uint32_t qcap, const HeavyQ &hq, uint32_t hq_base,
                                            int32_t *err, const GroupArgs &ga) {
     const unsigned long long m = __ballot(pred);

@@ -89,12 +89,11 @@ constexpr int32_t kLbDefault = LB_RULE | (LB_RULE << 2);  // sig option | bwd op
 constexpr float kPolicyMargin = 0.15f;
 constexpr int kMlpParams = kMlpH * kMlpIn + kMlpH + kMlpH * kMlpH + kMlpH + kMlpOut * kMlpH + kMlpOut;
 
-// Control block in device memory.  Written by the host before a run, then
-// only by the last workgroup of each step launch.
-struct Ctl {
-    // --- polled by the host after every chunk of launches (keep first)
+// State of the level machine.  Written by the host before a run, then only by
+// the last workgroup of each step launch, which works on a copy in LDS.
+struct Head {
     int32_t phase;
-    int32_t err;          // sticky device error bits (capacity, range)
+    int32_t policy;
     // --- progress
     int64_t pos;          // plain: index of the current source; batched: current batch
     int64_t n_items;      // plain: number of sources; batched: number of batches
@@ -102,7 +101,6 @@ struct Ctl {
     int32_t n_levels;     // levels of the finished forward (L)
     int32_t variant;      // discover variant of the current level
     int32_t prev_variant;
-    int32_t policy;
     int32_t mode;         // 0 = uint64 path counts, 1 = scaled FP64
     int32_t lanes;        // batched: sources in the current batch
     uint32_t epoch;       // batched: tag base of the current forward
@@ -112,19 +110,11 @@ struct Ctl {
     unsigned long long lane_mask;   // valid lanes of the batch
     unsigned long long active;      // lanes with a non-empty frontier at level l
     unsigned long long dead;        // lanes that overflowed in uint64 mode
-    // --- level under construction (atomics)
-    uint32_t blocks_done;
-    unsigned long long next_qc;  // appends to the next level: entries (low 32 bits), cost units (high 32)
-    unsigned long long next_edges;
-    unsigned long long next_active;
-    unsigned long long ovf_lanes;
-    int32_t overflow;     // plain: the current source overflowed
-    int32_t maxexp;       // plain FP64: max binary exponent of the level built
-    int32_t minexp;
+    unsigned long long next_edges;  // plain FP64: arcs of the level under construction
     uint32_t total_queued;
     uint32_t n_ovf;       // overflowed sources recorded
     // --- features of the frontier at level l
-    unsigned long long f_nf, f_mf, visited_n, visited_m, full_n, full_m;
+    unsigned long long visited_n, visited_m, full_n, full_m;
     unsigned long long range_nodeg, range_arcs;  // non-isolated vertices / arcs of the range
     // --- timing collection (policy training data)
     int32_t collect;      // 1 = run every forward level with each variant, every path-count
@@ -141,17 +131,12 @@ struct Ctl {
     int32_t dump_lane;    // batched: lane of the dumped source in its batch
     int32_t dump_state;   // 0 = pending, 1 = forward dumped, 2 = done
     int32_t f64_check;    // batched FP64 pass: hand back lanes whose counts stay below 2^65
-    int32_t lane_E[64];   // batched FP64: power of two of the current level's stored counts, per lane
-    int32_t lane_emax[64];  // batched FP64: largest binary exponent of a true count so far, per lane
     // --- wide weighted engine: the relaxation queue of the current round
     uint32_t w_cnt, w_groups;   // entries, work groups
     int32_t w_heavy, w_hsegs;   // heavy entries, their segments
-    // --- heavy entries of the level under construction: count | segments << 32
-    unsigned long long next_hq;
-    // --- per-slot counters and workgroup arrivals of the running step
-    unsigned long long slot[kSlots][kNCnt];
-    uint32_t arrive[kSlots];
-    uint32_t work[kSlots][32];  // per-slot work counters, one 128-byte line each
+    int32_t pad;
+    int32_t lane_E[64];   // batched FP64: power of two of the current level's stored counts, per lane
+    int32_t lane_emax[64];  // batched FP64: largest binary exponent of a true count so far, per lane
     // --- statistics
     unsigned long long st_steps, st_fwd_levels, st_var[3], st_arcs, st_lane_arcs, st_qentries,
         st_max_levels, st_batches;
@@ -162,6 +147,35 @@ struct Ctl {
     unsigned long long st_parcs[kPhases];    // arcs scanned per phase
     unsigned long long st_plarcs[kPhases];   // DAG (arc, source) pairs per phase
     unsigned long long st_ppairs[kPhases];   // matched neighbour rows per phase
+};
+static_assert(sizeof(Head) % 8 == 0, "copied in 8-byte words");
+
+// Control block in device memory.  A launch of parity p reads the state from
+// h[p] and its last workgroup writes the next one to h[1 - p], so a workgroup
+// without work may read it and leave at any time during the launch; only the workgroups
+// that take part count themselves in.  (A finished machine sets the phase of
+// both.)
+struct Ctl {
+    // --- polled by the host after every chunk of launches (keep first)
+    int32_t phase;        // of the state written last
+    int32_t err;          // sticky device error bits (capacity, range)
+    // --- level under construction (atomics)
+    unsigned long long next_qc;  // appends to the next level: entries (low 32 bits), cost units (high 32)
+    unsigned long long next_hq;  // heavy entries of the level under construction: count | segments << 32
+    uint32_t blocks_done;
+    uint32_t pad;
+    Head h[2];
+    // --- per-slot counters and workgroup arrivals of the running step
+    unsigned long long slot[kSlots][kNCnt];
+    uint32_t arrive[kSlots];
+    uint32_t work[kSlots][32];  // per-slot work counters, one 128-byte line each
+};
+// The same for a machine that one workgroup runs alone (block engine), in LDS.
+struct SoloCtl {
+    int32_t err;
+    unsigned long long next_qc, next_hq;
+    uint32_t work[1][1];
+    Head h[1];
 };
 
 enum : int32_t { ERR_QUEUE_CAP = 1, ERR_SIGMA_RANGE = 2, ERR_LEVEL_CAP = 4, ERR_OVF_CAP = 8 };
@@ -229,6 +243,7 @@ struct PlainArgs {
     GraphArgs g;
     PolicyArgs p;
     Ctl *ctl;
+    int32_t parity;          // of this launch (see Ctl)
     int32_t *d;              // int32[n], -1 = unvisited (kept -1 between sources)
     unsigned long long *sig; // uint64[n] or FP64 bits (mode 1); kept 0 between sources
     double *chat;            // FP64[n] scaled (1 + delta) / sigma
@@ -266,6 +281,7 @@ struct BatchArgs {
     GraphArgs g;
     PolicyArgs p;
     Ctl *ctl;
+    int32_t parity;              // of this launch (see Ctl)
     VisNext *vn;                 // [n]
     Tagged *fw0, *fw1;           // [n] each; level parity selects the buffer
     int32_t *lq_vtx;             // level queues: vertex
@@ -438,6 +454,7 @@ struct WideArgs {
     const int32_t *wt;           // weights of the out-arcs
     const int32_t *rev;          // out-arc -> the same arc's position among the in-arcs
     Ctl *ctl;
+    int32_t parity;              // of this launch (see Ctl)
     int32_t shift;               // log2 of a row's bytes (8 bytes per source of a batch)
     unsigned long long *dist, *sigma;  // rows of uint64 (sigma: FP64 bits in mode 1)
     double *chat, *delta;

@@ -42,7 +42,7 @@ __device__ __forceinline__ void plain_push_arcs(const PlainArgs &a, int l, unsig
                                                 unsigned long long &my_larcs, int &my_ovf, Stage &st, int &sn) {
     const int32_t *__restrict__ rp = a.g.row_ptr;
     const int32_t *__restrict__ col = a.g.col;
-    Ctl *c = a.ctl;
+    Ctl *gc = a.ctl;
     for (int eb = a0; eb < a1; eb += kWave) {
         const int e = eb + lane_id();
         bool newly = false;
@@ -66,7 +66,7 @@ __device__ __forceinline__ void plain_push_arcs(const PlainArgs &a, int l, unsig
                 my_edges += (unsigned)dw;
             }
         }
-        stage_push(newly, w, dw, st, sn, c, a.queue, qe, (uint32_t)a.g.n, a.hq, hqb, &c->err, GroupArgs{});
+        stage_push(newly, w, dw, st, sn, gc, a.queue, qe, (uint32_t)a.g.n, a.hq, hqb, &gc->err, GroupArgs{});
     }
 }
 
@@ -102,7 +102,7 @@ __device__ __forceinline__ void wave_sum_u128(unsigned long long &lo, unsigned l
 
 // Transition helpers run by the last workgroup (all threads present).
 template <int MODE>
-__device__ __forceinline__ void plain_begin_source(const PlainArgs &a, Ctl *c, int64_t pos, float *lds, LevelFeatures *sf) {
+__device__ __forceinline__ void plain_begin_source(const PlainArgs &a, Ctl *gc, Head *c, int64_t pos, float *lds, LevelFeatures *sf) {
     if (threadIdx.x == 0) {
         const int s = a.srcs[pos];
         a.d[s] = 0;
@@ -123,17 +123,15 @@ __device__ __forceinline__ void plain_begin_source(const PlainArgs &a, Ctl *c, i
             a.hq.off[1] = 0;
             a.hq.nseg[0] = 0;
         }
-        c->next_hq = 0;
+        gc->next_hq = 0;
         c->pos = pos;
         c->level = 0;
-        c->overflow = 0;
-        c->next_qc = 0ull;
-        c->next_edges = 0;
+        gc->next_qc = 0ull;
         c->visited_n = 1;
         c->visited_m = (unsigned long long)deg;
         c->prev_variant = V_PUSH_TPV;
         c->phase = PH_FWD;
-        level_rec(a.lvl, 0).entries += 1;
+        (void)atomicAdd(&level_rec(a.lvl, 0).entries, 1ull);
         c->st_lane_entries += 1;
         sf->nf = 1.0f;
         sf->mf = (float)deg;
@@ -148,7 +146,7 @@ __device__ __forceinline__ void plain_begin_source(const PlainArgs &a, Ctl *c, i
 }
 
 template <int MODE>
-__device__ __forceinline__ void plain_advance_level(const PlainArgs &a, Ctl *c, int l, uint32_t cnt, unsigned long long edges,
+__device__ __forceinline__ void plain_advance_level(const PlainArgs &a, Ctl *gc, Head *c, int l, uint32_t cnt, unsigned long long edges,
                                     float *lds, LevelFeatures *sf) {
     if (threadIdx.x == 0) {
         c->level = l + 1;
@@ -159,8 +157,7 @@ __device__ __forceinline__ void plain_advance_level(const PlainArgs &a, Ctl *c, 
         sf->nu = (float)((long long)a.g.n - (long long)c->visited_n);
         sf->mu = (float)((long long)a.g.nnz_lo - (long long)c->visited_m);
         sf->level = l + 1;
-        c->next_qc = 0ull;
-        c->next_edges = 0;
+        gc->next_qc = 0ull;
         c->prev_variant = c->variant;
         c->phase = PH_FWD;
     }
@@ -171,7 +168,7 @@ __device__ __forceinline__ void plain_advance_level(const PlainArgs &a, Ctl *c, 
 }
 
 // After the forward of the current source ended with L levels.
-__device__ __forceinline__ void plain_after_forward(const PlainArgs &a, Ctl *c, int L) {
+__device__ __forceinline__ void plain_after_forward(const PlainArgs &a, Head *c, int L) {
     c->n_levels = L;
     if ((unsigned long long)L > c->st_max_levels) c->st_max_levels = L;
     if (c->dump_pos == c->pos && c->dump_state == 0) {
@@ -189,13 +186,17 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
     __shared__ int s_phase, s_level, s_variant, s_last, s_qb, s_qe, s_qn, s_sh0, s_sh1, s_dump;
     __shared__ int s_h0, s_h1, s_hseg, s_hqb;
     __shared__ unsigned s_nblk;
-    __shared__ unsigned long long s_red[kSlots * kNCnt];
+    __shared__ unsigned long long s_red[kWavesPerBlock * kNCnt];
+    __shared__ Head s_head;
     __shared__ unsigned long long s_tot[kNCnt];
     __shared__ Stage s_stage[kWavesPerBlock];
     __shared__ float s_lds[2 * kMlpH + kMlpOut + 4];
     __shared__ LevelFeatures s_feat;
-    Ctl *c = a.ctl;
+    Ctl *gc = a.ctl;
+    Head *c = &s_head;
+    head_load<kBlock>(s_head, gc->h[a.parity]);
     const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    __syncthreads();
     if (tid == 0) {
         s_phase = c->phase;
         s_level = c->level;
@@ -253,13 +254,13 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
         } else if (s_phase == PH_DUMP_FWD) {
             items = (a.g.n + kWave - 1) / kWave;
         }
-        s_nblk = active_blocks(items);
+        s_nblk = active_blocks(items, gridDim.x);
     }
     __syncthreads();
     const int phase = s_phase;
     if (phase == PH_DONE || phase == PH_IDLE) return;
     const unsigned nblk = s_nblk;
-    const bool active = blockIdx.x < nblk;  // workgroups beyond nblk only count in
+    if (blockIdx.x >= nblk) return;  // no work for this workgroup
 
     const int gw = blockIdx.x * kWavesPerBlock + wid;
     const int nw = (int)nblk * kWavesPerBlock;
@@ -274,8 +275,7 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
     unsigned long long my_edges = 0, my_arcs = 0, my_larcs = 0;
     int my_ovf = 0, my_maxe = INT_MIN, my_mine = INT_MAX;
 
-    if (!active) {
-    } else if (phase == PH_FWD) {
+    if (phase == PH_FWD) {
         const int qb = s_qb, qe = s_qe, cnt = qe - qb;
         const int variant = s_variant;
         const uint32_t hqb = (uint32_t)s_hqb;
@@ -334,7 +334,7 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
                                 my_edges += (unsigned)dw;
                             }
                         }
-                        stage_push(newly, w, dw, st, sn, c, a.queue, (uint32_t)qe, (uint32_t)n, a.hq, hqb, &c->err, GroupArgs{});
+                        stage_push(newly, w, dw, st, sn, gc, a.queue, (uint32_t)qe, (uint32_t)n, a.hq, hqb, &gc->err, GroupArgs{});
                     }
                     // medium-degree vertices: the whole wavefront, one at a time
                     unsigned long long mm = __ballot(deg > kLightDeg && deg <= kSeg);
@@ -398,7 +398,7 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
                     }
                     const int deg = rp[w + 1] - rp[w];
                     if (newly) my_edges += (unsigned)deg;
-                    stage_push(newly, w, deg, st, sn, c, a.queue, (uint32_t)qe, (uint32_t)n, a.hq, hqb, &c->err, GroupArgs{});
+                    stage_push(newly, w, deg, st, sn, gc, a.queue, (uint32_t)qe, (uint32_t)n, a.hq, hqb, &gc->err, GroupArgs{});
                     continue;
                 }
                 const int w = it * kWave + lane;
@@ -470,10 +470,10 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
                     }
                     my_edges += (unsigned)deg;
                 }
-                stage_push(ok, w, deg, st, sn, c, a.queue, (uint32_t)qe, (uint32_t)n, a.hq, hqb, &c->err, GroupArgs{});
+                stage_push(ok, w, deg, st, sn, gc, a.queue, (uint32_t)qe, (uint32_t)n, a.hq, hqb, &gc->err, GroupArgs{});
             }
         }
-        stage_flush(st, sn, c, a.queue, (uint32_t)qe, (uint32_t)n, a.hq, hqb, &c->err, GroupArgs{});
+        stage_flush(st, sn, gc, a.queue, (uint32_t)qe, (uint32_t)n, a.hq, hqb, &gc->err, GroupArgs{});
     } else if (MODE == 1 && phase == PH_SIG) {
         // FP64 path counts of level l+1, pulled in CSR order
         const int qs = s_qe, cnt = s_qn - s_qe;
@@ -635,8 +635,7 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
     cn.v[SC_OVF] = my_ovf ? 1ull : 0ull;
     if (my_maxe != INT_MIN) cn.exponent(my_maxe);
     if (my_mine != INT_MAX) cn.exponent(my_mine);
-    if (!step_epilogue(c, cn, s_red, &s_last, active)) return;
-    collect_slots(c, s_tot, s_red);
+    if (!step_epilogue<kWavesPerBlock>(gc, cn, s_red, s_tot, &s_last, blockIdx.x, nblk)) return;
 
     // ---- the last workgroup advances the state machine
     int begin_pos = 0;
@@ -658,30 +657,30 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
         const int rl = (phase == PH_FWD || phase == PH_BWD) ? l : (phase == PH_SIG ? l + 1 : -1);
         if (rl >= 0) {
             LevelRec &r = level_rec(a.lvl, rl);
-            r.arcs += s_tot[SC_ARCS];
-            r.ticks += dt;
+            (void)atomicAdd(&r.arcs, s_tot[SC_ARCS]);
+            (void)atomicAdd(&r.ticks, dt);
             if (phase == PH_FWD) {
-                r.visits += 1;
-                r.var[s_variant] += 1;
+                (void)atomicAdd(&r.visits, 1ull);
+                (void)atomicAdd(&r.var[s_variant], 1ull);
             }
         }
         if (phase == PH_FWD) {
-            const uint32_t cnt = (uint32_t)ld_agent(&c->next_qc);
-            const unsigned long long nh = ld_agent(&c->next_hq);
-            const int qe = a.level_off[l + 1];
+            const uint32_t cnt = (uint32_t)ld_agent(&gc->next_qc);
+            const unsigned long long nh = ld_agent(&gc->next_hq);
+            const int qe = s_qe;  // level_off[l + 1]
             a.level_off[l + 2] = qe + (int)cnt;
-            a.hq.off[l + 2] = a.hq.off[l + 1] + (int)(uint32_t)nh;
+            a.hq.off[l + 2] = s_hqb + (int)(uint32_t)nh;
             a.hq.nseg[l + 1] = (int)(nh >> 32);
-            c->next_hq = 0;
+            gc->next_hq = 0;
             c->st_fwd_levels += 1;
             c->st_var[s_variant] += 1;
             c->st_qentries += cnt;
             c->st_lane_entries += cnt;
-            level_rec(a.lvl, l + 1).entries += cnt;
+            (void)atomicAdd(&level_rec(a.lvl, l + 1).entries, (unsigned long long)cnt);
             if (MODE == 0 && s_tot[SC_OVF]) {
                 const uint32_t k = c->n_ovf;
                 if (k < a.ovf_cap) a.ovf_list[k] = c->pos;
-                else c->err |= ERR_OVF_CAP;
+                else gc->err |= ERR_OVF_CAP;
                 c->n_ovf = k + 1;
                 c->total_queued = (uint32_t)(qe + (int)cnt);
                 c->phase = PH_FIN;
@@ -701,10 +700,10 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
             const int mx = (int)s_tot[SC_MAXE] - 4096, mn = 4096 - (int)s_tot[SC_MINE];
             int sh = 0;
             if (any && mx > kExpHigh) sh = mx - kExpTarget;
-            if (any && mn - sh < kExpLow) c->err |= ERR_SIGMA_RANGE;
+            if (any && mn - sh < kExpLow) gc->err |= ERR_SIGMA_RANGE;
             a.shift[l + 1] = sh;
             advance = 1;
-            cnt_next = (uint32_t)ld_agent(&c->next_qc);
+            cnt_next = (uint32_t)ld_agent(&gc->next_qc);
             edges_next = c->next_edges;
         } else if (phase == PH_BWD) {
             if (l - 1 >= 1) {
@@ -735,8 +734,9 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
         s_red[0] = edges_next;
     }
     __syncthreads();
-    if (s_qb == 1) plain_begin_source<MODE>(a, c, c->pos, s_lds, &s_feat);
-    else if (s_qe == 1) plain_advance_level<MODE>(a, c, l, (uint32_t)s_qn, s_red[0], s_lds, &s_feat);
+    if (s_qb == 1) plain_begin_source<MODE>(a, gc, c, c->pos, s_lds, &s_feat);
+    else if (s_qe == 1) plain_advance_level<MODE>(a, gc, c, l, (uint32_t)s_qn, s_red[0], s_lds, &s_feat);
+    head_store(gc, s_head, a.parity);
 }
 
 template __global__ void plain_step<0>(PlainArgs);

@@ -136,7 +136,7 @@ __device__ __forceinline__ void take_matches(unsigned long long &bal, unsigned l
 
 // Counters of a wavefront's path-count or backward items.
 struct ArcCounters {
-    unsigned long long larcs = 0, arcs = 0, pairs = 0;
+    unsigned larcs = 0, arcs = 0, pairs = 0;
 };
 
 // Sum over arcs [a0, a1) (one entry's, wavefront-uniform bounds) of the rows
@@ -175,7 +175,8 @@ __device__ __forceinline__ void row_arcs(Lanes lanes, unsigned long long m, int 
 
 // Per-lane counters the path-count finalisation feeds.
 struct SigCounters {
-    unsigned long long edges = 0, act = 0, ovf = 0, full_n = 0, full_m = 0, lent = 0;
+    unsigned edges = 0, full_n = 0, full_m = 0, lent = 0;
+    unsigned long long act = 0, ovf = 0;
     int maxe = INT_MIN, mine = INT_MAX;
     ArcCounters ac;
 };
@@ -214,7 +215,7 @@ __device__ __forceinline__ void bwd_values(unsigned long long raw, double acc, i
 // chunk (searching the prefix sums across lanes took six dependent LDS
 // round trips and five more to fetch the entry's values).
 constexpr int kPack = 64;                // entries of degree <= kPack are packed
-constexpr int kPackEntries = kBudget / 2;
+constexpr int kPackEntries = kBudget * kMergeMax / 2;
 constexpr int kPackWords = kPackEntries + 4;  // up to 64 positions per entry
 struct Packing {
     unsigned long long start[kPackWords];
@@ -385,6 +386,7 @@ __device__ __forceinline__ void bwd_finish(unsigned long long todo, unsigned lon
             bwd_values<MODE>(raw[q], as_f64(sum[q]), sh, shn, delta, c);
             row_store(chat.row(vq[q]), slot, as_u64(c));
             row_store(delta_slab.row(vq[q]), slot, as_u64(delta));
+            __builtin_amdgcn_sched_barrier(0);  // four divisions at once would not fit the registers
         }
     }
 }

@@ -350,7 +350,7 @@ __device__ __forceinline__ void back_group(const WideArgs &a, int qb, int i0, in
 // Set up batch b (last workgroup, all threads): its sources are the first
 // round of the relaxation and of the DAG rounds.
 template <int MODE>
-__device__ __forceinline__ void wide_begin(const WideArgs &a, Ctl *c, int64_t b, int *s_src, int *s_lead) {
+__device__ __forceinline__ void wide_begin(const WideArgs &a, Ctl *gc, Head *c, int64_t b, int *s_src, int *s_lead) {
     const int t = threadIdx.x;
     const int64_t start = a.batch_start[b];
     const int lanes = (int)(a.batch_start[b + 1] - start);
@@ -421,8 +421,8 @@ __device__ __forceinline__ void wide_begin(const WideArgs &a, Ctl *c, int64_t b,
         c->w_groups = ng;
         c->w_heavy = nh;
         c->w_hsegs = segs;
-        c->next_qc = 0ull;
-        c->next_hq = 0ull;
+        gc->next_qc = 0ull;
+        gc->next_hq = 0ull;
         c->visited_n = 0ull;  // no round before
         c->pos = b;
         c->lanes = lanes;
@@ -446,17 +446,21 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     __shared__ uint32_t s_gb, s_ng;
     __shared__ unsigned s_nblk;
     __shared__ unsigned long long s_dead, s_lmask;
-    __shared__ unsigned long long s_red[kSlots * kNCnt];
+    __shared__ unsigned long long s_red[kWavesPerBlock * kNCnt];
+    __shared__ Head s_head;
     __shared__ unsigned long long s_tot[kNCnt];
     __shared__ int s_src[kLanes], s_lead[kLanes];
     __shared__ union {
         WideScratch ws;
         double tile[kWave * 8];
     } s_scratch[kWavesPerBlock];
-    Ctl *c = a.ctl;
+    Ctl *gc = a.ctl;
+    Head *c = &s_head;
+    head_load<kBlock>(s_head, gc->h[a.parity]);
     const int tid = threadIdx.x, lane = tid & 63, wid = uniform(tid >> 6);
     const unsigned bid = blockIdx.x, grid = gridDim.x;
     const int n = a.g.n;
+    __syncthreads();
     if (tid == 0) {
         const int ph = c->phase, l = c->level;
         s_phase = ph;
@@ -506,9 +510,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     const int phase = uniform(s_phase);
     if (phase == PH_DONE || phase == PH_IDLE) return;
     const unsigned nblk = (unsigned)uniform((int)s_nblk);
-    const bool active = bid < nblk;
+    if (bid >= nblk) return;  // no work for this workgroup
     const int l = uniform(s_level);
-    const int hseg = uniform(s_hseg), h0 = uniform(s_h0), h1 = uniform(s_h1), n_groups = uniform((int)s_ng);
+    const int hseg = uniform(s_hseg), h0 = uniform(s_h0), h1 = uniform(s_h1);
+    int n_groups = uniform((int)s_ng);
+    const int ng = n_groups, gm = merge_groups((uint32_t)ng, grid * kWavesPerBlock);
+    n_groups = (ng + gm - 1) / gm;  // consecutive groups of a large round are taken together
     const int total = n_groups + hseg;
     const int32_t *rp = a.g.row_ptr;
     WideScratch &ws = s_scratch[wid].ws;
@@ -516,8 +523,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     ArcCounters ac;
     unsigned long long ovf = 0, lent = 0;
     int sn = 0;
-    if (!active) {
-    } else if (phase == WP_RELAX || phase == WP_MARK) {
+    if (phase == WP_RELAX || phase == WP_MARK) {
         const bool mark = phase == WP_MARK;
         const int r = l % 3, rn = (l + 1) % 3, rp3 = (l + 2) % 3;
         unsigned long long *fc = a.fm + (size_t)r * n;
@@ -541,11 +547,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         const int qb = uniform(s_qb), cnt = mark ? n : uniform(s_qe) - qb;
         const uint32_t *gs = mark ? a.sgs : a.rgs + uniform((int)s_gb);
         const unsigned long long all = uniform(s_lmask);
-        for (WorkCursor wc(c, nblk, bid); wc.item() < total; wc.next(total)) {
+        for (WorkCursor<> wc(gc, nblk, bid); wc.item() < total; wc.next(total)) {
             const int k = wc.item();
             const int it = k < hseg ? n_groups + k : k - hseg;  // heavy segments first
             if (it < n_groups) {
-                const int i0 = uniform((int)gs[it]), i1 = min(uniform((int)gs[it + 1]), cnt);
+                const int i0 = uniform((int)gs[it * gm]), i1 = min(uniform((int)gs[min(it * gm + gm, ng)]), cnt);
                 if (i1 <= i0) continue;
                 const bool valid = i0 + lane < i1;
                 if (!mark) {
@@ -590,7 +596,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             else offer_entry<false>(a, nx, m, dall, a0, a1, ws.st, sn, rc);
         }
         if (!mark)
-            stage_flush(ws.st, sn, c, nx.q, nx.qbase, nx.qcap, nx.hq, nx.hq_base, &c->err, nx.ga);
+            stage_flush(ws.st, sn, gc, nx.q, nx.qbase, nx.qcap, nx.hq, nx.hq_base, &gc->err, nx.ga);
     } else if (phase == WP_DAG) {
         const int qb = uniform(s_qb), qe = uniform(s_qe), cnt = qe - qb;
         const unsigned long long *mask = a.rdy + (size_t)(l % 3) * n;
@@ -610,11 +616,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         nx.ga.gb = a.gbase[l + 1];
         nx.ga.gcap = a.gcap;
         const uint32_t *gs = a.gstart + uniform((int)s_gb);
-        for (WorkCursor wc(c, nblk, bid); wc.item() < total; wc.next(total)) {
+        for (WorkCursor<> wc(gc, nblk, bid); wc.item() < total; wc.next(total)) {
             const int k = wc.item();
             const int it = k < hseg ? n_groups + k : k - hseg;  // heavy segments first
             if (it < n_groups) {
-                const int i0 = uniform((int)gs[it]), i1 = min(uniform((int)gs[it + 1]), cnt);
+                const int i0 = uniform((int)gs[it * gm]), i1 = min(uniform((int)gs[min(it * gm + gm, ng)]), cnt);
                 if (i1 > i0) dag_group<MODE>(a, nx, mask, l, qb, i0, i1, ws, sn, ovf, ac);
                 continue;
             }
@@ -653,16 +659,16 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             SigCounters sc;
             sig_store<OP>(sum, m, row_addr(a.sigma, v, a.shift), a.sigma_limit, ovf, sc);
         }
-        stage_flush(ws.st, sn, c, nx.q, nx.qbase, nx.qcap, nx.hq, nx.hq_base, &c->err, nx.ga);
+        stage_flush(ws.st, sn, gc, nx.q, nx.qbase, nx.qcap, nx.hq, nx.hq_base, &gc->err, nx.ga);
     } else if (phase == WP_BWD) {
         const int qb = uniform(s_qb), cnt = uniform(s_qe) - qb;
         const unsigned long long dead = uniform(s_dead);
         const uint32_t *gs = a.gstart + uniform((int)s_gb);
-        for (WorkCursor wc(c, nblk, bid); wc.item() < total; wc.next(total)) {
+        for (WorkCursor<> wc(gc, nblk, bid); wc.item() < total; wc.next(total)) {
             const int k = wc.item();
             const int it = k < hseg ? n_groups + k : k - hseg;
             if (it < n_groups) {
-                const int i0 = uniform((int)gs[it]), i1 = min(uniform((int)gs[it + 1]), cnt);
+                const int i0 = uniform((int)gs[it * gm]), i1 = min(uniform((int)gs[min(it * gm + gm, ng)]), cnt);
                 if (i1 > i0) back_group<MODE>(a, qb, i0, i1, dead, ws, ac);
                 continue;
             }
@@ -745,7 +751,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             for (; any; any &= any - 1)
                 row_store(row_addr(a.dist, base + __ffsll(any) - 1, a.shift), slot, kInf);
         }
-        if (bad) atomicOr(&c->err, ERR_SIGMA_RANGE);
+        if (bad) atomicOr(&gc->err, ERR_SIGMA_RANGE);
     }
 
     Counters cn;
@@ -754,8 +760,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     cn.v[SC_PAIRS] = ac.pairs;
     cn.v[SC_OVF] = ovf;
     cn.v[SC_LENT] = lent;
-    if (!step_epilogue(c, cn, s_red, &s_last, active, bid, grid)) return;
-    collect_slots(c, s_tot, s_red);
+    if (!step_epilogue<kWavesPerBlock>(gc, cn, s_red, s_tot, &s_last, bid, nblk)) return;
 
     // ---- the last workgroup advances the state machine
     if (tid == 0) {
@@ -768,17 +773,17 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         c->st_ticks[phase] += prev ? now - prev : 0ull;
         c->last_tick = now;
         int action = 0;
-        const unsigned long long qc = ld_agent(&c->next_qc), nh = ld_agent(&c->next_hq);
+        const unsigned long long qc = ld_agent(&gc->next_qc), nh = ld_agent(&gc->next_hq);
         const uint32_t cnt = (uint32_t)qc, cost = (uint32_t)(qc >> 32);
         if (phase == WP_RELAX) {
             c->st_fwd_levels += 1;
-            c->next_qc = 0ull;
-            c->next_hq = 0ull;
+            gc->next_qc = 0ull;
+            gc->next_hq = 0ull;
             c->visited_n = c->w_cnt;  // the queue whose masks the next step clears
             if (cnt == 0) {
                 c->phase = WP_MARK;
             } else if (l > n + 2) {  // cannot happen with positive weights
-                c->err |= ERR_LEVEL_CAP;
+                gc->err |= ERR_LEVEL_CAP;
                 c->phase = PH_DONE;
             } else {
                 const uint32_t gb = (uint32_t)((l + 1) % 3) * a.rgcap, ng = (cost - 1u) / (uint32_t)kBudget + 1u;
@@ -795,14 +800,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             c->phase = WP_DAG;
         } else if (phase == WP_DAG) {
             c->st_var[0] += 1;
-            c->next_qc = 0ull;
-            c->next_hq = 0ull;
+            gc->next_qc = 0ull;
+            gc->next_hq = 0ull;
             const unsigned long long o = s_tot[SC_OVF] & ~c->dead;
             const int64_t start = a.batch_start[c->pos];
             for (unsigned long long x = o; x; x &= x - 1) {
                 const uint32_t q = c->n_ovf;
                 if (q < a.ovf_cap) a.ovf_list[q] = start + __ffsll(x) - 1;
-                else c->err |= ERR_OVF_CAP;
+                else gc->err |= ERR_OVF_CAP;
                 c->n_ovf = q + 1;
             }
             c->dead |= o;
@@ -817,19 +822,19 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                     action = 1;
                 }
             } else if (l + 2 >= a.max_levels + 2) {
-                c->err |= ERR_LEVEL_CAP;
+                gc->err |= ERR_LEVEL_CAP;
                 c->phase = PH_DONE;
             } else {
-                const uint32_t gb = a.gbase[l + 1], ng = (cost - 1u) / (uint32_t)kBudget + 1u;
+                const uint32_t gb = s_gb + s_ng + 1u, ng = (cost - 1u) / (uint32_t)kBudget + 1u;
                 if ((unsigned long long)gb + ng + 1u > a.gcap) {
-                    c->err |= ERR_QUEUE_CAP;
+                    gc->err |= ERR_QUEUE_CAP;
                     c->phase = PH_DONE;
                 } else {
-                    a.level_off[l + 2] = a.level_off[l + 1] + (int)cnt;
+                    a.level_off[l + 2] = s_qe + (int)cnt;
                     a.gstart[gb] = 0u;
                     a.gstart[gb + ng] = cnt;
                     a.gbase[l + 2] = gb + ng + 1u;
-                    a.hq.off[l + 2] = a.hq.off[l + 1] + (int)(uint32_t)nh;
+                    a.hq.off[l + 2] = s_h1 + (int)(uint32_t)nh;
                     a.hq.nseg[l + 1] = (int)(nh >> 32);
                     c->level = l + 1;
                 }
@@ -850,7 +855,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         s_cnt = phase == WP_BEGIN;
     }
     __syncthreads();
-    if (s_cnt) wide_begin<MODE>(a, c, c->pos, s_src, s_lead);
+    if (s_cnt) wide_begin<MODE>(a, gc, c, c->pos, s_src, s_lead);
+    head_store(gc, s_head, a.parity);
 }
 
 template __global__ void wide_step<0>(WideArgs);
