@@ -278,7 +278,7 @@ struct bc_graph {
     // block engine (graphs of at most kBlockMaxN vertices; see run_block)
     bool blk_sized = false;            // per-graph facts below are computed
     int32_t blk_nmax = 0;              // largest graph
-    int64_t blk_cost_max = 0, blk_heavy_max = 0, blk_segs_max = 0;
+    int64_t blk_arcs_max = 0, blk_cost_max = 0, blk_heavy_max = 0, blk_segs_max = 0;
     int blk_wg = 0;                    // workgroups whose state is allocated
     size_t blk_stride = 0;
     BlockArgs blk_dims{};              // capacities of one workgroup's state
@@ -1444,7 +1444,7 @@ __global__ void block_clear_tags(char *scratch, size_t stride, size_t off, size_
     }
 }
 
-// Largest graph, cost units, heavy vertices and segments over the handle's
+// Largest graph, arcs, cost units, heavy vertices and segments over the handle's
 // graphs (entries classified by the larger of out- and in-degree).
 static bc_status block_facts(bc_graph *g) {
     if (g->blk_sized) return BC_OK;
@@ -1456,7 +1456,7 @@ static bc_status block_facts(bc_graph *g) {
         HIP_TRY(hipMemcpy(irp.data(), g->in_row_ptr, sizeof(int32_t) * ((size_t)n + 1), hipMemcpyDeviceToHost));
     }
     int32_t nmax = 0;
-    int64_t cmax = 0, hmax = 0, smax = 0;
+    int64_t cmax = 0, hmax = 0, smax = 0, amax = 0;
     for (int gi = 0; gi < g->n_graphs; ++gi) {
         const int32_t lo = g->voff[gi], hi = g->voff[gi + 1];
         int64_t cost = 0, heavy = 0, segs = 0;
@@ -1473,8 +1473,10 @@ static bc_status block_facts(bc_graph *g) {
         cmax = std::max(cmax, cost);
         hmax = std::max(hmax, heavy);
         smax = std::max(smax, segs);
+        amax = std::max(amax, (int64_t)rp[hi] - rp[lo]);
     }
     g->blk_nmax = nmax;
+    g->blk_arcs_max = amax;
     g->blk_cost_max = cmax;
     g->blk_heavy_max = hmax;
     g->blk_segs_max = smax;
@@ -1484,8 +1486,8 @@ static bc_status block_facts(bc_graph *g) {
 
 // Capacities of one workgroup's state (once per handle) and how many
 // workgroups can run: resident ones (occupancy) that fit in the memory
-// budget (half the free device memory, at most 96 GiB, under the handle's
-// cap).  Returns 0 workgroups when not even one fits.
+// budget (three quarters of the free device memory, at most 192 GiB, under the
+// handle's cap).  Returns 0 workgroups when not even one fits.
 static bc_status block_dims(bc_graph *g, int *resident) {
     BlockArgs &d = g->blk_dims;
     const int64_t nmax = std::max<int32_t>(g->blk_nmax, 1);
@@ -1506,7 +1508,8 @@ static bc_status block_dims(bc_graph *g, int *resident) {
     int dev = 0, cus = 0, per_cu = 0;
     HIP_TRY(hipGetDevice(&dev));
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)block_run<0, 4>, kBlock, 0));
+    HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)block_run<0, kBlockWaves>,
+                                                         kBlockWaves * kWave, 0));
     int64_t want = (int64_t)std::max(1, cus) * std::max(1, per_cu);
     size_t free_b = 0, total_b = 0;
     HIP_TRY(hipMemGetInfo(&free_b, &total_b));
@@ -1545,12 +1548,26 @@ static bc_status ensure_block(bc_graph *g, int need) {
 // The block engine is used for runs of the batched engine without a detail
 // dump over handles whose graphs all have at most kBlockMaxN vertices, always
 // with BC_RUN_BLOCKS, never with BC_RUN_NO_BLOCKS or BC_RUN_ONE_QUEUE, and by
-// default when every graph has at most kBlockDefaultN vertices and the list
-// fills 8 batches.  (A workgroup holds fewer wavefronts than a CU can run,
-// so on larger graphs, whose level steps keep the whole GPU busy, the
-// general engine is faster: 38.0 against 29.4 GTEPS on the BA union
-// sample; on ER(2000) the block engine is faster, 2.36 against 1.65.)
-constexpr int kBlockDefaultN = 16384;
+// default when every graph has at most kBlockDefaultN vertices (in a union
+// kBlockDefaultUnionN) and the list fills 8 batches and one more per 8,192
+// arcs of the largest graph.  A
+// workgroup alone takes a time that grows with the graph's arcs for its
+// batch, whatever the number of batches (up to one per CU: 13 ms on R-MAT of
+// 2^14 vertices and 452,000 arcs, 3 ms on ER with 4,000 and 32,000), the
+// general engine one that grows with the batches, so the line is where the
+// two meet.  General against block engine, in ms: ER(4000) 1.2 and 1.6 at 4
+// batches, 2.1 and 1.7 at 8, 5.5 and 2.5 at 32; R-MAT 2^12 (110,000 arcs)
+// 2.2 and 2.3 at 8, 5.2 and 2.9 at 32; R-MAT 2^14 2.6 and 7.8 at 8, 12.8 and
+// 11.1 at 64, 20.3 and 13.6 at 128; ER(16000) 7.7 and 8.9 at 32, 17.3 and
+// 12.6 at 64; a 100 x 100 grid 5.7 and 6.1 at 4, 10.8 and 7.0 at 8.  A single
+// graph of 2^16 vertices would need some 250 batches (32.3 and 56.6 at 128).
+// Unions keep every workgroup busy up to larger graphs: 64 graphs of up to
+// 16,000 vertices 99.8 and 29.6, of up to 60,000 60.1 and 52.7 (every 64th
+// vertex a source) or 385 and 261 (every 8th), all of 20,000 to 60,000 163 and
+// 129; with graphs of up to 100,000 they meet (108 and 111, 747 and 660), and
+// the state, which grows with the largest graph, passes 30 GB.
+constexpr int kBlockDefaultN = 16384, kBlockDefaultUnionN = 65536;
+constexpr int64_t kBlockArcsPerBatch = 8192;
 static bool use_block(bc_graph *g, const bc_run_options &o, int64_t ns, bool detail) {
     if (g->weighted || detail || o.batch == 1 || (o.flags & (BC_RUN_NO_BLOCKS | BC_RUN_ONE_QUEUE | BC_RUN_FORCE_F64)))
         return false;
@@ -1558,7 +1575,26 @@ static bool use_block(bc_graph *g, const bc_run_options &o, int64_t ns, bool det
     if (block_facts(g) != BC_OK || g->blk_nmax > kBlockMaxN || g->blk_nmax < 1) return false;
     if (o.flags & BC_RUN_BLOCKS) return true;
     const int K = o.batch >= 8 ? o.batch : 64;
-    return g->blk_nmax <= kBlockDefaultN && ns >= 8 * (int64_t)K;
+    return g->blk_nmax <= (g->n_graphs > 1 ? kBlockDefaultUnionN : kBlockDefaultN) &&
+           ns >= (8 + g->blk_arcs_max / kBlockArcsPerBatch) * K;
+}
+
+// Lanes of a block-engine batch when the caller leaves them open: the fewest
+// of 8, 16, 32 and 64 with which the list's batches still fit one per
+// resident workgroup, 64 if none do.  A batch of fewer lanes has fewer queue
+// entries and fewer levels, so it ends earlier, but two batches after one
+// another on a workgroup take longer than one of twice the lanes.  ER(2000),
+// 8 / 16 / 32 / 64 lanes: 1.53 / 1.64 / 1.8 / 2.0 ms (250 batches of 8);
+// ER(4000): 4.37 / 3.26 / 3.7 / 4.28 (500 of 8, 250 of 16); R-MAT 2^14, 8,192
+// sources: - / 19.3 / 13.6 / 15.3 (256 of 32); 96 graphs of 1,000 to 16,000
+// vertices: - / - / 50.3 / 42.3.
+static int block_lanes(const std::vector<int64_t> &runs, int resident) {
+    for (int K = 8; K < 64; K *= 2) {
+        int64_t nb = 0;
+        for (int64_t r : runs) nb += (r + K - 1) / K;
+        if (nb <= resident) return K;
+    }
+    return 64;
 }
 
 // One 64-bit pass over h_srcs on the block engine.  *fallback = true when a
@@ -1580,27 +1616,40 @@ static bc_status run_block(bc_graph *g, const RunCfg &cfg, const bc_run_options 
     s = grow(&g->srcs, &g->srcs_cap, ns, &g->acct);
     if (s != BC_OK) return s;
     HIP_TRY(hipMemcpyAsync(g->srcs, h_srcs, sizeof(int32_t) * ns, hipMemcpyHostToDevice, st));
-    // batches of up to K sources of one graph (as in the general engine)
-    std::vector<int64_t> bs;
-    std::vector<int32_t> blo, bhi, bg;
+    // runs of sources of one graph, cut into batches of up to K sources (as in
+    // the general engine)
+    std::vector<int64_t> runs;
+    std::vector<int32_t> run_g;
     for (int64_t i = 0; i < ns;) {
         const int32_t v = h_srcs[i];
         const int gi = (int)(std::upper_bound(g->voff.begin(), g->voff.end(), v) - g->voff.begin()) - 1;
         const int32_t glo = g->voff[gi], ghi = g->voff[gi + 1];
         int64_t j = i + 1;
-        while (j < ns && j - i < cfg.lanes && h_srcs[j] >= glo && h_srcs[j] < ghi) ++j;
-        bs.push_back(i);
-        blo.push_back(glo);
-        bhi.push_back(ghi);
-        bg.push_back(gi);
+        while (j < ns && h_srcs[j] >= glo && h_srcs[j] < ghi) ++j;
+        runs.push_back(j - i);
+        run_g.push_back(gi);
         i = j;
+    }
+    const int K = o.batch == 0 ? block_lanes(runs, resident) : cfg.lanes;
+    std::vector<int64_t> bs;
+    std::vector<int32_t> blo, bhi, bg;
+    int64_t at = 0;
+    for (size_t r = 0; r < runs.size(); ++r) {
+        const int gi = run_g[r];
+        for (int64_t i = 0; i < runs[r]; i += K) {
+            bs.push_back(at + i);
+            blo.push_back(g->voff[gi]);
+            bhi.push_back(g->voff[gi + 1]);
+            bg.push_back(gi);
+        }
+        at += runs[r];
     }
     bs.push_back(ns);
     const int64_t nb = (int64_t)blo.size();
-    // chunks: runs of at most C consecutive batches of one graph, about four
+    // chunks: runs of at most C consecutive batches of one graph, about eight
     // per resident workgroup
     const int64_t C =
-        std::min<int64_t>(64, std::max<int64_t>(1, (nb + 4 * (int64_t)resident - 1) / (4 * (int64_t)resident)));
+        std::min<int64_t>(64, std::max<int64_t>(1, (nb + 8 * (int64_t)resident - 1) / (8 * (int64_t)resident)));
     std::vector<int32_t> cb0, cb1;
     for (int64_t b = 0; b < nb;) {
         int64_t e = b + 1;
@@ -1719,7 +1768,7 @@ static bc_status run_block(bc_graph *g, const RunCfg &cfg, const bc_run_options 
     HIP_TRY(hipEventCreate(&e0));
     HIP_TRY(hipEventCreate(&e1));
     HIP_TRY(hipEventRecord(e0, st));
-    block_run<0, 4><<<(unsigned)nwg, kBlock, 0, st>>>(ra);
+    block_run<0, kBlockWaves><<<(unsigned)nwg, kBlockWaves * kWave, 0, st>>>(ra);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipEventRecord(e1, st));
     HIP_TRY(hipMemcpyAsync(hc.data(), g->blk_ctls, sizeof(Ctl) * hc.size(), hipMemcpyDeviceToHost, st));

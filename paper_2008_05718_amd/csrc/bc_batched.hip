@@ -1502,7 +1502,6 @@ __global__ __launch_bounds__(NW * kWave) void block_run(BlockArgs ra) {
     if (tid == 0) g.err = s_ctl.err;
 }
 
-template __global__ void block_run<0, 4>(BlockArgs);
-template __global__ void block_run<0, 16>(BlockArgs);
+template __global__ void block_run<0, kBlockWaves>(BlockArgs);
 
 }  // namespace bcx
