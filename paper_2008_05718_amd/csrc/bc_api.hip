@@ -299,15 +299,94 @@ struct bc_graph {
 };
 
 // One sub-union of a many-graph handle: a handle of its own over some of
-// the graphs (vertices renumbered consecutively), its stream, and the map
-// back to the parent's vertex ids.
+// the graphs (vertices renumbered consecutively) and the map back to the
+// parent's vertex ids.
 struct SubPart {
     bc_graph *h = nullptr;
     int32_t *to_parent = nullptr;           // device int32[h->n]
     std::vector<int32_t> to_parent_host;
-    hipStream_t stream = nullptr;
     bool ran = false;                       // had sources in the last run
 };
+
+// The streams that concurrent parts run on.  Each part needs a hardware queue
+// of its own: ordinary streams share the device's few queues with other
+// streams of the process, a stream with a CU mask (here one that enables every
+// CU) gets a dedicated queue.  The device runs about two dozen of those at
+// once and takes turns beyond that, so streams belong to a run and not to a
+// handle: three handles with 16 parts each, one of them running, took 291 ms
+// for what takes 107 ms when the other two do not exist.  A run borrows its
+// streams from here and gives them back; at most kMaxReplicas idle ones are
+// kept for a device, and none once no handle with parts is left.
+constexpr int kMaxReplicas = 16;
+class PartStreams {
+    struct Idle {
+        int dev;
+        bool plain;
+        hipStream_t s;
+    };
+    static std::mutex mu;
+    static std::vector<Idle> idle;
+    static int64_t handles;
+    int dev = 0;
+    bool plain = false;
+    std::vector<hipStream_t> own;
+
+public:
+    PartStreams() = default;
+    PartStreams(const PartStreams &) = delete;
+    PartStreams &operator=(const PartStreams &) = delete;
+    hipStream_t operator[](int i) const { return own[(size_t)i]; }
+    // n streams of the current device; plain: without a queue of their own
+    bc_status borrow(int n, bool plain_) {
+        plain = plain_;
+        HIP_TRY(hipGetDevice(&dev));
+        own.reserve((size_t)n);
+        {
+            std::lock_guard<std::mutex> lock(mu);
+            idle.reserve(idle.size() + (size_t)n);  // (giving back allocates nothing)
+            for (size_t i = idle.size(); i-- > 0 && (int)own.size() < n;)
+                if (idle[i].dev == dev && idle[i].plain == plain) {
+                    own.push_back(idle[i].s);
+                    idle.erase(idle.begin() + (std::ptrdiff_t)i);
+                }
+        }
+        int cus = 0;
+        if ((int)own.size() < n) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+        const std::vector<uint32_t> mask((size_t)std::max(1, (cus + 31) / 32), 0xffffffffu);
+        while ((int)own.size() < n) {
+            hipStream_t s = nullptr;
+            if (plain || hipExtStreamCreateWithCUMask(&s, (uint32_t)mask.size(), mask.data()) != hipSuccess) s = nullptr;
+            if (!s && hipStreamCreateWithFlags(&s, hipStreamNonBlocking) != hipSuccess)
+                return fail(BC_ERR_DEVICE, "part stream");
+            own.push_back(s);
+        }
+        return BC_OK;
+    }
+    ~PartStreams() {
+        std::lock_guard<std::mutex> lock(mu);
+        size_t kept = 0;
+        for (const Idle &i : idle) kept += i.dev == dev;
+        for (hipStream_t s : own) {
+            if (handles > 0 && kept < (size_t)kMaxReplicas && idle.size() < idle.capacity()) {
+                idle.push_back({dev, plain, s});
+                ++kept;
+            } else {
+                (void)hipStreamDestroy(s);
+            }
+        }
+    }
+    // a handle has got parts (+1) or lost them (-1)
+    static void count(int d) {
+        std::lock_guard<std::mutex> lock(mu);
+        handles += d;
+        if (handles > 0) return;
+        for (const Idle &i : idle) (void)hipStreamDestroy(i.s);
+        idle.clear();
+    }
+};
+std::mutex PartStreams::mu;
+std::vector<PartStreams::Idle> PartStreams::idle;
+int64_t PartStreams::handles = 0;
 
 static void free_graphs(bc_graph *g) {
     for (auto &cg : g->graphs) {
@@ -2308,9 +2387,15 @@ static void free_parts(bc_graph *g) {
     for (SubPart &pt : g->parts) {
         if (pt.h) bc_destroy(pt.h);
         if (pt.to_parent) (void)hipFree(pt.to_parent);
-        if (pt.stream) (void)hipStreamDestroy(pt.stream);
     }
+    if (!g->parts.empty()) PartStreams::count(-1);
     g->parts.clear();
+}
+
+// The handle's parts are complete, or given up after an error.
+static void set_parts(bc_graph *g, std::vector<SubPart> &&parts) {
+    g->parts = std::move(parts);
+    PartStreams::count(1);
 }
 
 // Replicas of a single graph: the run option, else 8 while one batch's steps
@@ -2319,7 +2404,6 @@ static void free_parts(bc_graph *g) {
 // -3 %; the damaged 1024^2 grid, whose levels are many and thin: 8 replicas
 // 5.83 GTEPS against 5.42 for 4 and 5.41 for 16, which the autotuner finds).
 // BC_REPLICAS overrides both (1 .. 16).
-constexpr int kMaxReplicas = 16;
 static int n_replicas(const bc_graph *g, const bc_run_options &o) {
     static const int env = [] {
         const char *e = std::getenv("BC_REPLICAS");
@@ -2399,10 +2483,6 @@ static bc_status ensure_replicas(bc_graph *g, int R) {
         if (!parts_fit(g, (size_t)R * (g->create_bytes + z.bytes + run_buffer_bytes(g->n))))
             return fail(BC_ERR_OUT_OF_MEMORY, "concurrent replicas do not fit under max_device_bytes");
     }
-    int cus = 0, dev = 0;
-    (void)hipGetDevice(&dev);
-    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    std::vector<uint32_t> cu_mask((size_t)std::max(1, (cus + 31) / 32), 0xffffffffu);
     std::vector<float> w;
     if (g->has_mlp) {
         w.resize(kMlpParams);
@@ -2416,17 +2496,13 @@ static bc_status ensure_replicas(bc_graph *g, int R) {
                                           (g->directed ? BC_DIRECTED : 0u),
                                       &pt.h);
         if (s == BC_OK && !w.empty()) s = bc_load_policy(pt.h, w.data(), kMlpParams);
-        if (s == BC_OK && hipExtStreamCreateWithCUMask(&pt.stream, (uint32_t)cu_mask.size(), cu_mask.data()) != hipSuccess)
-            pt.stream = nullptr;
-        if (s == BC_OK && !pt.stream && hipStreamCreateWithFlags(&pt.stream, hipStreamNonBlocking) != hipSuccess)
-            s = fail(BC_ERR_DEVICE, "replica stream");
         if (s != BC_OK) {
-            g->parts = std::move(parts);
+            set_parts(g, std::move(parts));
             free_parts(g);
             return s;
         }
     }
-    g->parts = std::move(parts);
+    set_parts(g, std::move(parts));
     g->replicas = true;
     return BC_OK;
 }
@@ -2488,13 +2564,6 @@ static bc_status ensure_parts(bc_graph *g) {
         HIP_TRY(hipMemcpy(w.data(), g->mlp, sizeof(float) * kMlpParams, hipMemcpyDeviceToHost));
     }
     std::vector<SubPart> parts(P);
-    // each part needs a hardware queue of its own: ordinary streams share the
-    // device's few queues with other streams of the process, a stream with
-    // a CU mask gets a dedicated queue (here the mask enables every CU)
-    int cus = 0, dev = 0;
-    (void)hipGetDevice(&dev);
-    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    std::vector<uint32_t> cu_mask((size_t)std::max(1, (cus + 31) / 32), 0xffffffffu);
     for (int p = 0; p < P; ++p) {
         std::vector<int32_t> srp(1, 0), scol, svoff(1, 0), map;
         for (int i = 0; i < G; ++i) {
@@ -2519,19 +2588,14 @@ static bc_status ensure_parts(bc_graph *g) {
         if (s == BC_OK && !map.empty() &&
             hipMemcpy(pt.to_parent, map.data(), sizeof(int32_t) * map.size(), hipMemcpyHostToDevice) != hipSuccess)
             s = fail(BC_ERR_DEVICE, "part vertex map copy");
-        if (s == BC_OK && std::getenv("BC_PART_PLAIN_STREAMS") == nullptr &&
-            hipExtStreamCreateWithCUMask(&pt.stream, (uint32_t)cu_mask.size(), cu_mask.data()) != hipSuccess)
-            pt.stream = nullptr;
-        if (s == BC_OK && !pt.stream && hipStreamCreateWithFlags(&pt.stream, hipStreamNonBlocking) != hipSuccess)
-            s = fail(BC_ERR_DEVICE, "part stream");
         pt.to_parent_host = std::move(map);
         if (s != BC_OK) {
-            g->parts = std::move(parts);
+            set_parts(g, std::move(parts));
             free_parts(g);
             return s;
         }
     }
-    g->parts = std::move(parts);
+    set_parts(g, std::move(parts));
     return BC_OK;
 }
 
@@ -2548,6 +2612,9 @@ static bc_status run_parts(bc_graph *g, const int32_t *sources, int64_t n_source
     if (ns < 0) return fail(BC_ERR_INVALID_ARG, "n_sources < 0");
     if (detail && (dump_index < 0 || dump_index >= ns)) return fail(BC_ERR_INVALID_ARG, "dump_index out of range");
     const int P = repl ? R : (int)g->parts.size();
+    PartStreams streams;
+    s = streams.borrow(P, !repl && std::getenv("BC_PART_PLAIN_STREAMS") != nullptr);
+    if (s != BC_OK) return s;
     std::vector<std::vector<int32_t>> lists(P);
     int dump_part = -1;
     int64_t dump_local = -1;
@@ -2585,7 +2652,7 @@ static bc_status run_parts(bc_graph *g, const int32_t *sources, int64_t n_source
     hipEvent_t ev0;
     HIP_TRY(hipEventCreateWithFlags(&ev0, hipEventDisableTiming));
     HIP_TRY(hipEventRecord(ev0, st));
-    for (int p = 0; p < P; ++p) HIP_TRY(hipStreamWaitEvent(g->parts[p].stream, ev0, 0));
+    for (int p = 0; p < P; ++p) HIP_TRY(hipStreamWaitEvent(streams[p], ev0, 0));
     (void)hipEventDestroy(ev0);
     // sub-detail buffers for the part that holds the dumped source
     const size_t dn = dump_part >= 0 ? (size_t)std::max<int32_t>(g->parts[dump_part].h->n, 1) : 0;
@@ -2614,9 +2681,9 @@ static bc_status run_parts(bc_graph *g, const int32_t *sources, int64_t n_source
             if (po.grid_blocks == 0) po.grid_blocks = part_grid;
             SubPart &pt = g->parts[p];
             if (p == dump_part)
-                res[p] = run_impl(pt.h, lists[p].data(), (int64_t)lists[p].size(), &po, pt.stream, dump_local, &sub_det);
+                res[p] = run_impl(pt.h, lists[p].data(), (int64_t)lists[p].size(), &po, streams[p], dump_local, &sub_det);
             else
-                res[p] = run_impl(pt.h, lists[p].data(), (int64_t)lists[p].size(), &po, pt.stream, -1, nullptr);
+                res[p] = run_impl(pt.h, lists[p].data(), (int64_t)lists[p].size(), &po, streams[p], -1, nullptr);
             if (res[p] != BC_OK) msg[p] = bc_last_error();
         });
     }
@@ -2630,12 +2697,12 @@ static bc_status run_parts(bc_graph *g, const int32_t *sources, int64_t n_source
         if (repl) {
             if (!lists[p].empty()) ps.p[ps.n++] = pt.h->bc;
         } else if (!(lists[p].empty() && !acc) && pt.h->n > 0) {
-            scatter_f64<<<grid_for(pt.h->n, 256, 4096), 256, 0, pt.stream>>>(g->bc, pt.h->bc, pt.to_parent, pt.h->n);
+            scatter_f64<<<grid_for(pt.h->n, 256, 4096), 256, 0, streams[p]>>>(g->bc, pt.h->bc, pt.to_parent, pt.h->n);
             HIP_TRY(hipGetLastError());
         }
         hipEvent_t ev;
         HIP_TRY(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
-        HIP_TRY(hipEventRecord(ev, pt.stream));
+        HIP_TRY(hipEventRecord(ev, streams[p]));
         HIP_TRY(hipStreamWaitEvent(st, ev, 0));
         (void)hipEventDestroy(ev);
     }
