@@ -19,10 +19,16 @@
 //
 // Backward (both modes): delta(v) = sigma(v) * sum over successors w of
 // c(w), c(w) = (1 + delta(w)) / sigma(w) -- Eq. 2 with sigma(v) factored
-// out.  Each vertex's sum is formed by one thread (degree <= kLightDeg), one
+// out.  Each vertex's sum is formed by kSub lanes (degree <= kSubDeg), one
 // wavefront (<= kSeg) or kSeg-arc segments combined in segment order by the
 // last segment to finish; no floating-point atomics, so results are bitwise
 // reproducible.
+//
+// What bounds a step is the chain of dependent loads behind an arc (vertex,
+// row bounds, column, level, value), not bytes, so the arcs are spread over
+// lanes and every lane requests kArcs of them together.  With a thread per
+// vertex instead, up to 32 arcs after one another, 32 sources on R-MAT 18 took
+// 27.3 ms, now 13.5; 4 on a 512 x 512 grid 38.6, now 24.5.
 #define BC_PLAIN_TU 1  // this engine's segment size: kSegPlain
 #include "bc_common.h"
 
@@ -34,70 +40,145 @@ __device__ __forceinline__ double norm_sigma(const PlainArgs &a, int v, int sh) 
     return ldexp(as_f64(a.sig[v]), -sh);
 }
 
-// Top-down over arcs [a0, a1) of frontier vertex v (path count sv): claim
-// unvisited neighbours, add sv to the neighbours on level l+1 (MODE 0).
-template <int MODE>
-__device__ __forceinline__ void plain_push_arcs(const PlainArgs &a, int l, unsigned long long sv, int a0, int a1,
+// A vertex's arcs [e0, e0 + len) are worked on by a group of G consecutive
+// lanes (kSub, or the wavefront), kArcs per lane at a time.
+// (R-MAT 18, 32 sources: 13.5 ms with 8 lanes, 13.8 with 4, 14.2 with 16; 2, 4
+// and 8 arcs per lane 14.5, 13.5 and 14.0; up to 32, 64 and 128 arcs 13.7, 13.5
+// and 13.5.)
+constexpr int kSub = 8;
+constexpr int kSubDeg = 64;
+constexpr int kArcs = 4;
+constexpr int kPullRun = 4;
+constexpr int kPullSpan = 32;  // vertices a wavefront looks over for unvisited ones
+template <int G>
+__device__ __forceinline__ bool group_any(bool x) {
+    const unsigned long long b = __ballot(x);
+    return G == kWave ? b != 0ull : ((b >> (lane_id() & ~(G - 1))) & ((1ull << (G & 63)) - 1)) != 0ull;
+}
+
+// Top-down over the arcs of a frontier vertex (path count sv): claim unvisited
+// neighbours, add sv to the neighbours on level l+1 (MODE 0).
+template <int MODE, int G>
+__device__ __forceinline__ void plain_push_arcs(const PlainArgs &a, int l, unsigned long long sv, int e0, int len,
                                                 uint32_t qe, uint32_t hqb, unsigned long long &my_edges,
                                                 unsigned long long &my_larcs, int &my_ovf, Stage &st, int &sn) {
     const int32_t *__restrict__ rp = a.g.row_ptr;
     const int32_t *__restrict__ col = a.g.col;
     Ctl *gc = a.ctl;
-    for (int eb = a0; eb < a1; eb += kWave) {
-        const int e = eb + lane_id();
-        bool newly = false;
-        int w = 0, dw = 0;
-        if (e < a1) {
-            w = col[e];
-            int dv = a.d[w];
-            if (dv == -1) {
-                const int old = atomicCAS(&a.d[w], -1, l + 1);
-                newly = (old == -1);
-                dv = newly ? l + 1 : old;
+    for (int t = lane_id() & (G - 1); __any(t < len); t += kArcs * G) {
+        int w[kArcs], dv[kArcs], dw[kArcs];
+        bool newly[kArcs];
+#pragma unroll
+        for (int q = 0; q < kArcs; ++q) w[q] = t + q * G < len ? col[e0 + t + q * G] : -1;
+#pragma unroll
+        for (int q = 0; q < kArcs; ++q) dv[q] = w[q] >= 0 ? a.d[w[q]] : -2;
+#pragma unroll
+        for (int q = 0; q < kArcs; ++q) {
+            newly[q] = false;
+            if (dv[q] == -1) {
+                const int old = atomicCAS(&a.d[w[q]], -1, l + 1);
+                newly[q] = (old == -1);
+                dv[q] = newly[q] ? l + 1 : old;
             }
-            if (MODE == 0 && dv == l + 1) {
-                const unsigned long long old = atomicAdd(&a.sig[w], sv);
+        }
+#pragma unroll
+        for (int q = 0; q < kArcs; ++q) {
+            dw[q] = newly[q] ? rp[w[q] + 1] - rp[w[q]] : 0;
+            if (MODE == 0 && dv[q] == l + 1) {
+                const unsigned long long old = atomicAdd(&a.sig[w[q]], sv);
                 const unsigned long long nv = old + sv;
                 if (nv < old || nv > a.sigma_limit) my_ovf = 1;
                 ++my_larcs;
             }
-            if (newly) {
-                dw = rp[w + 1] - rp[w];
-                my_edges += (unsigned)dw;
+        }
+#pragma unroll
+        for (int q = 0; q < kArcs; ++q) {
+            my_edges += (unsigned)dw[q];
+            stage_push(newly[q], w[q], dw[q], st, sn, gc, a.queue, qe, (uint32_t)a.g.n, a.hq, hqb, &gc->err,
+                       GroupArgs{});
+        }
+    }
+}
+
+// Bottom-up over the arcs of an unvisited vertex: is a neighbour on level l,
+// and (MODE 0) the exact sum of such neighbours' path counts.  MODE 1 stops at
+// the first round with one.  Every lane of the group gets the result.
+template <int MODE, int G>
+__device__ __forceinline__ bool plain_pull_arcs(const PlainArgs &a, int l, int e0, int len, unsigned long long &lo,
+                                                unsigned long long &hi, unsigned long long &my_arcs,
+                                                unsigned long long &my_larcs) {
+    const int32_t *__restrict__ col = a.g.col;
+    bool found = false;
+    lo = 0;
+    hi = 0;
+    for (int t = lane_id() & (G - 1); __any(t < len && !(MODE == 1 && found)); t += kArcs * G) {
+        int u[kArcs], du[kArcs];
+        unsigned long long x[kArcs];
+#pragma unroll
+        for (int q = 0; q < kArcs; ++q)
+            u[q] = t + q * G < len && !(MODE == 1 && found) ? col[e0 + t + q * G] : -1;
+#pragma unroll
+        for (int q = 0; q < kArcs; ++q) du[q] = u[q] >= 0 ? a.d[u[q]] : -2;
+#pragma unroll
+        for (int q = 0; q < kArcs; ++q) {
+            my_arcs += u[q] >= 0 ? 1u : 0u;
+            x[q] = MODE == 0 && du[q] == l ? a.sig[u[q]] : 0ull;
+        }
+        bool f = false;
+#pragma unroll
+        for (int q = 0; q < kArcs; ++q) {
+            f |= du[q] == l;
+            if (MODE == 0) {
+                lo += x[q];
+                hi += (lo < x[q]) ? 1ull : 0ull;
+                my_larcs += du[q] == l ? 1u : 0u;
             }
         }
-        stage_push(newly, w, dw, st, sn, gc, a.queue, qe, (uint32_t)a.g.n, a.hq, hqb, &gc->err, GroupArgs{});
+        if (MODE == 1) f = group_any<G>(f);
+        found |= f;
     }
-}
-
-// Sum over arcs [a0, a1) of the values of neighbours u with d[u] == want:
-// sigma (normalised by 2^-sh, MODE 1) or c.  Lane-strided, then a fixed
-// butterfly: every lane returns the same bits.
-__device__ __forceinline__ double plain_wave_sum(const PlainArgs &a, int a0, int a1, int want, bool use_chat, int sh,
-                                                 unsigned long long &my_larcs) {
-    const int32_t *__restrict__ col = a.g.col;
-    double p = 0.0;
-    for (int e = a0 + lane_id(); e < a1; e += kWave) {
-        const int u = col[e];
-        if (a.d[u] == want) {
-            p += use_chat ? a.chat[u] : ldexp(as_f64(a.sig[u]), -sh);
-            ++my_larcs;
+    if (MODE == 0) {
+        found = group_any<G>(found);
+#pragma unroll
+        for (int o = G / 2; o > 0; o >>= 1) {
+            const unsigned long long ol = shfl_u64(lo, lane_id() ^ o), oh = shfl_u64(hi, lane_id() ^ o);
+            const unsigned long long nl = lo + ol;
+            hi = hi + oh + ((nl < lo) ? 1ull : 0ull);
+            lo = nl;
         }
     }
-    return wave_sum_f64(p);
+    return found;
 }
 
-
-// Exact 128-bit wavefront sum of (lo, hi) pairs; every lane gets the total.
-__device__ __forceinline__ void wave_sum_u128(unsigned long long &lo, unsigned long long &hi) {
-    const int lane = lane_id();
+// Sum over a vertex's arcs of the values of neighbours u with d[u] == want:
+// sigma (normalised by 2^-sh, MODE 1) or c.  Lane-strided, then a fixed
+// butterfly: every lane of the group returns the same bits.
+template <int G>
+__device__ __forceinline__ double plain_sum(const PlainArgs &a, int e0, int len, int want, bool use_chat, int sh,
+                                            unsigned long long &my_larcs) {
+    const int32_t *__restrict__ col = a.g.col;
+    double p = 0.0;
+    for (int t = lane_id() & (G - 1); __any(t < len); t += kArcs * G) {
+        int u[kArcs], du[kArcs];
+        double x[kArcs];
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        const unsigned long long ol = shfl_u64(lo, lane ^ o), oh = shfl_u64(hi, lane ^ o);
-        const unsigned long long nl = lo + ol;
-        hi = hi + oh + ((nl < lo) ? 1ull : 0ull);
-        lo = nl;
+        for (int q = 0; q < kArcs; ++q) u[q] = t + q * G < len ? col[e0 + t + q * G] : -1;
+#pragma unroll
+        for (int q = 0; q < kArcs; ++q) du[q] = u[q] >= 0 ? a.d[u[q]] : -2;
+#pragma unroll
+        for (int q = 0; q < kArcs; ++q) {
+            x[q] = 0.0;
+            if (du[q] == want) {
+                x[q] = use_chat ? a.chat[u[q]] : as_f64(a.sig[u[q]]);
+                ++my_larcs;
+            }
+        }
+#pragma unroll
+        for (int q = 0; q < kArcs; ++q) p += use_chat ? x[q] : ldexp(x[q], -sh);
     }
+#pragma unroll
+    for (int o = G / 2; o > 0; o >>= 1) p += __shfl_xor(p, o);
+    return p;
 }
 
 // Transition helpers run by the last workgroup (all threads present).
@@ -242,13 +323,13 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
         long long items = 1;
         const int cnt = s_qe - s_qb;
         if (s_phase == PH_FWD) {
-            if (s_variant == V_PUSH_TPV) items = (cnt + kWave - 1) / kWave + s_hseg;
+            if (s_variant == V_PUSH_TPV) items = (cnt + kWave / kSub - 1) / (kWave / kSub) + s_hseg;
             else if (s_variant == V_PUSH_WPV) items = cnt + s_hseg;
-            else items = (a.g.n + kWave - 1) / kWave + s_hseg;
+            else items = (a.g.n + kPullSpan - 1) / kPullSpan + s_hseg;
         } else if (s_phase == PH_SIG) {
-            items = (s_qn - s_qe + kWave - 1) / kWave + s_hseg;
+            items = (s_qn - s_qe + kWave / kSub - 1) / (kWave / kSub) + s_hseg;
         } else if (s_phase == PH_BWD) {
-            items = (cnt + kWave - 1) / kWave + s_hseg;
+            items = (cnt + kWave / kSub - 1) / (kWave / kSub) + s_hseg;
         } else if (s_phase == PH_FIN) {
             items = (s_qe + kWave - 1) / kWave;
         } else if (s_phase == PH_DUMP_FWD) {
@@ -267,10 +348,12 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
     const int l = s_level;
     const int n = a.g.n;
     const int32_t *__restrict__ rp = a.g.row_ptr;
-    const int32_t *__restrict__ col = a.g.col;
     int32_t *d = a.d;
     unsigned long long *sig = a.sig;
     const int h0 = s_h0, h1 = s_h1, hseg = s_hseg;
+    const int sub = lane / kSub;             // the lane's entry of a wavefront's kPer
+    const bool lead = lane % kSub == 0;
+    constexpr int kPer = kWave / kSub;
 
     unsigned long long my_edges = 0, my_arcs = 0, my_larcs = 0;
     int my_ovf = 0, my_maxe = INT_MIN, my_mine = INT_MAX;
@@ -282,7 +365,7 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
         Stage &st = s_stage[wid];
         int sn = 0;
         if (variant == V_PUSH_TPV || variant == V_PUSH_WPV) {
-            const int n_light = variant == V_PUSH_TPV ? (cnt + kWave - 1) / kWave : cnt;
+            const int n_light = variant == V_PUSH_TPV ? (cnt + kPer - 1) / kPer : cnt;
             const int total = n_light + hseg;
             for (int k = gw; k < total; k += nw) {
                 const int it = k < hseg ? n_light + k : k - hseg;  // heavy segments first
@@ -294,61 +377,36 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
                     const int a0 = rp[v] + s * kSeg, a1 = min(rp[v + 1], a0 + kSeg);
                     if (lane == 0) my_arcs += (unsigned)(a1 - a0);
                     const unsigned long long sv = MODE == 0 ? sig[v] : 0ull;
-                    plain_push_arcs<MODE>(a, l, sv, a0, a1, (uint32_t)qe, hqb, my_edges, my_larcs, my_ovf, st, sn);
+                    plain_push_arcs<MODE, kWave>(a, l, sv, a0, a1 - a0, (uint32_t)qe, hqb, my_edges, my_larcs, my_ovf, st, sn);
                 } else if (variant == V_PUSH_WPV) {
                     const int v = a.queue[qb + it];
                     const int e0 = rp[v], e1 = rp[v + 1];
                     if (e1 - e0 > kSeg) continue;  // runs as segments
                     if (lane == 0) my_arcs += (unsigned)(e1 - e0);
                     const unsigned long long sv = MODE == 0 ? sig[v] : 0ull;
-                    plain_push_arcs<MODE>(a, l, sv, e0, e1, (uint32_t)qe, hqb, my_edges, my_larcs, my_ovf, st, sn);
-                } else {  // TPV: 64 frontier vertices per wavefront
-                    const int i = it * kWave + lane;
+                    plain_push_arcs<MODE, kWave>(a, l, sv, e0, e1 - e0, (uint32_t)qe, hqb, my_edges, my_larcs, my_ovf, st, sn);
+                } else {  // TPV: kPer frontier vertices per wavefront
+                    const int i = it * kPer + sub;
                     const bool valid = i < cnt;
                     const int v = valid ? a.queue[qb + i] : 0;
                     const int e0 = valid ? rp[v] : 0;
                     const int deg = valid ? rp[v + 1] - e0 : 0;
-                    const int len = deg <= kLightDeg ? deg : 0;
                     const unsigned long long sv = (MODE == 0 && valid) ? sig[v] : 0ull;
-                    my_arcs += (unsigned)(deg <= kSeg ? deg : 0);
-                    const int maxlen = wave_max_i(len);
-                    for (int t = 0; t < maxlen; ++t) {
-                        bool newly = false;
-                        int w = 0, dw = 0;
-                        if (t < len) {
-                            w = col[e0 + t];
-                            int dv = d[w];
-                            if (dv == -1) {
-                                const int old = atomicCAS(&d[w], -1, l + 1);
-                                newly = (old == -1);
-                                dv = newly ? l + 1 : old;
-                            }
-                            if (MODE == 0 && dv == l + 1) {
-                                const unsigned long long old = atomicAdd(&sig[w], sv);
-                                const unsigned long long nv = old + sv;
-                                if (nv < old || nv > a.sigma_limit) my_ovf = 1;
-                                ++my_larcs;
-                            }
-                            if (newly) {
-                                dw = rp[w + 1] - rp[w];
-                                my_edges += (unsigned)dw;
-                            }
-                        }
-                        stage_push(newly, w, dw, st, sn, gc, a.queue, (uint32_t)qe, (uint32_t)n, a.hq, hqb, &gc->err, GroupArgs{});
-                    }
+                    if (lead) my_arcs += (unsigned)(deg <= kSeg ? deg : 0);
+                    plain_push_arcs<MODE, kSub>(a, l, sv, e0, deg <= kSubDeg ? deg : 0, (uint32_t)qe, hqb, my_edges,
+                                                my_larcs, my_ovf, st, sn);
                     // medium-degree vertices: the whole wavefront, one at a time
-                    unsigned long long mm = __ballot(deg > kLightDeg && deg <= kSeg);
+                    unsigned long long mm = __ballot(lead && deg > kSubDeg && deg <= kSeg);
                     while (mm) {
                         const int j = __ffsll(mm) - 1;
                         mm &= mm - 1;
-                        const int m0 = __shfl(e0, j), m1 = m0 + __shfl(deg, j);
-                        plain_push_arcs<MODE>(a, l, shfl_u64(sv, j), m0, m1, (uint32_t)qe, hqb, my_edges, my_larcs,
-                                              my_ovf, st, sn);
+                        plain_push_arcs<MODE, kWave>(a, l, shfl_u64(sv, j), __shfl(e0, j), __shfl(deg, j),
+                                                     (uint32_t)qe, hqb, my_edges, my_larcs, my_ovf, st, sn);
                     }
                 }
             }
         } else {  // V_PULL: every unvisited vertex looks for neighbours on level l
-            const int n_light = (n + kWave - 1) / kWave;
+            const int n_light = (n + kPullSpan - 1) / kPullSpan;
             const int total = n_light + hseg;
             for (int k = gw; k < total; k += nw) {
                 const int it = k < hseg ? n_light + k : k - hseg;  // heavy segments first
@@ -362,32 +420,11 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
                     // claimed it during this step)
                     if (dw0 != -1 && dw0 != l + 1) continue;
                     const int a0 = rp[w] + s * kSeg, a1 = min(rp[w + 1], a0 + kSeg);
-                    unsigned long long lo = 0, hi = 0;
-                    bool found = false;
-                    int scanned = 0;
-                    for (int eb = a0; eb < a1; eb += kWave) {
-                        const int e = eb + lane;
-                        if (e < a1) {
-                            const int u = col[e];
-                            if (d[u] == l) {
-                                found = true;
-                                if (MODE == 0) {
-                                    const unsigned long long x = sig[u];
-                                    lo += x;
-                                    hi += (lo < x) ? 1ull : 0ull;
-                                    ++my_larcs;
-                                }
-                            }
-                        }
-                        scanned += min(kWave, a1 - eb);
-                        if (MODE == 1 && __any(found)) break;
-                    }
-                    if (lane == 0) my_arcs += (unsigned)scanned;
-                    const bool any = __any(found);
+                    unsigned long long lo, hi;
+                    const bool any = plain_pull_arcs<MODE, kWave>(a, l, a0, a1 - a0, lo, hi, my_arcs, my_larcs);
                     bool newly = false;
                     if (any) {
                         if (MODE == 0) {  // exact 128-bit sum of the segment, one atomic
-                            wave_sum_u128(lo, hi);
                             if (lane == 0) {
                                 const unsigned long long old = atomicAdd(&sig[w], lo);
                                 const unsigned long long nv = old + lo;
@@ -401,76 +438,49 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
                     stage_push(newly, w, deg, st, sn, gc, a.queue, (uint32_t)qe, (uint32_t)n, a.hq, hqb, &gc->err, GroupArgs{});
                     continue;
                 }
-                const int w = it * kWave + lane;
-                const bool cand = (w < n) && d[w] == -1;
-                const int e0 = cand ? rp[w] : 0;
-                const int deg = cand ? rp[w + 1] - e0 : 0;
-                const int len = deg <= kLightDeg ? deg : 0;
-                const int maxlen = wave_max_i(len);
-                unsigned long long lo = 0, hi = 0;
-                bool found = false;
-                int scanned = 0;
-                for (int t = 0; t < maxlen; ++t) {
-                    const bool scan = (t < len) && !(MODE == 1 && found);
-                    if (scan) {
-                        ++scanned;
-                        const int u = col[e0 + t];
-                        if (d[u] == l) {
-                            if (MODE == 0) {
-                                const unsigned long long x = sig[u];
-                                lo += x;
-                                hi += (lo < x) ? 1ull : 0ull;
-                                ++my_larcs;
-                            }
-                            found = true;
+                // runs of kPullRun vertices from every part of the numbering: hubs
+                // are numbered together, and a wavefront takes them one by one
+                const int w0 = ((lane / kPullRun) * n_light + it) * kPullRun + lane % kPullRun;
+                unsigned long long cm = __ballot(lane < kPullSpan && w0 < n && d[w0] == -1);
+                while (cm) {  // kPer unvisited vertices at a time
+                    int w = -1;
+#pragma unroll
+                    for (int j = 0; j < kPer; ++j) {
+                        const int i = cm ? __ffsll(cm) - 1 : 0;
+                        if (cm && sub == j) w = __builtin_amdgcn_readlane(w0, i);
+                        cm &= cm - 1;
+                    }
+                    const int e0 = w >= 0 ? rp[w] : 0;
+                    const int deg = w >= 0 ? rp[w + 1] - e0 : 0;
+                    unsigned long long lo, hi;
+                    bool found =
+                        plain_pull_arcs<MODE, kSub>(a, l, e0, deg <= kSubDeg ? deg : 0, lo, hi, my_arcs, my_larcs);
+                    // medium-degree candidates: the whole wavefront, one at a time
+                    unsigned long long mm = __ballot(lead && deg > kSubDeg && deg <= kSeg);
+                    while (mm) {
+                        const int j = __ffsll(mm) - 1;
+                        mm &= mm - 1;
+                        unsigned long long ml, mh;
+                        const bool mf = plain_pull_arcs<MODE, kWave>(a, l, __shfl(e0, j), __shfl(deg, j), ml, mh,
+                                                                     my_arcs, my_larcs);
+                        if (lane == j) {
+                            found = mf;
+                            lo = ml;
+                            hi = mh;
                         }
                     }
-                    if (MODE == 1 && !__any(t + 1 < len && !found)) break;
-                }
-                // medium-degree candidates: the whole wavefront, one at a time
-                unsigned long long mm = __ballot(deg > kLightDeg && deg <= kSeg);
-                while (mm) {
-                    const int j = __ffsll(mm) - 1;
-                    mm &= mm - 1;
-                    const int m0 = __shfl(e0, j), m1 = m0 + __shfl(deg, j);
-                    unsigned long long ml = 0, mh = 0;
-                    bool mf = false;
-                    for (int eb = m0; eb < m1; eb += kWave) {
-                        const int e = eb + lane;
-                        if (e < m1) {
-                            const int u = col[e];
-                            if (d[u] == l) {
-                                mf = true;
-                                if (MODE == 0) {
-                                    const unsigned long long x = sig[u];
-                                    ml += x;
-                                    mh += (ml < x) ? 1ull : 0ull;
-                                    ++my_larcs;
-                                }
-                            }
+                    const bool ok = lead && found && deg <= kSeg;
+                    if (ok) {
+                        d[w] = l + 1;
+                        if (MODE == 0) {
+                            sig[w] = lo;
+                            if (hi != 0 || lo > a.sigma_limit) my_ovf = 1;
                         }
-                        if (lane == 0) scanned += min(kWave, m1 - eb);
-                        if (MODE == 1 && __any(mf)) break;
+                        my_edges += (unsigned)deg;
                     }
-                    const bool fj = __any(mf);
-                    if (MODE == 0) wave_sum_u128(ml, mh);
-                    if (lane == j) {
-                        found = fj;
-                        lo = ml;
-                        hi = mh;
-                    }
+                    stage_push(ok, w, deg, st, sn, gc, a.queue, (uint32_t)qe, (uint32_t)n, a.hq, hqb, &gc->err,
+                               GroupArgs{});
                 }
-                my_arcs += (unsigned)scanned;
-                const bool ok = found && deg <= kSeg;
-                if (ok) {
-                    d[w] = l + 1;
-                    if (MODE == 0) {
-                        sig[w] = lo;
-                        if (hi != 0 || lo > a.sigma_limit) my_ovf = 1;
-                    }
-                    my_edges += (unsigned)deg;
-                }
-                stage_push(ok, w, deg, st, sn, gc, a.queue, (uint32_t)qe, (uint32_t)n, a.hq, hqb, &gc->err, GroupArgs{});
             }
         }
         stage_flush(st, sn, gc, a.queue, (uint32_t)qe, (uint32_t)n, a.hq, hqb, &gc->err, GroupArgs{});
@@ -478,7 +488,7 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
         // FP64 path counts of level l+1, pulled in CSR order
         const int qs = s_qe, cnt = s_qn - s_qe;
         const int sh = s_sh0;
-        const int n_light = (cnt + kWave - 1) / kWave;
+        const int n_light = (cnt + kPer - 1) / kPer;
         const int total = n_light + hseg;
         for (int k = gw; k < total; k += nw) {
             const int it = k < hseg ? n_light + k : k - hseg;  // heavy segments first
@@ -489,7 +499,7 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
                 const int w = a.queue[a.hq.pos[h]];
                 const int e0 = rp[w], e1 = rp[w + 1];
                 const int a0 = e0 + s * kSeg, a1 = min(e1, a0 + kSeg);
-                const double p = plain_wave_sum(a, a0, a1, l, false, sh, my_larcs);
+                const double p = plain_sum<kWave>(a, a0, a1 - a0, l, false, sh, my_larcs);
                 if (lane == 0) {
                     my_arcs += (unsigned)(a1 - a0);
                     part_store(&a.hq.part_lo[a.hq.seg[h] + s], as_u64(p));
@@ -510,30 +520,21 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
                 }
                 continue;
             }
-            const int i = it * kWave + lane;
+            const int i = it * kPer + sub;
             const bool valid = i < cnt;
             const int w = valid ? a.queue[qs + i] : 0;
             const int e0 = valid ? rp[w] : 0;
             const int deg = valid ? rp[w + 1] - e0 : 0;
-            const int len = deg <= kLightDeg ? deg : 0;
-            const int maxlen = wave_max_i(len);
-            double acc = 0.0;
-            for (int t = 0; t < maxlen; ++t) {
-                if (t < len) {
-                    const int u = col[e0 + t];
-                    if (d[u] == l) { acc += ldexp(as_f64(sig[u]), -sh); ++my_larcs; }
-                }
-            }
-            my_arcs += (unsigned)(deg <= kSeg ? deg : 0);
-            unsigned long long mm = __ballot(deg > kLightDeg && deg <= kSeg);
+            if (lead) my_arcs += (unsigned)(deg <= kSeg ? deg : 0);
+            double acc = plain_sum<kSub>(a, e0, deg <= kSubDeg ? deg : 0, l, false, sh, my_larcs);
+            unsigned long long mm = __ballot(lead && deg > kSubDeg && deg <= kSeg);
             while (mm) {
                 const int j = __ffsll(mm) - 1;
                 mm &= mm - 1;
-                const int m0 = __shfl(e0, j), m1 = m0 + __shfl(deg, j);
-                const double p = plain_wave_sum(a, m0, m1, l, false, sh, my_larcs);
+                const double p = plain_sum<kWave>(a, __shfl(e0, j), __shfl(deg, j), l, false, sh, my_larcs);
                 if (lane == j) acc = p;
             }
-            if (valid && deg <= kSeg) {
+            if (lead && valid && deg <= kSeg) {
                 sig[w] = as_u64(acc);
                 if (acc > 0.0) {
                     int ex;
@@ -547,7 +548,7 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
         const int qb = s_qb, cnt = s_qe - s_qb;
         const int sh = s_sh0, shn = s_sh1;
         const bool dump = s_dump != 0;
-        const int n_light = (cnt + kWave - 1) / kWave;
+        const int n_light = (cnt + kPer - 1) / kPer;
         const int total = n_light + hseg;
         for (int k = gw; k < total; k += nw) {
             const int it = k < hseg ? n_light + k : k - hseg;  // heavy segments first
@@ -558,7 +559,7 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
                 const int v = a.queue[a.hq.pos[h]];
                 const int e0 = rp[v], e1 = rp[v + 1];
                 const int a0 = e0 + s * kSeg, a1 = min(e1, a0 + kSeg);
-                const double p = plain_wave_sum(a, a0, a1, l + 1, true, 0, my_larcs);
+                const double p = plain_sum<kWave>(a, a0, a1 - a0, l + 1, true, 0, my_larcs);
                 if (lane == 0) {
                     my_arcs += (unsigned)(a1 - a0);
                     part_store(&a.hq.part_lo[a.hq.seg[h] + s], as_u64(p));
@@ -578,35 +579,28 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
                 }
                 continue;
             }
-            const int i = it * kWave + lane;
+            const int i = it * kPer + sub;
             const bool valid = i < cnt;
             const int v = valid ? a.queue[qb + i] : 0;
             const int e0 = valid ? rp[v] : 0;
             const int deg = valid ? rp[v + 1] - e0 : 0;
-            const int len = deg <= kLightDeg ? deg : 0;
-            const int maxlen = wave_max_i(len);
-            double acc = 0.0;
-            for (int t = 0; t < maxlen; ++t) {
-                if (t < len) {
-                    const int w = col[e0 + t];
-                    if (d[w] == l + 1) { acc += a.chat[w]; ++my_larcs; }
-                }
-            }
-            my_arcs += (unsigned)(deg <= kSeg ? deg : 0);
-            unsigned long long mm = __ballot(deg > kLightDeg && deg <= kSeg);
+            const bool fin = lead && valid && deg <= kSeg;
+            const double sv = fin ? norm_sigma<MODE>(a, v, sh) : 1.0;
+            const double bc0 = fin ? a.bc[v] : 0.0;
+            if (lead) my_arcs += (unsigned)(deg <= kSeg ? deg : 0);
+            double acc = plain_sum<kSub>(a, e0, deg <= kSubDeg ? deg : 0, l + 1, true, 0, my_larcs);
+            unsigned long long mm = __ballot(lead && deg > kSubDeg && deg <= kSeg);
             while (mm) {
                 const int j = __ffsll(mm) - 1;
                 mm &= mm - 1;
-                const int m0 = __shfl(e0, j), m1 = m0 + __shfl(deg, j);
-                const double p = plain_wave_sum(a, m0, m1, l + 1, true, 0, my_larcs);
+                const double p = plain_sum<kWave>(a, __shfl(e0, j), __shfl(deg, j), l + 1, true, 0, my_larcs);
                 if (lane == j) acc = p;
             }
-            if (valid && deg <= kSeg) {
-                const double sv = norm_sigma<MODE>(a, v, sh);
+            if (fin) {
                 double delta = sv * acc;
                 if (MODE == 1) delta = ldexp(delta, -shn);
                 a.chat[v] = (1.0 + delta) / sv;
-                a.bc[v] += delta;
+                a.bc[v] = bc0 + delta;
                 if (dump) a.dump_delta[v] = delta;
             }
         }
