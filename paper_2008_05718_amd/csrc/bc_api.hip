@@ -283,7 +283,7 @@ struct bc_graph {
     size_t blk_stride = 0;
     BlockArgs blk_dims{};              // capacities of one workgroup's state
     char *blk_scratch = nullptr;
-    Ctl *blk_ctls = nullptr;
+    SoloState *blk_states = nullptr;
     int32_t *blk_chunk = nullptr;      // b0, b1, order (3 x n_chunks), grown per run
     int64_t blk_chunk_cap = 0;
     int64_t *blk_part_off = nullptr;
@@ -414,7 +414,7 @@ extern "C" void bc_destroy(bc_graph *g) {
                    g->srcs, g->ovf, g->bstart, g->blo, g->bhi, g->mlp, g->hv_vtx, g->hv_seg, g->p_hv_vtx, g->p_hv_seg,
                    g->p_hq.pos, g->p_hq.seg, g->p_hq.cnt, g->p_hq.off, g->p_hq.nseg, g->p_hq.part_lo,
                    g->p_hq.part_hi, g->b_hq.pos, g->b_hq.seg, g->b_hq.cnt, g->b_hq.off, g->b_hq.nseg,
-                   g->b_hq.part_lo, g->b_hq.part_hi, g->lvl, g->blk_scratch, g->blk_ctls, g->blk_chunk,
+                   g->b_hq.part_lo, g->b_hq.part_hi, g->lvl, g->blk_scratch, g->blk_states, g->blk_chunk,
                    g->blk_part_off, g->blk_partials, g->blk_gsum, g->blk_next};
     for (void *p : dev)
         if (p) (void)hipFree(p);
@@ -1120,11 +1120,14 @@ static bc_status drive(bc_graph *g, const Args &args, void (*kern)(Args), const 
 }
 
 // A control block before its first launch (parity 0); returns the state to fill in.
+static Head *init_head(Head *h) {  // (zeroed by the caller)
+    h->dump_pos = -1;
+    h->dump_lane = -1;
+    return h;
+}
 static Head *init_ctl(Ctl *c) {
-    std::memset(c, 0, sizeof(*c));
-    c->h[0].dump_pos = -1;
-    c->h[0].dump_lane = -1;
-    return &c->h[0];
+    std::memset((void *)c, 0, sizeof(*c));
+    return init_head(&c->h[0]);
 }
 
 // The state written last: steps only grow.
@@ -1593,14 +1596,14 @@ static bc_status block_dims(bc_graph *g, int *resident) {
     size_t free_b = 0, total_b = 0;
     HIP_TRY(hipMemGetInfo(&free_b, &total_b));
     // what this handle already holds for the block engine counts as free
-    free_b += (size_t)g->blk_wg * (g->blk_stride + sizeof(Ctl));
+    free_b += (size_t)g->blk_wg * (g->blk_stride + sizeof(SoloState));
     size_t budget = std::min<size_t>(free_b / 4 * 3, (size_t)192 << 30);
     if (g->acct.limit) {
-        const size_t held = (size_t)g->blk_wg * (g->blk_stride + sizeof(Ctl));
+        const size_t held = (size_t)g->blk_wg * (g->blk_stride + sizeof(SoloState));
         const size_t room = g->acct.limit > g->acct.bytes - held ? g->acct.limit - (g->acct.bytes - held) : 0;
         budget = std::min(budget, room);
     }
-    want = std::min<int64_t>(want, (int64_t)(budget / (g->blk_stride + sizeof(Ctl))));
+    want = std::min<int64_t>(want, (int64_t)(budget / (g->blk_stride + sizeof(SoloState))));
     *resident = (int)std::max<int64_t>(want, 0);
     return BC_OK;
 }
@@ -1611,14 +1614,14 @@ static bc_status ensure_block(bc_graph *g, int need) {
     if (g->blk_scratch) {
         HIP_TRY(hipStreamSynchronize(nullptr));
         (void)hipFree(g->blk_scratch);
-        (void)hipFree(g->blk_ctls);
-        g->acct.bytes -= (size_t)g->blk_wg * (g->blk_stride + sizeof(Ctl));
+        (void)hipFree(g->blk_states);
+        g->acct.bytes -= (size_t)g->blk_wg * (g->blk_stride + sizeof(SoloState));
         g->blk_scratch = nullptr;
-        g->blk_ctls = nullptr;
+        g->blk_states = nullptr;
         g->blk_wg = 0;
     }
     HIP_TRY(dalloc(&g->blk_scratch, (size_t)need * g->blk_stride, &g->acct));
-    HIP_TRY(dalloc(&g->blk_ctls, (size_t)need, &g->acct));
+    HIP_TRY(dalloc(&g->blk_states, (size_t)need, &g->acct));
     if (!g->blk_next) HIP_TRY(dalloc(&g->blk_next, 1, &g->acct));
     g->blk_wg = need;
     return BC_OK;
@@ -1798,10 +1801,13 @@ static bc_status run_block(bc_graph *g, const RunCfg &cfg, const bc_run_options 
     HIP_TRY(hipMemcpyAsync(g->blk_chunk, chunk_host.data(), sizeof(int32_t) * chunk_host.size(), hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(g->blk_part_off, offs.data(), sizeof(int64_t) * offs.size(), hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(g->blk_gsum, gsum.data(), sizeof(int32_t) * gsum.size(), hipMemcpyHostToDevice, st));
-    // control blocks and tags
-    std::vector<Ctl> hc((size_t)nwg);
-    for (Ctl &c : hc) init_ctl(&c)->policy = cfg.policy;
-    HIP_TRY(hipMemcpyAsync(g->blk_ctls, hc.data(), sizeof(Ctl) * hc.size(), hipMemcpyHostToDevice, st));
+    // states and tags
+    std::vector<SoloState> hc((size_t)nwg);
+    for (SoloState &c : hc) {
+        std::memset(&c, 0, sizeof(c));
+        init_head(&c.h)->policy = cfg.policy;
+    }
+    HIP_TRY(hipMemcpyAsync(g->blk_states, hc.data(), sizeof(SoloState) * hc.size(), hipMemcpyHostToDevice, st));
     {
         const BlockLayout L((size_t)dm.nmax, dm.lq_cap, (size_t)dm.max_levels, dm.gcap, dm.hq_entries, dm.hq_levels,
                             dm.part_cap, dm.ovf_cap);
@@ -1834,7 +1840,7 @@ static bc_status run_block(bc_graph *g, const RunCfg &cfg, const bc_run_options 
     ra.a.sigma_limit = o.sigma_limit > 0 ? (unsigned long long)o.sigma_limit : ~0ull;
     ra.scratch = g->blk_scratch;
     ra.stride = g->blk_stride;
-    ra.ctls = g->blk_ctls;
+    ra.states = g->blk_states;
     ra.c_b0 = g->blk_chunk;
     ra.c_b1 = g->blk_chunk + nc;
     ra.order = g->blk_chunk + 2 * nc;
@@ -1850,7 +1856,7 @@ static bc_status run_block(bc_graph *g, const RunCfg &cfg, const bc_run_options 
     block_run<0, kBlockWaves><<<(unsigned)nwg, kBlockWaves * kWave, 0, st>>>(ra);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipEventRecord(e1, st));
-    HIP_TRY(hipMemcpyAsync(hc.data(), g->blk_ctls, sizeof(Ctl) * hc.size(), hipMemcpyDeviceToHost, st));
+    HIP_TRY(hipMemcpyAsync(hc.data(), g->blk_states, sizeof(SoloState) * hc.size(), hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
     float ms = 0.0f;
     (void)hipEventElapsedTime(&ms, e0, e1);
@@ -1872,7 +1878,7 @@ static bc_status run_block(bc_graph *g, const RunCfg &cfg, const bc_run_options 
     }
     const double bytes0 = algo_bytes(g->stats);
     for (int w = 0; w < used; ++w) {
-        const Head &last = hc[w].h[0];
+        const Head &last = hc[w].h;
         accumulate_stats(&g->stats, last, g->clock_khz);
         if (last.n_ovf) {
             std::vector<int64_t> tmp(last.n_ovf);

@@ -48,51 +48,32 @@ namespace bcx {
 // ------------------------------------------------------------------ pieces
 
 // Where a discover step appends the next level.
-template <class C>
+template <class To>
 struct Append {
-    C *gc;
-    Stage *st;
+    const To &to;
+    Stage &st;
     int n;  // staged entries (wavefront-uniform)
-    uint32_t qe, hq_base;
-    GroupArgs gr;
 };
-
-// Write out the staged vertices; their degrees are looked up here, together
-// (vertex by vertex, that lookup stood behind every atomic that found one).
-template <class C>
-__device__ __forceinline__ void append_flush(const BatchArgs &a, Append<C> &ap) {
-    if (ap.n == 0) return;
-    wave_lds_fence();
-    for (int i = lane_id(); i < ap.n; i += kWave) {
-        const int w = ap.st->w[i];
-        ap.st->deg[i] = class_deg(a.g, w, a.g.row_ptr[w + 1] - a.g.row_ptr[w]);
-    }
-    stage_flush(*ap.st, ap.n, ap.gc, a.lq_vtx, ap.qe, a.lq_cap, a.hq, ap.hq_base, &ap.gc->err, ap.gr);
-}
-template <class C>
-__device__ __forceinline__ void append(const BatchArgs &a, Append<C> &ap, bool pred, int w) {
-    const unsigned long long m = __ballot(pred);
-    if (m == 0) return;
-    if (pred) ap.st->w[ap.n + (int)lanes_below(m)] = w;
-    ap.n += __popcll(m);
-    if (ap.n >= kWave) append_flush(a, ap);
+template <class To>
+__device__ __forceinline__ void append(Append<To> &ap, bool pred, int w) {
+    stage_push(pred, w, ap.st, ap.n, ap.to);
 }
 
 // Push over the arc of each thread (far end w with visited/next words x, lanes
 // f of the arc's tail): vertices reached for the first time on the next level
 // are appended.
-template <class C>
-__device__ __forceinline__ void push_arc(const BatchArgs &a, Append<C> &ap, int w, unsigned long long f, VisNext x) {
+template <class To>
+__device__ __forceinline__ void push_arc(const BatchArgs &a, Append<To> &ap, int w, unsigned long long f, VisNext x) {
     const unsigned long long add = f & ~x.vis & ~x.nxt;
     bool newly = false;
     if (add) newly = atomicOr(&a.vn[w].nxt, add) == 0ull;
-    append(a, ap, newly, w);
+    append(ap, newly, w);
 }
 
 // Push from one frontier vertex (lanes f) over arcs [a0, a1) (uniform), 64 at a
 // time; the next chunk's columns and words are requested first.
-template <class C>
-__device__ __forceinline__ void push_arcs(const BatchArgs &a, Append<C> &ap, unsigned long long f, int a0, int a1,
+template <class To>
+__device__ __forceinline__ void push_arcs(const BatchArgs &a, Append<To> &ap, unsigned long long f, int a0, int a1,
                                           const int32_t *__restrict__ col) {
     if (a0 >= a1) return;
     const int lane = lane_id();
@@ -112,8 +93,8 @@ __device__ __forceinline__ void push_arcs(const BatchArgs &a, Append<C> &ap, uns
 
 // Push from a group of frontier entries: light ones packed like the sums'
 // groups, medium ones one at a time.  Returns (lane 0) the arcs followed.
-template <class C>
-__device__ __forceinline__ unsigned push_group(const BatchArgs &a, Append<C> &ap, Packing &pk, int qb, int i0, int i1,
+template <class To>
+__device__ __forceinline__ unsigned push_group(const BatchArgs &a, Append<To> &ap, Packing &pk, int qb, int i0, int i1,
                                                unsigned long long act, const int32_t *__restrict__ rp,
                                                const int32_t *__restrict__ col) {
     const int lane = lane_id();
@@ -575,6 +556,7 @@ __device__ __forceinline__ void batch_step_body(Load load, C *gc, const int pari
     __shared__ int s_lsrc[kLanes];
     __shared__ int s_lead[kLanes];
     __shared__ WaveScratch s_scratch[NW];
+    __shared__ StageTotals<NW> s_stot;
     __shared__ float s_lds[2 * kMlpH + kMlpOut + 4];
     __shared__ LevelFeatures s_feat;
     __shared__ float s_il;  // sources-per-entry threshold of this path-count / backward step
@@ -708,15 +690,13 @@ __device__ __forceinline__ void batch_step_body(Load load, C *gc, const int pari
         const uint32_t T = s_epoch + (uint32_t)l;
         const unsigned long long act = uniform(s_active);
         const int variant = uniform(s_variant);
-        Append<C> ap;
-        ap.gc = gc;
-        ap.st = &s_scratch[wid].w.st;
-        ap.n = 0;
-        ap.qe = (uint32_t)qe;
-        ap.hq_base = (uint32_t)uniform(s_hqb);
-        ap.gr.gstart = a.gstart;
-        ap.gr.gb = (uint32_t)uniform((int)s_gbn);
-        ap.gr.gcap = a.gcap;
+        GroupArgs gr;
+        gr.gstart = a.gstart;
+        gr.gb = (uint32_t)uniform((int)s_gbn);
+        gr.gcap = a.gcap;
+        const auto to = stage_to(gc, a.lq_vtx, (uint32_t)qe, a.lq_cap, a.hq, (uint32_t)uniform(s_hqb), gr,
+                                 [&](int w, bool) { return class_deg(a.g, w, rp[w + 1] - rp[w]); });
+        Append<decltype(to)> ap{to, s_scratch[wid].w.st, 0};
         Packing &pk = s_scratch[wid].w.pk;
         if (variant == V_PUSH_TPV || variant == V_PUSH_WPV) {
             const int ng = uniform((int)s_ng), gm = uniform(s_gm);
@@ -769,7 +749,7 @@ __device__ __forceinline__ void batch_step_body(Load load, C *gc, const int pari
                     if (lane == 0) my_arcs += (unsigned)scanned;
                     bool newly = false;
                     if (lane == 0 && got) newly = atomicOr(&a.vn[w].nxt, got) == 0ull;
-                    append(a, ap, newly, w);
+                    append(ap, newly, w);
                     continue;
                 }
                 const int w = lo + it * kWave + lane;
@@ -808,10 +788,10 @@ __device__ __forceinline__ void batch_step_body(Load load, C *gc, const int pari
                 my_arcs += (unsigned)scanned;
                 const bool found = got != 0ull && deg <= kSeg;
                 if (found) a.vn[w].nxt = got;
-                append(a, ap, found, w);
+                append(ap, found, w);
             }
         }
-        append_flush(a, ap);
+        stage_finish<NW>(ap.st, ap.n, s_stot, to);
     } else if (phase == PH_SIG) {
         const BatchArgs a = load();
         const int32_t *__restrict__ rp = a.g.row_ptr;
@@ -1389,7 +1369,7 @@ __global__ __launch_bounds__(NW * kWave) void block_run(BlockArgs ra) {
     __shared__ SoloCtl s_ctl;
     Head *c = &s_ctl.h[0];
     {
-        const Head &g = ra.ctls[blockIdx.x].h[0];
+        const Head &g = ra.states[blockIdx.x].h;
         for (int i = tid; i < (int)(sizeof(Head) / 8); i += NT)
             ((unsigned long long *)c)[i] = ((const unsigned long long *)&g)[i];
         if (tid == 0) {
@@ -1496,9 +1476,9 @@ __global__ __launch_bounds__(NW * kWave) void block_run(BlockArgs ra) {
     }
     // state and statistics back for the host
     __syncthreads();
-    Ctl &g = ra.ctls[blockIdx.x];
+    SoloState &g = ra.states[blockIdx.x];
     for (int i = tid; i < (int)(sizeof(Head) / 8); i += NT)
-        ((unsigned long long *)&g.h[0])[i] = ((const unsigned long long *)c)[i];
+        ((unsigned long long *)&g.h)[i] = ((const unsigned long long *)c)[i];
     if (tid == 0) g.err = s_ctl.err;
 }
 

@@ -222,7 +222,7 @@ __device__ __forceinline__ bool step_epilogue(C *c, Counters &cn, unsigned long 
         if (threadIdx.x == 0) {
             int last = 0;
             const unsigned in_slot = (nblk - slot + kSlots - 1) / kSlots;
-            if (atomicAdd(&c->arrive[slot], 1u) == in_slot - 1)
+            if (atomicAdd(&c->arrive[slot][0], 1u) == in_slot - 1)
                 last = atomicAdd(&c->blocks_done, 1u) == nslots - 1 ? 1 : 0;
             *s_last = last;
         }
@@ -248,7 +248,7 @@ __device__ __forceinline__ bool step_epilogue(C *c, Counters &cn, unsigned long 
             if (lane < (int)nslots) c->slot[lane][kk] = 0ull;
         }
         if (threadIdx.x < nslots) {
-            c->arrive[threadIdx.x] = 0u;
+            c->arrive[threadIdx.x][0] = 0u;
             c->work[threadIdx.x][0] = 0u;
         }
         if (threadIdx.x == 0) c->blocks_done = 0u;
@@ -260,10 +260,19 @@ __device__ __forceinline__ bool step_epilogue(C *c, Counters &cn, unsigned long 
 // ----------------------------------------------------------- staged appends
 // New level-queue entries are first gathered per wavefront in LDS and
 // written in runs, one position atomic per run instead of per append.
-constexpr int kStage = 128;
+// A vertex's degree is looked up when its run is written (vertex by vertex, that
+// lookup stood behind every atomic that found one) and kept as cost units, 0
+// for a heavy one.
+constexpr int kStage = 288;
 struct Stage {
     int32_t w[kStage];
-    int32_t deg[kStage];
+    uint8_t cost[kStage];
+};
+// What a workgroup's last runs take together.
+template <int NW>
+struct StageTotals {
+    unsigned n[NW], cost[NW];
+    unsigned long long at;
 };
 
 // Wavefront-inclusive prefix sum of an int, by the data-parallel row shifts and
@@ -300,8 +309,6 @@ __device__ __forceinline__ int class_deg(const GraphArgs &g, int v, int out_deg)
 }
 
 
-// Write the n staged entries of this wavefront to the level queue (absolute
-// positions qbase + counter), heavy ones also to the level's heavy list.
 #ifndef BC_BUDGET
 #define BC_BUDGET 16
 #endif
@@ -338,90 +345,149 @@ struct GroupArgs {
     uint32_t gcap = 0;
 };
 
-template <class C>
-__device__ __forceinline__ void stage_flush(Stage &st, int &n, C *c, int32_t *q, uint32_t qbase, uint32_t qcap,
-                                            const HeavyQ &hq, uint32_t hq_base, int32_t *err,
-                                            const GroupArgs &ga) {
-    if (n == 0) return;
+// Where an engine's next level is appended; deg(w, first) is the degree that
+// classifies vertex w (first: asked for the first time).
+template <class C, class Deg>
+struct StageTo {
+    C *c;
+    int32_t *q;
+    uint32_t qbase, qcap;
+    HeavyQ hq;
+    uint32_t hq_base;
+    GroupArgs ga;
+    Deg deg;
+};
+template <class C, class Deg>
+__device__ __forceinline__ StageTo<C, Deg> stage_to(C *c, int32_t *q, uint32_t qbase, uint32_t qcap, const HeavyQ &hq,
+                                                    uint32_t hq_base, const GroupArgs &ga, Deg deg) {
+    return StageTo<C, Deg>{c, q, qbase, qcap, hq, hq_base, ga, deg};
+}
+
+__device__ __forceinline__ void stage_fence() {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Degrees of the n staged entries; returns their cost units.
+template <class To>
+__device__ __forceinline__ unsigned stage_costs(Stage &st, int n, const To &to) {
+    stage_fence();
+    unsigned cost = 0;
+    for (int i = lane_id(); i < n; i += kWave) {
+        const int deg = to.deg(st.w[i], true);
+        const unsigned ci = entry_cost(deg);
+        st.cost[i] = deg > kSeg ? (uint8_t)0 : (uint8_t)ci;
+        cost += ci;
+    }
+    static_assert(1 + (kSeg + 7) / 8 <= 255, "cost units of an entry fit a byte");
+    return wave_sum_u32(cost);
+}
+
+// Write the n staged entries of this wavefront to the level queue (positions
+// qbase + base and on, cost units from cbase on), heavy ones also to the
+// level's heavy list.
+template <class To>
+__device__ __forceinline__ void stage_write(Stage &st, int n, unsigned base, unsigned cbase, const To &to) {
+    stage_fence();
     const int lane = lane_id();
-    // the run's entries and cost units, taken by one 64-bit atomic
-    unsigned run_cost = 0;
-    if (ga.gstart)
-        for (int i = lane; i < n; i += kWave) run_cost += entry_cost(st.deg[i]);
-    run_cost = (unsigned)wave_sum_u64(run_cost);
-    unsigned long long old = 0;
-    if (lane == 0)
-        old = atomicAdd(&c->next_qc, (unsigned long long)(unsigned)n | ((unsigned long long)run_cost << 32));
-    old = shfl_u64(old, 0);
-    const unsigned base = (unsigned)old;
-    unsigned cbase = (unsigned)(old >> 32);
     for (int i0 = 0; i0 < n; i0 += kWave) {
         const int i = i0 + lane;
         const bool on = i < n;
         const int w = on ? st.w[i] : 0;
-        const int deg = on ? st.deg[i] : 0;
-        const uint32_t p = qbase + base + (uint32_t)i;
+        const unsigned units = on ? st.cost[i] : 1u;
+        const bool heavy = on && units == 0u;
+        const uint32_t p = to.qbase + base + (uint32_t)i;
         if (on) {
-            if (p < qcap) q[p] = w;
-            else atomicOr(err, ERR_QUEUE_CAP);
+            if (p < to.qcap) to.q[p] = w;
+            else atomicOr(&to.c->err, ERR_QUEUE_CAP);
         }
-        if (ga.gstart) {
-            const unsigned ci = on ? entry_cost(deg) : 0u;
+        if (to.ga.gstart) {
+            const unsigned ci = heavy ? entry_cost(kSeg + 1) : on ? units : 0u;
             const unsigned incl = (unsigned)wave_incl_scan((int)ci);
             const unsigned P = cbase + incl - ci;
             for (unsigned k = P / kBudget + 1; on && k <= (P + ci) / kBudget; ++k) {
-                const unsigned long long at = (unsigned long long)ga.gb + k;
-                if (at < ga.gcap) ga.gstart[at] = base + (uint32_t)i + 1u;
-                else atomicOr(err, ERR_QUEUE_CAP);
+                const unsigned long long at = (unsigned long long)to.ga.gb + k;
+                if (at < to.ga.gcap) to.ga.gstart[at] = base + (uint32_t)i + 1u;
+                else atomicOr(&to.c->err, ERR_QUEUE_CAP);
             }
-            cbase += (unsigned)__shfl((int)incl, 63);
+            cbase += (unsigned)__builtin_amdgcn_readlane((int)incl, 63);
         }
-        const bool heavy = on && deg > kSeg;
         const unsigned long long hm = __ballot(heavy);
         if (hm) {
-            const int ns = heavy ? n_segments(deg) : 0;
+            const int ns = heavy ? n_segments(to.deg(w, false)) : 0;
             const int incl = wave_incl_scan(ns);
-            const int total = __shfl(incl, 63);
+            const int total = __builtin_amdgcn_readlane(incl, 63);
             const int hl = __ffsll((unsigned long long)hm) - 1;
             unsigned long long hold = 0;
             if (lane == hl)
-                hold = atomicAdd(&c->next_hq,
+                hold = atomicAdd(&to.c->next_hq,
                                  (unsigned long long)__popcll(hm) | ((unsigned long long)(unsigned)total << 32));
             hold = shfl_u64(hold, hl);
             if (heavy) {
-                const uint32_t idx = hq_base + (uint32_t)hold + lanes_below(hm);
-                if (idx < hq.cap) {
-                    hq.pos[idx] = (int32_t)p;
-                    hq.seg[idx] = (int32_t)(hold >> 32) + (incl - ns);
-                    hq.cnt[idx] = 0;
+                const uint32_t idx = to.hq_base + (uint32_t)hold + lanes_below(hm);
+                if (idx < to.hq.cap) {
+                    to.hq.pos[idx] = (int32_t)p;
+                    to.hq.seg[idx] = (int32_t)(hold >> 32) + (incl - ns);
+                    to.hq.cnt[idx] = 0;
                 } else {
-                    atomicOr(err, ERR_QUEUE_CAP);
+                    atomicOr(&to.c->err, ERR_QUEUE_CAP);
                 }
             }
         }
     }
+}
+
+// A run's entries and cost units are taken by one 64-bit atomic.
+template <class To>
+__device__ __forceinline__ unsigned long long stage_take(unsigned n, unsigned cost, const To &to) {
+    return atomicAdd(&to.c->next_qc, (unsigned long long)n | ((unsigned long long)(to.ga.gstart ? cost : 0u) << 32));
+}
+
+// Stage w for every lane with pred; a run is written once there is no room for
+// another 64.  n is the wavefront-uniform fill count.  The wavefront must be
+// converged.
+template <class To>
+__device__ __forceinline__ void stage_push(bool pred, int32_t w, Stage &st, int &n, const To &to) {
+    const unsigned long long m = __ballot(pred);
+    if (m == 0) return;
+    if (pred) st.w[n + (int)lanes_below(m)] = w;
+    n += __popcll(m);
+    if (n <= kStage - kWave) return;
+    const unsigned cost = stage_costs(st, n, to);
+    unsigned long long at = 0;
+    if (lane_id() == 0) at = stage_take((unsigned)n, cost, to);
+    at = shfl_u64(at, 0);
+    stage_write(st, n, (unsigned)at, (unsigned)(at >> 32), to);
     n = 0;
 }
 
-// Stage w (degree deg) for every lane with pred; flushes once 64 or more are
-// waiting.  n is the wavefront-uniform fill count.  The wavefront must be
-// converged.
-template <class C>
-__device__ __forceinline__ void stage_push(bool pred, int32_t w, int32_t deg, Stage &st, int &n, C *c, int32_t *q,
-                                           uint32_t qbase, uint32_t qcap, const HeavyQ &hq, uint32_t hq_base,
-                                           int32_t *err, const GroupArgs &ga) {
-    const unsigned long long m = __ballot(pred);
-    if (m == 0) return;
-    if (pred) {
-        const int pos = n + (int)lanes_below(m);
-        st.w[pos] = w;
-        st.deg[pos] = deg;
+// Write what the workgroup's wavefronts have staged at the end of a step, with
+// one atomic for all of them (all threads of the workgroup).  One per
+// wavefront, on the same word, bounded every step that ran on many: 66 us for
+// a pull level on R-MAT 18 with one source, now 50.
+template <int NW, class To>
+__device__ __forceinline__ void stage_finish(Stage &st, int n, StageTotals<NW> &tot, const To &to) {
+    const int wid = uniform((int)(threadIdx.x >> 6));
+    const unsigned cost = n ? stage_costs(st, n, to) : 0u;
+    if (lane_id() == 0) {
+        tot.n[wid] = (unsigned)n;
+        tot.cost[wid] = cost;
     }
-    n += __popcll(m);
-    if (n >= kWave) stage_flush(st, n, c, q, qbase, qcap, hq, hq_base, err, ga);
+    __syncthreads();
+    unsigned base = 0, cbase = 0, all = 0, call = 0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        if (w == wid) {
+            base = all;
+            cbase = call;
+        }
+        all += tot.n[w];
+        call += tot.cost[w];
+    }
+    if (threadIdx.x == 0 && all) tot.at = stage_take(all, call, to);
+    __syncthreads();
+    if (n) stage_write(st, n, (unsigned)tot.at + base, (unsigned)(tot.at >> 32) + cbase, to);
 }
 
 // Largest h in [h0, h1) with seg[h] <= t (seg ascending, seg[h0] = 0 <= t).

@@ -155,27 +155,39 @@ static_assert(sizeof(Head) % 8 == 0, "copied in 8-byte words");
 // without work may read it and leave at any time during the launch; only the workgroups
 // that take part count themselves in.  (A finished machine sets the phase of
 // both.)
-struct Ctl {
+//
+// Device-scope atomics on one word are served one by one, 12 ns each, on
+// different words of one 128-byte line 6 ns each, and lines work side by side
+// (measured: 6,144 wavefronts, one atomic each: 75 us on one word, 37 on 32
+// words of a line, 5 on 32 lines).  So every word or group of words that many
+// workgroups of a launch update has a line of its own.
+struct alignas(128) Ctl {
     // --- polled by the host after every chunk of launches (keep first)
     int32_t phase;        // of the state written last
     int32_t err;          // sticky device error bits (capacity, range)
     // --- level under construction (atomics)
-    unsigned long long next_qc;  // appends to the next level: entries (low 32 bits), cost units (high 32)
-    unsigned long long next_hq;  // heavy entries of the level under construction: count | segments << 32
-    uint32_t blocks_done;
-    uint32_t pad;
-    Head h[2];
-    // --- per-slot counters and workgroup arrivals of the running step
-    unsigned long long slot[kSlots][kNCnt];
-    uint32_t arrive[kSlots];
-    uint32_t work[kSlots][32];  // per-slot work counters, one 128-byte line each
+    alignas(128) unsigned long long next_qc;  // appends to the next level: entries (low 32 bits), cost units (high 32)
+    alignas(128) unsigned long long next_hq;  // heavy entries of the level under construction: count | segments << 32
+    alignas(128) uint32_t blocks_done;
+    alignas(128) Head h[2];
+    // --- per-slot counters, workgroup arrivals and work counters of the running step
+    alignas(128) unsigned long long slot[kSlots][16];
+    uint32_t arrive[kSlots][32];
+    uint32_t work[kSlots][32];
 };
+static_assert(kNCnt <= 16, "a slot's counters share one line");
 // The same for a machine that one workgroup runs alone (block engine), in LDS.
 struct SoloCtl {
     int32_t err;
     unsigned long long next_qc, next_hq;
     uint32_t work[1][1];
     Head h[1];
+};
+
+// What such a workgroup starts from and hands back.
+struct SoloState {
+    Head h;
+    int32_t err, pad;
 };
 
 enum : int32_t { ERR_QUEUE_CAP = 1, ERR_SIGMA_RANGE = 2, ERR_LEVEL_CAP = 4, ERR_OVF_CAP = 8 };
@@ -378,7 +390,7 @@ struct BlockArgs {
     BatchArgs a;                 // graph, policy, source list and batch table of the run
     char *scratch;               // per-workgroup state, `stride` bytes each (BlockLayout)
     size_t stride;
-    Ctl *ctls;                   // one control block per workgroup
+    SoloState *states;           // one per workgroup: the state it starts from and ends with
     int32_t nmax;
     uint32_t lq_cap, gcap, hq_entries, hq_levels, part_cap, ovf_cap;
     int32_t max_levels;

@@ -58,15 +58,13 @@ __device__ __forceinline__ bool group_any(bool x) {
 
 // Top-down over the arcs of a frontier vertex (path count sv): claim unvisited
 // neighbours, add sv to the neighbours on level l+1 (MODE 0).
-template <int MODE, int G>
+template <int MODE, int G, class To>
 __device__ __forceinline__ void plain_push_arcs(const PlainArgs &a, int l, unsigned long long sv, int e0, int len,
-                                                uint32_t qe, uint32_t hqb, unsigned long long &my_edges,
-                                                unsigned long long &my_larcs, int &my_ovf, Stage &st, int &sn) {
-    const int32_t *__restrict__ rp = a.g.row_ptr;
+                                                unsigned long long &my_larcs, int &my_ovf, Stage &st, int &sn,
+                                                const To &to) {
     const int32_t *__restrict__ col = a.g.col;
-    Ctl *gc = a.ctl;
     for (int t = lane_id() & (G - 1); __any(t < len); t += kArcs * G) {
-        int w[kArcs], dv[kArcs], dw[kArcs];
+        int w[kArcs], dv[kArcs];
         bool newly[kArcs];
 #pragma unroll
         for (int q = 0; q < kArcs; ++q) w[q] = t + q * G < len ? col[e0 + t + q * G] : -1;
@@ -83,7 +81,6 @@ __device__ __forceinline__ void plain_push_arcs(const PlainArgs &a, int l, unsig
         }
 #pragma unroll
         for (int q = 0; q < kArcs; ++q) {
-            dw[q] = newly[q] ? rp[w[q] + 1] - rp[w[q]] : 0;
             if (MODE == 0 && dv[q] == l + 1) {
                 const unsigned long long old = atomicAdd(&a.sig[w[q]], sv);
                 const unsigned long long nv = old + sv;
@@ -92,11 +89,7 @@ __device__ __forceinline__ void plain_push_arcs(const PlainArgs &a, int l, unsig
             }
         }
 #pragma unroll
-        for (int q = 0; q < kArcs; ++q) {
-            my_edges += (unsigned)dw[q];
-            stage_push(newly[q], w[q], dw[q], st, sn, gc, a.queue, qe, (uint32_t)a.g.n, a.hq, hqb, &gc->err,
-                       GroupArgs{});
-        }
+        for (int q = 0; q < kArcs; ++q) stage_push(newly[q], w[q], st, sn, to);
     }
 }
 
@@ -271,6 +264,7 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
     __shared__ Head s_head;
     __shared__ unsigned long long s_tot[kNCnt];
     __shared__ Stage s_stage[kWavesPerBlock];
+    __shared__ StageTotals<kWavesPerBlock> s_stot;
     __shared__ float s_lds[2 * kMlpH + kMlpOut + 4];
     __shared__ LevelFeatures s_feat;
     Ctl *gc = a.ctl;
@@ -364,6 +358,12 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
         const uint32_t hqb = (uint32_t)s_hqb;
         Stage &st = s_stage[wid];
         int sn = 0;
+        const auto to = stage_to(gc, a.queue, (uint32_t)qe, (uint32_t)n, a.hq, hqb, GroupArgs{},
+                                 [&](int w, bool first) {
+                                     const int deg = rp[w + 1] - rp[w];
+                                     if (first) my_edges += (unsigned)deg;
+                                     return deg;
+                                 });
         if (variant == V_PUSH_TPV || variant == V_PUSH_WPV) {
             const int n_light = variant == V_PUSH_TPV ? (cnt + kPer - 1) / kPer : cnt;
             const int total = n_light + hseg;
@@ -377,14 +377,14 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
                     const int a0 = rp[v] + s * kSeg, a1 = min(rp[v + 1], a0 + kSeg);
                     if (lane == 0) my_arcs += (unsigned)(a1 - a0);
                     const unsigned long long sv = MODE == 0 ? sig[v] : 0ull;
-                    plain_push_arcs<MODE, kWave>(a, l, sv, a0, a1 - a0, (uint32_t)qe, hqb, my_edges, my_larcs, my_ovf, st, sn);
+                    plain_push_arcs<MODE, kWave>(a, l, sv, a0, a1 - a0, my_larcs, my_ovf, st, sn, to);
                 } else if (variant == V_PUSH_WPV) {
                     const int v = a.queue[qb + it];
                     const int e0 = rp[v], e1 = rp[v + 1];
                     if (e1 - e0 > kSeg) continue;  // runs as segments
                     if (lane == 0) my_arcs += (unsigned)(e1 - e0);
                     const unsigned long long sv = MODE == 0 ? sig[v] : 0ull;
-                    plain_push_arcs<MODE, kWave>(a, l, sv, e0, e1 - e0, (uint32_t)qe, hqb, my_edges, my_larcs, my_ovf, st, sn);
+                    plain_push_arcs<MODE, kWave>(a, l, sv, e0, e1 - e0, my_larcs, my_ovf, st, sn, to);
                 } else {  // TPV: kPer frontier vertices per wavefront
                     const int i = it * kPer + sub;
                     const bool valid = i < cnt;
@@ -393,15 +393,15 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
                     const int deg = valid ? rp[v + 1] - e0 : 0;
                     const unsigned long long sv = (MODE == 0 && valid) ? sig[v] : 0ull;
                     if (lead) my_arcs += (unsigned)(deg <= kSeg ? deg : 0);
-                    plain_push_arcs<MODE, kSub>(a, l, sv, e0, deg <= kSubDeg ? deg : 0, (uint32_t)qe, hqb, my_edges,
-                                                my_larcs, my_ovf, st, sn);
+                    plain_push_arcs<MODE, kSub>(a, l, sv, e0, deg <= kSubDeg ? deg : 0, my_larcs,
+                                                my_ovf, st, sn, to);
                     // medium-degree vertices: the whole wavefront, one at a time
                     unsigned long long mm = __ballot(lead && deg > kSubDeg && deg <= kSeg);
                     while (mm) {
                         const int j = __ffsll(mm) - 1;
                         mm &= mm - 1;
                         plain_push_arcs<MODE, kWave>(a, l, shfl_u64(sv, j), __shfl(e0, j), __shfl(deg, j),
-                                                     (uint32_t)qe, hqb, my_edges, my_larcs, my_ovf, st, sn);
+                                                     my_larcs, my_ovf, st, sn, to);
                     }
                 }
             }
@@ -433,9 +433,7 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
                         }
                         if (lane == 0) newly = atomicCAS(&d[w], -1, l + 1) == -1;
                     }
-                    const int deg = rp[w + 1] - rp[w];
-                    if (newly) my_edges += (unsigned)deg;
-                    stage_push(newly, w, deg, st, sn, gc, a.queue, (uint32_t)qe, (uint32_t)n, a.hq, hqb, &gc->err, GroupArgs{});
+                    stage_push(newly, w, st, sn, to);
                     continue;
                 }
                 // runs of kPullRun vertices from every part of the numbering: hubs
@@ -476,14 +474,12 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
                             sig[w] = lo;
                             if (hi != 0 || lo > a.sigma_limit) my_ovf = 1;
                         }
-                        my_edges += (unsigned)deg;
                     }
-                    stage_push(ok, w, deg, st, sn, gc, a.queue, (uint32_t)qe, (uint32_t)n, a.hq, hqb, &gc->err,
-                               GroupArgs{});
+                    stage_push(ok, w, st, sn, to);
                 }
             }
         }
-        stage_flush(st, sn, gc, a.queue, (uint32_t)qe, (uint32_t)n, a.hq, hqb, &gc->err, GroupArgs{});
+        stage_finish<kWavesPerBlock>(st, sn, s_stot, to);
     } else if (MODE == 1 && phase == PH_SIG) {
         // FP64 path counts of level l+1, pulled in CSR order
         const int qs = s_qe, cnt = s_qn - s_qe;

@@ -103,14 +103,18 @@ __device__ __forceinline__ unsigned long long offer_arcs(const WideArgs &a, int 
     return hit;
 }
 
+// Class degree of a vertex that joins a round.
+struct WideDeg {
+    const GraphArgs &g;
+    __device__ __forceinline__ int operator()(int x, bool) const {
+        return class_deg(g, x, g.row_ptr[x + 1] - g.row_ptr[x]);
+    }
+};
+
 // Arcs that enter the next round's queue, or that are recorded (MARK).
 struct NextRound {
     unsigned long long *mask;  // [n] marks of the next round
-    int32_t *q;
-    uint32_t qbase, qcap;
-    HeavyQ hq;
-    uint32_t hq_base;
-    GroupArgs ga;
+    StageTo<Ctl, WideDeg> to;
 };
 
 // Mark the lanes `hit` of x (per thread) for the next round; a vertex marked
@@ -118,10 +122,8 @@ struct NextRound {
 __device__ __forceinline__ void mark_next(const WideArgs &a, const NextRound &nx, int x, unsigned long long hit,
                                           Stage &st, int &sn) {
     bool newly = false;
-    int cw = 0;
     if (hit) newly = atomicOr(&nx.mask[x], hit) == 0ull;
-    if (newly) cw = class_deg(a.g, x, a.g.row_ptr[x + 1] - a.g.row_ptr[x]);
-    stage_push(newly, x, cw, st, sn, a.ctl, nx.q, nx.qbase, nx.qcap, nx.hq, nx.hq_base, &a.ctl->err, nx.ga);
+    stage_push(newly, x, st, sn, nx.to);
 }
 
 template <bool MARK>
@@ -450,6 +452,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     __shared__ Head s_head;
     __shared__ unsigned long long s_tot[kNCnt];
     __shared__ int s_src[kLanes], s_lead[kLanes];
+    __shared__ StageTotals<kWavesPerBlock> s_stot;
     __shared__ union {
         WideScratch ws;
         double tile[kWave * 8];
@@ -534,16 +537,13 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             const int cz = uniform(s_prev1);
             for (int i = (int)bid * kBlock + tid; i < cz; i += (int)nblk * kBlock) fz[qz[i]] = 0ull;
         }
-        NextRound nx;
-        nx.mask = a.fm + (size_t)rn * n;
-        nx.q = a.rq;
-        nx.qbase = (uint32_t)rn * (uint32_t)n;
-        nx.qcap = nx.qbase + (uint32_t)n;
-        nx.hq = a.rhq;
-        nx.hq_base = (uint32_t)rn * a.rhcap;
-        nx.ga.gstart = a.rgs;
-        nx.ga.gb = (uint32_t)rn * a.rgcap;
-        nx.ga.gcap = nx.ga.gb + a.rgcap;
+        GroupArgs gr;
+        gr.gstart = a.rgs;
+        gr.gb = (uint32_t)rn * a.rgcap;
+        gr.gcap = gr.gb + a.rgcap;
+        const uint32_t qbase = (uint32_t)rn * (uint32_t)n;
+        const NextRound nx{a.fm + (size_t)rn * n, stage_to(gc, a.rq, qbase, qbase + (uint32_t)n, a.rhq,
+                                                           (uint32_t)rn * a.rhcap, gr, WideDeg{a.g})};
         const int qb = uniform(s_qb), cnt = mark ? n : uniform(s_qe) - qb;
         const uint32_t *gs = mark ? a.sgs : a.rgs + uniform((int)s_gb);
         const unsigned long long all = uniform(s_lmask);
@@ -596,7 +596,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             else offer_entry<false>(a, nx, m, dall, a0, a1, ws.st, sn, rc);
         }
         if (!mark)
-            stage_flush(ws.st, sn, gc, nx.q, nx.qbase, nx.qcap, nx.hq, nx.hq_base, &gc->err, nx.ga);
+            stage_finish<kWavesPerBlock>(ws.st, sn, s_stot, nx.to);
     } else if (phase == WP_DAG) {
         const int qb = uniform(s_qb), qe = uniform(s_qe), cnt = qe - qb;
         const unsigned long long *mask = a.rdy + (size_t)(l % 3) * n;
@@ -605,16 +605,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             const int z0 = uniform(s_prev0), z1 = uniform(s_prev1);
             for (int i = z0 + (int)bid * kBlock + tid; i < z1; i += (int)nblk * kBlock) fz[a.lq_vtx[i]] = 0ull;
         }
-        NextRound nx;
-        nx.mask = a.rdy + (size_t)((l + 1) % 3) * n;
-        nx.q = a.lq_vtx;
-        nx.qbase = (uint32_t)qe;
-        nx.qcap = a.lq_cap;
-        nx.hq = a.hq;
-        nx.hq_base = (uint32_t)h1;
-        nx.ga.gstart = a.gstart;
-        nx.ga.gb = a.gbase[l + 1];
-        nx.ga.gcap = a.gcap;
+        GroupArgs gr;
+        gr.gstart = a.gstart;
+        gr.gb = a.gbase[l + 1];
+        gr.gcap = a.gcap;
+        const NextRound nx{a.rdy + (size_t)((l + 1) % 3) * n, stage_to(gc, a.lq_vtx, (uint32_t)qe, a.lq_cap, a.hq,
+                                                                       (uint32_t)h1, gr, WideDeg{a.g})};
         const uint32_t *gs = a.gstart + uniform((int)s_gb);
         for (WorkCursor<> wc(gc, nblk, bid); wc.item() < total; wc.next(total)) {
             const int k = wc.item();
@@ -659,7 +655,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             SigCounters sc;
             sig_store<OP>(sum, m, row_addr(a.sigma, v, a.shift), a.sigma_limit, ovf, sc);
         }
-        stage_flush(ws.st, sn, gc, nx.q, nx.qbase, nx.qcap, nx.hq, nx.hq_base, &gc->err, nx.ga);
+        stage_finish<kWavesPerBlock>(ws.st, sn, s_stot, nx.to);
     } else if (phase == WP_BWD) {
         const int qb = uniform(s_qb), cnt = uniform(s_qe) - qb;
         const unsigned long long dead = uniform(s_dead);
