@@ -205,8 +205,9 @@ struct bc_graph {
     void *wd_mem[24] = {};            // its allocations
     size_t wd_bytes = 0;
     int64_t nonisolated = 0;
-    // vertices of degree > kSegBatched (ascending) and their segment prefix
-    // sums; p_*: the same for the plain engine's kSegPlain
+    // vertices of class degree above a segment of 2^seg_log arcs (ascending) and
+    // their segment prefix sums; p_*: the same for the per-source engine's segments
+    int32_t seg_log = kSegLogMax;
     int32_t *hv_vtx = nullptr, *hv_seg = nullptr;
     int32_t n_heavy = 0;
     int64_t heavy_segs = 0;
@@ -507,6 +508,25 @@ static void source_ranks(int32_t n_graphs, const std::vector<int32_t> &voff, con
     for (int32_t i = 0; i < n; ++i) (*rank)[order[i]] = i;
 }
 
+// Arcs of a heavy vertex's segment (binary logarithm), by the arcs of a graph.
+// A segment is one wavefront's, eight matched rows at a time, so on graphs
+// with few arcs the longest segment is what a path-count, backward or
+// relaxation step waits for; on large ones there are enough of them, and a pull
+// step over a short segment cannot stop early.  1,024 / 512 / 256 / 128 arcs:
+// R-MAT 2^12 (0.11 M arcs), 100 sources, 1.75 / 1.57 / 1.42 / 1.37 ms; R-MAT 2^14
+// (0.45 M), 64 sources, 1.21 / 0.97 / 0.83 / 0.80; R-MAT 2^16 (1.9 M), 256
+// sources, 2.65 / 2.39 / 2.43 / 2.46; directed R-MAT 2^18 (4 M), 1000 sources,
+// 15.5 / 14.9 / 16.0 / 17.5; R-MAT 2^18 (7.6 M), 2048 sources, 32.2 / 33.7 / 35.4 /
+// 46.9.  Weighted graphs, without pull steps: R-MAT 2^12, 128 sources, 4.3 / 3.1 /
+// 2.5 / 2.2; R-MAT 2^16, 512 sources, 24.8 / 21.7 / 19.7 / 19.4, 256 sources - / - /
+// 8.9 / 8.6; R-MAT 2^20 (32 M), 64 sources, 17.4 / 17.4 / 18.5 / -.
+static int segment_log(int64_t nnz, int32_t n_graphs, bool weighted) {
+    const int64_t arcs = nnz / std::max<int32_t>(n_graphs, 1);
+    if (arcs < (int64_t)1 << 20) return kSegLogMin;
+    if (arcs < (int64_t)6 << 20) return weighted ? 8 : 9;
+    return weighted ? 9 : kSegLogMax;
+}
+
 static bc_status create_impl(int32_t n_graphs, const int32_t *voff_in, int32_t n, int64_t nnz,
                              const int32_t *row_ptr, const int32_t *col_idx, uint32_t flags, bc_graph **out,
                              const int32_t *weights = nullptr) {
@@ -751,11 +771,12 @@ static bc_status create_impl(int32_t n_graphs, const int32_t *voff_in, int32_t n
             if (nnz) CR_TRY(hipMemcpy(g->wt, w.data(), sizeof(int32_t) * (size_t)nnz, hipMemcpyHostToDevice));
             if (!directed) g->in_wt = g->wt;
         }
+        g->seg_log = segment_log(nnz, n_graphs, weights != nullptr);
         int64_t cost_units = 0;
-        for (int32_t v = 0; v < n; ++v) cost_units += entry_cost(cdeg[v]);
+        for (int32_t v = 0; v < n; ++v) cost_units += entry_cost(cdeg[v], g->seg_log);
         g->cost_units = cost_units;
         for (int which = 0; which < 2; ++which) {
-            const int seg = which == 0 ? kSegBatched : kSegPlain;
+            const int seg = 1 << (which == 0 ? g->seg_log : kSegLogPlain);
             std::vector<int32_t> hv, hs(1, 0);
             int64_t segs = 0;
             for (int32_t v = 0; v < n; ++v) {
@@ -1241,7 +1262,7 @@ static bc_status run_pass(bc_graph *g, const RunCfg &cfg, const bc_run_options &
     hc->f64_check = cfg.f64_check ? 1 : 0;
     hc->dump_pos = dump_pos;
     const unsigned long long limit = o.sigma_limit > 0 ? (unsigned long long)o.sigma_limit : ~0ull;
-    GraphArgs ga;
+    GraphArgs ga{};
     ga.n = g->n;
     ga.nnz_lo = (int32_t)g->nnz;
     ga.row_ptr = g->row_ptr;
@@ -1253,12 +1274,14 @@ static bc_status run_pass(bc_graph *g, const RunCfg &cfg, const bc_run_options &
     ga.hv_vtx = g->hv_vtx;
     ga.hv_seg = g->hv_seg;
     ga.n_heavy = g->n_heavy;
+    ga.seg_log = g->seg_log;
     int64_t launches = 0;
     double dev_ms = 0.0;
     if (cfg.engine == 1) {
         ga.hv_vtx = g->p_hv_vtx;
         ga.hv_seg = g->p_hv_seg;
         ga.n_heavy = g->p_n_heavy;
+        ga.seg_log = kSegLogPlain;
         hc->phase = PH_FIN;
         hc->pos = -1;
         hc->n_items = ns;
@@ -1542,16 +1565,17 @@ static bc_status block_facts(bc_graph *g) {
     }
     int32_t nmax = 0;
     int64_t cmax = 0, hmax = 0, smax = 0, amax = 0;
+    const int32_t seg = 1 << g->seg_log;
     for (int gi = 0; gi < g->n_graphs; ++gi) {
         const int32_t lo = g->voff[gi], hi = g->voff[gi + 1];
         int64_t cost = 0, heavy = 0, segs = 0;
         for (int32_t v = lo; v < hi; ++v) {
             int32_t d = rp[v + 1] - rp[v];
             if (g->directed) d = std::max(d, irp[v + 1] - irp[v]);
-            cost += entry_cost(d);
-            if (d > kSegBatched) {
+            cost += entry_cost(d, g->seg_log);
+            if (d > seg) {
                 ++heavy;
-                segs += (d + kSegBatched - 1) / kSegBatched;
+                segs += (d + seg - 1) / seg;
             }
         }
         nmax = std::max(nmax, hi - lo);
@@ -1822,7 +1846,7 @@ static bc_status run_block(bc_graph *g, const RunCfg &cfg, const bc_run_options 
     HIP_TRY(hipGetLastError());
     BlockArgs ra = dm;
     std::memset(&ra.a, 0, sizeof(ra.a));
-    GraphArgs ga;
+    GraphArgs ga{};
     ga.n = g->n;
     ga.nnz_lo = (int32_t)g->nnz;
     ga.row_ptr = g->row_ptr;
@@ -1834,6 +1858,7 @@ static bc_status run_block(bc_graph *g, const RunCfg &cfg, const bc_run_options 
     ga.hv_vtx = g->hv_vtx;
     ga.hv_seg = g->hv_seg;
     ga.n_heavy = g->n_heavy;
+    ga.seg_log = g->seg_log;
     ra.a.g = ga;
     ra.a.p = policy_args(g, o);
     ra.a.srcs = g->srcs;
@@ -2235,7 +2260,7 @@ static bc_status ensure_wide(bc_graph *g, int k, hipStream_t st, bool *fits) {
         int32_t d = rp[v + 1] - rp[v];
         if (g->directed) d = std::max(d, irp[v + 1] - irp[v]);
         // (at least 2, so that a merged group fits a wavefront with isolated vertices, too)
-        const uint64_t next = cost + std::max(2u, entry_cost(d));
+        const uint64_t next = cost + std::max(2u, entry_cost(d, g->seg_log));
         for (uint64_t q = cost / kBudget + 1; q <= next / kBudget; ++q) gs[q] = (uint32_t)v + 1u;
         cost = next;
     }
@@ -2285,6 +2310,7 @@ static bc_status wide_pass(bc_graph *g, int mode, const bc_run_options &o, const
     a.g.directed = g->directed ? 1 : 0;
     a.g.in_row_ptr = g->directed ? g->in_row_ptr : g->row_ptr;
     a.g.in_col = g->directed ? g->in_col : g->col;
+    a.g.seg_log = g->seg_log;
     a.g.hv_vtx = g->hv_vtx;
     a.g.hv_seg = g->hv_seg;
     a.g.n_heavy = g->n_heavy;
@@ -2543,16 +2569,22 @@ static bc_status ensure_parts(bc_graph *g) {
     if (g->acct.limit) {
         // what the parts would hold: their graphs and batched engine state
         std::vector<int64_t> pn(P, 0), pnnz(P, 0), pcost(P, 0), pheavy(P, 0), psegs(P, 0);
+        std::vector<int> plog(P);
+        for (int i = 0; i < G; ++i) {
+            pnnz[g->part_of_graph[i]] += rp[g->voff[i + 1]] - rp[g->voff[i]];
+            ++plog[g->part_of_graph[i]];
+        }
+        for (int p = 0; p < P; ++p) plog[p] = segment_log(pnnz[p], plog[p], false);
         for (int i = 0; i < G; ++i) {
             const int p = g->part_of_graph[i];
+            const int32_t seg = 1 << plog[p];
             for (int32_t v = g->voff[i]; v < g->voff[i + 1]; ++v) {
                 const int32_t d = rp[v + 1] - rp[v];
                 pn[p] += 1;
-                pnnz[p] += d;
-                pcost[p] += entry_cost(d);
-                if (d > kSegBatched) {
+                pcost[p] += entry_cost(d, plog[p]);
+                if (d > seg) {
                     pheavy[p] += 1;
-                    psegs[p] += (d + kSegBatched - 1) / kSegBatched;
+                    psegs[p] += (d + seg - 1) / seg;
                 }
             }
         }

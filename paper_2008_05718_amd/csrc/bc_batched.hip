@@ -27,12 +27,11 @@
 //
 // Load balance: sums and pushes work on groups of level entries of about equal
 // cost; in a group the arcs of vertices of degree <= kPack are packed into
-// 64-arc chunks, a vertex of degree <= kSeg has the wavefront to itself, and a
-// heavier one is split into kSeg-arc segments, one wavefront each (pull: one
-// thread per vertex up to kLightDeg).  Segment
-// partial sums are combined in segment order by the last segment to finish,
-// so every sum has an order fixed by the vertex and the results are bitwise
-// reproducible.
+// 64-arc chunks, a vertex of up to a segment of arcs has the wavefront to itself,
+// and a heavier one is split into segments, one wavefront each (pull: one
+// thread per vertex up to kLightDeg).  Segment partial sums are combined in
+// segment order by the last segment to finish, so every sum has an order fixed
+// by the vertex and the results are bitwise reproducible.
 #include "bc_common.h"
 
 #ifndef BC_UNROLL
@@ -104,7 +103,7 @@ __device__ __forceinline__ unsigned push_group(const BatchArgs &a, Append<To> &a
     const unsigned long long f = valid ? (a.lq_mask[p] & act) : 0ull;
     const int e0 = f ? rp[u] : 0, od = f ? rp[u + 1] - e0 : 0;  // out-arcs to push over
     const int deg = f ? class_deg(a.g, u, od) : 0;
-    const bool light = f && deg <= kPack, medium = f && deg > kPack && deg <= kSeg;
+    const bool light = f && deg <= kPack, medium = f && deg > kPack && deg <= seg_arcs(a.g);
     int off;
     const int total = pack_entries(pk, light ? od : 0,
                                    make_uint4((unsigned)e0, (unsigned)f, (unsigned)(f >> 32), 0u),
@@ -179,7 +178,7 @@ union WaveScratch {
 
 // Path counts for the entries [i0, i1) of level l+1 (one group):
 // entries of degree <= kPack have their adjacencies packed into dense 64-arc
-// chunks; entries of degree <= kSeg follow one at a time; heavier ones run as
+// chunks; entries of up to a segment follow one at a time; heavier ones run as
 // segments elsewhere.  Every entry's sum keeps CSR order.
 //
 // What bounds it: on R-MAT 22 the bytes fetched beyond the L2 (5.8 TB/s: a
@@ -211,7 +210,7 @@ __device__ __forceinline__ void sig_group(const BatchArgs &a, const Tagged *fw_c
     const int od = (valid && a.g.directed) ? a.g.row_ptr[w + 1] - a.g.row_ptr[w] : na;  // out-degree
     const int deg = a.g.directed ? (valid ? max(na, od) : 0) : na;  // class degree
     const bool light = valid && deg <= kPack;
-    const bool medium = valid && deg > kPack && deg <= kSeg;
+    const bool medium = valid && deg > kPack && deg <= seg_arcs(a.g);
     unsigned long long vis = 0, nxt = 0;
     if (light || medium) {
         const VisNext x = a.vn[w];
@@ -302,7 +301,7 @@ __device__ __forceinline__ void bwd_group(const BatchArgs &a, const Tagged *fb_n
     const int na = valid ? rp[v + 1] - e0 : 0;  // successors: the out-arcs
     const int deg = valid ? class_deg(a.g, v, na) : 0;
     const bool light = valid && deg <= kPack;
-    const bool medium = valid && deg > kPack && deg <= kSeg;
+    const bool medium = valid && deg > kPack && deg <= seg_arcs(a.g);
     const unsigned long long Mf = (light || medium) ? a.lq_mask[p] : 0ull;
     const unsigned long long M = Mf & ~dead;
     unsigned long long todo = 0, parked = 0;  // entries to finish below; those with a sum in their delta row
@@ -465,14 +464,14 @@ __device__ __forceinline__ void batch_begin(const BatchArgs &a, Head *c, int64_t
         for (int j = 0; j < cnt; ++j) {
             const int deg = (int)(uint32_t)s_tmp[j], cdeg = (int)(s_tmp[j] >> 32);
             mf += (unsigned long long)deg;
-            const uint32_t ce = entry_cost(cdeg);
+            const uint32_t ce = entry_cost(cdeg, a.g.seg_log);
             for (uint32_t k = cost / kBudget + 1; k <= (cost + ce) / kBudget; ++k) a.gstart[k] = (uint32_t)j + 1u;
             cost += ce;
-            if (cdeg > kSeg) {  // heavy source: level-0 segments for the push
+            if (cdeg > seg_arcs(a.g)) {  // heavy source: level-0 segments for the push
                 a.hq.pos[nh] = j;
                 a.hq.seg[nh] = segs;
                 a.hq.cnt[nh] = 0;
-                segs += n_segments(cdeg);
+                segs += n_segments(a.g, cdeg);
                 ++nh;
             }
         }
@@ -694,7 +693,7 @@ __device__ __forceinline__ void batch_step_body(Load load, C *gc, const int pari
         gr.gstart = a.gstart;
         gr.gb = (uint32_t)uniform((int)s_gbn);
         gr.gcap = a.gcap;
-        const auto to = stage_to(gc, a.lq_vtx, (uint32_t)qe, a.lq_cap, a.hq, (uint32_t)uniform(s_hqb), gr,
+        const auto to = stage_to(gc, a.lq_vtx, (uint32_t)qe, a.lq_cap, a.hq, (uint32_t)uniform(s_hqb), gr, a.g,
                                  [&](int w, bool) { return class_deg(a.g, w, rp[w + 1] - rp[w]); });
         Append<decltype(to)> ap{to, s_scratch[wid].w.st, 0};
         Packing &pk = s_scratch[wid].w.pk;
@@ -712,15 +711,15 @@ __device__ __forceinline__ void batch_step_body(Load load, C *gc, const int pari
                     const int p = uniform(a.hq.pos[h]);
                     const int u = uniform(a.lq_vtx[p]);
                     const unsigned long long f = uniform(a.lq_mask[p]) & act;
-                    const int a0 = uniform(rp[u]) + s * kSeg;
-                    const int a1 = max(a0, min(uniform(rp[u + 1]), a0 + kSeg));
+                    const int a0 = uniform(rp[u]) + (s << a.g.seg_log);
+                    const int a1 = max(a0, min(uniform(rp[u + 1]), a0 + seg_arcs(a.g)));
                     if (lane == 0) my_arcs += (unsigned)(a1 - a0);
                     if (f) push_arcs(a, ap, f, a0, a1, col);
                 } else if (variant == V_PUSH_WPV) {
                     const int u = uniform(a.lq_vtx[qb + it]);
                     const unsigned long long f = uniform(a.lq_mask[qb + it]) & act;
                     const int e0 = uniform(rp[u]), e1 = uniform(rp[u + 1]);
-                    if (!f || uniform(class_deg(a.g, u, e1 - e0)) > kSeg) continue;  // heavy ones run as segments
+                    if (!f || uniform(class_deg(a.g, u, e1 - e0)) > seg_arcs(a.g)) continue;  // heavy ones run as segments
                     if (lane == 0) my_arcs += (unsigned)(e1 - e0);
                     push_arcs(a, ap, f, e0, e1, col);
                 } else {  // a group of frontier vertices per wavefront
@@ -743,7 +742,7 @@ __device__ __forceinline__ void batch_step_body(Load load, C *gc, const int pari
                     const int s = t - uniform(a.g.hv_seg[h]);
                     const int w = uniform(a.g.hv_vtx[h]);
                     const unsigned long long need = act & ~uniform(a.vn[w].vis);
-                    const int a0 = uniform(irp[w]) + s * kSeg, a1 = max(a0, min(uniform(irp[w + 1]), a0 + kSeg));
+                    const int a0 = uniform(irp[w]) + (s << a.g.seg_log), a1 = max(a0, min(uniform(irp[w + 1]), a0 + seg_arcs(a.g)));
                     int scanned = 0;
                     const unsigned long long got = pull_arcs(fw_cur, T, need, a0, a1, icol, scanned);
                     if (lane == 0) my_arcs += (unsigned)scanned;
@@ -777,7 +776,7 @@ __device__ __forceinline__ void batch_step_body(Load load, C *gc, const int pari
                     }
                 }
                 // medium-degree vertices: the whole wavefront, one at a time
-                for (unsigned long long mm = __ballot(deg > kLightDeg && deg <= kSeg); mm; mm &= mm - 1) {
+                for (unsigned long long mm = __ballot(deg > kLightDeg && deg <= seg_arcs(a.g)); mm; mm &= mm - 1) {
                     const int j = __ffsll(mm) - 1;
                     const int m0 = __builtin_amdgcn_readlane(e0, j), m1 = m0 + __builtin_amdgcn_readlane(ni, j);
                     int sc = 0;
@@ -786,7 +785,7 @@ __device__ __forceinline__ void batch_step_body(Load load, C *gc, const int pari
                     if (lane == j) got = gj;
                 }
                 my_arcs += (unsigned)scanned;
-                const bool found = got != 0ull && deg <= kSeg;
+                const bool found = got != 0ull && deg <= seg_arcs(a.g);
                 if (found) a.vn[w].nxt = got;
                 append(ap, found, w);
             }
@@ -825,7 +824,7 @@ __device__ __forceinline__ void batch_step_body(Load load, C *gc, const int pari
             const int e0 = uniform(a.g.in_row_ptr[w]), e1 = uniform(a.g.in_row_ptr[w + 1]);  // predecessors: in-arcs
             const int od = uniform(rp[w + 1] - rp[w]);
             const unsigned long long m = uniform(a.vn[w].nxt);
-            const int a0 = e0 + s * kSeg, a1 = max(a0, min(e1, a0 + kSeg));
+            const int a0 = e0 + (s << a.g.seg_log), a1 = max(a0, min(e1, a0 + seg_arcs(a.g)));
             RowSum<OP> sum;
             row_arcs<OP>(TagLanes{fw_cur, T}, m, a0, a1, sh, a.g.in_col, a.sigma, sum, sc.ac);
             const size_t slot = (size_t)(s0 + s) * kLanes + lane;
@@ -835,7 +834,7 @@ __device__ __forceinline__ void batch_step_body(Load load, C *gc, const int pari
             } else {
                 part_store(&a.hq.part_lo[slot], as_u64(sum.d));
             }
-            const int ns = n_segments(uniform(class_deg(a.g, w, od)));
+            const int ns = n_segments(a.g, uniform(class_deg(a.g, w, od)));
             if (!seg_arrive(&a.hq.cnt[h], ns)) continue;
             sum.clear();
             for (int k2 = 0; k2 < ns; ++k2) {  // combine in segment order
@@ -900,11 +899,11 @@ __device__ __forceinline__ void batch_step_body(Load load, C *gc, const int pari
             const unsigned long long Mf = uniform(a.lq_mask[p]);
             const unsigned long long M = Mf & ~dead;
             const int e0 = uniform(rp[v]), e1 = uniform(rp[v + 1]);  // successors: out-arcs
-            const int a0 = e0 + s * kSeg, a1 = max(a0, min(e1, a0 + kSeg));
+            const int a0 = e0 + (s << a.g.seg_log), a1 = max(a0, min(e1, a0 + seg_arcs(a.g)));
             RowSum<OP_C> sum;
             if (M) row_arcs<OP_C>(TagLanes{fb_nxt, TB + 1u}, M, a0, a1, 0, col, a.chat, sum, ac);
             part_store(&a.hq.part_lo[(size_t)(s0 + s) * kLanes + lane], as_u64(sum.d));
-            const int ns = n_segments(uniform(class_deg(a.g, v, e1 - e0)));
+            const int ns = n_segments(a.g, uniform(class_deg(a.g, v, e1 - e0)));
             if (!seg_arrive(&a.hq.cnt[h], ns)) continue;
             double acc = 0.0;
             for (int k2 = 0; k2 < ns; ++k2) acc += as_f64(part_load(&a.hq.part_lo[(size_t)(s0 + k2) * kLanes + lane]));

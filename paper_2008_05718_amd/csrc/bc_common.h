@@ -296,10 +296,13 @@ __device__ __forceinline__ unsigned long long shfl_u64(unsigned long long x, int
     return ((unsigned long long)hi << 32) | lo;
 }
 
-__device__ __forceinline__ int n_segments(int deg) { return (deg + kSeg - 1) / kSeg; }
+__device__ __forceinline__ int seg_arcs(const GraphArgs &g) { return 1 << g.seg_log; }
+__device__ __forceinline__ int n_segments(const GraphArgs &g, int deg) {
+    return (int)(((unsigned)deg + (unsigned)seg_arcs(g) - 1u) >> g.seg_log);
+}
 
 // Degree that decides how a level entry is processed (one thread, one
-// wavefront, or kSeg-arc segments) and what it costs: the larger of its out-
+// wavefront, or segments) and what it costs: the larger of its out-
 // and in-degree, so an entry is handled the same way in every phase, whichever
 // arcs the phase scans (out-arcs to push and to pull dependencies from
 // successors, in-arcs to pull discovery and path counts from predecessors).
@@ -329,8 +332,8 @@ __device__ __forceinline__ int merge_groups(uint32_t ng, unsigned waves) {
 // fixed part; heavy entries (split into segments elsewhere) count 2.  Every
 // entry costs at least 2 units, so a group never holds more than
 // kBudget / 2 entries.
-static __host__ __device__ __forceinline__ unsigned entry_cost(int deg) {
-    return deg > kSeg ? 2u : 1u + (unsigned)(deg + 7) / 8u;
+static __host__ __device__ __forceinline__ unsigned entry_cost(int deg, int seg_log) {
+    return deg > (1 << seg_log) ? 2u : 1u + (unsigned)(deg + 7) / 8u;
 }
 
 // Groups of a level: the entries whose cost prefix (in append order) starts
@@ -355,12 +358,14 @@ struct StageTo {
     HeavyQ hq;
     uint32_t hq_base;
     GroupArgs ga;
+    const GraphArgs &g;
     Deg deg;
 };
 template <class C, class Deg>
 __device__ __forceinline__ StageTo<C, Deg> stage_to(C *c, int32_t *q, uint32_t qbase, uint32_t qcap, const HeavyQ &hq,
-                                                    uint32_t hq_base, const GroupArgs &ga, Deg deg) {
-    return StageTo<C, Deg>{c, q, qbase, qcap, hq, hq_base, ga, deg};
+                                                    uint32_t hq_base, const GroupArgs &ga, const GraphArgs &g,
+                                                    Deg deg) {
+    return StageTo<C, Deg>{c, q, qbase, qcap, hq, hq_base, ga, g, deg};
 }
 
 __device__ __forceinline__ void stage_fence() {
@@ -376,11 +381,11 @@ __device__ __forceinline__ unsigned stage_costs(Stage &st, int n, const To &to) 
     unsigned cost = 0;
     for (int i = lane_id(); i < n; i += kWave) {
         const int deg = to.deg(st.w[i], true);
-        const unsigned ci = entry_cost(deg);
-        st.cost[i] = deg > kSeg ? (uint8_t)0 : (uint8_t)ci;
+        const unsigned ci = entry_cost(deg, to.g.seg_log);
+        st.cost[i] = deg > seg_arcs(to.g) ? (uint8_t)0 : (uint8_t)ci;
         cost += ci;
     }
-    static_assert(1 + (kSeg + 7) / 8 <= 255, "cost units of an entry fit a byte");
+    static_assert(1 + (kSegMax + 7) / 8 <= 255, "cost units of an entry fit a byte");
     return wave_sum_u32(cost);
 }
 
@@ -403,7 +408,7 @@ __device__ __forceinline__ void stage_write(Stage &st, int n, unsigned base, uns
             else atomicOr(&to.c->err, ERR_QUEUE_CAP);
         }
         if (to.ga.gstart) {
-            const unsigned ci = heavy ? entry_cost(kSeg + 1) : on ? units : 0u;
+            const unsigned ci = heavy ? 2u : on ? units : 0u;
             const unsigned incl = (unsigned)wave_incl_scan((int)ci);
             const unsigned P = cbase + incl - ci;
             for (unsigned k = P / kBudget + 1; on && k <= (P + ci) / kBudget; ++k) {
@@ -415,7 +420,7 @@ __device__ __forceinline__ void stage_write(Stage &st, int n, unsigned base, uns
         }
         const unsigned long long hm = __ballot(heavy);
         if (hm) {
-            const int ns = heavy ? n_segments(to.deg(w, false)) : 0;
+            const int ns = heavy ? n_segments(to.g, to.deg(w, false)) : 0;
             const int incl = wave_incl_scan(ns);
             const int total = __builtin_amdgcn_readlane(incl, 63);
             const int hl = __ffsll((unsigned long long)hm) - 1;

@@ -12,21 +12,12 @@ constexpr int kWave = 64;    // CDNA wavefront width
 constexpr int kWavesPerBlock = kBlock / kWave;
 constexpr int kLanes = 64;   // sources per batch = wavefront lanes
 constexpr int kLightDeg = 32;  // thread-per-vertex loops handle up to this many arcs
-#ifndef BC_SEG
-#define BC_SEG 1024
-#endif
-#ifndef BC_SEG_PLAIN
-#define BC_SEG_PLAIN 512
-#endif
-// heavy vertices (degree > kSeg) are split into kSeg-arc segments; each
-// engine has its own size (the plain engine is compiled with BC_PLAIN_TU)
-constexpr int kSegBatched = BC_SEG;
-constexpr int kSegPlain = BC_SEG_PLAIN;
-#ifdef BC_PLAIN_TU
-constexpr int kSeg = kSegPlain;
-#else
-constexpr int kSeg = kSegBatched;
-#endif
+// Heavy vertices (class degree above a segment) are split into segments of
+// 2^seg_log arcs, one wavefront each: fixed for the per-source engine, by the
+// graph's size for the others (GraphArgs::seg_log).
+constexpr int kSegLogPlain = 9;
+constexpr int kSegLogMin = 7, kSegLogMax = 10;
+constexpr int kSegMax = 1 << kSegLogMax;
 constexpr int kPhases = 10;
 // Scaled FP64 path counts (mode 1): a level whose largest binary exponent
 // exceeds kExpHigh is divided by a power of two that brings it to kExpTarget,
@@ -213,7 +204,8 @@ struct GraphArgs {
     const int32_t *row_ptr; // int32[n+1]
     const int32_t *col;     // int32[nnz]
     int64_t nonisolated;    // vertices with degree >= 1
-    // vertices of degree > kSeg in ascending order, and the exclusive prefix
+    int32_t seg_log;        // arcs of a segment, binary logarithm
+    // vertices of class degree above a segment in ascending order, and the exclusive prefix
     // sum of their segment counts (hv_seg[n_heavy] = all segments)
     const int32_t *hv_vtx;
     const int32_t *hv_seg;
@@ -226,7 +218,7 @@ struct GraphArgs {
     int32_t directed;
 };
 
-// Heavy entries of the level queues (vertices of degree > kSeg), per level:
+// Heavy entries of the level queues (vertices of more than a segment), per level:
 // entries hq_off[l] .. hq_off[l+1]; hq_seg holds each entry's first segment
 // relative to its level, hq_nseg[l] the level's segment count.
 struct HeavyQ {

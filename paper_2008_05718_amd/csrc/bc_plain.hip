@@ -20,7 +20,7 @@
 // Backward (both modes): delta(v) = sigma(v) * sum over successors w of
 // c(w), c(w) = (1 + delta(w)) / sigma(w) -- Eq. 2 with sigma(v) factored
 // out.  Each vertex's sum is formed by kSub lanes (degree <= kSubDeg), one
-// wavefront (<= kSeg) or kSeg-arc segments combined in segment order by the
+// wavefront (a segment) or segments combined in segment order by the
 // last segment to finish; no floating-point atomics, so results are bitwise
 // reproducible.
 //
@@ -29,7 +29,6 @@
 // lanes and every lane requests kArcs of them together.  With a thread per
 // vertex instead, up to 32 arcs after one another, 32 sources on R-MAT 18 took
 // 27.3 ms, now 13.5; 4 on a 512 x 512 grid 38.6, now 24.5.
-#define BC_PLAIN_TU 1  // this engine's segment size: kSegPlain
 #include "bc_common.h"
 
 namespace bcx {
@@ -187,12 +186,12 @@ __device__ __forceinline__ void plain_begin_source(const PlainArgs &a, Ctl *gc, 
         a.shift[0] = 0;
         const int deg = a.g.row_ptr[s + 1] - a.g.row_ptr[s];
         a.hq.off[0] = 0;
-        if (deg > kSeg) {  // heavy source: its level-0 push runs as segments
+        if (deg > seg_arcs(a.g)) {  // heavy source: its level-0 push runs as segments
             a.hq.pos[0] = 0;
             a.hq.seg[0] = 0;
             a.hq.cnt[0] = 0;
             a.hq.off[1] = 1;
-            a.hq.nseg[0] = n_segments(deg);
+            a.hq.nseg[0] = n_segments(a.g, deg);
         } else {
             a.hq.off[1] = 0;
             a.hq.nseg[0] = 0;
@@ -358,7 +357,7 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
         const uint32_t hqb = (uint32_t)s_hqb;
         Stage &st = s_stage[wid];
         int sn = 0;
-        const auto to = stage_to(gc, a.queue, (uint32_t)qe, (uint32_t)n, a.hq, hqb, GroupArgs{},
+        const auto to = stage_to(gc, a.queue, (uint32_t)qe, (uint32_t)n, a.hq, hqb, GroupArgs{}, a.g,
                                  [&](int w, bool first) {
                                      const int deg = rp[w + 1] - rp[w];
                                      if (first) my_edges += (unsigned)deg;
@@ -374,14 +373,14 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
                     const int h = seg_owner(a.hq.seg, h0, h1, t);
                     const int s = t - a.hq.seg[h];
                     const int v = a.queue[a.hq.pos[h]];
-                    const int a0 = rp[v] + s * kSeg, a1 = min(rp[v + 1], a0 + kSeg);
+                    const int a0 = rp[v] + (s << a.g.seg_log), a1 = min(rp[v + 1], a0 + seg_arcs(a.g));
                     if (lane == 0) my_arcs += (unsigned)(a1 - a0);
                     const unsigned long long sv = MODE == 0 ? sig[v] : 0ull;
                     plain_push_arcs<MODE, kWave>(a, l, sv, a0, a1 - a0, my_larcs, my_ovf, st, sn, to);
                 } else if (variant == V_PUSH_WPV) {
                     const int v = a.queue[qb + it];
                     const int e0 = rp[v], e1 = rp[v + 1];
-                    if (e1 - e0 > kSeg) continue;  // runs as segments
+                    if (e1 - e0 > seg_arcs(a.g)) continue;  // runs as segments
                     if (lane == 0) my_arcs += (unsigned)(e1 - e0);
                     const unsigned long long sv = MODE == 0 ? sig[v] : 0ull;
                     plain_push_arcs<MODE, kWave>(a, l, sv, e0, e1 - e0, my_larcs, my_ovf, st, sn, to);
@@ -392,11 +391,11 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
                     const int e0 = valid ? rp[v] : 0;
                     const int deg = valid ? rp[v + 1] - e0 : 0;
                     const unsigned long long sv = (MODE == 0 && valid) ? sig[v] : 0ull;
-                    if (lead) my_arcs += (unsigned)(deg <= kSeg ? deg : 0);
+                    if (lead) my_arcs += (unsigned)(deg <= seg_arcs(a.g) ? deg : 0);
                     plain_push_arcs<MODE, kSub>(a, l, sv, e0, deg <= kSubDeg ? deg : 0, my_larcs,
                                                 my_ovf, st, sn, to);
                     // medium-degree vertices: the whole wavefront, one at a time
-                    unsigned long long mm = __ballot(lead && deg > kSubDeg && deg <= kSeg);
+                    unsigned long long mm = __ballot(lead && deg > kSubDeg && deg <= seg_arcs(a.g));
                     while (mm) {
                         const int j = __ffsll(mm) - 1;
                         mm &= mm - 1;
@@ -419,7 +418,7 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
                     // unvisited before this level (another segment may have
                     // claimed it during this step)
                     if (dw0 != -1 && dw0 != l + 1) continue;
-                    const int a0 = rp[w] + s * kSeg, a1 = min(rp[w + 1], a0 + kSeg);
+                    const int a0 = rp[w] + (s << a.g.seg_log), a1 = min(rp[w + 1], a0 + seg_arcs(a.g));
                     unsigned long long lo, hi;
                     const bool any = plain_pull_arcs<MODE, kWave>(a, l, a0, a1 - a0, lo, hi, my_arcs, my_larcs);
                     bool newly = false;
@@ -454,7 +453,7 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
                     bool found =
                         plain_pull_arcs<MODE, kSub>(a, l, e0, deg <= kSubDeg ? deg : 0, lo, hi, my_arcs, my_larcs);
                     // medium-degree candidates: the whole wavefront, one at a time
-                    unsigned long long mm = __ballot(lead && deg > kSubDeg && deg <= kSeg);
+                    unsigned long long mm = __ballot(lead && deg > kSubDeg && deg <= seg_arcs(a.g));
                     while (mm) {
                         const int j = __ffsll(mm) - 1;
                         mm &= mm - 1;
@@ -467,7 +466,7 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
                             hi = mh;
                         }
                     }
-                    const bool ok = lead && found && deg <= kSeg;
+                    const bool ok = lead && found && deg <= seg_arcs(a.g);
                     if (ok) {
                         d[w] = l + 1;
                         if (MODE == 0) {
@@ -494,13 +493,13 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
                 const int s = t - a.hq.seg[h];
                 const int w = a.queue[a.hq.pos[h]];
                 const int e0 = rp[w], e1 = rp[w + 1];
-                const int a0 = e0 + s * kSeg, a1 = min(e1, a0 + kSeg);
+                const int a0 = e0 + (s << a.g.seg_log), a1 = min(e1, a0 + seg_arcs(a.g));
                 const double p = plain_sum<kWave>(a, a0, a1 - a0, l, false, sh, my_larcs);
                 if (lane == 0) {
                     my_arcs += (unsigned)(a1 - a0);
                     part_store(&a.hq.part_lo[a.hq.seg[h] + s], as_u64(p));
                 }
-                const int ns = n_segments(e1 - e0);
+                const int ns = n_segments(a.g, e1 - e0);
                 if (!seg_arrive(&a.hq.cnt[h], ns)) continue;
                 if (lane == 0) {
                     double acc = 0.0;
@@ -521,16 +520,16 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
             const int w = valid ? a.queue[qs + i] : 0;
             const int e0 = valid ? rp[w] : 0;
             const int deg = valid ? rp[w + 1] - e0 : 0;
-            if (lead) my_arcs += (unsigned)(deg <= kSeg ? deg : 0);
+            if (lead) my_arcs += (unsigned)(deg <= seg_arcs(a.g) ? deg : 0);
             double acc = plain_sum<kSub>(a, e0, deg <= kSubDeg ? deg : 0, l, false, sh, my_larcs);
-            unsigned long long mm = __ballot(lead && deg > kSubDeg && deg <= kSeg);
+            unsigned long long mm = __ballot(lead && deg > kSubDeg && deg <= seg_arcs(a.g));
             while (mm) {
                 const int j = __ffsll(mm) - 1;
                 mm &= mm - 1;
                 const double p = plain_sum<kWave>(a, __shfl(e0, j), __shfl(deg, j), l, false, sh, my_larcs);
                 if (lane == j) acc = p;
             }
-            if (lead && valid && deg <= kSeg) {
+            if (lead && valid && deg <= seg_arcs(a.g)) {
                 sig[w] = as_u64(acc);
                 if (acc > 0.0) {
                     int ex;
@@ -554,13 +553,13 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
                 const int s = t - a.hq.seg[h];
                 const int v = a.queue[a.hq.pos[h]];
                 const int e0 = rp[v], e1 = rp[v + 1];
-                const int a0 = e0 + s * kSeg, a1 = min(e1, a0 + kSeg);
+                const int a0 = e0 + (s << a.g.seg_log), a1 = min(e1, a0 + seg_arcs(a.g));
                 const double p = plain_sum<kWave>(a, a0, a1 - a0, l + 1, true, 0, my_larcs);
                 if (lane == 0) {
                     my_arcs += (unsigned)(a1 - a0);
                     part_store(&a.hq.part_lo[a.hq.seg[h] + s], as_u64(p));
                 }
-                const int ns = n_segments(e1 - e0);
+                const int ns = n_segments(a.g, e1 - e0);
                 if (!seg_arrive(&a.hq.cnt[h], ns)) continue;
                 if (lane == 0) {
                     double acc = 0.0;
@@ -580,12 +579,12 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
             const int v = valid ? a.queue[qb + i] : 0;
             const int e0 = valid ? rp[v] : 0;
             const int deg = valid ? rp[v + 1] - e0 : 0;
-            const bool fin = lead && valid && deg <= kSeg;
+            const bool fin = lead && valid && deg <= seg_arcs(a.g);
             const double sv = fin ? norm_sigma<MODE>(a, v, sh) : 1.0;
             const double bc0 = fin ? a.bc[v] : 0.0;
-            if (lead) my_arcs += (unsigned)(deg <= kSeg ? deg : 0);
+            if (lead) my_arcs += (unsigned)(deg <= seg_arcs(a.g) ? deg : 0);
             double acc = plain_sum<kSub>(a, e0, deg <= kSubDeg ? deg : 0, l + 1, true, 0, my_larcs);
-            unsigned long long mm = __ballot(lead && deg > kSubDeg && deg <= kSeg);
+            unsigned long long mm = __ballot(lead && deg > kSubDeg && deg <= seg_arcs(a.g));
             while (mm) {
                 const int j = __ffsll(mm) - 1;
                 mm &= mm - 1;

@@ -173,7 +173,7 @@ __device__ __forceinline__ void offer_group(const WideArgs &a, const NextRound &
     const int e0 = take ? a.g.row_ptr[v] : 0;
     const int na = take ? a.g.row_ptr[v + 1] - e0 : 0;
     const int deg = take ? class_deg(a.g, v, na) : 0;
-    const bool light = take && deg <= kPack, medium = take && deg > kPack && deg <= kSeg;
+    const bool light = take && deg <= kPack, medium = take && deg > kPack && deg <= seg_arcs(a.g);
     const unsigned long long er = row_addr(a.dist, v, a.shift);
     int off;
     const int total = pack_entries(ws.pk, light ? na : 0,
@@ -265,7 +265,7 @@ __device__ __forceinline__ void dag_group(const WideArgs &a, const NextRound &nx
     const int n0 = (valid && a.g.directed) ? a.g.in_row_ptr[v] : o0;
     const int ni = (valid && a.g.directed) ? a.g.in_row_ptr[v + 1] - n0 : no;
     const int deg = max(no, ni);
-    const bool light = valid && deg <= kPack, medium = valid && deg > kPack && deg <= kSeg;
+    const bool light = valid && deg <= kPack, medium = valid && deg > kPack && deg <= seg_arcs(a.g);
     if (light || medium) a.lq_mask[p] = M;
     int off;
     if (l > 0) {
@@ -322,7 +322,7 @@ __device__ __forceinline__ void back_group(const WideArgs &a, int qb, int i0, in
     const int v = valid ? a.lq_vtx[p] : 0;
     const int e0 = valid ? a.g.row_ptr[v] : 0, na = valid ? a.g.row_ptr[v + 1] - e0 : 0;
     const int deg = valid ? class_deg(a.g, v, na) : 0;
-    const bool light = valid && deg <= kPack, medium = valid && deg > kPack && deg <= kSeg;
+    const bool light = valid && deg <= kPack, medium = valid && deg > kPack && deg <= seg_arcs(a.g);
     const unsigned long long M = (light || medium) ? (a.lq_mask[p] & ~dead) : 0ull;
     const Slab sigma(a.sigma, a.shift), chat(a.chat, a.shift), delta(a.delta, a.shift);
     unsigned long long parked = 0;
@@ -390,19 +390,19 @@ __device__ __forceinline__ void wide_begin(const WideArgs &a, Ctl *gc, Head *c, 
             const int deg = class_deg(a.g, s, a.g.row_ptr[s + 1] - a.g.row_ptr[s]);
             a.rq[cnt] = s;
             a.lq_vtx[cnt] = s;
-            const uint32_t ce = entry_cost(deg);
+            const uint32_t ce = entry_cost(deg, a.g.seg_log);
             for (uint32_t g = cost / kBudget + 1; g <= (cost + ce) / kBudget; ++g) {
                 a.rgs[g] = cnt + 1u;
                 a.gstart[g] = cnt + 1u;
             }
             cost += ce;
-            if (deg > kSeg) {
+            if (deg > seg_arcs(a.g)) {
                 a.rhq.pos[nh] = (int32_t)cnt;
                 a.rhq.seg[nh] = segs;
                 a.hq.pos[nh] = (int32_t)cnt;
                 a.hq.seg[nh] = segs;
                 a.hq.cnt[nh] = 0;
-                segs += n_segments(deg);
+                segs += n_segments(a.g, deg);
                 ++nh;
             }
             ++cnt;
@@ -543,7 +543,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         gr.gcap = gr.gb + a.rgcap;
         const uint32_t qbase = (uint32_t)rn * (uint32_t)n;
         const NextRound nx{a.fm + (size_t)rn * n, stage_to(gc, a.rq, qbase, qbase + (uint32_t)n, a.rhq,
-                                                           (uint32_t)rn * a.rhcap, gr, WideDeg{a.g})};
+                                                           (uint32_t)rn * a.rhcap, gr, a.g, WideDeg{a.g})};
         const int qb = uniform(s_qb), cnt = mark ? n : uniform(s_qe) - qb;
         const uint32_t *gs = mark ? a.sgs : a.rgs + uniform((int)s_gb);
         const unsigned long long all = uniform(s_lmask);
@@ -587,8 +587,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             const int32_t *sp = mark ? a.g.hv_seg : a.rhq.seg;
             const int h = uniform(seg_owner(sp, h0, h1, t));
             const int v = uniform(mark ? a.g.hv_vtx[h] : a.rq[a.rhq.pos[h]]);
-            const int a0 = uniform(rp[v]) + (t - uniform(sp[h])) * kSeg;
-            const int a1 = max(a0, min(uniform(rp[v + 1]), a0 + kSeg));
+            const int a0 = uniform(rp[v]) + ((t - uniform(sp[h])) << a.g.seg_log);
+            const int a1 = max(a0, min(uniform(rp[v + 1]), a0 + seg_arcs(a.g)));
             const unsigned long long dall = row_load(row_addr(a.dist, v, a.shift), row_slot(all));
             const unsigned long long m = mark ? (__ballot(dall != kInf) & all) : uniform(fc[v]);
             if (!m && !(mark && a.g.directed)) continue;
@@ -610,7 +610,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         gr.gb = a.gbase[l + 1];
         gr.gcap = a.gcap;
         const NextRound nx{a.rdy + (size_t)((l + 1) % 3) * n, stage_to(gc, a.lq_vtx, (uint32_t)qe, a.lq_cap, a.hq,
-                                                                       (uint32_t)h1, gr, WideDeg{a.g})};
+                                                                       (uint32_t)h1, gr, a.g, WideDeg{a.g})};
         const uint32_t *gs = a.gstart + uniform((int)s_gb);
         for (WorkCursor<> wc(gc, nblk, bid); wc.item() < total; wc.next(total)) {
             const int k = wc.item();
@@ -628,18 +628,18 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             const unsigned long long m = uniform(mask[v]);
             if (s == 0 && lane == 0) a.lq_mask[p] = m;
             const int o0 = uniform(rp[v]), o1 = uniform(rp[v + 1]);
-            const int r0 = o0 + s * kSeg, r1 = max(r0, min(o1, r0 + kSeg));
+            const int r0 = o0 + (s << a.g.seg_log), r1 = max(r0, min(o1, r0 + seg_arcs(a.g)));
             release_entry(a, nx, m, r0, r1, ws.st, sn);
             if (lane == 0) ac.arcs += (unsigned)(r1 - r0);
             if (l == 0) continue;
             const int e0 = uniform(a.g.in_row_ptr[v]), e1 = uniform(a.g.in_row_ptr[v + 1]);
-            const int a0 = e0 + s * kSeg, a1 = max(a0, min(e1, a0 + kSeg));
+            const int a0 = e0 + (s << a.g.seg_log), a1 = max(a0, min(e1, a0 + seg_arcs(a.g)));
             RowSum<OP> sum;
             row_arcs<OP>(ArcLanes{a.dag_in}, m, a0, a1, 0, a.g.in_col, Slab(a.sigma, a.shift), sum, ac);
             const size_t slot = (size_t)(s0 + s) * kLanes + lane;
             part_store(&a.hq.part_lo[slot], MODE ? as_u64(sum.d) : sum.lo);
             if (MODE == 0) part_store(&a.hq.part_hi[slot], sum.hi);
-            const int ns = n_segments(max(o1 - o0, e1 - e0));
+            const int ns = n_segments(a.g, max(o1 - o0, e1 - e0));
             if (!seg_arrive(&a.hq.cnt[h], ns)) continue;
             sum.clear();
             for (int k2 = 0; k2 < ns; ++k2) {  // combine in segment order
@@ -675,11 +675,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             const int v = uniform(a.lq_vtx[p]);
             const unsigned long long M = uniform(a.lq_mask[p]) & ~dead;
             const int e0 = uniform(rp[v]), e1 = uniform(rp[v + 1]);
-            const int a0 = e0 + s * kSeg, a1 = max(a0, min(e1, a0 + kSeg));
+            const int a0 = e0 + (s << a.g.seg_log), a1 = max(a0, min(e1, a0 + seg_arcs(a.g)));
             RowSum<OP_C> sum;
             if (M) row_arcs<OP_C>(ArcLanes{a.dag_out}, M, a0, a1, 0, a.g.col, Slab(a.chat, a.shift), sum, ac);
             part_store(&a.hq.part_lo[(size_t)(s0 + s) * kLanes + lane], as_u64(sum.d));
-            const int ns = n_segments(uniform(class_deg(a.g, v, e1 - e0)));
+            const int ns = n_segments(a.g, uniform(class_deg(a.g, v, e1 - e0)));
             if (!seg_arrive(&a.hq.cnt[h], ns)) continue;
             double acc = 0.0;
             for (int k2 = 0; k2 < ns; ++k2) acc += as_f64(part_load(&a.hq.part_lo[(size_t)(s0 + k2) * kLanes + lane]));
