@@ -1658,25 +1658,24 @@ static bc_status ensure_block(bc_graph *g, int need) {
 // dump over handles whose graphs all have at most kBlockMaxN vertices, always
 // with BC_RUN_BLOCKS, never with BC_RUN_NO_BLOCKS or BC_RUN_ONE_QUEUE, and by
 // default when every graph has at most kBlockDefaultN vertices (in a union
-// kBlockDefaultUnionN) and the list fills 8 batches and one more per 8,192
-// arcs of the largest graph.  A
-// workgroup alone takes a time that grows with the graph's arcs for its
-// batch, whatever the number of batches (up to one per CU: 13 ms on R-MAT of
-// 2^14 vertices and 452,000 arcs, 3 ms on ER with 4,000 and 32,000), the
-// general engine one that grows with the batches, so the line is where the
-// two meet.  General against block engine, in ms: ER(4000) 1.2 and 1.6 at 4
-// batches, 2.1 and 1.7 at 8, 5.5 and 2.5 at 32; R-MAT 2^12 (110,000 arcs)
-// 2.2 and 2.3 at 8, 5.2 and 2.9 at 32; R-MAT 2^14 2.6 and 7.8 at 8, 12.8 and
-// 11.1 at 64, 20.3 and 13.6 at 128; ER(16000) 7.7 and 8.9 at 32, 17.3 and
-// 12.6 at 64; a 100 x 100 grid 5.7 and 6.1 at 4, 10.8 and 7.0 at 8.  A single
-// graph of 2^16 vertices would need some 250 batches (32.3 and 56.6 at 128).
-// Unions keep every workgroup busy up to larger graphs: 64 graphs of up to
-// 16,000 vertices 99.8 and 29.6, of up to 60,000 60.1 and 52.7 (every 64th
-// vertex a source) or 385 and 261 (every 8th), all of 20,000 to 60,000 163 and
-// 129; with graphs of up to 100,000 they meet (108 and 111, 747 and 660), and
-// the state, which grows with the largest graph, passes 30 GB.
+// kBlockDefaultUnionN) and the list fills 4 batches and one more per 4,096
+// arcs of the largest graph.  A workgroup alone takes a time that grows with the
+// graph's arcs for its batch, whatever the number of batches (up to one per
+// CU: 12 ms on R-MAT of 2^14 vertices and 452,000 arcs, 2 ms on ER with 4,000
+// and 32,000), the general engine one that grows with the batches, so the line
+// is where the two meet.  General against block engine, in ms: ER(4000) 1.1
+// and 1.6 at 4 batches, 1.8 and 1.7 at 8, 3.0 and 1.9 at 16; R-MAT 2^12 (110,000
+// arcs) 2.6 and 3.0 at 16, 4.2 and 3.1 at 32; R-MAT 2^14 10.2 and 13.9 at 64,
+// 17.6 and 16.9 at 128; ER(16000) (128,000) 7.6 and 8.7 at 32, 15.5 and 12.1 at
+// 64; a 100 x 100 grid 5.6 and 6.1 at 4, 10.6 and 6.7 at 8.  A single graph of
+// 2^16 vertices would need some 500 batches (30 and 61 at 128).  Unions keep
+// every workgroup busy up to larger graphs: 64 graphs of up to 16,000 vertices
+// 99.8 and 29.6, of up to 60,000 60.1 and 52.7 (every 64th vertex a source) or
+// 385 and 261 (every 8th), all of 20,000 to 60,000 163 and 129; with graphs of
+// up to 100,000 they meet (108 and 111, 747 and 660), and the state, which
+// grows with the largest graph, passes 30 GB.
 constexpr int kBlockDefaultN = 16384, kBlockDefaultUnionN = 65536;
-constexpr int64_t kBlockArcsPerBatch = 8192;
+constexpr int64_t kBlockArcsPerBatch = 4096;
 static bool use_block(bc_graph *g, const bc_run_options &o, int64_t ns, bool detail) {
     if (g->weighted || detail || o.batch == 1 || (o.flags & (BC_RUN_NO_BLOCKS | BC_RUN_ONE_QUEUE | BC_RUN_FORCE_F64)))
         return false;
@@ -1685,7 +1684,7 @@ static bool use_block(bc_graph *g, const bc_run_options &o, int64_t ns, bool det
     if (o.flags & BC_RUN_BLOCKS) return true;
     const int K = o.batch >= 8 ? o.batch : 64;
     return g->blk_nmax <= (g->n_graphs > 1 ? kBlockDefaultUnionN : kBlockDefaultN) &&
-           ns >= (8 + g->blk_arcs_max / kBlockArcsPerBatch) * K;
+           ns >= (4 + g->blk_arcs_max / kBlockArcsPerBatch) * K;
 }
 
 // Lanes of a block-engine batch when the caller leaves them open: the fewest
