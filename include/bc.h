@@ -116,9 +116,9 @@ bc_status bc_graph_create(int32_t n, int64_t nnz, const int32_t *row_ptr,
  * run in the ranked order described for bc_graph_create (by hop distance
  * from the vertex of largest degree, ...).  It runs the weighted
  * engine: batches of up to 64 sources, one at a time on the whole GPU, a launch
- * per round; or, for many sources of a small graph or on request
+ * per round; or, on small graphs, for many sources or on request
  * (bc_run_options.weighted_lanes), a persistent launch in which every
- * workgroup computes whole batches of 16 sources, or single sources.  Either
+ * workgroup computes single sources, or whole batches of 16.  Either
  * way distances by relaxation rounds, path
  * counts over the shortest-path DAG in rounds of ready vertices, Eq. 2 over
  * those rounds in reverse; uint64 path counts, redone in FP64 (unscaled; a
@@ -230,8 +230,10 @@ typedef struct bc_run_options {
                              together (1; 16; graphs above 2^27 vertices always
                              run one), or 0 = automatic: batches of up to 64 on
                              the whole GPU where the graph is large enough for
-                             the number of sources and the state fits, else 16.  Scores agree to rounding across
-                             values; a given value repeats bit for bit.     */
+                             the number of sources and the state fits, else one
+                             source, or 16 of a long list.  Scores agree to
+                             rounding across values; a given value repeats bit
+                             for bit.                                       */
     int32_t reserved[4];
 } bc_run_options;
 
@@ -394,7 +396,7 @@ typedef struct bc_stats {
        mode_* = the engine's launches; algo_bytes_arcs = algo_bytes without
        64 B per reached (vertex, source) pair.  One source per workgroup
        (weighted_lanes 1): algo_bytes = 16 per arc read + 64 per reached pair.
-       Lane batches (weighted_lanes 16, or 0; arcs counted once per round entry,
+       Lane batches (weighted_lanes 16; arcs counted once per round entry,
        for all of its sources): phase_lane_arcs[1] and [2] = (arc, source)
        pairs of the relaxation rounds and of the four passes; algo_bytes = 8
        per arc read (far end and weight) + 8 per (arc, source) pair (that

@@ -1945,11 +1945,19 @@ __global__ void sum_partials(double *dst, const double *partials, int64_t n, int
 }
 
 // Sources one workgroup runs together on a weighted graph: the run option,
-// else kWL; one when the lane batches' round records (n * kWL entries,
-// 32-bit offsets) would not fit.
-static int weighted_lanes(const bc_graph *g, const bc_run_options &o) {
+// else one for lists of up to kOneSourceLists sources and kWL beyond; always one
+// when the lane batches' round records (n * kWL entries, 32-bit offsets) would
+// not fit.  A workgroup's batch of 16 takes four to five times as long as one
+// source, and about 512 sources run at once singly against 4,096 in batches:
+// R-MAT 2^10, 64 sources 1.1 ms singly and 5.5 in batches, 1024 sources 1.7 and
+// 5.4; R-MAT 2^13, 1024 sources 14.8 and 31.0, 4096 sources 60 and 36; ER(20000),
+// 1024 sources 30 and 67, 4096 sources 124 and 82; a path of 5000 vertices, 64
+// sources 34 and 276.
+constexpr int64_t kOneSourceAtOnce = 512, kOneSourceLists = 5 * kOneSourceAtOnce;
+static int weighted_lanes(const bc_graph *g, const bc_run_options &o, int64_t ns) {
     if (o.weighted_lanes == 1 || (int64_t)g->n * kWL > (int64_t)INT32_MAX) return 1;
-    return kWL;
+    if (o.weighted_lanes == kWL) return kWL;
+    return ns <= kOneSourceLists ? 1 : kWL;
 }
 
 static bc_status ensure_weighted(bc_graph *g, int lanes) {
@@ -1988,12 +1996,11 @@ static bc_status ensure_weighted(bc_graph *g, int lanes) {
 
 // One pass over the run positions `pos` (sources h_srcs[pos[i]]) with the
 // given path-count mode; overflowed positions (mode 0) are returned.
-static bc_status weighted_pass(bc_graph *g, int mode, const bc_run_options &o, const int32_t *h_srcs,
+static bc_status weighted_pass(bc_graph *g, int lanes, int mode, const bc_run_options &o, const int32_t *h_srcs,
                                const std::vector<int64_t> &pos, int64_t dump_pos_run, DumpBufs *dump, hipStream_t st,
                                std::vector<int64_t> *ovf, bool *dumped) {
     ovf->clear();
     if (pos.empty()) return BC_OK;
-    const int lanes = weighted_lanes(g, o);
     bc_status s = ensure_weighted(g, lanes);
     if (s != BC_OK) return s;
     const int64_t ns = (int64_t)pos.size(), n = std::max<int32_t>(g->n, 1);
@@ -2149,16 +2156,23 @@ static void free_wide(bc_graph *g) {
 // list's values closer together.
 static int wide_lanes(int64_t ns) { return ns <= 8 ? 8 : (ns <= 16 ? 16 : (ns <= 32 ? 32 : 64)); }
 
-// Whether one batch at a time on the whole GPU beats a batch of 16 per
-// workgroup.  A wide batch of 64 takes about as long as its rounds' launches
-// (3 to 7 ms on R-MAT 10 to 18) while a workgroup's batch grows with the arcs
-// (6 ms at 12 thousand, 93 ms at 450 thousand, 1.2 s at 7.6 million), but up
-// to 256 of those run at once.  With one wide batch worth nnz / 16384 of them:
-// R-MAT 18, 4096 sources 427 ms wide against 1556 ms; R-MAT 14, 512 sources 27
-// against 96 ms; ER(2000), 16 sources 2.7 against 8.4 ms, but all 2000 sources
-// 98 against 9.5 ms; a path of 5000 vertices 441 against 282 ms.
+// Whether one batch at a time on the whole GPU beats a source, or a batch of
+// 16, per workgroup.  A wide batch of 64 takes about as long as its rounds'
+// launches, a little longer on large graphs (1.0 to 2.3 ms on R-MAT 2^10 to 2^14, 2.0
+// to 3.9 on 2^16); a workgroup's source grows with the arcs (1.1 ms at 21
+// thousand, 3.9 at 96 thousand, 15.8 at 426 thousand, 76 at 1.8 million), with
+// the list beyond kOneSourceAtOnce, and not at all between kOneSourceLists and
+// 4,096.  Wide against the better of the others: R-MAT 2^12, 64 sources 1.0 and
+// 3.9 ms, 256 sources 3.2 and 4.2, 1024 sources 12.1 and 6.7; R-MAT 2^14, 1024
+// sources 14.8 and 34.8; ER(2000), 64 sources 1.3 and 1.3, 1024 sources 17.6
+// and 2.4; a 200 x 200 grid, 64 sources 11.1 and 34, 512 sources 80 and 47; a
+// path of 5000 vertices, 64 sources 227 and 34.
 static bool wide_pays(const bc_graph *g, int64_t ns) {
-    return ((ns + kLanes - 1) / kLanes) * 16384 <= g->nnz * ((ns + 16 * 256 - 1) / (16 * 256));
+    const double nnz = (double)g->nnz, batches = (double)((ns + kLanes - 1) / kLanes);
+    const double wide_ms = batches * (1.2 + 1e-6 * nnz);
+    double lists = std::max(1.0, (double)ns / kOneSourceAtOnce);
+    lists = std::min(lists, (double)kOneSourceLists / kOneSourceAtOnce * std::max(1.0, (double)ns / (kWL * 256)));
+    return wide_ms < (0.6 + 3.5e-5 * nnz) * lists;
 }
 
 // State for batches of k sources.  *fits = false (and BC_OK): it does not fit
@@ -2390,14 +2404,17 @@ static bc_status run_weighted(bc_graph *g, const int32_t *src, int64_t ns, const
     for (int64_t i = 0; i < ns; ++i) all[i] = i;
     bool dumped = false;
     const bool force = (o.flags & BC_RUN_FORCE_F64) != 0;
-    // unless the caller asks for a batch per workgroup, the whole GPU works on
-    // one batch at a time
+    // unless the caller asks for one or 16 sources per workgroup
     bool wide = false;
     bc_status s = BC_OK;
     if (o.weighted_lanes == 0 && ns > 0 && wide_pays(g, ns)) s = ensure_wide(g, wide_lanes(ns), st, &wide);
     if (s != BC_OK) return s;
-    const auto run_sources = wide ? wide_pass : weighted_pass;
-    s = run_sources(g, force ? 1 : 0, o, src, all, dump_index, db, st, &ovf, &dumped);
+    const int lanes = weighted_lanes(g, o, ns);
+    const auto run_sources = [&](int mode, const std::vector<int64_t> &pos, std::vector<int64_t> *over, bool *done) {
+        return wide ? wide_pass(g, mode, o, src, pos, dump_index, db, st, over, done)
+                    : weighted_pass(g, lanes, mode, o, src, pos, dump_index, db, st, over, done);
+    };
+    s = run_sources(force ? 1 : 0, all, &ovf, &dumped);
     if (s != BC_OK) return s;
     *dump_mode = force ? 1 : 0;
     if (force) {
@@ -2406,7 +2423,7 @@ static bc_status run_weighted(bc_graph *g, const int32_t *src, int64_t ns, const
     }
     if (!ovf.empty()) {
         bool dumped2 = false;
-        s = run_sources(g, 1, o, src, ovf, dump_index, db, st, &none, &dumped2);
+        s = run_sources(1, ovf, &none, &dumped2);
         if (s != BC_OK) return s;
         if (dumped2) *dump_mode = 1;
     }

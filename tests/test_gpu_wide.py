@@ -36,12 +36,12 @@ def _check(g, srcs, dumps, **opts):
 @pytest.mark.parametrize("directed", [False, True])
 @pytest.mark.parametrize("k", [1, 8, 9, 16, 17, 32, 33, 64, 65, 200])
 def test_list_lengths(k, directed):
-    base = W.rmat_directed(12, 16, seed=31) if directed else W.rmat(11, 16, seed=31)
+    base = W.rmat_directed(13, 16, seed=31) if directed else W.rmat(12, 16, seed=31)
     g = W.with_weights(base, 1, 30, seed=5)
     srcs = W.choose_sources(base, 200, seed=6)[:k]
     say(f"[wide] k={k} directed={directed}")
     st, _ = _check(g, srcs, {0, k - 1})
-    # n_batches counts this engine's batches only: 16384 arcs carry one of 64
+    # n_batches counts this engine's batches only (about 100,000 arcs carry two of 64)
     if k <= 128:
         assert st["n_batches"] == -(-k // (8 if k <= 8 else 16 if k <= 16 else 32 if k <= 32 else 64))
 
@@ -62,7 +62,7 @@ def test_degree_classes_and_weights(wmax, directed):
     else:
         base = W.csr_from_edges(n, u, v)
     g = W.with_weights(base, 1, wmax, seed=8)
-    srcs = np.concatenate([np.arange(pool, n), rng.choice(pool, 60, replace=False)]).astype(np.int32)
+    srcs = np.concatenate([np.arange(pool, n), rng.choice(pool, 50, replace=False)]).astype(np.int32)
     say(f"[wide] degree classes wmax={wmax} directed={directed}")
     _check(g, srcs, (0, 9, 11, 40))
 
@@ -75,7 +75,7 @@ def test_overflow_limit_and_fp64():
     assert modes[0] == 1 and st["f64_sources"] == int(modes.sum())
     base = W.rmat(11, 16, seed=64)
     g = W.with_weights(base, 1, 2, seed=8)
-    srcs = W.choose_sources(base, 120, seed=9)
+    srcs = W.choose_sources(base, 60, seed=9)
     lim = 195
     over = sum(bool((oracle.source(g, int(s)).sigma_u64 > lim).any()) for s in srcs)
     assert 0 < over < len(srcs)
@@ -89,7 +89,7 @@ def test_overflow_limit_and_fp64():
 
 
 def test_long_path_accumulate_and_isolated():
-    n = 9000
+    n = 14000
     u = np.arange(n - 2)
     base = W.csr_from_edges(n, u, u + 1)  # the last vertex is isolated
     g = W.with_weights(base, 1, 9, seed=5)
@@ -106,7 +106,7 @@ def test_long_path_accumulate_and_isolated():
 def test_memory_cap_falls_back():
     base = W.rmat(11, 16, seed=65)
     g = W.with_weights(base, 1, 50, seed=9)
-    srcs = W.choose_sources(base, 100, seed=10)
+    srcs = W.choose_sources(base, 60, seed=10)
     ref, _ = oracle.bc(g, srcs)
     with b.Graph(g) as G:
         floor = G.info()["device_bytes"]
