@@ -208,6 +208,7 @@ struct bc_graph {
     // vertices of class degree above a segment of 2^seg_log arcs (ascending) and
     // their segment prefix sums; p_*: the same for the per-source engine's segments
     int32_t seg_log = kSegLogMax;
+    int32_t pull_log = 6;
     int32_t *hv_vtx = nullptr, *hv_seg = nullptr;
     int32_t n_heavy = 0;
     int64_t heavy_segs = 0;
@@ -527,6 +528,28 @@ static int segment_log(int64_t nnz, int32_t n_graphs, bool weighted) {
     return weighted ? 9 : kSegLogMax;
 }
 
+// Consecutive vertices (binary logarithm) a wavefront of a batched pull step
+// takes: 64, which reads the visited words and, on graphs with local numbering,
+// the neighbours' words best; 8 from each of eight places where vertices of more
+// than kLightDeg arcs are numbered together (hubs first), since a wavefront
+// takes those one after another: at least twice as many beside such a vertex
+// as a random numbering would put there, and 4 more.  64 and 8: R-MAT 2^18, 64
+// sources 2.85 and 2.38 ms, 2048 sources 32.2 and 31.6; R-MAT 2^14, 64 sources
+// 0.80 and 0.73; the damaged 1024^2 grid, 256 sources, 93.8 and 96.9.  Graphs of
+// 2^24 arcs and more have wavefronts enough (R-MAT 2^20, 256 sources, 18.6 and 18.9).
+static int pull_run_log(const std::vector<int32_t> &cdeg, int32_t n, int64_t nnz) {
+    if (nnz >= (int64_t)1 << 24) return 6;
+    int64_t all = 0, beside = 0;
+    for (int32_t b = 0; b < n; b += kWave) {
+        int64_t c = 0;
+        for (int32_t v = b; v < n && v < b + kWave; ++v) c += cdeg[v] > kLightDeg ? 1 : 0;
+        all += c;
+        beside += c * c;
+    }
+    if (!all) return 6;
+    return (double)beside / (double)all >= 2.0 * kWave * (double)all / n + 4.0 ? 3 : 6;
+}
+
 static bc_status create_impl(int32_t n_graphs, const int32_t *voff_in, int32_t n, int64_t nnz,
                              const int32_t *row_ptr, const int32_t *col_idx, uint32_t flags, bc_graph **out,
                              const int32_t *weights = nullptr) {
@@ -775,6 +798,7 @@ static bc_status create_impl(int32_t n_graphs, const int32_t *voff_in, int32_t n
         int64_t cost_units = 0;
         for (int32_t v = 0; v < n; ++v) cost_units += entry_cost(cdeg[v], g->seg_log);
         g->cost_units = cost_units;
+        g->pull_log = pull_run_log(cdeg, n, nnz);
         for (int which = 0; which < 2; ++which) {
             const int seg = 1 << (which == 0 ? g->seg_log : kSegLogPlain);
             std::vector<int32_t> hv, hs(1, 0);
@@ -1275,6 +1299,7 @@ static bc_status run_pass(bc_graph *g, const RunCfg &cfg, const bc_run_options &
     ga.hv_seg = g->hv_seg;
     ga.n_heavy = g->n_heavy;
     ga.seg_log = g->seg_log;
+    ga.pull_log = g->pull_log;
     int64_t launches = 0;
     double dev_ms = 0.0;
     if (cfg.engine == 1) {
@@ -1858,6 +1883,7 @@ static bc_status run_block(bc_graph *g, const RunCfg &cfg, const bc_run_options 
     ga.hv_seg = g->hv_seg;
     ga.n_heavy = g->n_heavy;
     ga.seg_log = g->seg_log;
+    ga.pull_log = g->pull_log;
     ra.a.g = ga;
     ra.a.p = policy_args(g, o);
     ra.a.srcs = g->srcs;

@@ -751,8 +751,10 @@ __device__ __forceinline__ void batch_step_body(Load load, C *gc, const int pari
                     append(ap, newly, w);
                     continue;
                 }
-                const int w = lo + it * kWave + lane;
-                const bool valid = it * kWave + lane < span;
+                // runs of 2^pull_log consecutive vertices from all over the range
+                const int i = (((lane >> a.g.pull_log) * n_light + it) << a.g.pull_log) + (lane & ((1 << a.g.pull_log) - 1));
+                const int w = lo + i;
+                const bool valid = i < span;
                 const unsigned long long vis = valid ? a.vn[w].vis : ~0ull;
                 const unsigned long long need = act & ~vis;
                 const int e0 = need ? irp[w] : 0;

@@ -205,6 +205,7 @@ struct GraphArgs {
     const int32_t *col;     // int32[nnz]
     int64_t nonisolated;    // vertices with degree >= 1
     int32_t seg_log;        // arcs of a segment, binary logarithm
+    int32_t pull_log;       // batched pull: consecutive vertices in a wavefront, binary logarithm
     // vertices of class degree above a segment in ascending order, and the exclusive prefix
     // sum of their segment counts (hv_seg[n_heavy] = all segments)
     const int32_t *hv_vtx;
