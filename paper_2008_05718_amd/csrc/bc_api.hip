@@ -826,11 +826,11 @@ static bc_status create_impl(int32_t n_graphs, const int32_t *voff_in, int32_t n
         // one full wave of workgroups: every CU holds as many as occupancy allows
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0) {
             int bp = 0, bb = 0;
-            // the plain engine's levels are small: half a wave of workgroups
-            // keeps the per-step arrival count (and idle launches) down
+            // the per-source engine: four per CU (R-MAT 2^18, 32 sources 13.4 / 12.0 /
+            // 11.4 / 11.8 ms with 2 / 3 / 4 / 8; R-MAT 2^20, 8 sources 6.8 with 3, 6.0 with 4)
             if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&bp, (const void *)plain_step<0>, kBlock, 0) == hipSuccess &&
                 bp > 0)
-                g->grid_plain = std::max(cus, cus * bp / 2);
+                g->grid_plain = cus * std::min(bp, 4);
             if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&bb, (const void *)batch_step<0>, kBlock, 0) == hipSuccess &&
                 bb > 0)
                 g->grid_batch = cus * bb;
