@@ -35,7 +35,7 @@
 #include "bc_common.h"
 
 #ifndef BC_UNROLL
-#define BC_UNROLL 8
+#define BC_UNROLL 16
 #endif
 namespace bcx {
 constexpr int kUnroll = BC_UNROLL;  // matched neighbours whose rows are loaded together
@@ -190,8 +190,10 @@ union WaveScratch {
 // tag-then-mask loads: path-count and backward device time on R-MAT 18 (2048
 // sources, summed over 8 replicas) 90 + 95 -> 70 + 85 ms, R-MAT 22 (1024
 // sources, 4 replicas) 342 + 439 -> 327 + 385 ms; ER(2000), all sources, in the
-// block engine 7.1 -> 5.0 ms.  8 matches at a time: R-MAT 18 38.2 ms a run
-// against 39.2 for 4 and 38.4 for 16.
+// block engine 7.1 -> 5.0 ms.  Matches at a time, 4 / 8 / 16 / 24 / 32: R-MAT 18,
+// 2048 sources, 35.3 / 31.6 / 30.2 / 31.2 / 33.3 ms a run, R-MAT 22, 1024 sources,
+// 279.7 / 264.6 / 261.0 / 265.8 / 278.6 (where a register or two more spill, the
+// gain is lost).
 template <int MODE>
 __device__ __forceinline__ void sig_group(const BatchArgs &a, const Tagged *fw_cur, Tagged *fw_nxt, uint32_t T, int qs,
                                           int i0, int i1, int sh, unsigned long long lmask, SigCounters &sc, int l,
