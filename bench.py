@@ -322,7 +322,7 @@ def main():
     ap.add_argument("--tune-cache-out", help="write the process's tune cache here after tuning")
     ap.add_argument("--retune", action="store_true", help="tune even when the cache holds a result")
     ap.add_argument("--weighted-lanes", type=int, default=0, choices=[0, 1, 16],
-                    help="graphs with arc weights: sources per workgroup (0 = library default, 16)")
+                    help="graphs with arc weights: sources per workgroup (0 = by the sizes)")
     ap.add_argument("--policy-margin", type=float, default=0.0,
                     help="learned policy: log2 gain needed to override the rule (0 = library default, <0 = none)")
     ap.add_argument("--calibrate-copy", type=int, default=0, metavar="MIB",
