@@ -25,16 +25,6 @@ __device__ __forceinline__ unsigned long long uniform(unsigned long long x) {
     return ((unsigned long long)hi << 32) | lo;
 }
 
-__device__ __forceinline__ int wave_max_i(int x) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x = max(x, __shfl_xor(x, o));
-    return x;
-}
-__device__ __forceinline__ int wave_min_i(int x) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) x = min(x, __shfl_xor(x, o));
-    return x;
-}
 __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long x) {
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o);
@@ -55,23 +45,6 @@ __device__ __forceinline__ double wave_sum_f64(double x) {
 
 __device__ __forceinline__ double as_f64(unsigned long long u) { return __longlong_as_double((long long)u); }
 __device__ __forceinline__ unsigned long long as_u64(double x) { return (unsigned long long)__double_as_longlong(x); }
-
-// Append w for every lane with pred to dst (one atomic per wavefront).  The
-// wavefront must be converged.  Positions are relative to dst.
-__device__ __forceinline__ void wave_append(bool pred, int32_t w, uint32_t *counter, int32_t *dst,
-                                            uint32_t cap, int32_t *err) {
-    const unsigned long long m = __ballot(pred);
-    if (m == 0) return;
-    const int leader = __ffsll((unsigned long long)m) - 1;
-    unsigned base = 0;
-    if (lane_id() == leader) base = atomicAdd(counter, (unsigned)__popcll(m));
-    base = __shfl(base, leader);
-    if (pred) {
-        const unsigned p = base + lanes_below(m);
-        if (p < cap) dst[p] = w;
-        else atomicOr(err, ERR_QUEUE_CAP);
-    }
-}
 
 // ---------------------------------------------------------------- counters
 struct Counters {
@@ -515,20 +488,6 @@ __device__ __forceinline__ int lower_bound_i32(const int32_t *a, int n, int x) {
         else hi = mid;
     }
     return lo;
-}
-
-// Block-wide sum of one unsigned 64-bit value per thread; result valid in
-// thread 0.  Uses the caller's shared scratch of kWavesPerBlock entries.
-__device__ __forceinline__ unsigned long long block_sum_u64(unsigned long long x, unsigned long long *sh) {
-    x = wave_sum_u64(x);
-    const int w = threadIdx.x >> 6;
-    __syncthreads();
-    if (lane_id() == 0) sh[w] = x;
-    __syncthreads();
-    unsigned long long t = 0;
-    if (threadIdx.x == 0)
-        for (int i = 0; i < kWavesPerBlock; ++i) t += sh[i];
-    return t;
 }
 
 // Features of a level, normalised as documented for the policy network.
