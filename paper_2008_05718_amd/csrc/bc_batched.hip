@@ -1054,7 +1054,8 @@ __device__ __forceinline__ void batch_step_body(Load load, C *gc, const int pari
             __atomic_signal_fence(__ATOMIC_SEQ_CST);
         }
     }
-    if (!step_epilogue<NW>(gc, cn, s_red, s_tot, &s_last, bid, nblk)) return;
+    const float *mlp = c->policy == POL_MLP && phase == PH_SIG ? load().p.mlp : nullptr;
+    if (!step_epilogue<NW>(gc, cn, s_red, s_tot, &s_last, bid, nblk, mlp)) return;
 
     // ---- the last workgroup advances the state machine
     int action = 0;  // 1 = begin batch, 2 = advance level

@@ -149,10 +149,11 @@ __device__ __forceinline__ void head_store(Ctl *c, const Head &s, int parity) {
 // here, a caller's exponent ranges) must have completed before it counts
 // itself in: each wave that issued one waits for its memory counters first.
 // A step of one workgroup (nblk = 1) exchanges nothing.
-// s_red needs NW * kNCnt entries.
+// s_red needs NW * kNCnt entries.  mlp: weights the last workgroup will need, or
+// nullptr.
 template <int NW, class C>
 __device__ __forceinline__ bool step_epilogue(C *c, Counters &cn, unsigned long long *s_red, unsigned long long *s_tot,
-                                              int *s_last, unsigned bid, unsigned nblk) {
+                                              int *s_last, unsigned bid, unsigned nblk, const float *mlp = nullptr) {
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
 #pragma unroll
     for (int k = 0; k < kNCnt; ++k) {
@@ -201,6 +202,10 @@ __device__ __forceinline__ bool step_epilogue(C *c, Counters &cn, unsigned long 
         }
         __syncthreads();
         if (!*s_last) return false;
+        // the policy network's weights into this XCD's L2 while the totals are on
+        // their way (a word of every 64 bytes)
+        float near = 0.0f;
+        if (mlp && (int)threadIdx.x * 16 < kMlpParams) near = mlp[threadIdx.x * 16];
         // totals: wavefront w takes counters w, w + 4, ..., lane = slot
         unsigned long long x[(kNCnt + NW - 1) / NW];
 #pragma unroll
@@ -225,6 +230,7 @@ __device__ __forceinline__ bool step_epilogue(C *c, Counters &cn, unsigned long 
             c->work[threadIdx.x][0] = 0u;
         }
         if (threadIdx.x == 0) c->blocks_done = 0u;
+        asm volatile("" ::"v"(near));
         __syncthreads();
     }
     return true;
@@ -259,6 +265,10 @@ __device__ __forceinline__ int wave_incl_scan(int x) {
     x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
     x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
     return x;
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp_f32(float x) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xf, 0xf, false));
 }
 __device__ __forceinline__ unsigned wave_sum_u32(unsigned x) {
     return (unsigned)__builtin_amdgcn_readlane(wave_incl_scan((int)x), 63);
@@ -550,7 +560,7 @@ __device__ __forceinline__ int choose_variant(const PolicyArgs &p, int policy, i
         // Eight threads to a unit of the later layers, and every weight requested
         // before the first layer: layer by layer, row by row in one thread,
         // this stood with three rounds of 32 loads at the end of every forward
-        // step (R-MAT 2^16, 512 sources: 3.29 and 3.24 ms).
+        // step (with the choices of the rule, R-MAT 2^16, 512 sources: 2.1 % of the run, now 1.0).
         static_assert(kMlpH == 32 && kMlpOut <= 32, "eight threads hold a row of weights, four each");
         const int t = threadIdx.x, u = t >> 3, q = t & 7;
         float w1[kMlpIn], c1 = 0.0f, c2 = 0.0f, c3 = 0.0f;
@@ -572,8 +582,10 @@ __device__ __forceinline__ int choose_variant(const PolicyArgs &p, int policy, i
         float *h1 = lds, *h2 = lds + kMlpH, *y = lds + 2 * kMlpH;
         auto row = [&](const float4 &w, const float *h) {
             float s = w.x * h[4 * q] + w.y * h[4 * q + 1] + w.z * h[4 * q + 2] + w.w * h[4 * q + 3];
-            for (int o = 1; o < 8; o <<= 1) s += __shfl_xor(s, o);
-            return s;
+            // sums over eight threads: neighbours, pairs, then the half row mirrored
+            s += dpp_f32<0xB1>(s);
+            s += dpp_f32<0x4E>(s);
+            return s + dpp_f32<0x141>(s);
         };
         if (t < kMlpH) {
             float s = c1;
