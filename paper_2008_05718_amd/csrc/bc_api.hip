@@ -1986,16 +1986,59 @@ static int weighted_lanes(const bc_graph *g, const bc_run_options &o, int64_t ns
     return ns <= kOneSourceLists ? 1 : kWL;
 }
 
-static bc_status ensure_weighted(bc_graph *g, int lanes) {
-    if (g->w_wg > 0 && g->w_lanes == lanes) return BC_OK;
-    if (g->w_scratch) {  // the other engine's state
-        (void)hipFree(g->w_scratch);
-        g->acct.bytes -= std::min(g->acct.bytes, (size_t)g->w_wg * g->w_stride);
-        g->w_scratch = nullptr;
-        g->w_wg = 0;
-    }
-    const size_t n = (size_t)std::max<int32_t>(g->n, 1);
-    g->w_stride = lanes == 1 ? WeightedLayout(n).bytes : WBLayout(n).bytes;
+// Chunks of a pass over ns sources on nwg workgroups: whole batches of `lanes`
+// sources, up to two chunks per workgroup, and at most 8 GiB of partial scores.
+static int64_t weighted_chunks(int64_t ns, int64_t n, int lanes, int64_t nwg) {
+    const int64_t nc = std::min<int64_t>((ns + lanes - 1) / lanes, 2 * nwg);
+    return std::max<int64_t>(1, std::min<int64_t>(nc, ((int64_t)8 << 30) / (8 * n)));
+}
+
+// Device bytes of a weighted run's lists: as held, or, for a pass over ns sources
+// in nc chunks, as they will be (keep: a list held longer stays so).
+static size_t weighted_lists_held(const bc_graph *g) {
+    return (size_t)(g->srcs_cap + g->w_chunk_cap) * 4 +
+           (size_t)(g->w_pos_cap + g->ovf_cap + g->bcap[0] + g->w_partials_cap) * 8;
+}
+static size_t weighted_lists_need(const bc_graph *g, int64_t ns, int64_t nc, bool keep) {
+    const int64_t n = std::max<int32_t>(g->n, 1);
+    const auto cap = [&](int64_t held, int64_t need) {
+        return (size_t)std::max<int64_t>(std::max<int64_t>(need, 16), keep ? held : 0);
+    };
+    return (cap(g->srcs_cap, ns) + cap(g->w_chunk_cap, 3 * nc)) * 4 +
+           (cap(g->w_pos_cap, ns) + cap(g->ovf_cap, ns) + (keep ? (size_t)g->bcap[0] : 0) +
+            cap(g->w_partials_cap, nc * n)) * 8;
+}
+
+// Give back the per-workgroup state and every list of a weighted run (made
+// anew by the next one).
+static void free_weighted(bc_graph *g) {
+    const auto drop = [&](auto **p, size_t bytes) {
+        if (*p) (void)hipFree(*p);
+        *p = nullptr;
+        g->acct.bytes -= std::min(g->acct.bytes, bytes);
+    };
+    drop(&g->w_scratch, (size_t)g->w_wg * g->w_stride);
+    drop(&g->srcs, (size_t)g->srcs_cap * 4);
+    drop(&g->w_chunk, (size_t)g->w_chunk_cap * 4);
+    drop(&g->w_pos, (size_t)g->w_pos_cap * 8);
+    drop(&g->ovf, (size_t)g->ovf_cap * 8);
+    drop(&g->bstart, (size_t)g->bcap[0] * 8);
+    drop(&g->w_partials, (size_t)g->w_partials_cap * 8);
+    g->w_wg = 0;
+    g->srcs_cap = g->w_chunk_cap = g->w_pos_cap = g->ovf_cap = g->bcap[0] = g->w_partials_cap = 0;
+}
+
+// State of the per-workgroup engines for a run of ns sources: as many workgroups as
+// the CUs hold (each works through its sources alone, so resident workgroups
+// are what hides memory latency), within the memory budget.  Under a cap, as
+// many as fit beside the run's lists when nothing else of a weighted run is
+// held, whatever earlier runs have left (the wide engine's state, longer lists):
+// that is given back where it stands in the way.
+static bc_status ensure_weighted(bc_graph *g, int lanes, int64_t ns) {
+    const bool capped = g->acct.limit != 0;
+    if (!capped && g->w_wg > 0 && g->w_lanes == lanes) return BC_OK;
+    const int64_t n = std::max<int32_t>(g->n, 1);
+    const size_t stride = lanes == 1 ? WeightedLayout((size_t)n).bytes : WBLayout((size_t)n).bytes;
     int dev = 0, cus = 0, per_cu = 0;
     HIP_TRY(hipGetDevice(&dev));
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
@@ -2003,41 +2046,70 @@ static bc_status ensure_weighted(bc_graph *g, int lanes) {
         HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)weighted_run<0>, kBlock, 0));
     else
         HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)wbatch_run<0>, kWBatchBlock, 0));
-    // as many workgroups as the CUs hold (each works through its sources
-    // alone, so resident workgroups are what hides memory latency), within
-    // the memory budget
     int64_t want = (int64_t)std::max(1, cus) * std::max(1, std::min(per_cu, 8));
+    const size_t held = (size_t)g->w_wg * g->w_stride;
+    if (!g->w_ctr) HIP_TRY(dalloc(&g->w_ctr, 16, &g->acct));
     size_t free_b = 0, total_b = 0;
     HIP_TRY(hipMemGetInfo(&free_b, &total_b));
-    size_t budget = std::min<size_t>(free_b / 2, (size_t)64 << 30);
-    if (g->acct.limit) budget = std::min(budget, g->acct.limit > g->acct.bytes ? g->acct.limit - g->acct.bytes : 0);
-    want = std::min<int64_t>(want, (int64_t)(budget / g->w_stride));
+    free_b += held + g->wd_bytes;
+    want = std::min<int64_t>(want, (int64_t)(std::min<size_t>(free_b / 2, (size_t)64 << 30) / stride));
+    if (capped) {
+        const size_t rest = g->acct.bytes - held - weighted_lists_held(g) - g->wd_bytes;
+        const auto fits = [&](int64_t wg) {
+            return rest + (size_t)wg * stride + weighted_lists_need(g, ns, weighted_chunks(ns, n, lanes, wg), false) <=
+                   g->acct.limit;
+        };
+        while (want > 0 && !fits(want)) --want;
+    }
     if (want < 1) return fail(BC_ERR_OUT_OF_MEMORY, "the weighted engine's per-workgroup state does not fit");
-    HIP_TRY(dalloc(&g->w_scratch, (size_t)want * g->w_stride, &g->acct));
-    if (!g->w_ctr) HIP_TRY(dalloc(&g->w_ctr, 16, &g->acct));
+    const auto lists_fit = [&](size_t scratch) {
+        return !capped || g->acct.bytes - (size_t)g->w_wg * g->w_stride + scratch - weighted_lists_held(g) +
+                                  weighted_lists_need(g, ns, weighted_chunks(ns, n, lanes, want), true) <=
+                              g->acct.limit;
+    };
+    const size_t bytes = (size_t)want * stride;
+    if (!lists_fit(bytes)) {
+        free_wide(g);
+        if (!lists_fit(bytes)) free_weighted(g);
+    }
+    if (g->w_wg == want && g->w_lanes == lanes) return BC_OK;
+    if (g->w_scratch) {
+        (void)hipFree(g->w_scratch);
+        g->acct.bytes -= std::min(g->acct.bytes, (size_t)g->w_wg * g->w_stride);
+        g->w_scratch = nullptr;
+        g->w_wg = 0;
+    }
+    hipError_t e = dalloc(&g->w_scratch, bytes, &g->acct);
+    if (e != hipSuccess && g->wd_k) {  // the device is full: the wide engine's state gives way
+        (void)hipGetLastError();
+        free_wide(g);
+        e = dalloc(&g->w_scratch, bytes, &g->acct);
+    }
+    if (e != hipSuccess) {
+        (void)hipGetLastError();
+        return hip_fail(e, "the weighted engine's per-workgroup state");
+    }
+    g->w_stride = stride;
     g->w_wg = (int)want;
     g->w_lanes = lanes;
     return BC_OK;
 }
 
 // One pass over the run positions `pos` (sources h_srcs[pos[i]]) with the
-// given path-count mode; overflowed positions (mode 0) are returned.
+// given path-count mode; overflowed positions (mode 0) are returned.  The state
+// (ensure_weighted) is there.
 static bc_status weighted_pass(bc_graph *g, int lanes, int mode, const bc_run_options &o, const int32_t *h_srcs,
                                const std::vector<int64_t> &pos, int64_t dump_pos_run, DumpBufs *dump, hipStream_t st,
                                std::vector<int64_t> *ovf, bool *dumped) {
     ovf->clear();
     if (pos.empty()) return BC_OK;
-    bc_status s = ensure_weighted(g, lanes);
-    if (s != BC_OK) return s;
+    bc_status s = BC_OK;
     const int64_t ns = (int64_t)pos.size(), n = std::max<int32_t>(g->n, 1);
-    // chunks of consecutive positions, whole batches of `lanes` sources: up
-    // to two per workgroup, and at most 8 GiB of partial scores
     const int64_t nbatch = (ns + lanes - 1) / lanes;
-    int64_t nc = std::min<int64_t>(nbatch, 2 * (int64_t)g->w_wg);
-    nc = std::max<int64_t>(1, std::min<int64_t>(nc, ((int64_t)8 << 30) / (8 * n)));
+    const int64_t nc = weighted_chunks(ns, n, lanes, g->w_wg);
     const int nwg = (int)std::min<int64_t>(g->w_wg, nc);
     std::vector<int32_t> ch(3 * (size_t)nc), list((size_t)ns);
-    for (int64_t t = 0; t < nc; ++t) {
+    for (int64_t t = 0; t < nc; ++t) {  // chunks of consecutive positions
         ch[t] = (int32_t)std::min<int64_t>(ns, lanes * (nbatch * t / nc));
         ch[nc + t] = (int32_t)std::min<int64_t>(ns, lanes * (nbatch * (t + 1) / nc));
         ch[2 * nc + t] = (int32_t)t;
@@ -2201,14 +2273,17 @@ static bool wide_pays(const bc_graph *g, int64_t ns) {
     return wide_ms < (0.6 + 3.5e-5 * nnz) * lists;
 }
 
+// Whether the graph is within the engine's 32-bit positions.
+static bool wide_possible(const bc_graph *g) {
+    return (int64_t)std::max<int32_t>(g->n, 1) * kLanes <= (int64_t)INT32_MAX &&
+           g->cost_units < (int64_t)UINT32_MAX / kLanes;
+}
+
 // State for batches of k sources.  *fits = false (and BC_OK): it does not fit
-// under the handle's cap or in the device, or the graph is beyond the engine's
-// 32-bit positions; the caller uses the engine that gives a batch to a
-// workgroup.
+// under the handle's cap or in the device.
 static bc_status ensure_wide(bc_graph *g, int k, hipStream_t st, bool *fits) {
     *fits = false;
     const int64_t n = std::max<int32_t>(g->n, 1), nnz = std::max<int64_t>(g->nnz, 1);
-    if (n * kLanes > (int64_t)INT32_MAX || g->cost_units >= (int64_t)UINT32_MAX / kLanes) return BC_OK;
     if (g->wd_k >= k) {
         *fits = true;
         return BC_OK;
@@ -2312,7 +2387,28 @@ static bc_status ensure_wide(bc_graph *g, int k, hipStream_t st, bool *fits) {
     return BC_OK;
 }
 
-// One pass over the run positions `pos`, as weighted_pass.
+// State and lists for a run of ns sources.  What the per-workgroup engines
+// hold gives way; *fits = false (and BC_OK): not even then does it fit, and the caller
+// uses one of those.
+static bc_status wide_ready(bc_graph *g, int64_t ns, hipStream_t st, bool *fits) {
+    const int k = wide_lanes(ns);
+    for (int attempt = 0; attempt < 2; ++attempt) {
+        *fits = false;
+        bc_status s = grow(&g->srcs, &g->srcs_cap, ns, &g->acct);
+        if (s == BC_OK) s = grow(&g->ovf, &g->ovf_cap, ns, &g->acct);
+        if (s == BC_OK) s = grow(&g->bstart, &g->bcap[0], (ns + k - 1) / k + 1, &g->acct);
+        if (s == BC_OK) s = ensure_wide(g, k, st, fits);
+        if (s != BC_OK && s != BC_ERR_OUT_OF_MEMORY) return s;
+        if (*fits) return BC_OK;
+        (void)hipGetLastError();
+        free_wide(g);
+        free_weighted(g);
+    }
+    return BC_OK;
+}
+
+// One pass over the run positions `pos`, as weighted_pass (wide_ready has
+// been called for the run).
 static bc_status wide_pass(bc_graph *g, int mode, const bc_run_options &o, const int32_t *h_srcs,
                            const std::vector<int64_t> &pos, int64_t dump_pos_run, DumpBufs *dump, hipStream_t st,
                            std::vector<int64_t> *ovf, bool *dumped) {
@@ -2329,10 +2425,6 @@ static bc_status wide_pass(bc_graph *g, int mode, const bc_run_options &o, const
     const int64_t nb = (ns + k - 1) / k;
     std::vector<int64_t> bs((size_t)nb + 1);
     for (int64_t b = 0; b <= nb; ++b) bs[b] = std::min<int64_t>(ns, b * k);
-    bc_status s = grow(&g->srcs, &g->srcs_cap, ns, &g->acct);
-    if (s == BC_OK) s = grow(&g->ovf, &g->ovf_cap, ns, &g->acct);
-    if (s == BC_OK) s = grow(&g->bstart, &g->bcap[0], nb + 1, &g->acct);
-    if (s != BC_OK) return s;
     HIP_TRY(hipMemcpyAsync(g->srcs, list.data(), sizeof(int32_t) * ns, hipMemcpyHostToDevice, st));
     HIP_TRY(hipMemcpyAsync(g->bstart, bs.data(), sizeof(int64_t) * bs.size(), hipMemcpyHostToDevice, st));
     WideArgs a;
@@ -2384,7 +2476,7 @@ static bc_status wide_pass(bc_graph *g, int mode, const bc_run_options &o, const
     int64_t launches = 0;
     double dev_ms = 0.0;
     const int64_t max_steps = (nb + 1) * (3 * (n + 4) + 8) + 64;
-    s = drive(g, a, mode ? wide_step<1> : wide_step<0>, cfg, st, max_steps, &launches, &dev_ms);
+    bc_status s = drive(g, a, mode ? wide_step<1> : wide_step<0>, cfg, st, max_steps, &launches, &dev_ms);
     g->stats.launches += launches;
     if (s != BC_OK) return s;
     HIP_TRY(hipMemcpyAsync(hctl, g->ctl, sizeof(Ctl), hipMemcpyDeviceToHost, st));
@@ -2433,9 +2525,11 @@ static bc_status run_weighted(bc_graph *g, const int32_t *src, int64_t ns, const
     // unless the caller asks for one or 16 sources per workgroup
     bool wide = false;
     bc_status s = BC_OK;
-    if (o.weighted_lanes == 0 && ns > 0 && wide_pays(g, ns)) s = ensure_wide(g, wide_lanes(ns), st, &wide);
+    if (o.weighted_lanes == 0 && ns > 0 && wide_possible(g) && wide_pays(g, ns)) s = wide_ready(g, ns, st, &wide);
     if (s != BC_OK) return s;
     const int lanes = weighted_lanes(g, o, ns);
+    if (!wide && ns > 0) s = ensure_weighted(g, lanes, ns);
+    if (s != BC_OK) return s;
     const auto run_sources = [&](int mode, const std::vector<int64_t> &pos, std::vector<int64_t> *over, bool *done) {
         return wide ? wide_pass(g, mode, o, src, pos, dump_index, db, st, over, done)
                     : weighted_pass(g, lanes, mode, o, src, pos, dump_index, db, st, over, done);
