@@ -188,10 +188,11 @@ struct bc_graph {
     // same array for an undirected graph); the weighted engine's state
     bool weighted = false;
     int32_t *wt = nullptr, *in_wt = nullptr;
-    int w_lanes = 0;                  // sources per workgroup of the allocated state (1 or kWL)
-    int w_wg = 0;                     // workgroups whose state is allocated
-    size_t w_stride = 0;
-    char *w_scratch = nullptr;
+    int w_wg = 0;                     // workgroups of the current run
+    size_t w_stride = 0;              // and the bytes of each one's state
+    int w_wgs[2] = {0, 0};            // without a cap: workgroups with one source each, with kWL (0 = not decided)
+    char *w_scratch = nullptr;        // shared by both widths: a launch clears what it uses
+    size_t w_bytes = 0;
     unsigned long long *w_ctr = nullptr;  // [0] work queue, [1] overflow count, [2] error bits, [4..14] statistics
     int32_t *w_chunk = nullptr;       // s0, s1, order
     int64_t w_chunk_cap = 0;
@@ -2017,14 +2018,14 @@ static void free_weighted(bc_graph *g) {
         *p = nullptr;
         g->acct.bytes -= std::min(g->acct.bytes, bytes);
     };
-    drop(&g->w_scratch, (size_t)g->w_wg * g->w_stride);
+    drop(&g->w_scratch, g->w_bytes);
     drop(&g->srcs, (size_t)g->srcs_cap * 4);
     drop(&g->w_chunk, (size_t)g->w_chunk_cap * 4);
     drop(&g->w_pos, (size_t)g->w_pos_cap * 8);
     drop(&g->ovf, (size_t)g->ovf_cap * 8);
     drop(&g->bstart, (size_t)g->bcap[0] * 8);
     drop(&g->w_partials, (size_t)g->w_partials_cap * 8);
-    g->w_wg = 0;
+    g->w_bytes = 0;
     g->srcs_cap = g->w_chunk_cap = g->w_pos_cap = g->ovf_cap = g->bcap[0] = g->w_partials_cap = 0;
 }
 
@@ -2033,10 +2034,12 @@ static void free_weighted(bc_graph *g) {
 // are what hides memory latency), within the memory budget.  Under a cap, as
 // many as fit beside the run's lists when nothing else of a weighted run is
 // held, whatever earlier runs have left (the wide engine's state, longer lists):
-// that is given back where it stands in the way.
+// that is given back where it stands in the way.  Runs with one source and with
+// kWL per workgroup use the same memory, grown to the larger need and then kept:
+// lists on either side of kOneSourceLists would otherwise free and allocate
+// up to 64 GiB at every change.
 static bc_status ensure_weighted(bc_graph *g, int lanes, int64_t ns) {
     const bool capped = g->acct.limit != 0;
-    if (!capped && g->w_wg > 0 && g->w_lanes == lanes) return BC_OK;
     const int64_t n = std::max<int32_t>(g->n, 1);
     const size_t stride = lanes == 1 ? WeightedLayout((size_t)n).bytes : WBLayout((size_t)n).bytes;
     int dev = 0, cus = 0, per_cu = 0;
@@ -2047,12 +2050,14 @@ static bc_status ensure_weighted(bc_graph *g, int lanes, int64_t ns) {
     else
         HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)wbatch_run<0>, kWBatchBlock, 0));
     int64_t want = (int64_t)std::max(1, cus) * std::max(1, std::min(per_cu, 8));
-    const size_t held = (size_t)g->w_wg * g->w_stride;
+    const size_t held = g->w_bytes;
     if (!g->w_ctr) HIP_TRY(dalloc(&g->w_ctr, 16, &g->acct));
     size_t free_b = 0, total_b = 0;
     HIP_TRY(hipMemGetInfo(&free_b, &total_b));
     free_b += held + g->wd_bytes;
     want = std::min<int64_t>(want, (int64_t)(std::min<size_t>(free_b / 2, (size_t)64 << 30) / stride));
+    int &decided = g->w_wgs[lanes == 1 ? 0 : 1];
+    if (!capped && decided > 0) want = decided;
     if (capped) {
         const size_t rest = g->acct.bytes - held - weighted_lists_held(g) - g->wd_bytes;
         const auto fits = [&](int64_t wg) {
@@ -2062,23 +2067,28 @@ static bc_status ensure_weighted(bc_graph *g, int lanes, int64_t ns) {
         while (want > 0 && !fits(want)) --want;
     }
     if (want < 1) return fail(BC_ERR_OUT_OF_MEMORY, "the weighted engine's per-workgroup state does not fit");
+    const size_t bytes = (size_t)want * stride;
     const auto lists_fit = [&](size_t scratch) {
-        return !capped || g->acct.bytes - (size_t)g->w_wg * g->w_stride + scratch - weighted_lists_held(g) +
+        return !capped || g->acct.bytes - g->w_bytes + scratch - weighted_lists_held(g) +
                                   weighted_lists_need(g, ns, weighted_chunks(ns, n, lanes, want), true) <=
                               g->acct.limit;
     };
-    const size_t bytes = (size_t)want * stride;
-    if (!lists_fit(bytes)) {
+    const auto drop_scratch = [&]() {
+        if (g->w_scratch) (void)hipFree(g->w_scratch);
+        g->w_scratch = nullptr;
+        g->acct.bytes -= std::min(g->acct.bytes, g->w_bytes);
+        g->w_bytes = 0;
+    };
+    if (!lists_fit(std::max(bytes, g->w_bytes))) {
         free_wide(g);
+        if (!lists_fit(std::max(bytes, g->w_bytes))) drop_scratch();
         if (!lists_fit(bytes)) free_weighted(g);
     }
-    if (g->w_wg == want && g->w_lanes == lanes) return BC_OK;
-    if (g->w_scratch) {
-        (void)hipFree(g->w_scratch);
-        g->acct.bytes -= std::min(g->acct.bytes, (size_t)g->w_wg * g->w_stride);
-        g->w_scratch = nullptr;
-        g->w_wg = 0;
-    }
+    g->w_wg = (int)want;
+    g->w_stride = stride;
+    if (!capped) decided = (int)want;
+    if (g->w_bytes >= bytes) return BC_OK;
+    drop_scratch();
     hipError_t e = dalloc(&g->w_scratch, bytes, &g->acct);
     if (e != hipSuccess && g->wd_k) {  // the device is full: the wide engine's state gives way
         (void)hipGetLastError();
@@ -2087,11 +2097,10 @@ static bc_status ensure_weighted(bc_graph *g, int lanes, int64_t ns) {
     }
     if (e != hipSuccess) {
         (void)hipGetLastError();
+        decided = 0;
         return hip_fail(e, "the weighted engine's per-workgroup state");
     }
-    g->w_stride = stride;
-    g->w_wg = (int)want;
-    g->w_lanes = lanes;
+    g->w_bytes = bytes;
     return BC_OK;
 }
 

@@ -106,3 +106,23 @@ def test_longer_list_beside_the_wide_state():
         assert _runs(G, srcs) == "workgroups"
         assert_bc_close(G.scores(), ref)
         assert _runs(G, srcs[:64]) == "wide"
+
+
+def test_alternating_widths_keep_their_memory():
+    # one source and 16 per workgroup in turn, asked for and chosen by the
+    # length of the list (1 up to 2,560 sources on this path, 16 beyond)
+    base = W.csr_from_edges(600, np.arange(599), np.arange(1, 600))
+    g = W.with_weights(base, 1, 9, seed=5)
+    rng = np.random.default_rng(3)
+    short, long = (rng.integers(0, g.n, k).astype(np.int32) for k in (40, 2700))
+    refs = [oracle.bc(g, s)[0] for s in (short, long)]
+    with b.Graph(g) as G:
+        held = []
+        for r in range(3):
+            for s, ref in zip((short, long), refs):
+                for lanes in (0, 1, 16):
+                    G.run(s, weighted_lanes=lanes)
+                    assert_bc_close(G.scores(), ref)
+                    held.append(G.info()["device_bytes"])
+    say(f"[weighted memory] device bytes run by run {held}")
+    assert len(set(held[6:])) == 1
