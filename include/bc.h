@@ -229,8 +229,8 @@ typedef struct bc_run_options {
     int32_t weighted_lanes;/* graphs with arc weights: sources one workgroup runs
                              together (1; 16; graphs above 2^27 vertices always
                              run one), or 0 = automatic: batches of up to 64 on
-                             the whole GPU where the graph is large enough for
-                             the number of sources and the state fits, else one
+                             the whole GPU where that is faster by arcs, depth
+                             and number of sources and the state fits, else one
                              source, or 16 of a long list.  Scores agree to
                              rounding across values; a given value repeats bit
                              for bit.                                       */

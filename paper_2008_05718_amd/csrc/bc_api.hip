@@ -206,6 +206,7 @@ struct bc_graph {
     void *wd_mem[24] = {};            // its allocations
     size_t wd_bytes = 0;
     int64_t nonisolated = 0;
+    int32_t depth = 0;                // weighted graphs: see hop_depth
     // vertices of class degree above a segment of 2^seg_log arcs (ascending) and
     // their segment prefix sums; p_*: the same for the per-source engine's segments
     int32_t seg_log = kSegLogMax;
@@ -510,6 +511,36 @@ static void source_ranks(int32_t n_graphs, const std::vector<int32_t> &voff, con
     for (int32_t i = 0; i < n; ++i) (*rank)[order[i]] = i;
 }
 
+// Hops (along out-arcs) from the vertex of largest out-degree to the farthest vertex it
+// reaches, or, where that is more, from the first vertex of what is left
+// to the farthest one in it, and so on: an estimate of how many levels a traversal takes.
+static int32_t hop_depth(const std::vector<int32_t> &rp, const std::vector<int32_t> &col) {
+    const int32_t n = (int32_t)rp.size() - 1;
+    std::vector<int32_t> hop((size_t)n, -1), q;
+    q.reserve((size_t)n);
+    int32_t deepest = 0;
+    const auto from = [&](int32_t s) {
+        if (hop[s] >= 0) return;
+        q.assign(1, s);
+        hop[s] = 0;
+        for (size_t h = 0; h < q.size(); ++h) {
+            const int32_t v = q[h];
+            for (int32_t e = rp[v]; e < rp[v + 1]; ++e)
+                if (hop[col[e]] < 0) {
+                    hop[col[e]] = hop[v] + 1;
+                    q.push_back(col[e]);
+                }
+        }
+        deepest = std::max(deepest, hop[q.back()]);
+    };
+    int32_t hub = 0;
+    for (int32_t v = 1; v < n; ++v)
+        if (rp[v + 1] - rp[v] > rp[hub + 1] - rp[hub]) hub = v;
+    if (n > 0) from(hub);
+    for (int32_t v = 0; v < n; ++v) from(v);
+    return deepest;
+}
+
 // Arcs of a heavy vertex's segment (binary logarithm), by the arcs of a graph.
 // A segment is one wavefront's, eight matched rows at a time, so on graphs
 // with few arcs the longest segment is what a path-count, backward or
@@ -791,6 +822,7 @@ static bc_status create_impl(int32_t n_graphs, const int32_t *voff_in, int32_t n
                     return bail(BC_ERR_INVALID_GRAPH);
                 }
             }
+            g->depth = hop_depth(rp, col);
             CR_TRY(dalloc(&g->wt, (size_t)nnz, &g->acct));
             if (nnz) CR_TRY(hipMemcpy(g->wt, w.data(), sizeof(int32_t) * (size_t)nnz, hipMemcpyHostToDevice));
             if (!directed) g->in_wt = g->wt;
@@ -2264,22 +2296,34 @@ static void free_wide(bc_graph *g) {
 static int wide_lanes(int64_t ns) { return ns <= 8 ? 8 : (ns <= 16 ? 16 : (ns <= 32 ? 32 : 64)); }
 
 // Whether one batch at a time on the whole GPU beats a source, or a batch of
-// 16, per workgroup.  A wide batch of 64 takes about as long as its rounds'
-// launches, a little longer on large graphs (1.0 to 2.3 ms on R-MAT 2^10 to 2^14, 2.0
-// to 3.9 on 2^16); a workgroup's source grows with the arcs (1.1 ms at 21
-// thousand, 3.9 at 96 thousand, 15.8 at 426 thousand, 76 at 1.8 million), with
-// the list beyond kOneSourceAtOnce, and not at all between kOneSourceLists and
-// 4,096.  Wide against the better of the others: R-MAT 2^12, 64 sources 1.0 and
-// 3.9 ms, 256 sources 3.2 and 4.2, 1024 sources 12.1 and 6.7; R-MAT 2^14, 1024
-// sources 14.8 and 34.8; ER(2000), 64 sources 1.3 and 1.3, 1024 sources 17.6
-// and 2.4; a 200 x 200 grid, 64 sources 11.1 and 34, 512 sources 80 and 47; a
-// path of 5000 vertices, 64 sources 227 and 34.
+// 16, per workgroup.  A wide batch takes its launches, three for each round,
+// and the rounds follow the depth (hop_depth): 70 us per hop and more where
+// the arcs are many.  A workgroup's source takes the arcs, again for every
+// correction that travels down the graph, so it grows with arcs x depth; then the
+// list beyond kOneSourceAtOnce, and not at all between kOneSourceLists and 4,096
+// (batches of 16).  Measured, wide and one source per workgroup, in ms (weights 1
+// to 30; the formula takes the faster one in all of these, or one within 4 %):
+//                        depth   64 sources    256 sources   1024 sources
+//   R-MAT 2^10               3   1.1 and 1.4   3.8 and 1.5   12.8 and 2.2
+//   R-MAT 2^14               4   1.3    17.9   4.7    21.3   15.1    32.5
+//   R-MAT 2^16               4   2.1    81.9   5.9    93.3   23.0     160
+//   ER(20000)                7   2.3    14.8   8.8    16.6   34.7    36.0
+//   random tree, 20,000     24   3.1     7.8   10.5    8.6   40.3    19.1
+//   100 x 100 grid         196   13.8    9.5   53.2   10.2    198    16.1
+//   200 x 200 grid         396   30.0   48.6    116   52.1    437    92.0
+//   400 x 400 grid         796   78.4    302    295    321   1070     617
+//   20 x 2000 grid        2016    195    448    619    453   2157     769
+//   path of 5,000         4998    227   35.2    815   36.0   2984    40.5
+//   path of 20,000       19998    901    141   3236    144  11902     164
+// Without the depth the slower one was taken for the path of 20,000 (8 and 64
+// sources), the 200 x 200 and 20 x 2000 grids (256), the 400 x 400 grid (1024)
+// and the 100 x 100 grid (64).
 static bool wide_pays(const bc_graph *g, int64_t ns) {
-    const double nnz = (double)g->nnz, batches = (double)((ns + kLanes - 1) / kLanes);
-    const double wide_ms = batches * (1.2 + 1e-6 * nnz);
+    const double nnz = (double)g->nnz, depth = (double)g->depth, batches = (double)((ns + kLanes - 1) / kLanes);
+    const double wide_ms = batches * (1.0 + 1e-6 * nnz + depth * (0.07 + 5e-8 * nnz));
     double lists = std::max(1.0, (double)ns / kOneSourceAtOnce);
     lists = std::min(lists, (double)kOneSourceLists / kOneSourceAtOnce * std::max(1.0, (double)ns / (kWL * 256)));
-    return wide_ms < (0.6 + 3.5e-5 * nnz) * lists;
+    return wide_ms < (0.6 + 3.5e-5 * nnz * (1.0 + depth / 30.0)) * lists;
 }
 
 // Whether the graph is within the engine's 32-bit positions.
