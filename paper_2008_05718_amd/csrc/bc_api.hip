@@ -1734,7 +1734,29 @@ static bc_status ensure_block(bc_graph *g, int need) {
 // grows with the largest graph, passes 30 GB.
 constexpr int kBlockDefaultN = 16384, kBlockDefaultUnionN = 65536;
 constexpr int64_t kBlockArcsPerBatch = 4096;
-static bool use_block(bc_graph *g, const bc_run_options &o, int64_t ns, bool detail) {
+
+// Whether a list (nullptr: every vertex) fills `want` batches of K sources.  In a
+// union a batch holds sources of one graph, so a graph's last sources count as a
+// batch however few they are (96 graphs of 1,000 to 16,000 vertices with 8
+// sources each: 5.0 ms on the block engine, 13.8 on the general one; 300 of 500
+// to 4,000 with one each: 0.9 and 28).
+static bool fills_batches(const bc_graph *g, const int32_t *src, int64_t ns, int K, int64_t want) {
+    if (g->n_graphs == 1) return ns >= want * K;
+    int64_t nb = 0;
+    if (!src) {
+        for (int gi = 0; gi < g->n_graphs; ++gi) nb += (g->voff[gi + 1] - g->voff[gi] + K - 1) / K;
+        return nb >= want;
+    }
+    for (int64_t i = 0; i < ns && nb < want; ++nb) {
+        const int gi = (int)(std::upper_bound(g->voff.begin(), g->voff.end(), src[i]) - g->voff.begin()) - 1;
+        if (gi < 0 || gi >= g->n_graphs) return false;  // (not a vertex: the run refuses the list)
+        const int32_t lo = g->voff[gi], hi = g->voff[gi + 1];
+        for (int k = 0; k < K && i < ns && src[i] >= lo && src[i] < hi; ++k) ++i;
+    }
+    return nb >= want;
+}
+
+static bool use_block(bc_graph *g, const bc_run_options &o, const int32_t *src, int64_t ns, bool detail) {
     if (g->weighted || detail || o.batch == 1 || (o.flags & (BC_RUN_NO_BLOCKS | BC_RUN_ONE_QUEUE | BC_RUN_FORCE_F64)))
         return false;
     if (o.batch == 0 && ns < 2) return false;
@@ -1742,7 +1764,7 @@ static bool use_block(bc_graph *g, const bc_run_options &o, int64_t ns, bool det
     if (o.flags & BC_RUN_BLOCKS) return true;
     const int K = o.batch >= 8 ? o.batch : 64;
     return g->blk_nmax <= (g->n_graphs > 1 ? kBlockDefaultUnionN : kBlockDefaultN) &&
-           ns >= (4 + g->blk_arcs_max / kBlockArcsPerBatch) * K;
+           fills_batches(g, src, ns, K, 4 + g->blk_arcs_max / kBlockArcsPerBatch);
 }
 
 // Lanes of a block-engine batch when the caller leaves them open: the fewest
@@ -3032,7 +3054,7 @@ static bc_status run_impl(bc_graph *g, const int32_t *sources, int64_t n_sources
     }
     if (o.weighted_lanes != 0 && o.weighted_lanes != 1 && o.weighted_lanes != kWL)
         return fail(BC_ERR_INVALID_ARG, "weighted_lanes must be 0, 1 or 16");
-    const bool blk = use_block(g, o, sources ? n_sources : g->n, detail != nullptr);
+    const bool blk = use_block(g, o, sources, sources ? n_sources : g->n, detail != nullptr);
     if (!blk && !g->weighted && use_parts(g, o, sources ? n_sources : g->n)) {
         g->last_parts = true;
         const bc_status ps = run_parts(g, sources, n_sources, o, stream, dump_index, detail);

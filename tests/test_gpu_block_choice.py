@@ -1,0 +1,45 @@
+"""When a run of the batched engine goes to the block engine by default, and
+what it then depends on.  Scores against the oracle within 1e-10 relative
+(non-negative terms)."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+from gpu_util import assert_bc_close, say
+from paper_2008_05718_amd import binding as b
+from paper_2008_05718_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _union(count, n=700):
+    # about 8 n arcs a graph: one batch more than four for every 4,096
+    return W.union([W.barabasi_albert(n + 7 * i, 4, seed=900 + i) for i in range(count)])
+
+
+def _bits(G):
+    return G.scores().view(np.uint64).copy()
+
+
+@pytest.mark.parametrize("count,each,block", [(12, 1, True), (12, 70, True), (4, 60, False), (4, 65, True), (3, 60, False)])
+def test_a_graph_s_last_sources_are_a_batch(count, each, block):
+    # (5 batches are asked for: 12 graphs with one source have 12, 4 graphs with
+    # 60 have 4, with 65 they have 8)
+    u = _union(count)
+    assert 4096 <= max(np.diff(u.row_ptr[u.vtx_offsets])) < 8192
+    srcs = np.concatenate([np.arange(o, o + each) for o in u.vtx_offsets[:-1]]).astype(np.int32)
+    ref, _ = oracle.bc(u, srcs)
+    with b.Graph(u) as G:
+        G.run(srcs)
+        st = G.stats()
+        say(f"[block choice] {count} graphs, {each} each: workgroups {st['block_workgroups']}")
+        assert (st["block_workgroups"] > 0) == block
+        assert_bc_close(G.scores(), ref)
+        G.run(None, batch=64)  # every vertex: 12 batches a graph
+        assert G.stats()["block_workgroups"] > 0
+        with pytest.raises(b.BCError):
+            G.run(np.array([0, u.n], np.int32))
+        with pytest.raises(b.BCError):
+            G.run(np.array([-1, 0], np.int32))
