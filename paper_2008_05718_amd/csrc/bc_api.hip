@@ -1693,21 +1693,36 @@ static bc_status block_dims(bc_graph *g, int *resident) {
     return BC_OK;
 }
 
+// Give back what the block engine holds.
+static void free_block(bc_graph *g) {
+    const auto drop = [&](auto **p, size_t bytes) {
+        if (*p) (void)hipFree(*p);
+        *p = nullptr;
+        g->acct.bytes -= std::min(g->acct.bytes, bytes);
+    };
+    drop(&g->blk_scratch, (size_t)g->blk_wg * g->blk_stride);
+    drop(&g->blk_states, (size_t)g->blk_wg * sizeof(SoloState));
+    drop(&g->blk_chunk, (size_t)g->blk_chunk_cap * sizeof(int32_t));
+    drop(&g->blk_part_off, (size_t)g->blk_part_off_cap * sizeof(int64_t));
+    drop(&g->blk_partials, (size_t)g->blk_partials_cap * sizeof(double));
+    drop(&g->blk_gsum, (size_t)g->blk_gsum_cap * sizeof(int32_t));
+    g->blk_wg = 0;
+    g->blk_chunk_cap = g->blk_part_off_cap = g->blk_partials_cap = g->blk_gsum_cap = 0;
+}
+
 // State for `need` workgroups (kept and grown across runs).
 static bc_status ensure_block(bc_graph *g, int need) {
     if (g->blk_wg >= need) return BC_OK;
-    if (g->blk_scratch) {
-        HIP_TRY(hipStreamSynchronize(nullptr));
-        (void)hipFree(g->blk_scratch);
-        (void)hipFree(g->blk_states);
-        g->acct.bytes -= (size_t)g->blk_wg * (g->blk_stride + sizeof(SoloState));
-        g->blk_scratch = nullptr;
-        g->blk_states = nullptr;
-        g->blk_wg = 0;
-    }
-    HIP_TRY(dalloc(&g->blk_scratch, (size_t)need * g->blk_stride, &g->acct));
-    HIP_TRY(dalloc(&g->blk_states, (size_t)need, &g->acct));
+    if (g->blk_scratch) free_block(g);
     if (!g->blk_next) HIP_TRY(dalloc(&g->blk_next, 1, &g->acct));
+    HIP_TRY(dalloc(&g->blk_scratch, (size_t)need * g->blk_stride, &g->acct));
+    const hipError_t e = dalloc(&g->blk_states, (size_t)need, &g->acct);
+    if (e != hipSuccess) {
+        (void)hipFree(g->blk_scratch);
+        g->blk_scratch = nullptr;
+        g->acct.bytes -= (size_t)need * g->blk_stride;
+        return hip_fail(e, "the block engine's states");
+    }
     g->blk_wg = need;
     return BC_OK;
 }
@@ -3063,6 +3078,7 @@ static bc_status run_impl(bc_graph *g, const int32_t *sources, int64_t n_sources
     }
     g->last_parts = false;
     std::vector<int32_t> all;
+    const int32_t *const given = sources;
     const int32_t *src = sources;
     int64_t ns = n_sources;
     if (!sources) {
@@ -3195,7 +3211,22 @@ static bc_status run_impl(bc_graph *g, const int32_t *sources, int64_t n_sources
         bool fb = false;
         s = run_block(g, cfg, o, src, ns, st, &ovf, &fb);
         if (s != BC_OK) { free_dump(); return s; }
-        if (!fb) {
+        if (fb) {
+            // its state does not fit, or a batch exceeded a workgroup's capacities:
+            // on as if the block engine had not been considered
+            (void)hipGetLastError();  // (an allocation that failed)
+            free_block(g);
+            if (use_parts(g, o, ns)) {
+                g->last_parts = true;
+                const bc_status ps = run_parts(g, given, ns, o, stream, -1, nullptr);
+                if (!(ps == BC_ERR_OUT_OF_MEMORY && g->parts_refused)) {
+                    g->stats.ms =
+                        std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
+                    return ps;
+                }
+                g->last_parts = false;
+            }
+        } else {
             std::vector<int64_t> none;
             s = pass(1, false, ovf, &none);
             if (s != BC_OK) { free_dump(); return s; }

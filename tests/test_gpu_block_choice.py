@@ -43,3 +43,28 @@ def test_a_graph_s_last_sources_are_a_batch(count, each, block):
             G.run(np.array([0, u.n], np.int32))
         with pytest.raises(b.BCError):
             G.run(np.array([-1, 0], np.int32))
+
+
+@pytest.mark.parametrize("graphs", [1, 5])
+def test_a_run_that_exceeds_the_capacities_goes_on_as_usual(graphs):
+    # a path of 6,000 vertices has more levels than a workgroup holds: the run
+    # ends on the concurrent state machines that it would have had without the
+    # block engine (same bits), and the block engine's memory is given back
+    one = W.csr_from_edges(6000, np.arange(5999), np.arange(1, 6000))
+    u = one if graphs == 1 else W.union([one] * graphs)
+    srcs = np.concatenate([np.linspace(o, o + 5999, 640 // graphs) for o in range(0, u.n, 6000)]).astype(np.int32)
+    ref, _ = oracle.bc(u, srcs)
+    with b.Graph(u) as G:
+        G.run(srcs, batch=64, flags=b.BC_RUN_NO_BLOCKS)
+        want, st0, held = _bits(G), G.stats(), G.info()["device_bytes"]
+        G.run(srcs, batch=64, flags=b.BC_RUN_BLOCKS)
+        st = G.stats()
+        say(f"[block choice] {graphs} paths: {st0['ms']:.0f} ms without, {st['ms']:.0f} ms after the block engine's pass")
+        assert st["block_workgroups"] == 0 and st["grid_blocks"] == st0["grid_blocks"]
+        assert st["n_batches"] == st0["n_batches"] and st["steps"] == st0["steps"]
+        assert np.array_equal(_bits(G), want)
+        assert_bc_close(G.scores(), ref)
+        assert G.info()["device_bytes"] <= held + (1 << 20)
+        G.run(srcs[:320], batch=64, flags=b.BC_RUN_BLOCKS)
+        G.run(srcs[320:], batch=64, flags=b.BC_RUN_BLOCKS | b.BC_RUN_ACCUMULATE)
+        assert_bc_close(G.scores(), ref)
