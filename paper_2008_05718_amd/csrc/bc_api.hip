@@ -957,11 +957,38 @@ static bc_status alloc_hq(bc_graph *g, HeavyQ *q, int64_t entries, int64_t level
     return BC_OK;
 }
 
+// Give back what the block engine holds.
+static void free_block(bc_graph *g) {
+    const auto drop = [&](auto **p, size_t bytes) {
+        if (*p) (void)hipFree(*p);
+        *p = nullptr;
+        g->acct.bytes -= std::min(g->acct.bytes, bytes);
+    };
+    drop(&g->blk_scratch, (size_t)g->blk_wg * g->blk_stride);
+    drop(&g->blk_states, (size_t)g->blk_wg * sizeof(SoloState));
+    drop(&g->blk_chunk, (size_t)g->blk_chunk_cap * sizeof(int32_t));
+    drop(&g->blk_part_off, (size_t)g->blk_part_off_cap * sizeof(int64_t));
+    drop(&g->blk_partials, (size_t)g->blk_partials_cap * sizeof(double));
+    drop(&g->blk_gsum, (size_t)g->blk_gsum_cap * sizeof(int32_t));
+    g->blk_wg = 0;
+    g->blk_chunk_cap = g->blk_part_off_cap = g->blk_partials_cap = g->blk_gsum_cap = 0;
+}
+
+// Before another engine allocates `need` bytes: what the block engine holds
+// gives way where they would not fit beside it under the cap or in the device.
+static void make_room(bc_graph *g, size_t need) {
+    if (!g->blk_scratch) return;
+    size_t free_b = 0, total_b = 0;
+    if (over_cap(&g->acct, need) || (hipMemGetInfo(&free_b, &total_b) == hipSuccess && free_b < need + (need >> 4)))
+        free_block(g);
+}
+
 static bc_status ensure_plain(bc_graph *g, hipStream_t st) {
     const int64_t n = g->n;
     if (!g->plain_ready) {
         const size_t need = (size_t)(g->p_n_heavy + 1) * 12 + (size_t)(n + 3) * 8 + (size_t)(g->p_heavy_segs + 1) * 16 +
                             (size_t)std::max<int64_t>(n, 1) * 24 + (size_t)(n + 2) * 8;
+        make_room(g, need);
         if (over_cap(&g->acct, need))
             return fail(BC_ERR_OUT_OF_MEMORY, "per-source engine state (" + std::to_string(need) +
                                                   " bytes) is over the handle's max_device_bytes");
@@ -1020,6 +1047,7 @@ static bc_status ensure_batched(bc_graph *g) {
     if (g->cost_units >= (int64_t)UINT32_MAX)
         return fail(BC_ERR_NOT_SUPPORTED, "graph too large for the batched engine: use batch = 1");
     const BatchedSizes z = batched_sizes(n, g->cost_units, g->n_heavy, g->heavy_segs);
+    make_room(g, z.bytes);
     if (over_cap(&g->acct, z.bytes))
         return fail(BC_ERR_OUT_OF_MEMORY, "batched engine state (" + std::to_string(z.bytes) +
                                               " bytes) is over the handle's max_device_bytes");
@@ -1685,29 +1713,13 @@ static bc_status block_dims(bc_graph *g, int *resident) {
     size_t budget = std::min<size_t>(free_b / 4 * 3, (size_t)192 << 30);
     if (g->acct.limit) {
         const size_t held = (size_t)g->blk_wg * (g->blk_stride + sizeof(SoloState));
-        const size_t room = g->acct.limit > g->acct.bytes - held ? g->acct.limit - (g->acct.bytes - held) : 0;
+        const size_t rest = total_bytes(g) - held;  // with the concurrent parts
+        const size_t room = g->acct.limit > rest ? g->acct.limit - rest : 0;
         budget = std::min(budget, room);
     }
     want = std::min<int64_t>(want, (int64_t)(budget / (g->blk_stride + sizeof(SoloState))));
     *resident = (int)std::max<int64_t>(want, 0);
     return BC_OK;
-}
-
-// Give back what the block engine holds.
-static void free_block(bc_graph *g) {
-    const auto drop = [&](auto **p, size_t bytes) {
-        if (*p) (void)hipFree(*p);
-        *p = nullptr;
-        g->acct.bytes -= std::min(g->acct.bytes, bytes);
-    };
-    drop(&g->blk_scratch, (size_t)g->blk_wg * g->blk_stride);
-    drop(&g->blk_states, (size_t)g->blk_wg * sizeof(SoloState));
-    drop(&g->blk_chunk, (size_t)g->blk_chunk_cap * sizeof(int32_t));
-    drop(&g->blk_part_off, (size_t)g->blk_part_off_cap * sizeof(int64_t));
-    drop(&g->blk_partials, (size_t)g->blk_partials_cap * sizeof(double));
-    drop(&g->blk_gsum, (size_t)g->blk_gsum_cap * sizeof(int32_t));
-    g->blk_wg = 0;
-    g->blk_chunk_cap = g->blk_part_off_cap = g->blk_partials_cap = g->blk_gsum_cap = 0;
 }
 
 // State for `need` workgroups (kept and grown across runs).
@@ -1811,6 +1823,12 @@ static bc_status run_block(bc_graph *g, const RunCfg &cfg, const bc_run_options 
     int resident = 0;
     bc_status s = block_dims(g, &resident);
     if (s != BC_OK) return s;
+    if (g->acct.limit && !g->parts.empty() && resident < 1) {
+        free_parts(g);  // concurrent parts of earlier runs give way under a cap
+        g->replicas = false;
+        s = block_dims(g, &resident);
+        if (s != BC_OK) return s;
+    }
     if (resident < 1) {
         *fallback = true;
         return BC_OK;
@@ -2719,6 +2737,7 @@ static bool use_parts(const bc_graph *g, const bc_run_options &o, int64_t ns) {
 // state they would allocate fits beside what the handle holds; otherwise the
 // handle runs on its own level state machine (same results to rounding).
 static bool parts_fit(bc_graph *g, size_t need) {
+    make_room(g, need);
     if (!g->acct.limit) return true;
     const size_t have = g->acct.bytes;
     if (have + need <= g->acct.limit) return true;
@@ -2792,7 +2811,7 @@ static bc_status ensure_parts(bc_graph *g) {
         const int k = r % (2 * P);
         g->part_of_graph[order[r]] = k < P ? k : 2 * P - 1 - k;
     }
-    if (g->acct.limit) {
+    if (g->acct.limit || g->blk_scratch) {
         // what the parts would hold: their graphs and batched engine state
         std::vector<int64_t> pn(P, 0), pnnz(P, 0), pcost(P, 0), pheavy(P, 0), psegs(P, 0);
         std::vector<int> plog(P);

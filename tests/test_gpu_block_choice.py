@@ -68,3 +68,67 @@ def test_a_run_that_exceeds_the_capacities_goes_on_as_usual(graphs):
         G.run(srcs[:320], batch=64, flags=b.BC_RUN_BLOCKS)
         G.run(srcs[320:], batch=64, flags=b.BC_RUN_BLOCKS | b.BC_RUN_ACCUMULATE)
         assert_bc_close(G.scores(), ref)
+
+
+def _smallest(u, srcs, lo, hi, ok, **opts):
+    """Smallest cap (bytes above the handle's own, to 64 KiB) with which a new handle's run is `ok`."""
+    def test(x):
+        with b.Graph(u) as G:
+            G.set_device_limit(G.info()["device_bytes"] + x)
+            try:
+                G.run(srcs, **opts)
+            except b.BCError as e:
+                assert e.status == 3
+                return False
+            return ok(G.stats())
+    assert test(hi) and not test(lo)
+    while hi - lo > 65536:
+        mid = (lo + hi) // 2
+        lo, hi = (lo, mid) if test(mid) else (mid, hi)
+    return hi
+
+
+def test_engines_give_way_to_each_other_under_a_cap():
+    # a cap under which each engine runs alone: they run in any order, and the
+    # handle never holds more than the cap (parts of a union included)
+    u = _union(12, 3000)
+    srcs = np.concatenate([np.arange(o, o + 40) for o in u.vtx_offsets[:-1]]).astype(np.int32)
+    ref, _ = oracle.bc(u, srcs)
+    runs = {"block": dict(batch=64, flags=b.BC_RUN_BLOCKS), "general": dict(batch=64, flags=b.BC_RUN_NO_BLOCKS),
+            "per source": dict(batch=1)}
+    cap = _smallest(u, srcs, 0, 4 << 30, lambda st: st["block_workgroups"] > 0, **runs["block"])
+    cap = max(cap, _smallest(u, srcs, 0, 4 << 30, lambda st: True, **runs["general"]))
+    cap += 2 << 20  # the per-source state beside the general engine's
+    say(f"[block choice] cap {cap >> 20} MiB above the handle")
+    for top in (cap, cap + (256 << 20), cap + (1 << 30)):
+        with b.Graph(u) as G:
+            floor = G.info()["device_bytes"]
+            G.set_device_limit(floor + top)
+            for what in ("block", "general", "block", "per source", "general", "block"):
+                G.run(srcs, **runs[what])
+                st = G.stats()
+                say(f"  {what}: workgroups {st['block_workgroups']}, {(G.info()['device_bytes'] - floor) >> 20} MiB")
+                assert G.info()["device_bytes"] <= floor + top
+                if what != "block":
+                    assert st["block_workgroups"] == 0
+                assert_bc_close(G.scores(), ref)
+
+
+def test_overflowed_sources_find_room_under_a_cap():
+    # the FP64 pass after the block engine's 64-bit pass takes the general engine
+    u = W.union([W.barabasi_albert(900, 4, seed=31), W.grid(60, 0.05, 0.0, seed=21), W.barabasi_albert(1500, 4, seed=32)])
+    srcs = np.arange(0, u.n, 7, dtype=np.int32)
+    ref, modes = oracle.bc(u, srcs)
+    assert modes.any()
+    opts = dict(batch=64, flags=b.BC_RUN_BLOCKS)
+    general = _smallest(u, srcs, 0, 2 << 30, lambda st: True, batch=64, flags=b.BC_RUN_NO_BLOCKS)
+    for extra in (0, 2 << 20, 16 << 20, 64 << 20):
+        with b.Graph(u) as G:
+            floor = G.info()["device_bytes"]
+            G.set_device_limit(floor + general + extra)
+            G.run(srcs, **opts)
+            st = G.stats()
+            say(f"[block choice] {extra >> 20} MiB more: workgroups {st['block_workgroups']}, f64 {st['f64_sources']}")
+            assert st["f64_sources"] == int(modes.sum())
+            assert G.info()["device_bytes"] <= floor + general + extra
+            assert_bc_close(G.scores(), ref)
