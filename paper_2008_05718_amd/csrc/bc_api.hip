@@ -1680,9 +1680,7 @@ static bc_status block_facts(bc_graph *g) {
 }
 
 // Capacities of one workgroup's state (once per handle) and how many
-// workgroups can run: resident ones (occupancy) that fit in the memory
-// budget (three quarters of the free device memory, at most 192 GiB, under the
-// handle's cap).  Returns 0 workgroups when not even one fits.
+// workgroups the compute units hold at once.
 static bc_status block_dims(bc_graph *g, int *resident) {
     BlockArgs &d = g->blk_dims;
     const int64_t nmax = std::max<int32_t>(g->blk_nmax, 1);
@@ -1705,20 +1703,38 @@ static bc_status block_dims(bc_graph *g, int *resident) {
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     HIP_TRY(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void *)block_run<0, kBlockWaves>,
                                                          kBlockWaves * kWave, 0));
-    int64_t want = (int64_t)std::max(1, cus) * std::max(1, per_cu);
+    *resident = std::max(1, cus) * std::max(1, per_cu);
+    return BC_OK;
+}
+
+// Make room for the state of up to `want` workgroups and a run's lists (`lists`
+// bytes): as many as fit in the memory budget -- three quarters of the free
+// device memory, at most 192 GiB, and under the handle's cap.  What the
+// handle holds for the block engine counts as free, under a cap its concurrent
+// parts, too; both are given back where they are in the way.  *fit = 0 when fewer
+// than `least` fit (nothing is given back then).
+static bc_status block_fit(bc_graph *g, int64_t want, int64_t least, size_t lists, int64_t *fit) {
+    const size_t per = g->blk_stride + sizeof(SoloState), held = (size_t)g->blk_wg * per;
     size_t free_b = 0, total_b = 0;
     HIP_TRY(hipMemGetInfo(&free_b, &total_b));
-    // what this handle already holds for the block engine counts as free
-    free_b += (size_t)g->blk_wg * (g->blk_stride + sizeof(SoloState));
-    size_t budget = std::min<size_t>(free_b / 4 * 3, (size_t)192 << 30);
-    if (g->acct.limit) {
-        const size_t held = (size_t)g->blk_wg * (g->blk_stride + sizeof(SoloState));
-        const size_t rest = total_bytes(g) - held;  // with the concurrent parts
-        const size_t room = g->acct.limit > rest ? g->acct.limit - rest : 0;
-        budget = std::min(budget, room);
+    const int64_t room = (int64_t)(std::min<size_t>((free_b + held) / 4 * 3, (size_t)192 << 30) / per);
+    *fit = 0;
+    if (!g->acct.limit) {
+        if (room >= least) *fit = std::min(want, room);
+        return BC_OK;
     }
-    want = std::min<int64_t>(want, (int64_t)(budget / (g->blk_stride + sizeof(SoloState))));
-    *resident = (int)std::max<int64_t>(want, 0);
+    const size_t held_lists = (size_t)(g->blk_chunk_cap + g->blk_gsum_cap) * 4 +
+                              (size_t)(g->blk_part_off_cap + g->blk_partials_cap) * 8;
+    const size_t own = g->acct.bytes - held - held_lists + lists, parts = total_bytes(g) - g->acct.bytes;
+    const int64_t n = std::min<int64_t>({want, room, g->acct.limit > own ? (int64_t)((g->acct.limit - own) / per) : 0});
+    if (n < least) return BC_OK;
+    *fit = n;
+    const size_t mine = own + std::max(held, (size_t)n * per);
+    if (mine + parts > g->acct.limit && parts) {
+        free_parts(g);
+        g->replicas = false;
+    }
+    if (mine + held_lists > g->acct.limit) free_block(g);
     return BC_OK;
 }
 
@@ -1823,16 +1839,6 @@ static bc_status run_block(bc_graph *g, const RunCfg &cfg, const bc_run_options 
     int resident = 0;
     bc_status s = block_dims(g, &resident);
     if (s != BC_OK) return s;
-    if (g->acct.limit && !g->parts.empty() && resident < 1) {
-        free_parts(g);  // concurrent parts of earlier runs give way under a cap
-        g->replicas = false;
-        s = block_dims(g, &resident);
-        if (s != BC_OK) return s;
-    }
-    if (resident < 1) {
-        *fallback = true;
-        return BC_OK;
-    }
     const BlockArgs &dm = g->blk_dims;
     s = grow(&g->srcs, &g->srcs_cap, ns, &g->acct);
     if (s != BC_OK) return s;
@@ -1880,7 +1886,25 @@ static bc_status run_block(bc_graph *g, const RunCfg &cfg, const bc_run_options 
         b = e;
     }
     const int64_t nc = (int64_t)cb0.size();
-    const int nwg = (int)std::min<int64_t>(resident, nc);
+    // what fits decides on the workgroups alone: batches and chunks, and with them
+    // the order of the additions, follow from the sizes
+    const int64_t want = std::min<int64_t>(resident, nc);
+    int64_t tot = 0, fit = 0;
+    for (int64_t t = 0; t < nc; ++t) tot += bhi[cb0[t]] - blo[cb0[t]];
+    const auto lists = [&](int64_t held, int64_t need) { return (size_t)std::max<int64_t>(need, 16) - (size_t)std::min(held, need); };
+    const size_t list_bytes = (size_t)(3 * nc + 4 * (int64_t)g->n_graphs + 64) * 4 + (size_t)(2 * nc + tot + 64) * 8 +
+                              lists(g->bcap[0], nb + 1) * 8 + (lists(g->bcap[1], nb + 1) + lists(g->bcap[2], nb + 1)) * 4;
+    // By default only with workgroups enough: use_block's rule was measured with all
+    // of them, and graphs up to kBlockDefaultN vertices run two to three times as fast as
+    // on the general engine, larger ones up to 1.5 times.
+    const int64_t least = (o.flags & BC_RUN_BLOCKS) ? 1 : g->blk_nmax > kBlockDefaultN ? want : (want + 1) / 2;
+    s = block_fit(g, want, least, list_bytes, &fit);
+    if (s != BC_OK) return s;
+    if (fit < 1) {
+        *fallback = true;
+        return BC_OK;
+    }
+    const int nwg = (int)fit;
     s = ensure_block(g, nwg);
     if (s == BC_ERR_OUT_OF_MEMORY) {  // the general engine needs less: let it run
         *fallback = true;
@@ -1888,11 +1912,7 @@ static bc_status run_block(bc_graph *g, const RunCfg &cfg, const bc_run_options 
     }
     if (s != BC_OK) return s;
     std::vector<int64_t> part_off((size_t)nc);
-    int64_t tot = 0;
-    for (int64_t t = 0; t < nc; ++t) {
-        part_off[t] = tot;
-        tot += bhi[cb0[t]] - blo[cb0[t]];
-    }
+    for (int64_t t = 1; t < nc; ++t) part_off[t] = part_off[t - 1] + bhi[cb0[t - 1]] - blo[cb0[t - 1]];
     // per graph, its chunks in batch order (the summation order)
     std::vector<std::vector<int64_t>> per_graph((size_t)g->n_graphs);
     for (int64_t t = 0; t < nc; ++t) per_graph[bg[cb0[t]]].push_back(t);

@@ -132,3 +132,50 @@ def test_overflowed_sources_find_room_under_a_cap():
             assert st["f64_sources"] == int(modes.sum())
             assert G.info()["device_bytes"] <= floor + general + extra
             assert_bc_close(G.scores(), ref)
+
+
+def test_bits_do_not_depend_on_the_memory_that_is_left():
+    # lanes and chunks follow from the sizes; a cap only takes workgroups away
+    u = _union(12, 3000)
+    srcs = np.concatenate([np.arange(o, o + 200) for o in u.vtx_offsets[:-1]]).astype(np.int32)
+    ref, _ = oracle.bc(u, srcs)
+    opts = dict(flags=b.BC_RUN_BLOCKS)
+    with b.Graph(u) as G:
+        G.run(srcs, **opts)
+        st0, want = G.stats(), _bits(G)
+        assert_bc_close(G.scores(), ref)
+    # (lists of the run included: about 12 MiB of partial scores)
+    need = _smallest(u, srcs, 0, 4 << 30, lambda st: st["block_workgroups"] > 0, **opts)
+    for extra in (0, 40 << 20, 400 << 20):
+        with b.Graph(u) as G:
+            floor = G.info()["device_bytes"]
+            G.set_device_limit(floor + need + extra)
+            G.run(srcs, **opts)
+            st = G.stats()
+            say(f"[block choice] {(need + extra) >> 20} MiB: workgroups {st['block_workgroups']} of {st0['block_workgroups']}")
+            assert 0 < st["block_workgroups"] < st0["block_workgroups"]
+            assert st["n_batches"] == st0["n_batches"] and st["block_chunks"] == st0["block_chunks"]
+            assert np.array_equal(_bits(G), want)
+            assert G.info()["device_bytes"] <= floor + need + extra
+
+
+def test_default_needs_half_of_the_workgroups():
+    u = _union(12, 3000)
+    srcs = np.concatenate([np.arange(o, o + 200) for o in u.vtx_offsets[:-1]]).astype(np.int32)
+    ref, _ = oracle.bc(u, srcs)
+    with b.Graph(u) as G:
+        G.run(srcs)
+        full = G.stats()["block_workgroups"]
+        held = G.info()["device_bytes"]
+    for share, block in ((0.3, False), (0.9, True)):
+        with b.Graph(u) as G:
+            floor = G.info()["device_bytes"]
+            cap = int((held - floor) * share)
+            G.set_device_limit(floor + cap)
+            for _ in range(2):
+                G.run(srcs)
+                st = G.stats()
+                say(f"[block choice] {share} of {(held - floor) >> 20} MiB: workgroups {st['block_workgroups']} of {full}, {st['ms']:.2f} ms")
+                assert (st["block_workgroups"] > 0) == block
+                assert G.info()["device_bytes"] <= floor + cap
+                assert_bc_close(G.scores(), ref)
