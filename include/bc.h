@@ -189,7 +189,14 @@ bc_status bc_set_device_limit(bc_graph *g, int64_t max_device_bytes);
                                     level state machine instead of concurrent parts */
 #define BC_RUN_BLOCKS      0x20u /* batched work of graphs of at most 131072 vertices runs on
                                     the block engine (one persistent launch; every workgroup
-                                    owns whole batches) even for short source lists       */
+                                    owns whole batches) even for short source lists.  By
+                                    default lists of enough batches do, on graphs of up to
+                                    16,384 vertices, in a union 65,536.  Its state, kept
+                                    with the handle, takes 1.9 to 2.4 KB per vertex of the
+                                    largest graph on each of up to 256 workgroups (8 to 10
+                                    GB at 16,384 vertices, up to 40 GB at 65,536); where
+                                    less than that is left, under bc_set_device_limit or in
+                                    the device, a default run takes the other engines  */
 #define BC_RUN_NO_BLOCKS   0x40u /* never use the block engine                               */
 #define BC_RUN_TUNED       0x8u  /* K, policy, workgroups, chunk and WPV threshold left
                                     automatic (zero) come from bc_autotune's result */

@@ -206,7 +206,7 @@ struct bc_graph {
     void *wd_mem[24] = {};            // its allocations
     size_t wd_bytes = 0;
     int64_t nonisolated = 0;
-    int32_t depth = 0;                // weighted graphs: see hop_depth
+    int32_t depth = -1, reach = -1;   // see HopSearch (-1: not known)
     // vertices of class degree above a segment of 2^seg_log arcs (ascending) and
     // their segment prefix sums; p_*: the same for the per-source engine's segments
     int32_t seg_log = kSegLogMax;
@@ -283,8 +283,9 @@ struct bc_graph {
     bool blk_sized = false;            // per-graph facts below are computed
     int32_t blk_nmax = 0;              // largest graph
     int64_t blk_arcs_max = 0, blk_cost_max = 0, blk_heavy_max = 0, blk_segs_max = 0;
-    int blk_wg = 0;                    // workgroups whose state is allocated
-    size_t blk_stride = 0;
+    int blk_wg = 0;                    // workgroups with an entry in blk_states
+    size_t blk_bytes = 0;              // of blk_scratch (a run sets up what it uses of it)
+    size_t blk_stride = 0;             // of one workgroup in the current run
     BlockArgs blk_dims{};              // capacities of one workgroup's state
     char *blk_scratch = nullptr;
     SoloState *blk_states = nullptr;
@@ -450,6 +451,75 @@ static int grid_for(int64_t work, int per_block, int cap) {
     return (int)b;
 }
 
+constexpr int32_t kBlockLevels = 4096;  // levels a workgroup of the block engine holds
+
+// Breadth-first searches over the arcs of a handle's graphs, one for each
+// component (of a directed graph: for what the searches before have not
+// reached): an estimate of how many levels traversals take.
+struct HopSearch {
+    const std::vector<int32_t> &rp, &col;
+    const bool directed;
+    std::vector<int32_t> hop, q;  // hop: -1 = not reached yet; q: the last search's vertices in order
+    int32_t depth = 0;            // hops to the farthest vertex, over all searches
+    int32_t reach = 0;            // where twice that could pass kBlockLevels, the same from the farthest
+                                  // vertex: close to the longest traversal, and never above it
+    HopSearch(const std::vector<int32_t> &rp_, const std::vector<int32_t> &col_, bool directed_)
+        : rp(rp_), col(col_), directed(directed_), hop(rp_.size() - 1, -1) {
+        q.reserve(hop.size());
+    }
+    void search(int32_t s) {
+        q.assign(1, s);
+        hop[s] = 0;
+        for (size_t h = 0; h < q.size(); ++h) {
+            const int32_t v = q[h];
+            for (int32_t e = rp[v]; e < rp[v + 1]; ++e)
+                if (hop[col[e]] < 0) {
+                    hop[col[e]] = hop[v] + 1;
+                    q.push_back(col[e]);
+                }
+        }
+    }
+    // Count the component that search() has just gone through.
+    void count() {
+        const int32_t far = hop[q.back()];
+        depth = std::max(depth, far);
+        reach = std::max(reach, far);
+        if (directed || 2 * far + 2 <= kBlockLevels) return;
+        const int32_t s = q.back();
+        for (int32_t v : q) hop[v] = -1;
+        search(s);
+        reach = std::max(reach, hop[q.back()]);
+    }
+    // Vertices [lo, hi) that no search has reached.
+    void rest(int32_t lo, int32_t hi) {
+        for (int32_t v = lo; v < hi; ++v)
+            if (hop[v] < 0) {
+                search(v);
+                count();
+            }
+    }
+};
+static int32_t largest_degree(const std::vector<int32_t> &rp, int32_t lo, int32_t hi) {
+    int32_t hub = lo;
+    for (int32_t v = lo; v < hi; ++v)
+        if (rp[v + 1] - rp[v] > rp[hub + 1] - rp[hub]) hub = v;
+    return hub;
+}
+
+// What HopSearch counts over a handle's graphs, each from its vertex of largest degree on.
+static void hop_depth(const std::vector<int32_t> &voff, const std::vector<int32_t> &rp, const std::vector<int32_t> &col,
+                      bool directed, int32_t *depth, int32_t *reach) {
+    HopSearch hs(rp, col, directed);
+    for (size_t gi = 0; gi + 1 < voff.size(); ++gi) {
+        if (voff[gi] == voff[gi + 1]) continue;
+        hs.search(largest_degree(rp, voff[gi], voff[gi + 1]));
+        hs.count();
+        hs.rest(voff[gi], voff[gi + 1]);
+    }
+    *depth = hs.depth;
+    *reach = hs.reach;
+}
+
 // Rank of every vertex as a source.  Within each graph, sources are taken
 // by hop distance from the graph's vertex of largest degree (the hub), then
 // by their parent in the hub's BFS tree (the neighbour one hop closer, of
@@ -457,32 +527,22 @@ static int grid_for(int64_t work, int per_block, int cap) {
 // degree.  Sources equally far from the hub that hang off the same parent
 // reach most vertices at the same depth, so a batch of them shares frontier
 // entries: fewer level-queue entries, and neighbour rows read for more lanes
-// at once.
+// at once.  The searches also give the depth (see HopSearch).
 static void source_ranks(int32_t n_graphs, const std::vector<int32_t> &voff, const std::vector<int32_t> &rp,
-                         const std::vector<int32_t> &col, std::vector<int32_t> *rank) {
+                         const std::vector<int32_t> &col, bool directed, std::vector<int32_t> *rank, int32_t *depth,
+                         int32_t *reach) {
     const int32_t n = (int32_t)rp.size() - 1;
     const int32_t kFar = INT32_MAX;
-    std::vector<int32_t> dist((size_t)n, kFar), par((size_t)n, -1), q;
-    q.reserve((size_t)n);
+    std::vector<int32_t> dist((size_t)n, kFar), par((size_t)n, -1);
+    HopSearch hs(rp, col, directed);
     auto deg = [&](int32_t v) { return v < 0 ? INT32_MAX : rp[v + 1] - rp[v]; };
     for (int gi = 0; gi < n_graphs; ++gi) {
         const int32_t lo = voff[gi], hi = voff[gi + 1];
         if (lo == hi) continue;
-        int32_t hub = lo;
-        for (int32_t v = lo; v < hi; ++v)
-            if (deg(v) > deg(hub)) hub = v;
-        q.clear();
-        q.push_back(hub);
-        dist[hub] = 0;
-        for (size_t h = 0; h < q.size(); ++h) {
-            const int32_t v = q[h];
-            for (int32_t e = rp[v]; e < rp[v + 1]; ++e)
-                if (dist[col[e]] == kFar) {
-                    dist[col[e]] = dist[v] + 1;
-                    q.push_back(col[e]);
-                }
-        }
-        for (int32_t v : q) {
+        const int32_t hub = largest_degree(rp, lo, hi);
+        hs.search(hub);
+        for (int32_t v : hs.q) dist[v] = hs.hop[v];
+        for (int32_t v : hs.q) {
             if (v == hub) continue;
             int32_t p = -1;
             for (int32_t e = rp[v]; e < rp[v + 1]; ++e) {
@@ -491,7 +551,11 @@ static void source_ranks(int32_t n_graphs, const std::vector<int32_t> &voff, con
             }
             par[v] = p;
         }
+        hs.count();
+        hs.rest(lo, hi);
     }
+    *depth = hs.depth;
+    *reach = hs.reach;
     std::vector<int32_t> order((size_t)n), gidx((size_t)n);
     for (int gi = 0; gi < n_graphs; ++gi)
         for (int32_t v = voff[gi]; v < voff[gi + 1]; ++v) gidx[v] = gi;
@@ -509,36 +573,6 @@ static void source_ranks(int32_t n_graphs, const std::vector<int32_t> &voff, con
     });
     rank->assign((size_t)n, 0);
     for (int32_t i = 0; i < n; ++i) (*rank)[order[i]] = i;
-}
-
-// Hops (along out-arcs) from the vertex of largest out-degree to the farthest vertex it
-// reaches, or, where that is more, from the first vertex of what is left
-// to the farthest one in it, and so on: an estimate of how many levels a traversal takes.
-static int32_t hop_depth(const std::vector<int32_t> &rp, const std::vector<int32_t> &col) {
-    const int32_t n = (int32_t)rp.size() - 1;
-    std::vector<int32_t> hop((size_t)n, -1), q;
-    q.reserve((size_t)n);
-    int32_t deepest = 0;
-    const auto from = [&](int32_t s) {
-        if (hop[s] >= 0) return;
-        q.assign(1, s);
-        hop[s] = 0;
-        for (size_t h = 0; h < q.size(); ++h) {
-            const int32_t v = q[h];
-            for (int32_t e = rp[v]; e < rp[v + 1]; ++e)
-                if (hop[col[e]] < 0) {
-                    hop[col[e]] = hop[v] + 1;
-                    q.push_back(col[e]);
-                }
-        }
-        deepest = std::max(deepest, hop[q.back()]);
-    };
-    int32_t hub = 0;
-    for (int32_t v = 1; v < n; ++v)
-        if (rp[v + 1] - rp[v] > rp[hub + 1] - rp[hub]) hub = v;
-    if (n > 0) from(hub);
-    for (int32_t v = 0; v < n; ++v) from(v);
-    return deepest;
 }
 
 // Arcs of a heavy vertex's segment (binary logarithm), by the arcs of a graph.
@@ -775,11 +809,11 @@ static bc_status create_impl(int32_t n_graphs, const int32_t *voff_in, int32_t n
                 CR_TRY(dalloc(&g->inv_dev, (size_t)n, &g->acct));
                 CR_TRY(hipMemcpy(g->inv_dev, g->inv.data(), sizeof(int32_t) * (size_t)n, hipMemcpyHostToDevice));
                 CR_TRY(dalloc(&g->bc_out, (size_t)n, &g->acct));
-                source_ranks(n_graphs, voff, rp, ncol, &g->srank);
+                source_ranks(n_graphs, voff, rp, ncol, directed, &g->srank, &g->depth, &g->reach);
             } else if (any_hubs) {  // hubs already first: keep the numbering, still order the sources
                 std::vector<int32_t> col((size_t)nnz);
                 CR_TRY(hipMemcpy(col.data(), g->col, sizeof(int32_t) * (size_t)nnz, hipMemcpyDeviceToHost));
-                source_ranks(n_graphs, voff, rp, col, &g->srank);
+                source_ranks(n_graphs, voff, rp, col, directed, &g->srank, &g->depth, &g->reach);
             }
         }
         if ((weights || directed) && !keep_sources && n > 0 && nnz > 0) {
@@ -788,7 +822,7 @@ static bc_status create_impl(int32_t n_graphs, const int32_t *voff_in, int32_t n
             // a batch then holds sources near each other
             std::vector<int32_t> col((size_t)nnz);
             CR_TRY(hipMemcpy(col.data(), g->col, sizeof(int32_t) * (size_t)nnz, hipMemcpyDeviceToHost));
-            source_ranks(n_graphs, voff, rp, col, &g->srank);
+            source_ranks(n_graphs, voff, rp, col, directed, &g->srank, &g->depth, &g->reach);
         }
         // vertices heavier than one segment, for the split load balancing
         // (one list per engine segment size)
@@ -822,7 +856,7 @@ static bc_status create_impl(int32_t n_graphs, const int32_t *voff_in, int32_t n
                     return bail(BC_ERR_INVALID_GRAPH);
                 }
             }
-            g->depth = hop_depth(rp, col);
+            if (g->depth < 0) hop_depth(voff, rp, col, directed, &g->depth, &g->reach);
             CR_TRY(dalloc(&g->wt, (size_t)nnz, &g->acct));
             if (nnz) CR_TRY(hipMemcpy(g->wt, w.data(), sizeof(int32_t) * (size_t)nnz, hipMemcpyHostToDevice));
             if (!directed) g->in_wt = g->wt;
@@ -964,13 +998,14 @@ static void free_block(bc_graph *g) {
         *p = nullptr;
         g->acct.bytes -= std::min(g->acct.bytes, bytes);
     };
-    drop(&g->blk_scratch, (size_t)g->blk_wg * g->blk_stride);
+    drop(&g->blk_scratch, g->blk_bytes);
     drop(&g->blk_states, (size_t)g->blk_wg * sizeof(SoloState));
     drop(&g->blk_chunk, (size_t)g->blk_chunk_cap * sizeof(int32_t));
     drop(&g->blk_part_off, (size_t)g->blk_part_off_cap * sizeof(int64_t));
     drop(&g->blk_partials, (size_t)g->blk_partials_cap * sizeof(double));
     drop(&g->blk_gsum, (size_t)g->blk_gsum_cap * sizeof(int32_t));
     g->blk_wg = 0;
+    g->blk_bytes = 0;
     g->blk_chunk_cap = g->blk_part_off_cap = g->blk_partials_cap = g->blk_gsum_cap = 0;
 }
 
@@ -1679,25 +1714,8 @@ static bc_status block_facts(bc_graph *g) {
     return BC_OK;
 }
 
-// Capacities of one workgroup's state (once per handle) and how many
-// workgroups the compute units hold at once.
-static bc_status block_dims(bc_graph *g, int *resident) {
-    BlockArgs &d = g->blk_dims;
-    const int64_t nmax = std::max<int32_t>(g->blk_nmax, 1);
-    d.nmax = (int32_t)nmax;
-    d.max_levels = (int32_t)std::min<int64_t>(nmax + 2, 4096);
-    // every (vertex, lane) pair enters a batch's queues at most once: small
-    // graphs get that bound, larger ones 16 entries per vertex
-    d.lq_cap = (uint32_t)std::min<int64_t>(std::max<int64_t>(16 * nmax + 4096, (int64_t)1 << 20),
-                                           (int64_t)kLanes * nmax + 64);
-    d.gcap = (uint32_t)((int64_t)kLanes * g->blk_cost_max / kBudget + 2 * ((int64_t)d.max_levels + 2) + 64);
-    d.hq_entries = (uint32_t)(g->blk_heavy_max * kLanes + kLanes);
-    d.hq_levels = (uint32_t)d.max_levels + 3;
-    d.part_cap = (uint32_t)(g->blk_segs_max + 1);
-    d.ovf_cap = 4096;
-    const BlockLayout L((size_t)d.nmax, d.lq_cap, (size_t)d.max_levels, d.gcap, d.hq_entries, d.hq_levels,
-                        d.part_cap, d.ovf_cap);
-    g->blk_stride = L.bytes;
+// Workgroups that the compute units hold at once.
+static bc_status block_resident(int *resident) {
     int dev = 0, cus = 0, per_cu = 0;
     HIP_TRY(hipGetDevice(&dev));
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
@@ -1707,6 +1725,28 @@ static bc_status block_dims(bc_graph *g, int *resident) {
     return BC_OK;
 }
 
+// Capacities of one workgroup's state for batches of K sources.
+static void block_dims(bc_graph *g, int K) {
+    BlockArgs &d = g->blk_dims;
+    const int64_t nmax = std::max<int32_t>(g->blk_nmax, 1);
+    d.nmax = (int32_t)nmax;
+    d.max_levels = (int32_t)std::min<int64_t>(nmax + 2, kBlockLevels);
+    // A vertex enters a batch's queues at most once for each lane, and once for
+    // each level that it is on for some lane; its distances from the
+    // sources differ by at most twice the depth.
+    const int64_t entries = !g->directed && g->depth >= 0 ? std::min<int64_t>(K, 2 * (int64_t)g->depth + 1) : K;
+    d.lq_cap = (uint32_t)std::min<int64_t>(
+        std::max<int64_t>({16 * nmax + 4096, (int64_t)1 << 20, entries * nmax + 64}), (int64_t)kLanes * nmax + 64);
+    d.gcap = (uint32_t)((int64_t)kLanes * g->blk_cost_max / kBudget + 2 * ((int64_t)d.max_levels + 2) + 64);
+    d.hq_entries = (uint32_t)(g->blk_heavy_max * kLanes + kLanes);
+    d.hq_levels = (uint32_t)d.max_levels + 3;
+    d.part_cap = (uint32_t)(g->blk_segs_max + 1);
+    d.ovf_cap = 4096;
+    const BlockLayout L((size_t)d.nmax, d.lq_cap, (size_t)d.max_levels, d.gcap, d.hq_entries, d.hq_levels,
+                        d.part_cap, d.ovf_cap);
+    g->blk_stride = L.bytes;
+}
+
 // Make room for the state of up to `want` workgroups and a run's lists (`lists`
 // bytes): as many as fit in the memory budget -- three quarters of the free
 // device memory, at most 192 GiB, and under the handle's cap.  What the
@@ -1714,7 +1754,7 @@ static bc_status block_dims(bc_graph *g, int *resident) {
 // parts, too; both are given back where they are in the way.  *fit = 0 when fewer
 // than `least` fit (nothing is given back then).
 static bc_status block_fit(bc_graph *g, int64_t want, int64_t least, size_t lists, int64_t *fit) {
-    const size_t per = g->blk_stride + sizeof(SoloState), held = (size_t)g->blk_wg * per;
+    const size_t per = g->blk_stride + sizeof(SoloState), held = g->blk_bytes + (size_t)g->blk_wg * sizeof(SoloState);
     size_t free_b = 0, total_b = 0;
     HIP_TRY(hipMemGetInfo(&free_b, &total_b));
     const int64_t room = (int64_t)(std::min<size_t>((free_b + held) / 4 * 3, (size_t)192 << 30) / per);
@@ -1740,17 +1780,19 @@ static bc_status block_fit(bc_graph *g, int64_t want, int64_t least, size_t list
 
 // State for `need` workgroups (kept and grown across runs).
 static bc_status ensure_block(bc_graph *g, int need) {
-    if (g->blk_wg >= need) return BC_OK;
-    if (g->blk_scratch) free_block(g);
+    const size_t bytes = (size_t)need * g->blk_stride;
+    if (g->blk_wg >= need && g->blk_bytes >= bytes) return BC_OK;
+    free_block(g);
     if (!g->blk_next) HIP_TRY(dalloc(&g->blk_next, 1, &g->acct));
-    HIP_TRY(dalloc(&g->blk_scratch, (size_t)need * g->blk_stride, &g->acct));
+    HIP_TRY(dalloc(&g->blk_scratch, bytes, &g->acct));
     const hipError_t e = dalloc(&g->blk_states, (size_t)need, &g->acct);
     if (e != hipSuccess) {
         (void)hipFree(g->blk_scratch);
         g->blk_scratch = nullptr;
-        g->acct.bytes -= (size_t)need * g->blk_stride;
+        g->acct.bytes -= bytes;
         return hip_fail(e, "the block engine's states");
     }
+    g->blk_bytes = bytes;
     g->blk_wg = need;
     return BC_OK;
 }
@@ -1774,9 +1816,27 @@ static bc_status ensure_block(bc_graph *g, int need) {
 // 99.8 and 29.6, of up to 60,000 60.1 and 52.7 (every 64th vertex a source) or
 // 385 and 261 (every 8th), all of 20,000 to 60,000 163 and 129; with graphs of
 // up to 100,000 they meet (108 and 111, 747 and 660), and the state, which
-// grows with the largest graph, passes 30 GB.
+// grows with the largest graph, is at its largest: 1.9 KB a vertex and workgroup,
+// 31 GB for graphs of 65,536 vertices on 256, and 2.4 KB where a batch may be on many levels.
+//
+// A run that exceeds the levels that a workgroup holds is lost time, and graphs
+// with more of them (see HopSearch) are left to the general engine: a path
+// of 6,000 vertices, 700 sources, 654 ms, 2250 after an attempt.
 constexpr int kBlockDefaultN = 16384, kBlockDefaultUnionN = 65536;
 constexpr int64_t kBlockArcsPerBatch = 4096;
+
+// Whether a workgroup holds the levels of the handle's graphs.
+static bool block_levels_fit(bc_graph *g) {
+    if (g->blk_nmax + 2 <= kBlockLevels) return true;
+    if (g->depth < 0) {  // a handle without ranked sources
+        std::vector<int32_t> rp((size_t)g->n + 1), col((size_t)g->nnz);
+        if (hipMemcpy(rp.data(), g->row_ptr, sizeof(int32_t) * rp.size(), hipMemcpyDeviceToHost) != hipSuccess ||
+            hipMemcpy(col.data(), g->col, sizeof(int32_t) * col.size(), hipMemcpyDeviceToHost) != hipSuccess)
+            return false;
+        hop_depth(g->voff, rp, col, g->directed, &g->depth, &g->reach);
+    }
+    return g->reach + 2 < kBlockLevels;
+}
 
 // Whether a list (nullptr: every vertex) fills `want` batches of K sources.  In a
 // union a batch holds sources of one graph, so a graph's last sources count as a
@@ -1807,7 +1867,7 @@ static bool use_block(bc_graph *g, const bc_run_options &o, const int32_t *src, 
     if (o.flags & BC_RUN_BLOCKS) return true;
     const int K = o.batch >= 8 ? o.batch : 64;
     return g->blk_nmax <= (g->n_graphs > 1 ? kBlockDefaultUnionN : kBlockDefaultN) &&
-           fills_batches(g, src, ns, K, 4 + g->blk_arcs_max / kBlockArcsPerBatch);
+           fills_batches(g, src, ns, K, 4 + g->blk_arcs_max / kBlockArcsPerBatch) && block_levels_fit(g);
 }
 
 // Lanes of a block-engine batch when the caller leaves them open: the fewest
@@ -1837,7 +1897,7 @@ static bc_status run_block(bc_graph *g, const RunCfg &cfg, const bc_run_options 
     ovf_positions->clear();
     if (ns == 0) return BC_OK;
     int resident = 0;
-    bc_status s = block_dims(g, &resident);
+    bc_status s = block_resident(&resident);
     if (s != BC_OK) return s;
     const BlockArgs &dm = g->blk_dims;
     s = grow(&g->srcs, &g->srcs_cap, ns, &g->acct);
@@ -1858,6 +1918,7 @@ static bc_status run_block(bc_graph *g, const RunCfg &cfg, const bc_run_options 
         i = j;
     }
     const int K = o.batch == 0 ? block_lanes(runs, resident) : cfg.lanes;
+    block_dims(g, K);
     std::vector<int64_t> bs;
     std::vector<int32_t> blo, bhi, bg;
     int64_t at = 0;

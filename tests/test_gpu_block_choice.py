@@ -179,3 +179,70 @@ def test_default_needs_half_of_the_workgroups():
                 assert (st["block_workgroups"] > 0) == block
                 assert G.info()["device_bytes"] <= floor + cap
                 assert_bc_close(G.scores(), ref)
+
+
+def _caterpillar(spine, leaves):
+    """A path whose vertices have `leaves` leaves each."""
+    s = np.arange(spine)
+    u = np.concatenate([s[:-1], np.repeat(s, leaves)])
+    v = np.concatenate([s[1:], np.arange(spine, spine * (1 + leaves))])
+    return W.csr_from_edges(spine * (1 + leaves), u, v)
+
+
+def _strip(rows, cols):
+    ids = np.arange(rows * cols).reshape(cols, rows)  # (numbered across: local)
+    u = np.concatenate([ids[:, :-1].ravel(), ids[:-1].ravel()])
+    v = np.concatenate([ids[:, 1:].ravel(), ids[1:].ravel()])
+    return W.csr_from_edges(rows * cols, u, v)
+
+
+def _star_and_cycles(n):
+    """A star, and a cycle of `n` vertices beside it."""
+    c = np.arange(n)
+    return W.csr_from_edges(n + 100, np.concatenate([c, np.full(99, n)]),
+                            np.concatenate([np.roll(c, -1), np.arange(n + 1, n + 100)]))
+
+
+LEVELS = {
+    # large and thin: a vertex is on as many levels as a batch has sources (32 and 64)
+    "caterpillars, 32": (lambda: W.union([_caterpillar(3000, 9)] * 4), 1500, 0, True),
+    "caterpillars, 64": (lambda: W.union([_caterpillar(3000, 9)] * 4), 2900, 0, True),
+    "caterpillars, 64, kept": (lambda: W.union([_caterpillar(3000, 9)] * 4), 2900, b.BC_KEEP_ORDER, True),
+    "strips": (lambda: W.union([_strip(4, 4500 + i) for i in range(4)]), 560, 0, False),  # more than 4,096 levels
+    # as large, few levels
+    "preferential": (lambda: W.union([W.barabasi_albert(18000 + 500 * i, 4, seed=i) for i in range(8)]), 420, 0, True),
+    "preferential, kept": (lambda: W.union([W.barabasi_albert(18000 + 500 * i, 4, seed=i) for i in range(8)]), 420,
+                           b.BC_KEEP_ORDER, True),
+    "path 4000": (lambda: _strip(1, 4000), 700, 0, True),
+    "path 6000": (lambda: _strip(1, 6000), 700, 0, False),  # 6,000 levels, 4,096 fit
+    "path 6000, kept": (lambda: _strip(1, 6000), 700, b.BC_KEEP_ORDER, False),
+    "strip 2 x 4000": (lambda: _strip(2, 4000), 900, 0, True),
+    "strip 2 x 4100": (lambda: _strip(2, 4100), 900, 0, False),
+    "star, cycle 8000": (lambda: _star_and_cycles(8000), 700, 0, True),
+    "star, cycle 8300": (lambda: _star_and_cycles(8300), 700, 0, False),
+}
+
+
+@pytest.mark.parametrize("name", LEVELS)
+def test_default_keeps_to_a_workgroup_s_queue_and_levels(name):
+    # a run is never tried on the block engine only to be given up: where it is not
+    # taken, the handle holds no more than one that was told not to use it
+    make, each, flags, block = LEVELS[name]
+    u = make()
+    off = u.vtx_offsets if getattr(u, "vtx_offsets", None) is not None and len(u.vtx_offsets) > 2 else [0, u.n]
+    rng = np.random.default_rng(1)
+    srcs = np.concatenate([np.sort(rng.permutation(min(o1 - o0, 3000 if "cat" in name else o1 - o0))[:each]) + o0
+                           for o0, o1 in zip(off[:-1], off[1:])]).astype(np.int32)
+    seen = []
+    for opts in ({}, {"flags": b.BC_RUN_NO_BLOCKS})[: 1 if block else 2]:
+        with b.Graph(u, flags=flags) as G:
+            G.run(srcs, **opts)
+            st = G.stats()
+            seen.append((G.info()["device_bytes"], hash(_bits(G).tobytes())))
+            say(f"[block choice] {name} {opts}: workgroups {st['block_workgroups']}, {st['ms']:.1f} ms, {seen[-1][0] >> 20} MiB")
+            assert (st["block_workgroups"] > 0) == block
+    assert len(set(seen)) == 1
+    with b.Graph(u, flags=flags) as G:  # and against the oracle, over fewer sources
+        few = srcs[:: max(1, len(srcs) // 24)]
+        G.run(few, flags=b.BC_RUN_BLOCKS)
+        assert_bc_close(G.scores(), oracle.bc_sliced(u, few, threads=8)[0])
