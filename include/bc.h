@@ -270,13 +270,15 @@ bc_status bc_run(bc_graph *g, const int32_t *sources, int64_t n_sources,
  * dimension at a time starting from base (NULL = defaults): batch K in
  * {64, 32, 16, 8, 1} (K = 1, the per-source engine, is timed on the first
  * 32 sources of the sample and scaled to the whole sample, since it runs
- * sources one after another), policy {heuristic, learned when weights are loaded},
+ * sources one after another), or left open (0) where the block engine then chooses it
+ * by the list of each run, policy {heuristic, learned when weights are loaded},
  * workgroups per step {default, 1/2, 1/4}, level steps per captured chunk
  * {8, 16, 32}, push WPV degree threshold {12, 24, 48}, sources per entry
  * below which groups are summed by (entry, source) pairs {never, 2, 4, 12},
  * concurrent replicas of a single graph {half, default, twice}.
  * Each candidate is
- * timed (host clock around a synchronised run, best of two) after one
+ * timed (host clock around a synchronised run, best of two, of up to ten
+ * within 20 ms) after one
  * untimed run that builds its captured graphs; a value replaces the current
  * one only when it is at least 2 % faster.  The result goes to *best
  * (non-NULL) and stays in the handle for bc_run with BC_RUN_TUNED (which
