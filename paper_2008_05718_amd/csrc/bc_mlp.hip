@@ -42,7 +42,7 @@ static_assert(kP == kMlpParams, "parameter layout");
 constexpr int kTile = 64;
 constexpr int kStride = kTile + 1;  // LDS rows of a unit's values: no bank conflicts across units
 constexpr int kMaxTiles = 256;      // workgroups of mlp_tiles
-constexpr int kPart = kP + 2;       // partial gradient, loss, measured targets
+constexpr int kPart = kP + 2;       // partial gradient, loss, measured targets (a whole number in the last word)
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 static int mlp_blocks(int64_t n) { return (int)std::min<int64_t>((n + kTile - 1) / kTile, kMaxTiles); }
@@ -52,11 +52,13 @@ __global__ __launch_bounds__(256) void mlp_tiles(const float *__restrict__ w, co
                                                  int64_t n, float *__restrict__ part) {
     __shared__ float sx[(kIn + 1) * kStride];  // features, and a row of ones
     __shared__ float h1[kH * kStride], h2[kH * kStride], d1[kH * kStride], d2[kH * kStride], d3[kOut * kStride];
-    __shared__ float se[4 * kTile], sc[4 * kTile];
+    __shared__ float se[4 * kTile];
+    __shared__ unsigned sc[4 * kTile];
     const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int row = lane & 31, half = lane >> 5;
     f32x16 acc = {};
-    float bias = 0.0f, loss = 0.0f, count = 0.0f;
+    float bias = 0.0f, loss = 0.0f;
+    unsigned count = 0;  // (a workgroup has n / 256 samples: below 2^32 up to 10^11)
     for (int64_t base = (int64_t)blockIdx.x * kTile; base < n; base += (int64_t)gridDim.x * kTile) {
         // samples beyond the last one repeat it with nothing measured
         const int64_t r = min(base + lane, n - 1);
@@ -89,7 +91,8 @@ __global__ __launch_bounds__(256) void mlp_tiles(const float *__restrict__ w, co
             for (int j = 0; j < 8; ++j) h2[(8 * wv + j) * kStride + lane] = fmaxf(s[j], 0.0f);
         }
         __syncthreads();
-        float e = 0.0f, c = 0.0f;
+        float e = 0.0f;
+        unsigned c = 0;
         for (int k = wv; k < kOut; k += 4) {
             float s = w[oB3 + k];
             for (int i = 0; i < kH; ++i) s += w[oW3 + k * kH + i] * h2[i * kStride + lane];
@@ -97,7 +100,7 @@ __global__ __launch_bounds__(256) void mlp_tiles(const float *__restrict__ w, co
             const float diff = m ? s - Y[r * kOut + k] : 0.0f;
             d3[k * kStride + lane] = diff;
             e += diff * diff;
-            c += m ? 1.0f : 0.0f;
+            c += m ? 1u : 0u;
         }
         se[wv * kTile + lane] = 0.5f * e;
         sc[wv * kTile + lane] = c;
@@ -145,12 +148,15 @@ __global__ __launch_bounds__(256) void mlp_tiles(const float *__restrict__ w, co
             for (int k = 0; k < kTile; ++k) t += D[k];
             bias += t;
         } else if (lane < kH + kOut + 8) {  // loss and targets, 64 of the 256 values per lane
-            const int q = lane - (kH + kOut);
-            const float *D = (q < 4 ? se : sc) + (q & 3) * kTile;
+            const int q = lane - (kH + kOut), at = (q & 3) * kTile;
             float t = 0.0f;
-            for (int k = 0; k < kTile; ++k) t += D[k];
+            unsigned u = 0;
+            for (int k = 0; k < kTile; ++k) {
+                t += se[at + k];
+                u += sc[at + k];
+            }
             if (q < 4) loss += t;
-            else count += t;
+            else count += u;
         }
         __syncthreads();
     }
@@ -172,12 +178,12 @@ __global__ __launch_bounds__(256) void mlp_tiles(const float *__restrict__ w, co
     } else {
         const float l4 = __shfl(loss, kH + kOut) + __shfl(loss, kH + kOut + 1) + __shfl(loss, kH + kOut + 2) +
                          __shfl(loss, kH + kOut + 3);
-        const float c4 = __shfl(count, kH + kOut + 4) + __shfl(count, kH + kOut + 5) + __shfl(count, kH + kOut + 6) +
-                         __shfl(count, kH + kOut + 7);
+        const unsigned c4 = __shfl(count, kH + kOut + 4) + __shfl(count, kH + kOut + 5) + __shfl(count, kH + kOut + 6) +
+                            __shfl(count, kH + kOut + 7);
         if (lane < kH) p[oB2 + lane] = bias;
         else if (lane < kH + kOut) p[oB3 + lane - kH] = bias;
         else if (lane == kH + kOut) p[kP] = l4;
-        else if (lane == kH + kOut + 1) p[kP + 1] = c4;
+        else if (lane == kH + kOut + 1) p[kP + 1] = __uint_as_float(c4);
     }
 }
 
@@ -190,19 +196,18 @@ struct AdamArgs {
 
 // Sum of the partials, workgroup by workgroup, one thread per parameter (8
 // loads in flight); thread kP sums the loss.  With adam.w the weights are
-// updated by the same thread.  The number of measured targets of a workgroup is a
-// whole number below 2^24 (and so is their sum's rounding far below that of the terms);
-// none measured: loss and gradient are zero.
+// updated by the same thread.  The measured targets are counted in whole
+// numbers; none measured: loss and gradient are zero.
 __global__ __launch_bounds__(64) void mlp_combine(const float *__restrict__ part, int blocks, float *__restrict__ grad,
                                                   float *__restrict__ loss, AdamArgs adam) {
-    __shared__ float s_cnt[64];
-    float c = 0.0f;
-    for (int b = threadIdx.x; b < blocks; b += 64) c += part[(size_t)b * kPart + kP + 1];
+    __shared__ unsigned long long s_cnt[64];
+    unsigned long long c = 0;
+    for (int b = threadIdx.x; b < blocks; b += 64) c += __float_as_uint(part[(size_t)b * kPart + kP + 1]);
     s_cnt[threadIdx.x] = c;
     __syncthreads();
-    double total = 0.0;
-    for (int i = 0; i < 64; ++i) total += (double)s_cnt[i];
-    const float inv = total > 0.0 ? (float)(1.0 / total) : 0.0f;
+    unsigned long long total = 0;
+    for (int i = 0; i < 64; ++i) total += s_cnt[i];
+    const float inv = total ? (float)(1.0 / (double)total) : 0.0f;
     const int p = blockIdx.x * 64 + threadIdx.x;
     if (p > kP) return;
     float g = 0.0f;
