@@ -32,7 +32,7 @@ static_assert(kP == kMlpParams, "parameter layout");
 // product per wavefront, the remaining bias sums on the fourth.  The
 // accumulators stay in registers from tile to tile; every workgroup writes one
 // partial gradient, and mlp_combine adds the partials in workgroup order and
-// scales by 1 / (number of measured targets).  The partition depends only on
+// scales them (mlp_scale).  The partition depends only on
 // the number of samples, so the same samples give the same bits.
 //
 // What bounds it: the latency of the two launches and of one tile's dependent
@@ -45,11 +45,21 @@ constexpr int kMaxTiles = 256;      // workgroups of mlp_tiles
 constexpr int kPart = kP + 2;       // partial gradient, loss, measured targets (a whole number in the last word)
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
+// The loss is a mean, and a sum over all samples may leave FP32 where the mean
+// does not.  So every error is taken times 2^-k, the power of two at or below
+// 1 / (targets of all samples), from the start, and the sums times 2^k / (targets measured).
+// (A power of two changes no rounding.)
+static int mlp_scale(int64_t n) {
+    int k = 0;
+    while (k < 62 && ((int64_t)1 << k) < n * kOut) ++k;
+    return k;
+}
+
 static int mlp_blocks(int64_t n) { return (int)std::min<int64_t>((n + kTile - 1) / kTile, kMaxTiles); }
 
 __global__ __launch_bounds__(256) void mlp_tiles(const float *__restrict__ w, const float *__restrict__ X,
                                                  const float *__restrict__ Y, const uint8_t *__restrict__ mask,
-                                                 int64_t n, float *__restrict__ part) {
+                                                 int64_t n, float scale, float *__restrict__ part) {
     __shared__ float sx[(kIn + 1) * kStride];  // features, and a row of ones
     __shared__ float h1[kH * kStride], h2[kH * kStride], d1[kH * kStride], d2[kH * kStride], d3[kOut * kStride];
     __shared__ float se[4 * kTile];
@@ -98,8 +108,9 @@ __global__ __launch_bounds__(256) void mlp_tiles(const float *__restrict__ w, co
             for (int i = 0; i < kH; ++i) s += w[oW3 + k * kH + i] * h2[i * kStride + lane];
             const bool m = on && mask[r * kOut + k] != 0;
             const float diff = m ? s - Y[r * kOut + k] : 0.0f;
-            d3[k * kStride + lane] = diff;
-            e += diff * diff;
+            const float d = diff * scale;
+            d3[k * kStride + lane] = d;
+            e += d * diff;
             c += m ? 1u : 0u;
         }
         se[wv * kTile + lane] = 0.5f * e;
@@ -198,8 +209,8 @@ struct AdamArgs {
 // loads in flight); thread kP sums the loss.  With adam.w the weights are
 // updated by the same thread.  The measured targets are counted in whole
 // numbers; none measured: loss and gradient are zero.
-__global__ __launch_bounds__(64) void mlp_combine(const float *__restrict__ part, int blocks, float *__restrict__ grad,
-                                                  float *__restrict__ loss, AdamArgs adam) {
+__global__ __launch_bounds__(64) void mlp_combine(const float *__restrict__ part, int blocks, double unscale,
+                                                  float *__restrict__ grad, float *__restrict__ loss, AdamArgs adam) {
     __shared__ unsigned long long s_cnt[64];
     unsigned long long c = 0;
     for (int b = threadIdx.x; b < blocks; b += 64) c += __float_as_uint(part[(size_t)b * kPart + kP + 1]);
@@ -207,7 +218,7 @@ __global__ __launch_bounds__(64) void mlp_combine(const float *__restrict__ part
     __syncthreads();
     unsigned long long total = 0;
     for (int i = 0; i < 64; ++i) total += s_cnt[i];
-    const float inv = total ? (float)(1.0 / (double)total) : 0.0f;
+    const float inv = total ? (float)(unscale / (double)total) : 0.0f;
     const int p = blockIdx.x * 64 + threadIdx.x;
     if (p > kP) return;
     float g = 0.0f;
@@ -330,8 +341,9 @@ static bc_status mlp_check(const float *weights, const float *X, const float *Y,
 
 static void mlp_step_grad(MlpBufs &b, int64_t n, hipStream_t st, const AdamArgs &adam = AdamArgs{}) {
     const int blocks = mlp_blocks(n);
-    mlp_tiles<<<blocks, 256, 0, st>>>(b.w, b.X, b.Y, b.mask, n, b.part);
-    mlp_combine<<<(kP + 1 + 63) / 64, 64, 0, st>>>(b.part, blocks, b.grad, b.loss, adam);
+    const int k = mlp_scale(n);
+    mlp_tiles<<<blocks, 256, 0, st>>>(b.w, b.X, b.Y, b.mask, n, std::ldexp(1.0f, -k), b.part);
+    mlp_combine<<<(kP + 1 + 63) / 64, 64, 0, st>>>(b.part, blocks, std::ldexp(1.0, k), b.grad, b.loss, adam);
 }
 
 extern "C" bc_status bc_mlp_loss_grad(const float *weights, const float *X, const float *Y, const uint8_t *mask,
