@@ -278,7 +278,7 @@ struct bc_graph {
     std::vector<struct SubPart> parts;
     std::vector<int32_t> part_of_graph, local_base;  // per parent graph
     bool replicas = false;  // parts are full copies of a single graph (see ensure_replicas)
-    bool parts_refused = false;  // concurrent parts would not fit under the cap (see parts_fit)
+    int32_t parts_refused = INT32_MAX;  // as many concurrent parts do not fit under the cap (see parts_fit)
     // block engine (graphs of at most kBlockMaxN vertices; see run_block)
     bool blk_sized = false;            // per-graph facts below are computed
     int32_t blk_nmax = 0;              // largest graph
@@ -962,7 +962,7 @@ extern "C" bc_status bc_set_device_limit(bc_graph *g, int64_t max_device_bytes) 
     if (!g) return fail(BC_ERR_INVALID_ARG, "NULL handle");
     if (max_device_bytes < 0) return fail(BC_ERR_INVALID_ARG, "max_device_bytes < 0");
     g->acct.limit = (size_t)max_device_bytes;
-    g->parts_refused = false;  // decided again at the next run
+    g->parts_refused = INT32_MAX;  // decided again at the next run
     if (g->acct.limit && !g->parts.empty() && total_bytes(g) > g->acct.limit) {
         // the parts already made do not fit under the new cap: drop them
         (void)hipDeviceSynchronize();
@@ -1017,13 +1017,23 @@ static void make_room(bc_graph *g, size_t need) {
     if (over_cap(&g->acct, need) || (hipMemGetInfo(&free_b, &total_b) == hipSuccess && free_b < need + (need >> 4)))
         free_block(g);
 }
+// The same for the handle's own state machine, which concurrent parts of earlier
+// runs give way to under the cap, too.
+static void make_own_room(bc_graph *g, size_t need) {
+    make_room(g, need);
+    if (g->acct.limit && !g->parts.empty() && total_bytes(g) + need > g->acct.limit) {
+        (void)hipDeviceSynchronize();
+        free_parts(g);
+        g->replicas = false;
+    }
+}
 
 static bc_status ensure_plain(bc_graph *g, hipStream_t st) {
     const int64_t n = g->n;
     if (!g->plain_ready) {
         const size_t need = (size_t)(g->p_n_heavy + 1) * 12 + (size_t)(n + 3) * 8 + (size_t)(g->p_heavy_segs + 1) * 16 +
                             (size_t)std::max<int64_t>(n, 1) * 24 + (size_t)(n + 2) * 8;
-        make_room(g, need);
+        make_own_room(g, need);
         if (over_cap(&g->acct, need))
             return fail(BC_ERR_OUT_OF_MEMORY, "per-source engine state (" + std::to_string(need) +
                                                   " bytes) is over the handle's max_device_bytes");
@@ -1082,7 +1092,7 @@ static bc_status ensure_batched(bc_graph *g) {
     if (g->cost_units >= (int64_t)UINT32_MAX)
         return fail(BC_ERR_NOT_SUPPORTED, "graph too large for the batched engine: use batch = 1");
     const BatchedSizes z = batched_sizes(n, g->cost_units, g->n_heavy, g->heavy_segs);
-    make_room(g, z.bytes);
+    make_own_room(g, z.bytes);
     if (over_cap(&g->acct, z.bytes))
         return fail(BC_ERR_OUT_OF_MEMORY, "batched engine state (" + std::to_string(z.bytes) +
                                               " bytes) is over the handle's max_device_bytes");
@@ -2807,11 +2817,10 @@ static int concurrent_grid(const bc_graph *g) {
 
 static bool use_parts(const bc_graph *g, const bc_run_options &o, int64_t ns) {
     if ((o.flags & BC_RUN_ONE_QUEUE) || o.batch == 1 || std::getenv("BC_ONE_QUEUE")) return false;
-    if (g->parts_refused) return false;
     if (o.batch == 0 && ns < 2) return false;  // the per-source engine would be chosen
-    if (g->n_graphs >= 4) return true;
+    if (g->n_graphs >= 4) return g->parts_refused == INT32_MAX;
     const int K = o.batch >= 8 ? o.batch : 64;
-    return n_replicas(g, o) >= 2 && ns >= 2 * (int64_t)K;
+    return n_replicas(g, o) >= 2 && ns >= 2 * (int64_t)K && run_replicas(g, o, ns) < g->parts_refused;
 }
 
 // Single graph: parts are full copies of the graph (own per-vertex state);
@@ -2820,13 +2829,14 @@ static bool use_parts(const bc_graph *g, const bc_run_options &o, int64_t ns) {
 // additions are grouped differently from one state machine.
 // Under a device-memory cap, concurrent parts are created only when the
 // state they would allocate fits beside what the handle holds; otherwise the
-// handle runs on its own level state machine (same results to rounding).
-static bool parts_fit(bc_graph *g, size_t need) {
+// run is one of the handle's own level state machine (same results to rounding),
+// and runs that ask for fewer of them still have theirs.
+static bool parts_fit(bc_graph *g, int32_t count, size_t need) {
     make_room(g, need);
     if (!g->acct.limit) return true;
     const size_t have = g->acct.bytes;
     if (have + need <= g->acct.limit) return true;
-    g->parts_refused = true;
+    g->parts_refused = std::min(g->parts_refused, count);
     return false;
 }
 
@@ -2836,17 +2846,17 @@ static size_t run_buffer_bytes(int64_t ns) { return (size_t)(ns + 16) * 12 + (si
 
 static bc_status ensure_replicas(bc_graph *g, int R) {
     if ((int)g->parts.size() >= R) return BC_OK;  // a run uses the first R
-    if (!g->parts.empty()) {  // more are asked for: make them again
-        (void)hipDeviceSynchronize();
-        free_parts(g);
-        g->replicas = false;
-    }
     {
         // a replica holds the graph (created with the parent's internal
         // numbering) and its own batched engine state
         const BatchedSizes z = batched_sizes(g->n, g->cost_units, g->n_heavy, g->heavy_segs);
-        if (!parts_fit(g, (size_t)R * (g->create_bytes + z.bytes + run_buffer_bytes(g->n))))
+        if (!parts_fit(g, R, (size_t)R * (g->create_bytes + z.bytes + run_buffer_bytes(g->n))))
             return fail(BC_ERR_OUT_OF_MEMORY, "concurrent replicas do not fit under max_device_bytes");
+    }
+    if (!g->parts.empty()) {  // more are asked for: make them again
+        (void)hipDeviceSynchronize();
+        free_parts(g);
+        g->replicas = false;
     }
     std::vector<float> w;
     if (g->has_mlp) {
@@ -2923,7 +2933,7 @@ static bc_status ensure_parts(bc_graph *g) {
             need += (size_t)(pn[p] + 1) * 24 + (size_t)pnnz[p] * 4 + sizeof(Ctl) + (size_t)kLevelRecs * sizeof(LevelRec) +
                     (size_t)pheavy[p] * 16 + 4096 + batched_sizes(pn[p], pcost[p], pheavy[p], psegs[p]).bytes +
                     run_buffer_bytes(pn[p]);
-        if (!parts_fit(g, need)) {
+        if (!parts_fit(g, P, need)) {
             g->part_of_graph.clear();
             return fail(BC_ERR_OUT_OF_MEMORY, "concurrent sub-unions do not fit under max_device_bytes");
         }
@@ -3177,7 +3187,7 @@ static bc_status run_impl(bc_graph *g, const int32_t *sources, int64_t n_sources
     if (!blk && !g->weighted && use_parts(g, o, sources ? n_sources : g->n)) {
         g->last_parts = true;
         const bc_status ps = run_parts(g, sources, n_sources, o, stream, dump_index, detail);
-        if (!(ps == BC_ERR_OUT_OF_MEMORY && g->parts_refused)) return ps;
+        if (!(ps == BC_ERR_OUT_OF_MEMORY && !use_parts(g, o, sources ? n_sources : g->n))) return ps;
         // the parts were refused under the cap before anything ran: one state machine
     }
     g->last_parts = false;
@@ -3323,7 +3333,7 @@ static bc_status run_impl(bc_graph *g, const int32_t *sources, int64_t n_sources
             if (use_parts(g, o, ns)) {
                 g->last_parts = true;
                 const bc_status ps = run_parts(g, given, ns, o, stream, -1, nullptr);
-                if (!(ps == BC_ERR_OUT_OF_MEMORY && g->parts_refused)) {
+                if (!(ps == BC_ERR_OUT_OF_MEMORY && !use_parts(g, o, ns))) {
                     g->stats.ms =
                         std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - t0).count();
                     return ps;
