@@ -75,18 +75,19 @@ template <class To>
 __device__ __forceinline__ void push_arcs(const BatchArgs &a, Append<To> &ap, unsigned long long f, int a0, int a1,
                                           const int32_t *__restrict__ col) {
     if (a0 >= a1) return;
-    const int lane = lane_id();
-    int w = col[min(a0 + lane, a1 - 1)], wn = col[min(a0 + kWave + lane, a1 - 1)];
+    const int lane = lane_id(), n = a1 - a0;
+    col += a0;
+    int w = col[min(lane, n - 1)], wn = col[min(kWave + lane, n - 1)];
     VisNext x = a.vn[w];
-    for (int eb = a0; eb < a1; eb += kWave) {
+    for (int i = 0; i < n; i += kWave) {
         const int wc = w;
         const VisNext xc = x;
-        if (eb + kWave < a1) {
+        if (i + kWave < n) {
             w = wn;
             x = a.vn[w];
-            wn = col[min(eb + 2 * kWave + lane, a1 - 1)];
+            wn = col[min(i + 2 * kWave + lane, n - 1)];
         }
-        push_arc(a, ap, wc, eb + lane < a1 ? f : 0ull, xc);
+        push_arc(a, ap, wc, i + lane < n ? f : 0ull, xc);
     }
 }
 
@@ -378,13 +379,14 @@ __device__ __forceinline__ unsigned long long pull_arcs(const Tagged *fw, uint32
                                                         int a1, const int32_t *__restrict__ col, int &scanned) {
     unsigned long long got = 0;
     if (!need || a0 >= a1) return 0ull;
-    const int lane = lane_id();
-    int u = col[min(a0 + lane, a1 - 1)];
-    for (int eb = a0; eb < a1 && got != need; eb += kWave) {
+    const int lane = lane_id(), n = a1 - a0;
+    col += a0;
+    int u = col[min(lane, n - 1)];
+    for (int i = 0; i < n && got != need; i += kWave) {
         const unsigned long long f = tagged_lanes(fw, u, T, need);  // (the last arc again beyond the end)
-        if (eb + kWave < a1) u = col[min(eb + kWave + lane, a1 - 1)];
+        if (i + kWave < n) u = col[min(i + kWave + lane, n - 1)];
         got |= wave_or_u64(f);
-        scanned += min(kWave, a1 - eb);
+        scanned += min(kWave, n - i);
     }
     return got;
 }
@@ -713,8 +715,8 @@ __device__ __forceinline__ void batch_step_body(Load load, C *gc, const int pari
                     const int p = uniform(a.hq.pos[h]);
                     const int u = uniform(a.lq_vtx[p]);
                     const unsigned long long f = uniform(a.lq_mask[p]) & act;
-                    const int a0 = uniform(rp[u]) + (s << a.g.seg_log);
-                    const int a1 = max(a0, min(uniform(rp[u + 1]), a0 + seg_arcs(a.g)));
+                    const int a0 = seg_begin(a.g, uniform(rp[u]), s);
+                    const int a1 = seg_end(a.g, uniform(rp[u]), uniform(rp[u + 1]), s);
                     if (lane == 0) my_arcs += (unsigned)(a1 - a0);
                     if (f) push_arcs(a, ap, f, a0, a1, col);
                 } else if (variant == V_PUSH_WPV) {
@@ -744,7 +746,8 @@ __device__ __forceinline__ void batch_step_body(Load load, C *gc, const int pari
                     const int s = t - uniform(a.g.hv_seg[h]);
                     const int w = uniform(a.g.hv_vtx[h]);
                     const unsigned long long need = act & ~uniform(a.vn[w].vis);
-                    const int a0 = uniform(irp[w]) + (s << a.g.seg_log), a1 = max(a0, min(uniform(irp[w + 1]), a0 + seg_arcs(a.g)));
+                    const int a0 = seg_begin(a.g, uniform(irp[w]), s);
+                    const int a1 = seg_end(a.g, uniform(irp[w]), uniform(irp[w + 1]), s);
                     int scanned = 0;
                     const unsigned long long got = pull_arcs(fw_cur, T, need, a0, a1, icol, scanned);
                     if (lane == 0) my_arcs += (unsigned)scanned;
@@ -828,7 +831,7 @@ __device__ __forceinline__ void batch_step_body(Load load, C *gc, const int pari
             const int e0 = uniform(a.g.in_row_ptr[w]), e1 = uniform(a.g.in_row_ptr[w + 1]);  // predecessors: in-arcs
             const int od = uniform(rp[w + 1] - rp[w]);
             const unsigned long long m = uniform(a.vn[w].nxt);
-            const int a0 = e0 + (s << a.g.seg_log), a1 = max(a0, min(e1, a0 + seg_arcs(a.g)));
+            const int a0 = seg_begin(a.g, e0, s), a1 = seg_end(a.g, e0, e1, s);
             RowSum<OP> sum;
             row_arcs<OP>(TagLanes{fw_cur, T}, m, a0, a1, sh, a.g.in_col, a.sigma, sum, sc.ac);
             const size_t slot = (size_t)(s0 + s) * kLanes + lane;
@@ -903,7 +906,7 @@ __device__ __forceinline__ void batch_step_body(Load load, C *gc, const int pari
             const unsigned long long Mf = uniform(a.lq_mask[p]);
             const unsigned long long M = Mf & ~dead;
             const int e0 = uniform(rp[v]), e1 = uniform(rp[v + 1]);  // successors: out-arcs
-            const int a0 = e0 + (s << a.g.seg_log), a1 = max(a0, min(e1, a0 + seg_arcs(a.g)));
+            const int a0 = seg_begin(a.g, e0, s), a1 = seg_end(a.g, e0, e1, s);
             RowSum<OP_C> sum;
             if (M) row_arcs<OP_C>(TagLanes{fb_nxt, TB + 1u}, M, a0, a1, 0, col, a.chat, sum, ac);
             part_store(&a.hq.part_lo[(size_t)(s0 + s) * kLanes + lane], as_u64(sum.d));

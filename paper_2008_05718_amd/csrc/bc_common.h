@@ -284,6 +284,24 @@ __device__ __forceinline__ int n_segments(const GraphArgs &g, int deg) {
     return (int)(((unsigned)deg + (unsigned)seg_arcs(g) - 1u) >> g.seg_log);
 }
 
+// Segment s of a row [e0, e1): its first arc and its end (the same where the row
+// has fewer segments).  A row may end at 2^31 - 1, so nothing is added to a
+// position before it is known that the row goes on: sums over a row's
+// arcs count from its first one, and a segment's arcs are what is left of the row.
+__host__ __device__ __forceinline__ constexpr int seg_len(int left, int s, int seg_log) {
+    const int l = left - (int)((unsigned)s << seg_log);
+    return l < 0 ? 0 : l < (1 << seg_log) ? l : 1 << seg_log;
+}
+static_assert(seg_len(1024, 0, 10) == 1024 && seg_len(1025, 0, 10) == 1024 && seg_len(1025, 1, 10) == 1 &&
+                  seg_len(5, 1, 10) == 0 && seg_len(INT_MAX, 0, 10) == 1024 && seg_len(INT_MAX, (INT_MAX >> 10), 10) == 1023,
+              "a row's last segment is what is left of it");
+__device__ __forceinline__ int seg_begin(const GraphArgs &g, int e0, int s) {
+    return (int)((unsigned)e0 + ((unsigned)s << g.seg_log));
+}
+__device__ __forceinline__ int seg_end(const GraphArgs &g, int e0, int e1, int s) {
+    return seg_begin(g, e0, s) + seg_len(e1 - e0, s, g.seg_log);
+}
+
 // Degree that decides how a level entry is processed (one thread, one
 // wavefront, or segments) and what it costs: the larger of its out-
 // and in-degree, so an entry is handled the same way in every phase, whichever

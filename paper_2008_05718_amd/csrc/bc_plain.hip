@@ -373,7 +373,7 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
                     const int h = seg_owner(a.hq.seg, h0, h1, t);
                     const int s = t - a.hq.seg[h];
                     const int v = a.queue[a.hq.pos[h]];
-                    const int a0 = rp[v] + (s << a.g.seg_log), a1 = min(rp[v + 1], a0 + seg_arcs(a.g));
+                    const int a0 = seg_begin(a.g, rp[v], s), a1 = seg_end(a.g, rp[v], rp[v + 1], s);
                     if (lane == 0) my_arcs += (unsigned)(a1 - a0);
                     const unsigned long long sv = MODE == 0 ? sig[v] : 0ull;
                     plain_push_arcs<MODE, kWave>(a, l, sv, a0, a1 - a0, my_larcs, my_ovf, st, sn, to);
@@ -418,7 +418,7 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
                     // unvisited before this level (another segment may have
                     // claimed it during this step)
                     if (dw0 != -1 && dw0 != l + 1) continue;
-                    const int a0 = rp[w] + (s << a.g.seg_log), a1 = min(rp[w + 1], a0 + seg_arcs(a.g));
+                    const int a0 = seg_begin(a.g, rp[w], s), a1 = seg_end(a.g, rp[w], rp[w + 1], s);
                     unsigned long long lo, hi;
                     const bool any = plain_pull_arcs<MODE, kWave>(a, l, a0, a1 - a0, lo, hi, my_arcs, my_larcs);
                     bool newly = false;
@@ -493,7 +493,7 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
                 const int s = t - a.hq.seg[h];
                 const int w = a.queue[a.hq.pos[h]];
                 const int e0 = rp[w], e1 = rp[w + 1];
-                const int a0 = e0 + (s << a.g.seg_log), a1 = min(e1, a0 + seg_arcs(a.g));
+                const int a0 = seg_begin(a.g, e0, s), a1 = seg_end(a.g, e0, e1, s);
                 const double p = plain_sum<kWave>(a, a0, a1 - a0, l, false, sh, my_larcs);
                 if (lane == 0) {
                     my_arcs += (unsigned)(a1 - a0);
@@ -553,7 +553,7 @@ __global__ __launch_bounds__(kBlock) void plain_step(PlainArgs a) {
                 const int s = t - a.hq.seg[h];
                 const int v = a.queue[a.hq.pos[h]];
                 const int e0 = rp[v], e1 = rp[v + 1];
-                const int a0 = e0 + (s << a.g.seg_log), a1 = min(e1, a0 + seg_arcs(a.g));
+                const int a0 = seg_begin(a.g, e0, s), a1 = seg_end(a.g, e0, e1, s);
                 const double p = plain_sum<kWave>(a, a0, a1 - a0, l + 1, true, 0, my_larcs);
                 if (lane == 0) {
                     my_arcs += (unsigned)(a1 - a0);

@@ -148,19 +148,20 @@ __device__ __forceinline__ void row_arcs(Lanes lanes, unsigned long long m, int 
                                          const int32_t *__restrict__ col, Slab slab, RowSum<OP> &acc,
                                          ArcCounters &ac) {
     if (a0 >= a1) return;
-    const int lane = lane_id();
-    int u = col[min(a0 + lane, a1 - 1)];
-    int un = col[min(a0 + kWave + lane, a1 - 1)];
-    unsigned long long f = lanes(min(a0 + lane, a1 - 1), u, m);
+    const int lane = lane_id(), n = a1 - a0;
+    col += a0;
+    int u = col[min(lane, n - 1)];
+    int un = col[min(kWave + lane, n - 1)];
+    unsigned long long f = lanes(a0 + min(lane, n - 1), u, m);
     unsigned larcs = 0, pairs = 0;
-    for (int eb = a0; eb < a1; eb += kWave) {
-        const unsigned long long xj = eb + lane < a1 ? f : 0ull;
+    for (int i = 0; i < n; i += kWave) {
+        const unsigned long long xj = i + lane < n ? f : 0ull;
         const unsigned long long rj = slab.row(u);
         unsigned long long bal = __ballot(xj != 0ull);
-        if (eb + kWave < a1) {
+        if (i + kWave < n) {
             u = un;
-            f = lanes(min(eb + kWave + lane, a1 - 1), u, m);
-            un = col[min(eb + 2 * kWave + lane, a1 - 1)];
+            f = lanes(a0 + min(i + kWave + lane, n - 1), u, m);
+            un = col[min(i + 2 * kWave + lane, n - 1)];
         }
         larcs += (unsigned)__popcll(xj);
         pairs += (unsigned)__popcll(bal);
@@ -341,14 +342,15 @@ __device__ __forceinline__ unsigned item_arcs(const Tagged *fw, uint32_t T, int 
                                               const int32_t *__restrict__ col, const unsigned long long *slab,
                                               Use use) {
     unsigned matched = 0;
-    for (int e = e0; e < e1; e += 4) {
+    const int n = e1 - e0;
+    for (int t = 0; t < n; t += 4) {
         int u[4];
         bool on[4];
         unsigned long long v[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) u[q] = col[min(e + q, e1 - 1)];
+        for (int q = 0; q < 4; ++q) u[q] = col[e0 + min(t + q, n - 1)];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) on[q] = e + q < e1 && tagged_lanes(fw, u[q], T, 1ull << k) != 0ull;
+        for (int q = 0; q < 4; ++q) on[q] = t + q < n && tagged_lanes(fw, u[q], T, 1ull << k) != 0ull;
 #pragma unroll
         for (int q = 0; q < 4; ++q) v[q] = on[q] ? slab[(size_t)u[q] * kLanes + k] : 0ull;
 #pragma unroll
