@@ -349,11 +349,18 @@ public:
         {
             std::lock_guard<std::mutex> lock(mu);
             idle.reserve(idle.size() + (size_t)n);  // (giving back allocates nothing)
-            for (size_t i = idle.size(); i-- > 0 && (int)own.size() < n;)
+            // in the order in which they were given back: a handle that runs again has
+            // each part on the stream it had (taken from the back, every other
+            // run had them in reverse, and R-MAT 2^16, 512 sources, took 3.24 and 3.28
+            // ms in turn)
+            for (size_t i = 0; i < idle.size() && (int)own.size() < n;) {
                 if (idle[i].dev == dev && idle[i].plain == plain) {
                     own.push_back(idle[i].s);
                     idle.erase(idle.begin() + (std::ptrdiff_t)i);
+                } else {
+                    ++i;
                 }
+            }
         }
         int cus = 0;
         if ((int)own.size() < n) (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
