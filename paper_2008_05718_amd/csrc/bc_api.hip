@@ -2081,6 +2081,7 @@ static bc_status run_block(bc_graph *g, const RunCfg &cfg, const bc_run_options 
     ra.a.batch_lo = g->blo;
     ra.a.batch_hi = g->bhi;
     ra.a.sigma_limit = o.sigma_limit > 0 ? (unsigned long long)o.sigma_limit : ~0ull;
+    ra.a.lvl = g->lvl;
     ra.scratch = g->blk_scratch;
     ra.stride = g->blk_stride;
     ra.states = g->blk_states;
@@ -3337,6 +3338,9 @@ static bc_status run_impl(bc_graph *g, const int32_t *sources, int64_t n_sources
             // on as if the block engine had not been considered
             (void)hipGetLastError();  // (an allocation that failed)
             free_block(g);
+            fill_u64<<<grid_for((int64_t)kLevelRecs * 8, 256, 4096), 256, 0, st>>>((unsigned long long *)g->lvl,
+                                                                                   (int64_t)kLevelRecs * 8, 0ull);
+            HIP_TRY(hipGetLastError());
             if (use_parts(g, o, ns)) {
                 g->last_parts = true;
                 const bc_status ps = run_parts(g, given, ns, o, stream, -1, nullptr);

@@ -410,8 +410,14 @@ __device__ __forceinline__ void set_level_variant(const BatchArgs &a, Head *c, i
     }
 }
 
-template <int MODE>
-__device__ __forceinline__ void batch_begin(const BatchArgs &a, Head *c, int64_t b, float *lds, LevelFeatures *sf,
+// Where a machine counts its steps on level l.
+__device__ __forceinline__ LevelRec &level_of(const Ctl *, const BatchArgs &a, int l) { return level_rec(a.lvl, l); }
+__device__ __forceinline__ LevelRec &level_of(SoloCtl *c, const BatchArgs &a, int l) {
+    return l < kSoloLevels ? c->lvl[l] : level_rec(a.lvl, l);
+}
+
+template <int MODE, class C>
+__device__ __forceinline__ void batch_begin(const BatchArgs &a, C *gc, Head *c, int64_t b, float *lds, LevelFeatures *sf,
                                             int *s_lsrc, int *s_cnt, unsigned long long *s_tmp, int *s_lead) {
     const int t = threadIdx.x;
     const int64_t start = a.batch_start[b], end = a.batch_start[b + 1];
@@ -507,7 +513,7 @@ __device__ __forceinline__ void batch_begin(const BatchArgs &a, Head *c, int64_t
         c->phase = PH_FWD;
         c->st_batches += 1;
         c->st_lane_entries += (unsigned long long)lanes;
-        if (a.lvl) (void)atomicAdd(&level_rec(a.lvl, 0).entries, (unsigned long long)cnt);
+        if (a.lvl) (void)atomicAdd(&level_of(gc, a, 0).entries, (unsigned long long)cnt);
         const int64_t dp = c->dump_pos;
         c->dump_lane = (dp >= start && dp < end && c->dump_state == 0) ? (int)(dp - start) : -1;
         sf->nf = (float)cnt;
@@ -1078,7 +1084,7 @@ __device__ __forceinline__ void batch_step_body(Load load, C *gc, const int pari
         c->last_tick = now;
         const int rl = (phase == PH_FWD || phase == PH_BWD) ? l : (phase == PH_SIG ? l + 1 : -1);
         if (rl >= 0 && a.lvl) {  // (atomics that nothing waits for)
-            LevelRec &r = level_rec(a.lvl, rl);
+            LevelRec &r = level_of(gc, a, rl);
             (void)atomicAdd(&r.arcs, s_tot[SC_ARCS]);
             (void)atomicAdd(&r.ticks, dt);
             if (phase == PH_FWD) {
@@ -1151,7 +1157,7 @@ __device__ __forceinline__ void batch_step_body(Load load, C *gc, const int pari
             c->st_fwd_levels += 1;
             c->st_var[s_variant] += 1;
             c->st_qentries += cnt;
-            if (a.lvl) (void)atomicAdd(&level_rec(a.lvl, l + 1).entries, (unsigned long long)cnt);
+            if (a.lvl) (void)atomicAdd(&level_of(gc, a, l + 1).entries, (unsigned long long)cnt);
             a.hq.off[l + 2] = s_hqb + (int)(uint32_t)nh;
             a.hq.nseg[l + 1] = (int)(nh >> 32);
             gc->next_hq = 0;
@@ -1234,7 +1240,7 @@ __device__ __forceinline__ void batch_step_body(Load load, C *gc, const int pari
     if (action == 1) {
         gc->next_qc = 0ull;
         gc->next_hq = 0ull;
-        batch_begin<MODE>(a, c, c->pos, s_lds, &s_feat, s_lsrc, &s_qn, s_tmp, s_lead);
+        batch_begin<MODE>(a, gc, c, c->pos, s_lds, &s_feat, s_lsrc, &s_qn, s_tmp, s_lead);
     } else if (action == 2) {
         // finish level l+1: lane deaths, FP64 shifts, features, policy
         if (tid == 0) {
@@ -1385,6 +1391,8 @@ __global__ __launch_bounds__(NW * kWave) void block_run(BlockArgs ra) {
             s_ctl.next_hq = 0ull;
             s_ctl.work[0][0] = 0u;
         }
+        static_assert(sizeof(LevelRec) == 64, "taken in 8-byte words");
+        for (int i = tid; i < kSoloLevels * 8; i += NT) ((unsigned long long *)s_ctl.lvl)[i] = 0ull;
     }
     char *base = ra.scratch + (size_t)blockIdx.x * ra.stride;
     const BlockLayout L((size_t)ra.nmax, ra.lq_cap, (size_t)ra.max_levels, ra.gcap, ra.hq_entries, ra.hq_levels,
@@ -1393,7 +1401,6 @@ __global__ __launch_bounds__(NW * kWave) void block_run(BlockArgs ra) {
         BatchArgs &a = s_a;
         a = ra.a;
         a.ctl = nullptr;
-        a.lvl = nullptr;
         a.lq_vtx = (int32_t *)(base + L.lq_vtx);
         a.lq_mask = (unsigned long long *)(base + L.lq_mask);
         a.lq_cap = ra.lq_cap;
@@ -1487,6 +1494,10 @@ __global__ __launch_bounds__(NW * kWave) void block_run(BlockArgs ra) {
     for (int i = tid; i < (int)(sizeof(Head) / 8); i += NT)
         ((unsigned long long *)&g.h)[i] = ((const unsigned long long *)c)[i];
     if (tid == 0) g.err = s_ctl.err;
+    for (int i = tid; i < kSoloLevels * 8; i += NT) {
+        const unsigned long long x = ((const unsigned long long *)s_ctl.lvl)[i];
+        if (x) (void)atomicAdd((unsigned long long *)ra.a.lvl + i, x);
+    }
 }
 
 template __global__ void block_run<0, kBlockWaves>(BlockArgs);

@@ -167,25 +167,12 @@ struct alignas(128) Ctl {
     uint32_t work[kSlots][32];
 };
 static_assert(kNCnt <= 16, "a slot's counters share one line");
-// The same for a machine that one workgroup runs alone (block engine), in LDS.
-struct SoloCtl {
-    int32_t err;
-    unsigned long long next_qc, next_hq;
-    uint32_t work[1][1];
-    Head h[1];
-};
-
-// What such a workgroup starts from and hands back.
-struct SoloState {
-    Head h;
-    int32_t err, pad;
-};
 
 enum : int32_t { ERR_QUEUE_CAP = 1, ERR_SIGMA_RANGE = 2, ERR_LEVEL_CAP = 4, ERR_OVF_CAP = 8 };
 
 // Per-level record of a run (statistics): index = distance from the source;
-// levels at or beyond kLevelRecs - 1 share the last record.  Written only by
-// the last workgroup of a step launch.
+// levels at or beyond kLevelRecs - 1 share the last record.  Written by the
+// last workgroup of a step launch, and by workgroups of the block engine.
 constexpr int kLevelRecs = 65538;
 struct LevelRec {
     unsigned long long visits;   // forward steps at this level (batches or sources that reached it)
@@ -196,6 +183,24 @@ struct LevelRec {
     unsigned long long pad;
 };
 __device__ __forceinline__ LevelRec &level_rec(LevelRec *r, int l) { return r[l < kLevelRecs ? l : kLevelRecs - 1]; }
+
+// The control block of a machine that one workgroup runs alone (block engine), in
+// LDS.  Such workgroups are on the same few levels at the same time, so the
+// records of those are collected there, too, and added up at the end.
+constexpr int kSoloLevels = 32;
+struct SoloCtl {
+    int32_t err;
+    unsigned long long next_qc, next_hq;
+    uint32_t work[1][1];
+    Head h[1];
+    LevelRec lvl[kSoloLevels];
+};
+
+// What such a workgroup starts from and hands back.
+struct SoloState {
+    Head h;
+    int32_t err, pad;
+};
 
 // Read-only graph description passed to every kernel.
 struct GraphArgs {
