@@ -2138,6 +2138,7 @@ static bc_status run_block(bc_graph *g, const RunCfg &cfg, const bc_run_options 
     g->stats.mode_launches[0] += 1;
     g->stats.mode_ms[0] += ms;
     g->stats.mode_algo_bytes[0] += algo_bytes(g->stats) - bytes0;
+    g->stats.batch = K;
     g->stats.block_workgroups = used;
     g->stats.block_chunks = nc;
     HIP_TRY(hipStreamSynchronize(st));
@@ -3224,7 +3225,7 @@ static bc_status run_impl(bc_graph *g, const int32_t *sources, int64_t n_sources
                                                                            (int64_t)kLevelRecs * 8, 0ull);
     HIP_TRY(hipGetLastError());
     g->stats.n_sources = ns;
-    g->stats.batch = cfg.engine;
+    g->stats.batch = cfg.engine == 1 ? 1 : cfg.lanes;
     g->stats.policy = cfg.policy;
     g->stats.grid_blocks = cfg.grid;
     g->stats.chunk_steps = cfg.use_graphs ? cfg.chunk : 0;

@@ -54,3 +54,18 @@ def test_records_after_a_pass_that_was_given_up():
         G.run(srcs, batch=64, flags=b.BC_RUN_BLOCKS)
         got = G.level_stats()
     assert np.array_equal(got["visits"], want["visits"]) and np.array_equal(got["entries"], want["entries"])
+
+
+@pytest.mark.parametrize("ns,flags,batch,used", [
+    (600, b.BC_RUN_BLOCKS, 0, 8), (2100, b.BC_RUN_BLOCKS, 0, 16), (600, b.BC_RUN_BLOCKS, 32, 32),
+    (600, b.BC_RUN_NO_BLOCKS, 0, 64), (600, b.BC_RUN_NO_BLOCKS, 16, 16), (600, b.BC_RUN_NO_BLOCKS | b.BC_RUN_ONE_QUEUE, 8, 8),
+    (20, 0, 1, 1)])
+def test_statistics_name_the_width_that_was_used(ns, flags, batch, used):
+    g = W.erdos_renyi(1500, 8.0, seed=3)
+    srcs = np.random.default_rng(5).integers(0, g.n, ns).astype(np.int32)
+    with b.Graph(g) as G:
+        G.run(srcs, batch=batch, flags=flags)
+        st = G.stats()
+        assert st["batch"] == used
+        if used > 1:
+            assert st["n_batches"] == -(-ns // used)
