@@ -2854,7 +2854,18 @@ static bool parts_fit(bc_graph *g, int32_t count, size_t need) {
 static size_t run_buffer_bytes(int64_t ns) { return (size_t)(ns + 16) * 12 + (size_t)(ns + 17) * 16; }
 
 static bc_status ensure_replicas(bc_graph *g, int R) {
-    if ((int)g->parts.size() >= R) return BC_OK;  // a run uses the first R
+    if ((int)g->parts.size() >= R) {
+        // A run uses the first R.  Lists of different lengths take turns with four
+        // and the size's default, so those are kept; more stay only while
+        // they are asked for (the autotuner and the replicas option go up to 16).
+        const size_t keep = (size_t)std::max(R, n_replicas(g, bc_run_options{}));
+        if (g->parts.size() > keep) (void)hipDeviceSynchronize();
+        while (g->parts.size() > keep) {
+            bc_destroy(g->parts.back().h);
+            g->parts.pop_back();
+        }
+        return BC_OK;
+    }
     {
         // a replica holds the graph (created with the parent's internal
         // numbering) and its own batched engine state

@@ -64,3 +64,23 @@ def test_the_handle_s_own_machine_counts_beside_its_parts():
             say(f"[replica cap] {opts}: {(G.info()['device_bytes'] - floor) >> 10} of {(cap - floor) >> 10} KiB")
             assert G.info()["device_bytes"] <= cap
             assert_bc_close(G.scores(), ref)
+
+
+def test_more_machines_than_usual_are_given_back():
+    # 16 while they are asked for, then as many as a handle that never had them
+    g = W.rmat(11, 16, seed=31)
+    short, long = W.choose_sources(g, 320, seed=7), W.choose_sources(g, 512, seed=8)
+    with b.Graph(g) as G:
+        _run(G, long)
+        want, usual = _run(G, short), G.info()["device_bytes"]  # 8, of which a short list uses 4
+    with b.Graph(g) as G:
+        _run(G, long, replicas=16)
+        most = G.info()["device_bytes"]
+        assert most > 1.8 * usual
+        _run(G, long, replicas=16)
+        assert G.info()["device_bytes"] == most
+        assert np.array_equal(_run(G, short), want)
+        assert G.info()["device_bytes"] <= usual + (1 << 20)
+        _run(G, long)
+        assert np.array_equal(_run(G, short), want)
+        assert G.info()["device_bytes"] <= usual + (1 << 20)
