@@ -583,7 +583,7 @@ static void source_ranks(int32_t n_graphs, const std::vector<int32_t> &voff, con
 }
 
 // Arcs of a heavy vertex's segment (binary logarithm), by the arcs of a graph.
-// A segment is one wavefront's, eight matched rows at a time, so on graphs
+// A segment is one wavefront's, 16 matched rows at a time, so on graphs
 // with few arcs the longest segment is what a path-count, backward or
 // relaxation step waits for; on large ones there are enough of them, and a pull
 // step over a short segment cannot stop early.  1,024 / 512 / 256 / 128 arcs:
@@ -1892,10 +1892,10 @@ static bool use_block(bc_graph *g, const bc_run_options &o, const int32_t *src, 
 // resident workgroup, 64 if none do.  A batch of fewer lanes has fewer queue
 // entries and fewer levels, so it ends earlier, but two batches after one
 // another on a workgroup take longer than one of twice the lanes.  ER(2000),
-// 8 / 16 / 32 / 64 lanes: 1.53 / 1.64 / 1.8 / 2.0 ms (250 batches of 8);
-// ER(4000): 4.37 / 3.26 / 3.7 / 4.28 (500 of 8, 250 of 16); R-MAT 2^14, 8,192
-// sources: - / 19.3 / 13.6 / 15.3 (256 of 32); 96 graphs of 1,000 to 16,000
-// vertices: - / - / 50.3 / 42.3.
+// 8 / 16 / 32 / 64 lanes: 1.2 / 1.4 / 1.7 / 1.8 ms (250 batches of 8);
+// ER(4000): 3.9 / 2.8 / 3.2 / 3.8 (500 of 8, 250 of 16); R-MAT 2^14, 8,192
+// sources: 35.2 / 24.0 / 15.6 / 17.7 (256 of 32); 96 graphs of 1,000 to 16,000
+// vertices: - / 70.4 / 52.8 / 46.2.
 static int block_lanes(const std::vector<int64_t> &runs, int resident) {
     for (int K = 8; K < 64; K *= 2) {
         int64_t nb = 0;
@@ -2233,6 +2233,12 @@ static bc_status ensure_weighted(bc_graph *g, int lanes, int64_t ns) {
     const bool capped = g->acct.limit != 0;
     const int64_t n = std::max<int32_t>(g->n, 1);
     const size_t stride = lanes == 1 ? WeightedLayout((size_t)n).bytes : WBLayout((size_t)n).bytes;
+    int &decided = g->w_wgs[lanes == 1 ? 0 : 1];
+    if (!capped && decided > 0 && g->w_bytes >= (size_t)decided * stride) {
+        g->w_wg = decided;
+        g->w_stride = stride;
+        return BC_OK;
+    }
     int dev = 0, cus = 0, per_cu = 0;
     HIP_TRY(hipGetDevice(&dev));
     HIP_TRY(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
@@ -2247,8 +2253,7 @@ static bc_status ensure_weighted(bc_graph *g, int lanes, int64_t ns) {
     HIP_TRY(hipMemGetInfo(&free_b, &total_b));
     free_b += held + g->wd_bytes;
     want = std::min<int64_t>(want, (int64_t)(std::min<size_t>(free_b / 2, (size_t)64 << 30) / stride));
-    int &decided = g->w_wgs[lanes == 1 ? 0 : 1];
-    if (!capped && decided > 0) want = decided;
+    if (!capped && decided > 0) want = std::min<int64_t>(want, decided);  // (as before, where it fits)
     if (capped) {
         const size_t rest = g->acct.bytes - held - weighted_lists_held(g) - g->wd_bytes;
         const auto fits = [&](int64_t wg) {
@@ -2572,7 +2577,7 @@ static bc_status ensure_wide(bc_graph *g, int k, hipStream_t st, bool *fits) {
     reverse_arcs<<<grid_for((int64_t)g->n * 64, 256, 8192), 256, 0, st>>>(
         g->n, g->row_ptr, g->col, g->directed ? g->in_row_ptr : g->row_ptr, g->directed ? g->in_col : g->col, rev);
     HIP_TRY(hipGetLastError());
-    // work groups over all vertices in order (as stage_flush forms them)
+    // work groups over all vertices in order (as stage_write forms them)
     std::vector<int32_t> rp((size_t)g->n + 1), irp;
     HIP_TRY(hipMemcpyAsync(rp.data(), g->row_ptr, sizeof(int32_t) * rp.size(), hipMemcpyDeviceToHost, st));
     if (g->directed) {

@@ -1,10 +1,11 @@
-// bc_mlp.hip -- the level-policy network: 5 features -> 32 -> 32 -> 3,
+// bc_mlp.hip -- the level-policy network: 5 features -> 32 -> 32 -> 9,
 // ReLU hidden layers, FP32.  Training kernels (forward, backward, Adam) and
 // batch prediction.  The same weights drive the per-level choice inside the
 // step kernels (choose_variant in bc_common.h).
 //
 // Loss over n samples (x_i, y_i, mask_i), y_ij = log2 of the measured time of
-// variant j at that level, mask_ij = 1 when it was measured:
+// choice j at that level (three discover variants, three summation options of the
+// path-count step and three of the backward step), mask_ij = 1 when it was measured:
 //     L = sum_ij mask_ij (f(x_i)_j - y_ij)^2 / (2 * sum_ij mask_ij).
 // Gradients are sums over tiles of samples in a fixed order, so they do not
 // depend on anything but the samples.

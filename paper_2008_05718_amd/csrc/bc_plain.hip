@@ -28,7 +28,8 @@
 // row bounds, column, level, value), not bytes, so the arcs are spread over
 // lanes and every lane requests kArcs of them together.  With a thread per
 // vertex instead, up to 32 arcs after one another, 32 sources on R-MAT 18 took
-// 27.3 ms, now 13.5; 4 on a 512 x 512 grid 38.6, now 24.5.
+// 27.3 ms and 4 on a damaged 512 x 512 grid 38.6; with this 13.5 and 24.5, and 10.9
+// and 21.4 with four workgroups per compute unit and no word that all of them update.
 #include "bc_common.h"
 
 namespace bcx {
@@ -41,9 +42,9 @@ __device__ __forceinline__ double norm_sigma(const PlainArgs &a, int v, int sh) 
 
 // A vertex's arcs [e0, e0 + len) are worked on by a group of G consecutive
 // lanes (kSub, or the wavefront), kArcs per lane at a time.
-// (R-MAT 18, 32 sources: 13.5 ms with 8 lanes, 13.8 with 4, 14.2 with 16; 2, 4
-// and 8 arcs per lane 14.5, 13.5 and 14.0; up to 32, 64 and 128 arcs 13.7, 13.5
-// and 13.5.)
+// (R-MAT 18, 32 sources, when a run took 13.5 ms: 8 lanes 13.5, 4 13.8, 16 14.2;
+// 2, 4 and 8 arcs per lane 14.5, 13.5 and 14.0; up to 32, 64 and 128 arcs 13.7,
+// 13.5 and 13.5.)
 constexpr int kSub = 8;
 constexpr int kSubDeg = 64;
 constexpr int kArcs = 4;
