@@ -120,8 +120,11 @@ def _csv_rows(directory, suffix):
 
 
 def _kernel_match(name: str, kernel: str) -> bool:
-    """'batch_step<0>' matches 'void bcx::batch_step<0>(bcx::BatchArgs)'."""
-    return kernel in name.replace(" ", "")
+    """'batch_step<0>' matches 'void bcx::batch_step<0>(bcx::BatchArgs)', and
+    'block_run<0>' 'void bcx::block_run<0, 16>(bcx::BlockArgs)' with the number
+    of wavefronts after the mode."""
+    name = name.replace(" ", "")
+    return kernel in name or kernel[:-1] + "," in name
 
 
 def _counter_per_dispatch(directory, counter, kernel):
