@@ -1973,12 +1973,15 @@ static bc_status run_block(bc_graph *g, const RunCfg &cfg, const bc_run_options 
     const int64_t want = std::min<int64_t>(resident, nc);
     int64_t tot = 0, fit = 0;
     for (int64_t t = 0; t < nc; ++t) tot += bhi[cb0[t]] - blo[cb0[t]];
-    const auto lists = [&](int64_t held, int64_t need) { return (size_t)std::max<int64_t>(need, 16) - (size_t)std::min(held, need); };
+    const auto lists = [](int64_t held, int64_t need) {
+        return (size_t)std::max<int64_t>(need, 16) - (size_t)std::min(held, need);
+    };
     const size_t list_bytes = (size_t)(3 * nc + 4 * (int64_t)g->n_graphs + 64) * 4 + (size_t)(2 * nc + tot + 64) * 8 +
                               lists(g->bcap[0], nb + 1) * 8 + (lists(g->bcap[1], nb + 1) + lists(g->bcap[2], nb + 1)) * 4;
     // By default only with workgroups enough: use_block's rule was measured with all
     // of them, and graphs up to kBlockDefaultN vertices run two to three times as fast as
-    // on the general engine, larger ones up to 1.5 times.
+    // on the general engine, larger ones up to 2.6 times (18,000 to 21,500 vertices),
+    // less the larger they are.
     const int64_t least = (o.flags & BC_RUN_BLOCKS) ? 1 : g->blk_nmax > kBlockDefaultN ? want : (want + 1) / 2;
     s = block_fit(g, want, least, list_bytes, &fit);
     if (s != BC_OK) return s;
@@ -4023,8 +4026,9 @@ extern "C" bc_status bc_autotune(bc_graph *g, const int32_t *sample, int64_t n_s
     }
     // a warm-up run (builds the captured graphs), then the best of two timed
     // runs, of up to ten within 20 ms (the first runs of a millisecond after new
-    // state was allocated take up to a fifth longer); the per-source engine (K = 1) runs its sources one after another,
-    // so it is timed on a prefix of the sample and scaled to the whole
+    // state was allocated take up to a fifth longer); the per-source engine (K = 1)
+    // runs its sources one after another, so it is timed on a prefix of the
+    // sample and scaled to the whole
     auto time_one = [&](const bc_run_options &o, double *ms) -> bc_status {
         const int64_t m = o.batch == 1 ? std::min<int64_t>(n_sample, 32) : n_sample;
         bc_status r = run_impl(g, sample, m, &o, st, -1, nullptr);
