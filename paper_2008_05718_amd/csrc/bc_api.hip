@@ -1774,7 +1774,9 @@ static bc_status block_fit(bc_graph *g, int64_t want, int64_t least, size_t list
     const size_t per = g->blk_stride + sizeof(SoloState), held = g->blk_bytes + (size_t)g->blk_wg * sizeof(SoloState);
     size_t free_b = 0, total_b = 0;
     HIP_TRY(hipMemGetInfo(&free_b, &total_b));
-    const int64_t room = (int64_t)(std::min<size_t>((free_b + held) / 4 * 3, (size_t)192 << 30) / per);
+    // (what is held already fits, however little is left beside it)
+    const int64_t room = std::max<int64_t>((int64_t)(std::min<size_t>((free_b + held) / 4 * 3, (size_t)192 << 30) / per),
+                                           std::min<int64_t>(g->blk_wg, (int64_t)(g->blk_bytes / g->blk_stride)));
     *fit = 0;
     if (!g->acct.limit) {
         if (room >= least) *fit = std::min(want, room);

@@ -246,3 +246,31 @@ def test_default_keeps_to_a_workgroup_s_queue_and_levels(name):
         few = srcs[:: max(1, len(srcs) // 24)]
         G.run(few, flags=b.BC_RUN_BLOCKS)
         assert_bc_close(G.scores(), oracle.bc_sliced(u, few, threads=8)[0])
+
+
+def test_memory_that_is_held_stays_in_use():
+    # graphs of 60,000 vertices take some 100 MB a workgroup; with the rest of the
+    # device memory taken after the first run, the second has what it needs
+    import torch
+
+    u = W.union([W.barabasi_albert(60000, 3, seed=40 + i) for i in range(4)])
+    srcs = np.concatenate([np.arange(o, o + 2048) for o in u.vtx_offsets[:-1]]).astype(np.int32)
+    with b.Graph(u) as G:
+        before = G.info()["device_bytes"]
+        G.run(srcs, batch=64)
+        st0, want, held = G.stats(), _bits(G), G.info()["device_bytes"]
+        assert st0["block_workgroups"] == 128
+        left = (held - before) // 5  # (three quarters of 1.2 times would be too little)
+        take = torch.cuda.mem_get_info()[0] - left
+        say(f"[block choice] {(held - before) >> 20} MiB held, {take >> 20} MiB taken, {left >> 20} MiB left")
+        assert left >= 2 << 30 and take > 0
+        rest = torch.empty(take, dtype=torch.uint8, device="cuda")
+        try:
+            G.run(srcs, batch=64)
+        finally:
+            del rest
+            torch.cuda.empty_cache()
+        st = G.stats()
+        say(f"[block choice] workgroups {st['block_workgroups']}, {st['ms']:.1f} ms after {st0['ms']:.1f} ms")
+        assert st["block_workgroups"] == st0["block_workgroups"]
+        assert np.array_equal(_bits(G), want) and G.info()["device_bytes"] == held
